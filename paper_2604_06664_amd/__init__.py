@@ -144,11 +144,30 @@ def _ptr(t):
     return t.data_ptr()
 
 
-def _stream(stream):
-    if stream is None:
+_raw_stream = None  # () -> hipStream_t of torch's current stream on the current device
+
+
+def _current_stream():
+    """torch's current stream as a raw handle.  torch.cuda.current_stream() builds a Stream object
+    for it, 2.9 us a call on the MI355X host and a third of what a whole binding call took there
+    (8.8 us, of which the kernel launch is about 3); the raw handle comes in 0.2 us."""
+    global _raw_stream
+    if _raw_stream is None:
         import torch
 
-        return torch.cuda.current_stream().cuda_stream
+        handle = torch.cuda.current_stream().cuda_stream  # also initializes torch's GPU state
+        raw, dev = (getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+        if raw is None or dev is None:
+            _raw_stream = lambda: torch.cuda.current_stream().cuda_stream  # noqa: E731
+        else:
+            _raw_stream = lambda: raw(dev())  # noqa: E731
+        return handle
+    return _raw_stream()
+
+
+def _stream(stream):
+    if stream is None:
+        return _current_stream()
     return getattr(stream, "cuda_stream", stream)
 
 

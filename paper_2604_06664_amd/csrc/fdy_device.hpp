@@ -4,6 +4,8 @@
 #include <hip/hip_ext.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "fdy.h"
 #include "fdy_internal.h"
 
@@ -97,6 +99,37 @@ __device__ inline u64 block_excl_scan(u64 v, u64* s_buf, u64& total) {
   total = s_buf[16];
   __syncthreads();
   return r;
+}
+
+// The current device and what the launches need to know about it.  Asking the runtime costs
+// 0.2-0.4 us a question, which the latency-bound calls feel, so a device's compute-unit count is
+// kept once known.  Devices beyond the cache are asked every time.
+constexpr int kCachedDevices = 64;
+inline int current_device(int* dev, int* n_cu) {
+  static std::atomic<int> cached[kCachedDevices];
+  FDY_HIP_TRY(hipGetDevice(dev));
+  const bool cacheable = *dev >= 0 && *dev < kCachedDevices;
+  int n = cacheable ? cached[*dev].load(std::memory_order_relaxed) : 0;
+  if (n == 0) {
+    FDY_HIP_TRY(hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, *dev));
+    if (cacheable) cached[*dev].store(n, std::memory_order_relaxed);
+  }
+  *n_cu = n;
+  return FDY_OK;
+}
+
+// Lets `kernel` be launched with up to the whole LDS as dynamic shared memory (a limit, not a
+// request); one runtime call per kernel and device.
+template <typename Fn>
+inline int allow_full_lds(Fn kernel, int dev, std::atomic<u64>& done) {
+  const bool cacheable = dev >= 0 && dev < kCachedDevices;
+  if (cacheable && (done.load(std::memory_order_relaxed) >> dev & 1)) return FDY_OK;
+  hipFuncAttributes attr;
+  FDY_HIP_TRY(hipFuncGetAttributes(&attr, (const void*)kernel));
+  FDY_HIP_TRY(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  (int)(160 * 1024 - attr.sharedSizeBytes)));
+  if (cacheable) done.fetch_or(1ull << dev, std::memory_order_relaxed);
+  return FDY_OK;
 }
 
 // One kernel launch on the caller's stream; when the bench has switched timing on for `slot`,

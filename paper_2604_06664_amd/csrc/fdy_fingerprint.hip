@@ -404,17 +404,23 @@ static int fingerprint_launch(FpArgs a, uint32_t n_graphs, uint32_t n_boundaries
   if (big) a.counter = nullptr;  // grouping by launches of its own
   if (n_graphs) {
     const size_t lds = a.counter && n_graphs > 1 ? lds_table : 0;
-    if (lds > 32768)
-      FDY_HIP_TRY(hipFuncSetAttribute((const void*)fp_key_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      (int)(kLdsSlots * 4)));
+    if (lds > 32768) {
+      static std::atomic<u64> allowed;
+      int dev, n_cu;
+      if (const int rc = current_device(&dev, &n_cu)) return rc;
+      if (const int rc = allow_full_lds(fp_key_kernel, dev, allowed)) return rc;
+    }
     launch(FDY_PROF_FP_KEYS, fp_key_kernel, dim3(n_graphs), dim3(kFpBlock), lds, stream, a);
     FDY_HIP_TRY(hipGetLastError());
     if (n_graphs == 1 || a.counter) return FDY_OK;  // the key kernel has written the grouping too
   }
   if (!big) {
-    if (lds_table > 32768)
-      FDY_HIP_TRY(hipFuncSetAttribute((const void*)fp_group_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      (int)(kLdsSlots * 4)));
+    if (lds_table > 32768) {
+      static std::atomic<u64> allowed;
+      int dev, n_cu;
+      if (const int rc = current_device(&dev, &n_cu)) return rc;
+      if (const int rc = allow_full_lds(fp_group_kernel, dev, allowed)) return rc;
+    }
     launch(FDY_PROF_FP_GROUP, fp_group_kernel, dim3(1), dim3(1024), lds_table, stream, (const u64*)a.keys, n_graphs,
            a.template_id, a.tmpl_graph, a.n_templates);
     FDY_HIP_TRY(hipGetLastError());

@@ -1866,8 +1866,7 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
   hipStream_t stream = (hipStream_t)hip_stream;
   (void)hipGetLastError();  // drop any stale error left by earlier, unrelated runtime calls
   int dev = 0, n_cu = 256;
-  FDY_HIP_TRY(hipGetDevice(&dev));
-  FDY_HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
+  if (const int rc = current_device(&dev, &n_cu)) return rc;
   const u32 per_cu = (u32)fdy__tune_get(FDY_TUNE_SCAN_WG_PER_CU);
   u32 grid = (u32)n_cu * per_cu;  // persistent workgroups
   if (grid > rp.n_chunks) grid = rp.n_chunks;
@@ -1948,8 +1947,8 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
     const u32 n_groups = (rp.n_sub + kFusedG - 1) / kFusedG;
     u32 fgrid = (u32)n_cu;  // one workgroup per compute unit (256 registers per lane)
     if (fgrid > (n_groups + kWaves - 1) / kWaves) fgrid = (n_groups + kWaves - 1) / kWaves;
-    FDY_HIP_TRY(hipFuncSetAttribute((const void*)scan_rebase_kernel,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    static std::atomic<u64> allowed;
+    if (const int rc = allow_full_lds(scan_rebase_kernel, dev, allowed)) return rc;
     launch(FDY_PROF_SCAN_REBASE, scan_rebase_kernel, dim3(fgrid), dim3(kBlock), lds, stream, p);
     FDY_HIP_TRY(hipGetLastError());
     return FDY_OK;
@@ -1968,7 +1967,9 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
                                             : scan_kernel<kGroupsBig, kGBig, false, false, st>);
   };
   auto kern = stage ? pick(std::true_type{}) : pick(std::false_type{});
-  FDY_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  static std::atomic<u64> allowed[12];  // one per instance that pick() can return
+  if (const int rc = allow_full_lds(kern, dev, allowed[(stage ? 6 : 0) + (rp.g == kGSmall ? 3 : 0) + (half ? 0 : ordered_out ? 1 : 2)]))
+    return rc;
   const int slot = ordered_out ? FDY_PROF_SCAN_OUT : FDY_PROF_SCAN_MAIN;
   launch(slot, kern, dim3(grid), dim3(kBlock), lds, stream, p);
   FDY_HIP_TRY(hipGetLastError());
