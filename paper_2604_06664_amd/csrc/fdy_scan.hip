@@ -130,6 +130,7 @@ struct ScanParams {
   const uint4* leafmap;     // ordered scan with output: 128 bytes per 8 entries, the compact line and
                             // behind it the eight regions' new bases (null: not built)
   u64* cstate;     // [n_chunks] per-chunk totals / inclusive prefixes
+  u32* turn;       // tables without packed levels: whose turn the two sets of states are (see FlatTurn)
   u32* done;       // workgroups that have finished (the last one resets the state behind it)
   u64* acc;        // fused scan + rebase: hits so far
   u32 n_chunks;
@@ -148,6 +149,17 @@ struct ScanParams {
   u64* out;             // with a rebased output only: [n_words]
   u32 key_bits;         // width of the level-0 keys: 31 (32-bit keys in LDS) or 16 + bucket_log2 (16-bit keys)
 };
+
+// One state word per chunk, sized for the smallest chunks any launch uses.
+constexpr int kSmallestChunk = 7;
+// Chunk states of the flat scan lie 64 bytes apart (in words): read by every workgroup in flight,
+// packed ones are served by too few memory channels (5.8 M words: 30.8 us packed, 25.2 apart).
+constexpr u32 kFlatStateStride = 8;
+constexpr int kFlatLook = 2;  // 64-chunk blocks per look-back step (1: 26 us, 4: 26 us)
+__host__ __device__ __forceinline__ size_t chunk_state_bytes(u64 n_words) {
+  const u64 n_sub = (n_words + kSub - 1) / kSub;
+  return ((size_t)((n_sub + kSmallestChunk - 1) / kSmallestChunk) * 8 + 255) & ~(size_t)255;
+}
 
 constexpr u64 kFlagAgg = 1ull << 62;
 constexpr u64 kFlagInc = 2ull << 62;
@@ -188,29 +200,51 @@ __device__ __forceinline__ bool spin_once(u32& spins, u32 spin_limit, u32* d_sta
   return true;
 }
 
-// Number of hits in all chunks before `chunk`.
-__device__ __forceinline__ u64 chunk_exclusive_prefix(const u64* cstate, u32 chunk, u32 spin_limit,
-                                                      u32* d_status) {
+// The 64 K states last, last - 1, ... (before chunk 0: prefix 0), as far as the first inclusive
+// prefix among them: their sum, and whether it ends in such a prefix.
+struct WindowSum {
+  u64 sum;
+  bool inc;
+};
+template <int K, u32 kStride>
+__device__ __forceinline__ WindowSum window_sum(const u64* cstate, int last, u32 spin_limit, u32* d_status) {
   const u32 l = lane_id();
-  if (chunk == 0) return 0;
-  u64 excl = 0;
-  int pos = (int)chunk - 1;
   u32 spins = 0;
   for (;;) {
-    const int idx = pos - (int)l;
-    const u64 v = idx >= 0 ? ld_state(&cstate[idx]) : kFlagInc;  // before chunk 0: prefix 0
-    const u32 flag = (u32)(v >> 62);
-    const u64 inc_mask = ballot(flag == 2);
-    const u64 empty_mask = ballot(flag == 0);
-    const u32 first_inc = inc_mask ? (u32)__ffsll((long long)inc_mask) - 1 : 64;
-    const u64 need = first_inc >= 63 ? ~0ull : ((2ull << first_inc) - 1);  // lanes 0..first_inc
-    if (empty_mask & need) {
-      if (!spin_once(spins, spin_limit, d_status)) break;
-      continue;
+    u64 v[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int idx = last - k * 64 - (int)l;
+      v[k] = idx >= 0 ? ld_state(&cstate[(u64)idx * kStride]) : kFlagInc;
     }
-    excl += wave_sum_u64(((need >> l) & 1) ? (v & kValMask) : 0);
-    if (first_inc < 64) break;
-    pos -= 64;
+    u64 mine = 0;
+    bool inc = false, wait = false;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      if (inc || wait) break;
+      const u32 flag = (u32)(v[k] >> 62);
+      const u64 inc_mask = ballot(flag == 2);
+      const u64 empty_mask = ballot(flag == 0);
+      const u32 first_inc = inc_mask ? (u32)__ffsll((long long)inc_mask) - 1 : 64;
+      const u64 need = first_inc >= 63 ? ~0ull : ((2ull << first_inc) - 1);  // lanes 0..first_inc
+      wait = (empty_mask & need) != 0;
+      inc = first_inc < 64;
+      mine += ((need >> l) & 1) ? (v[k] & kValMask) : 0;
+    }
+    if (!wait) return WindowSum{wave_sum_u64(mine), inc};
+    if (!spin_once(spins, spin_limit, d_status)) return WindowSum{0, true};
+  }
+}
+
+// Number of hits in all chunks before `chunk`, K 64-chunk blocks per step; states kStride apart.
+template <int K, u32 kStride>
+__device__ __forceinline__ u64 chunk_exclusive_prefix(const u64* cstate, u32 chunk, u32 spin_limit,
+                                                      u32* d_status) {
+  u64 excl = 0;
+  for (int pos = (int)chunk - 1; pos >= 0; pos -= 64 * K) {
+    const WindowSum s = window_sum<K, kStride>(cstate, pos, spin_limit, d_status);
+    excl += s.sum;
+    if (s.inc) break;
   }
   return excl;
 }
@@ -235,6 +269,7 @@ struct PreparedHeader {
 };
 constexpr u64 kPreparedMagic = 0x3159445f4c424154ull;  // "TABL_DY1"
 constexpr size_t kPreparedHeader = 256;
+constexpr size_t kPreparedTurn = 128;  // byte offset of the turn (fdy_segment_fingerprint's counter lies at 64)
 
 // Is the caller's prepared table one that was made for this table, this tuning and at least
 // this many words?  (The host cannot look into device memory without a round trip.)
@@ -1028,6 +1063,358 @@ __device__ __forceinline__ void write_round(const ScanParams& p, const RoundResu
   }
 }
 
+// ---- tables whose every base has its key in the LDS level (levels == 0) ---------------------
+// Most tables are this small (up to 2^14 allocations), and then a candidate costs a few LDS
+// reads and ONE request, the table entry itself.  What bounds such a scan is not the rate of
+// requests but the chains around them: with the general kernel below (two waves per SIMD, its
+// look-back in the way of a searching wave) 5.8 M words against 4,096 allocations took 41.5 us,
+// 14 us of which went when the look-back was left out.  Hence
+//   - 128 registers instead of 256: a wave has one sub-tile in hand, not two, and room for a
+//     result per word (a queue of 256 candidates, refilled once if there are more): there is no
+//     dense case, no staging area and no second search, whatever the share of candidates;
+//   - one wave of the workgroup, the clerk, owns no words: it draws the tickets and looks back
+//     for the chunk before while the others search, so that a round takes the longer of the two
+//     instead of their sum (36.6 -> 25.2 us with the states spread out);
+//   - chunk states 64 bytes apart, and reset without a count at the end (see FlatTurn).
+// The same input now takes 25.2 us, 3.7 M words against 16,384 allocations 20.9 (28.2), 0.76 M
+// words 10.6 (13.8); at 33 M words and a quarter pointers 101 us (116), 4.0 TB/s of words in and
+// relocations out.
+constexpr int kFlatWorkers = 7, kFlatWorkersBig = 15;
+constexpr u32 kFlatQ = 256;      // queue entries per wave
+constexpr int kFlatRounds = 8;   // rounds of 64 candidates per sub-tile: one sub-tile's words
+constexpr u32 kFlatPad = 8;      // keys behind the last one (all ones)
+
+// What a workgroup stages and knows before its first word.
+struct FlatLevel {
+  const unsigned char* keys;  // u32 keys, addressed in bytes
+  const unsigned short* bst;
+  u64 span_lo, span_len;
+  u32 key_shift, bucket_shift, last_at;  // last_at: byte offset of a key that is padding
+};
+__host__ __device__ __forceinline__ size_t flat_level_bytes(u32 top_n, u32 bucket_log2) {
+  return (((size_t)top_n * 4 + 15) & ~(size_t)15) + kFlatPad * 4 + ((((((size_t)1) << bucket_log2) + 1) * 2 + 15) & ~(size_t)15);
+}
+template <u32 kThreads>
+__device__ __forceinline__ FlatLevel flat_stage(const ScanParams& p, unsigned char* smem) {
+  FlatLevel f;
+  const u32 n_bst = (1u << p.bucket_log2) + 1, tid = threadIdx.x;
+  const u32 key_vec = (p.top_n + 3) / 4, bst_vec = (n_bst * 2 + 15) / 16;
+  uint4* dst = reinterpret_cast<uint4*>(smem);
+  const uint4 *ks = reinterpret_cast<const uint4*>(p.top), *bs = reinterpret_cast<const uint4*>(p.bstart);
+  for (u32 i = tid; i < key_vec; i += kThreads) dst[i] = ks[i];
+  for (u32 i = tid; i < bst_vec; i += kThreads) dst[key_vec + kFlatPad / 4 + i] = bs[i];
+  if (tid < kFlatPad / 4) dst[key_vec + tid] = make_uint4(~0u, ~0u, ~0u, ~0u);
+  f.keys = smem;
+  f.bst = reinterpret_cast<const unsigned short*>(smem + (size_t)(key_vec * 16 + kFlatPad * 4));
+  f.last_at = key_vec * 16;
+  f.span_lo = p.table[0].base;
+  f.span_len = p.table[p.n_alloc - 1].base + p.table[p.n_alloc - 1].size - f.span_lo;
+  f.key_shift = key_shift_for(f.span_len, 31);
+  f.bucket_shift = bucket_shift_for(f.span_len, f.key_shift, p.bucket_log2);
+  return f;
+}
+
+// Interval search of N distances d = word - span_lo per lane: region, and the offset inside it if
+// the entry holds the word (else any value at or above the entry's size: see hit).
+// The place among the keys of the bucket is found without branches: the step count is the one
+// that the fullest of the wave's buckets needs, a step that leads past the bucket meets keys
+// above the word's (keys ascend over the whole table) or the padding.
+template <int N>
+__device__ __forceinline__ void flat_search(const ScanParams& p, const FlatLevel& f, const u64 (&d)[N], u32 (&n)[N],
+                                            u64 (&off)[N], bool (&hit)[N]) {
+  u32 kw[N], at[N], most = 0;  // at: byte offset of the first key not known to be at or below the word's
+#pragma unroll
+  for (int c = 0; c < N; ++c) {
+    kw[c] = (u32)(d[c] >> f.key_shift);
+    const u32 bk = kw[c] >> f.bucket_shift;
+    const u32 lo = f.bst[bk], hi = f.bst[bk + 1];
+    at[c] = lo * 4;
+    most |= hi - lo;
+  }
+  u32 steps = 0;
+  while (ballot((most >> steps) != 0)) ++steps;  // 2^steps > every lane's count
+  for (; steps > 3; --steps) {
+    const u32 step = 4u << (steps - 1);
+    u32 k[N];
+#pragma unroll
+    for (int c = 0; c < N; ++c) k[c] = *reinterpret_cast<const u32*>(f.keys + min(at[c] + step - 4, f.last_at));
+#pragma unroll
+    for (int c = 0; c < N; ++c) at[c] += k[c] <= kw[c] ? step : 0u;
+  }
+  auto fixed = [&](auto step_c) {
+    constexpr u32 step = decltype(step_c)::value;
+    u32 k[N];
+#pragma unroll
+    for (int c = 0; c < N; ++c) k[c] = *reinterpret_cast<const u32*>(f.keys + at[c] + (step - 4));
+#pragma unroll
+    for (int c = 0; c < N; ++c) at[c] += k[c] <= kw[c] ? step : 0u;
+  };
+  if (steps >= 3) fixed(std::integral_constant<u32, 16>{});
+  if (steps >= 2) fixed(std::integral_constant<u32, 8>{});
+  if (steps >= 1) fixed(std::integral_constant<u32, 4>{});
+  const unsigned char* table = reinterpret_cast<const unsigned char*>(p.table);
+  u64x2 e[N];
+#pragma unroll
+  for (int c = 0; c < N; ++c) {
+    at[c] -= 4;  // the last key not above the word's; key 0 is 0
+    e[c] = *reinterpret_cast<const u64x2*>(table + at[c] * 4);
+  }
+  // a base with the word's own truncated key may still lie above the word: one entry back, or,
+  // where a run of blocks shares a key, a search among the exact bases
+#pragma unroll
+  for (int c = 0; c < N; ++c) {
+    const u64 w = d[c] + f.span_lo;
+    n[c] = at[c] >> 2;
+    for (u32 step = 0; e[c].x > w; ++step) {
+      if (step < 4) {
+        --n[c];
+      } else {
+        u32 a = 0, b = n[c];  // the last entry of [a, b) that is not above the word
+        while (b - a > 1) {
+          const u32 mid = a + ((b - a) >> 1);
+          if (p.table[mid].base <= w) a = mid;
+          else b = mid;
+        }
+        n[c] = a;
+      }
+      e[c] = *reinterpret_cast<const u64x2*>(&p.table[n[c]]);
+    }
+    off[c] = w - e[c].x;
+    hit[c] = off[c] < e[c].y;
+  }
+}
+
+// A wave's sub-tile: the candidates go to the wave's queue in word order, as distances from
+// the span's start, and are searched in dense rounds of 64.  Round r's lane l holds in tag / off
+// what became of candidate 64 r + l: tag = region << 9 | word of the sub-tile, kMiss if no hit.
+struct FlatResult {
+  u32 tag[kFlatRounds];
+  u64 off[kFlatRounds];
+  u32 Q, H, sub;
+};
+
+template <int N, int R0>
+__device__ __forceinline__ void flat_rounds(const ScanParams& p, const FlatLevel& f, u32 wn, const u64* qw,
+                                            const unsigned short* qi, FlatResult& r) {
+  const u32 lane = lane_id();
+  u64 d[N];
+  u32 n[N], idx[N];
+  bool hit[N];
+  u64 off[N];
+#pragma unroll
+  for (int c = 0; c < N; ++c) {
+    const u32 q = (u32)c * 64 + lane;
+    d[c] = qw[q];
+    idx[c] = qi[q];
+    if (c == N - 1 && q >= wn) d[c] = 0;  // rounds before the last are full
+  }
+  flat_search<N>(p, f, d, n, off, hit);
+#pragma unroll
+  for (int c = 0; c < N; ++c) {
+    if (c == N - 1) hit[c] = hit[c] && (u32)c * 64 + lane < wn;
+    r.tag[R0 + c] = hit[c] ? (n[c] << 9 | idx[c]) : kMiss;
+    r.off[R0 + c] = off[c];
+    r.H += __popcll(ballot(hit[c]));
+  }
+}
+
+// Candidates with rank in [win, win + kFlatQ), in word order, to the queue.  Returns the sub-tile's
+// candidates.
+template <bool kHalf>
+__device__ __forceinline__ u32 flat_enqueue(const FlatLevel& f, const u64 (&w)[kWpl], u32 win, u64* qw,
+                                            unsigned short* qi) {
+  constexpr int kPer = kHalf ? 4 : 2;
+  const u32 lane = lane_id();
+  u32 Q = 0;
+  wave_lds_fence();
+#pragma unroll
+  for (int k = 0; k < kWpl / kPer; ++k) {
+    u32 rank = Q - win;  // of this lane's first candidate in the piece
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      const u64 m = ballot(w[kPer * k + j] - f.span_lo < f.span_len);
+      rank = __builtin_amdgcn_mbcnt_hi((u32)(m >> 32), __builtin_amdgcn_mbcnt_lo((u32)m, rank));
+      Q += __popcll(m);
+    }
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      const u64 d = w[kPer * k + j] - f.span_lo;
+      if (d < f.span_len) {
+        if (rank < kFlatQ) {
+          qw[rank] = d;
+          qi[rank] = (unsigned short)pos_in_sub<kHalf>(kPer * k + j, lane);
+        }
+        ++rank;
+      }
+    }
+  }
+  wave_lds_fence();
+  return Q;
+}
+
+template <int kWin>
+__device__ __forceinline__ void flat_window(const ScanParams& p, const FlatLevel& f, const u64* qw,
+                                            const unsigned short* qi, FlatResult& r) {
+  constexpr int R0 = kWin * (int)(kFlatQ / 64);
+  const u32 left = r.Q - kWin * kFlatQ, wn = left < kFlatQ ? left : kFlatQ;
+  if (wn > 192) flat_rounds<4, R0>(p, f, wn, qw, qi, r);
+  else if (wn > 128) flat_rounds<3, R0>(p, f, wn, qw, qi, r);
+  else if (wn > 64) flat_rounds<2, R0>(p, f, wn, qw, qi, r);
+  else flat_rounds<1, R0>(p, f, wn, qw, qi, r);
+}
+
+template <bool kHalf>
+__device__ __forceinline__ void flat_classify(const ScanParams& p, const FlatLevel& f, u32 sub, const u64 (&w)[kWpl],
+                                              u64* qw, unsigned short* qi, FlatResult& r) {
+  r.Q = flat_enqueue<kHalf>(f, w, 0, qw, qi);
+  r.H = 0;
+  r.sub = sub;
+  if (r.Q) flat_window<0>(p, f, qw, qi, r);
+  if (r.Q > kFlatQ) {
+    flat_enqueue<kHalf>(f, w, kFlatQ, qw, qi);
+    flat_window<1>(p, f, qw, qi, r);
+  }
+  static_assert(2 * kFlatQ == kSub, "two windows hold every word");
+}
+
+__device__ __forceinline__ void flat_write(const ScanParams& p, const FlatResult& r, u64 pos) {
+  const u32 wbase = r.sub * (u32)kSub;
+#pragma unroll
+  for (int k = 0; k < kFlatRounds; ++k) {
+    if ((u32)k * 64 < r.Q) {
+      const bool hit = r.tag[k] != kMiss;
+      const u64 m = ballot(hit);
+      if (hit)
+        store_reloc(p, pos + __builtin_amdgcn_mbcnt_hi((u32)(m >> 32), __builtin_amdgcn_mbcnt_lo((u32)m, 0)),
+                    wbase + (r.tag[k] & 511u), r.tag[k] >> 9, r.off[k]);
+      pos += __popcll(m);
+    }
+  }
+}
+
+// The ordered scan's state is left ready for the next call without a count of the workgroups
+// that are through (256 additions to one address at 12 ns each, at the end of the launch where
+// nothing hides them): there are two sets of chunk states, launches take turns with them, and
+// each launch clears what the one before it wrote in the other set.  Ticket and turn are reset by
+// whoever makes the launch's last draw: every workgroup has read the turn before its first
+// draw, so nobody looks at either again.
+struct FlatTurn {
+  u64 *cstate, *other;  // this launch's states; those of the launch before
+  u32 dirty;            // states that the launch before has written
+};
+__device__ __forceinline__ FlatTurn flat_turn(const ScanParams& p, u32 turn) {
+  const u64 max_words = p.prepared ? p.prepared[2] : p.n_words;
+  const u64 stride = chunk_state_bytes(max_words) / 8 * kFlatStateStride;
+  FlatTurn t;
+  t.dirty = turn >> 1;
+  t.cstate = p.cstate + (turn & 1 ? stride : 0);
+  t.other = p.cstate + (turn & 1 ? 0 : stride);
+  return t;
+}
+__device__ __forceinline__ u32 flat_draw(const ScanParams& p, u32 turn, u32 last_draw) {
+  const u32 got = atomicAdd(p.ticket, 1u);
+  if (got == last_draw) {
+    __hip_atomic_store(p.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(p.turn, p.n_chunks << 1 | (~turn & 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  return got;
+}
+
+// The ordered scan, as scan_kernel below: chunks (a sub-tile per wave) by ticket, the look-back
+// one round late, by one wave.
+template <int kW, bool kHalf>
+__global__ __launch_bounds__((kW + 1) * 64) void scan_flat_kernel(ScanParams p) {
+  constexpr u32 kThreads = (kW + 1) * 64;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  __shared__ u32 s_next[2], s_cnt[2][kW], s_turn;
+  __shared__ u64 s_excl[2];
+  const u32 tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const bool clerk = wave == kW;
+  u32 turn = 0;  // (lies in the prepared table's first block, which the check reads too)
+  if (clerk) turn = __hip_atomic_load(p.turn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (!prepared_ok(p)) {  // every workgroup sees the same: nothing is read or written
+    if (blockIdx.x == 0 && tid == 0) raise_status(p.d_status, FDY_ST_BAD_PREPARED);
+    return;
+  }
+  const bool single = gridDim.x >= p.n_chunks;  // every workgroup's first draw is its only chunk
+  // the draw after which nobody draws again
+  const u32 last_draw = single ? gridDim.x - 1 : p.n_chunks + gridDim.x - 1;
+  if (clerk && lane == 0) {
+    asm volatile("" : "+v"(turn) : : "memory");  // the turn has arrived before the draw goes out
+    s_turn = turn;
+    s_next[0] = flat_draw(p, turn, last_draw);
+  }
+  const FlatLevel f = flat_stage<kThreads>(p, smem_raw);
+  __syncthreads();
+  u32 chunk = s_next[0];
+  const FlatTurn states = flat_turn(p, s_turn);
+  if (clerk) {
+    for (u32 i = blockIdx.x * 64 + lane; i < states.dirty; i += gridDim.x * 64) st_state(&states.other[(u64)i * kFlatStateStride], 0);
+    u64* const cstate = states.cstate;
+    u32 prev = 0, prev_total = 0, b = 1;
+    // the exclusive prefix of the chunk before, for the workers that wait to write it
+    auto close = [&](u32 slot) {
+      const u64 excl = chunk_exclusive_prefix<kFlatLook, kFlatStateStride>(cstate, prev, p.spin_limit, p.d_status);
+      if (lane == 0) {
+        if (prev != 0) st_state(&cstate[(u64)prev * kFlatStateStride], kFlagInc | ((excl + prev_total) & kValMask));
+        if (prev + 1 == p.n_chunks) {  // the last chunk: the grand total
+          *p.d_count = excl + prev_total;
+          if (excl + prev_total > p.capacity) raise_status(p.d_status, FDY_ST_CAPACITY);
+        }
+        s_excl[slot] = excl;
+      }
+    };
+    bool have_prev = false;
+    for (; chunk < p.n_chunks; b ^= 1) {
+      u32 next = p.n_chunks;
+      if (lane == 0 && !single) next = flat_draw(p, turn, last_draw);
+      if (have_prev) close(b);
+      if (lane == 0) s_next[b] = next;
+      __syncthreads();
+      u32 total = 0;
+#pragma unroll
+      for (int i = 0; i < kW; ++i) total += s_cnt[b][i];
+      if (lane == 0) st_state(&cstate[(u64)chunk * kFlatStateStride], (chunk == 0 ? kFlagInc : kFlagAgg) | total);
+      prev = chunk;
+      prev_total = total;
+      have_prev = true;
+      chunk = s_next[b];
+    }
+    if (have_prev) {
+      close(b);
+      __syncthreads();
+    }
+    return;
+  }
+  unsigned char* qb = smem_raw + flat_level_bytes(p.top_n, p.bucket_log2);
+  u64* qw = reinterpret_cast<u64*>(qb) + wave * kFlatQ;
+  unsigned short* qi = reinterpret_cast<unsigned short*>(qb + (size_t)kW * kFlatQ * 8) + wave * kFlatQ;
+  u64 w[kWpl];
+  load_words<kHalf>(p, chunk * kW + wave, f.span_lo, w);
+  FlatResult cur, prev;
+  u32 prev_before = 0, b = 1;
+  bool have_prev = false;
+  for (; chunk < p.n_chunks; b ^= 1) {
+    flat_classify<kHalf>(p, f, chunk * kW + wave, w, qw, qi, cur);
+    if (lane == 0) s_cnt[b][wave] = cur.H;
+    __syncthreads();  // counts, the next ticket and the previous chunk's prefix are visible
+    const u32 nchunk = s_next[b];
+    load_words<kHalf>(p, nchunk * kW + wave, f.span_lo, w);  // in flight during the write
+    u32 before = 0;
+#pragma unroll
+    for (int i = 0; i < kW; ++i) before += (u32)i < wave ? s_cnt[b][i] : 0;
+    if (have_prev) flat_write(p, prev, s_excl[b] + prev_before);
+    prev = cur;
+    prev_before = before;
+    have_prev = true;
+    chunk = nchunk;
+  }
+  if (have_prev) {
+    __syncthreads();
+    flat_write(p, prev, s_excl[b] + prev_before);
+  }
+}
+
 // kOut: the scan also writes the rebased copy of the words (p.out, p.new_base).  A wave then
 // keeps the words of its group in LDS instead of queueing the candidates' values (the queue
 // holds their indices only and the search reads them through those); a hit's word is
@@ -1186,7 +1573,7 @@ __global__ __launch_bounds__(kBlock) void scan_kernel(ScanParams p) {
     if (closer && have_prev) {
       const u32 pchunk = prev.base / kChunk;
       const u64 total = __shfl(prev.cnt_incl, 63);
-      const u64 excl = chunk_exclusive_prefix(p.cstate, pchunk, p.spin_limit, p.d_status);
+      const u64 excl = chunk_exclusive_prefix<1, 1>(p.cstate, pchunk, p.spin_limit, p.d_status);
       if (lane == 0) {
         if (pchunk != 0) st_state(&p.cstate[pchunk], kFlagInc | ((excl + total) & kValMask));
         if (prev.base + kChunk >= p.n_sub) {  // the last chunk: the grand total
@@ -1222,7 +1609,7 @@ __global__ __launch_bounds__(kBlock) void scan_kernel(ScanParams p) {
     if (closer) {
       const u32 pchunk = prev.base / kChunk;
       const u64 total = __shfl(prev.cnt_incl, 63);
-      const u64 excl = chunk_exclusive_prefix(p.cstate, pchunk, p.spin_limit, p.d_status);
+      const u64 excl = chunk_exclusive_prefix<1, 1>(p.cstate, pchunk, p.spin_limit, p.d_status);
       if (lane == 0) {
         if (pchunk != 0) st_state(&p.cstate[pchunk], kFlagInc | ((excl + total) & kValMask));
         if (prev.base + kChunk >= p.n_sub) {  // the last chunk: the grand total
@@ -1710,10 +2097,9 @@ struct RunPlan {
 };
 
 constexpr size_t kStateHeader = 256;
-size_t state_bytes(u64 n_words) {
-  const u64 n_sub = (n_words + kSub - 1) / kSub;
-  const u64 small_chunk = (u64)kWaves * kGroupsSmall * kGSmall;
-  return kStateHeader + align256((size_t)((n_sub + small_chunk - 1) / small_chunk) * 8);
+// Tables without packed levels have two sets of chunk states (see FlatTurn).
+size_t state_bytes(u64 n_words, u32 levels) {
+  return kStateHeader + chunk_state_bytes(n_words) * (levels ? 1 : 2 * kFlatStateStride);
 }
 
 void plan_run(u64 n_words, RunPlan* rp) {
@@ -1730,7 +2116,11 @@ void plan_run(u64 n_words, RunPlan* rp) {
   rp->stage_wgs = rp->n_chunks < kStageWgs ? rp->n_chunks : kStageWgs;
   rp->stage_bytes = align256((size_t)rp->stage_wgs * 2 * chunk * kSub * sizeof(fdy_reloc));
 }
-
+// Workers per workgroup of the scans of tables without packed levels.  Measured (us, 7 / 15
+// workers, a quarter pointers, 4,096 allocations): 17 sub-tiles 6.0 / 9.0, 1,024 9.4 / 9.2, 1,536
+// 10.3 / 9.6, 2,048 12.9 / 10.4, 4,096 23 / 14.5, 16,384 50 / 33: many small workgroups start
+// sooner and share the staging's latency, but each chunk costs a ticket and a look-back.
+u32 flat_workers(u32 n_sub) { return n_sub < 1536 ? kFlatWorkers : kFlatWorkersBig; }
 
 void fill_init(ScanInit* a, const fdy_alloc* d_table, u32 n_alloc, const TablePlan& tp, unsigned char* tb) {
   a->table = d_table;
@@ -1781,7 +2171,7 @@ extern "C" size_t fdy_scan_workspace_bytes(uint64_t n_words, uint32_t n_alloc) {
   if (n_words > kMaxWords) return 0;
   TablePlan tp;
   if (!plan_table(n_alloc, &tp)) return 0;
-  return state_bytes(n_words) + tp.bytes;
+  return state_bytes(n_words, tp.levels) + tp.bytes;
 }
 
 extern "C" size_t fdy_scan_staging_bytes(uint64_t n_words) {
@@ -1795,7 +2185,7 @@ extern "C" size_t fdy_scan_table_bytes(uint32_t n_alloc, uint64_t max_words) {
   if (max_words > kMaxWords) return 0;
   TablePlan tp;
   if (!plan_table(n_alloc, &tp)) return 0;
-  return kPreparedHeader + state_bytes(max_words) + tp.bytes;
+  return kPreparedHeader + state_bytes(max_words, tp.levels) + tp.bytes;
 }
 
 extern "C" int fdy_scan_table_prepare(const fdy_alloc* d_table, uint32_t n_alloc, uint64_t max_words,
@@ -1804,7 +2194,7 @@ extern "C" int fdy_scan_table_prepare(const fdy_alloc* d_table, uint32_t n_alloc
   if (n_alloc && (!d_table || ((uintptr_t)d_table & 15))) return FDY_ERR_INVALID_ARG;
   TablePlan tp;
   if (!plan_table(n_alloc, &tp)) return FDY_ERR_INVALID_ARG;
-  const size_t need = kPreparedHeader + state_bytes(max_words) + tp.bytes;
+  const size_t need = kPreparedHeader + state_bytes(max_words, tp.levels) + tp.bytes;
   if (!d_prepared || ((uintptr_t)d_prepared & 255) || prepared_bytes < need) return FDY_ERR_WORKSPACE;
   hipStream_t stream = (hipStream_t)hip_stream;
   (void)hipGetLastError();
@@ -1819,7 +2209,7 @@ extern "C" int fdy_scan_table_prepare(const fdy_alloc* d_table, uint32_t n_alloc
   a.hdr.table_ptr = (u64)(uintptr_t)d_table;
   a.header = (u32*)(pb + kPreparedHeader + tp.bytes);
   a.cstate = (u64*)(pb + kPreparedHeader + tp.bytes + kStateHeader);
-  a.n_chunks = (u32)((state_bytes(max_words) - kStateHeader) / 8);
+  a.n_chunks = (u32)((state_bytes(max_words, tp.levels) - kStateHeader) / 8);
   a.d_count = nullptr;
   const u32 n_init = init_threads(tp, a.n_chunks);
   launch(FDY_PROF_SCAN_INIT, scan_init_kernel, dim3((n_init + 255) / 256), dim3(256), 0, stream, a);
@@ -1845,6 +2235,9 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
   if (!plan_table(n_alloc, &tp)) return FDY_ERR_INVALID_ARG;
   RunPlan rp;
   plan_run(n_words, &rp);
+  const bool flat = tp.levels == 0 && !d_out;  // every base has its key in LDS
+  const u32 flat_w = flat_workers(rp.n_sub);
+  const u32 n_chunks = flat ? (rp.n_sub + flat_w - 1) / flat_w : rp.n_chunks;
   // where things lie
   unsigned char* ws = (unsigned char*)d_workspace;
   unsigned char *state, *tb, *stage;
@@ -1857,10 +2250,10 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
     if (ws && ((uintptr_t)ws & 255)) return FDY_ERR_WORKSPACE;
     stage = ws && workspace_bytes >= rp.stage_bytes ? ws : nullptr;
   } else {
-    const size_t need = state_bytes(n_words) + tp.bytes;
+    const size_t need = state_bytes(n_words, tp.levels) + tp.bytes;
     if (!ws || ((uintptr_t)ws & 255) || workspace_bytes < need) return FDY_ERR_WORKSPACE;
     state = ws;
-    tb = ws + state_bytes(n_words);
+    tb = ws + state_bytes(n_words, tp.levels);
     stage = workspace_bytes >= need + rp.stage_bytes ? tb + tp.bytes : nullptr;
   }
   hipStream_t stream = (hipStream_t)hip_stream;
@@ -1884,9 +2277,9 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
   } else {
     a.header = (u32*)state;
     a.cstate = (u64*)(state + kStateHeader);
-    a.n_chunks = rp.n_chunks;
+    a.n_chunks = flat ? n_chunks * kFlatStateStride : n_chunks;
     a.d_count = nothing ? (u64*)d_count : nullptr;
-    const u32 n_init = init_threads(tp, rp.n_chunks);
+    const u32 n_init = init_threads(tp, a.n_chunks);
     launch(FDY_PROF_SCAN_INIT, scan_init_kernel, dim3((n_init + 255) / 256), dim3(256), 0, stream, a);
     FDY_HIP_TRY(hipGetLastError());
   }
@@ -1909,8 +2302,9 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
   p.ticket = (u32*)state;
   p.done = (u32*)state + 1;
   p.acc = (u64*)state + 1;
+  p.turn = d_prepared ? (u32*)const_cast<void*>(d_prepared) + kPreparedTurn / 4 : (u32*)state + 8;
   p.cstate = (u64*)(state + kStateHeader);
-  p.n_chunks = rp.n_chunks;
+  p.n_chunks = n_chunks;
   p.self_clean = d_prepared ? 1u : 0u;
   p.prepared = (const u64*)d_prepared;
   p.top_log2 = (u32)fdy__tune_get(FDY_TUNE_SCAN_TOP_LOG2);
@@ -1940,6 +2334,25 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
   p.spin_limit = (u32)fdy__tune_get(FDY_TUNE_SCAN_SPIN_LIMIT);
   p.new_base = (const u64*)d_new_base;
   p.out = (u64*)d_out;
+
+  if (flat) {
+    const size_t lds = flat_level_bytes(tp.top_n, p.bucket_log2) + (size_t)flat_w * kFlatQ * 10;
+    // as many workgroups as can be resident (128 registers per lane: 16 waves per compute unit)
+    const u32 fit = (u32)(160 * 1024 / (lds + 512)), room = 16u / (flat_w + 1);
+    u32 fgrid = (u32)n_cu * (fit < room ? fit : room);
+    if (fgrid > p.n_chunks) fgrid = p.n_chunks;
+    auto form = [&](auto w_c) {
+      constexpr int kW = decltype(w_c)::value;
+      return half ? scan_flat_kernel<kW, true> : scan_flat_kernel<kW, false>;
+    };
+    const bool wide = flat_w == kFlatWorkersBig;
+    auto kern = wide ? form(std::integral_constant<int, kFlatWorkersBig>{}) : form(std::integral_constant<int, kFlatWorkers>{});
+    static std::atomic<u64> allowed[4];  // one per instance that form() can return
+    if (const int rc = allow_full_lds(kern, dev, allowed[(wide ? 2 : 0) + (half ? 1 : 0)])) return rc;
+    launch(FDY_PROF_SCAN_MAIN, kern, dim3(fgrid), dim3((flat_w + 1) * 64), lds, stream, p);
+    FDY_HIP_TRY(hipGetLastError());
+    return FDY_OK;
+  }
 
   const size_t lds0 = level0_key_bytes(tp.top_n, ordered_out) + (((((size_t)1 << p.bucket_log2) + 1) * 2 + 15) & ~(size_t)15);
   if (fused) {
