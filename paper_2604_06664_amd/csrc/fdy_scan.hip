@@ -1079,7 +1079,7 @@ __device__ __forceinline__ void write_round(const ScanParams& p, const RoundResu
 // The same input now takes 25.2 us, 3.7 M words against 16,384 allocations 20.9 (28.2), 0.76 M
 // words 10.6 (13.8); at 33 M words and a quarter pointers 101 us (116), 4.0 TB/s of words in and
 // relocations out.
-constexpr int kFlatWorkers = 7, kFlatWorkersBig = 15;
+constexpr int kFlatWorkers = 7, kFlatWorkersBig = 15, kFlatWorkersOut = 11, kRebaseWaves = 8;
 constexpr u32 kFlatQ = 256;      // queue entries per wave
 constexpr int kFlatRounds = 8;   // rounds of 64 candidates per sub-tile: one sub-tile's words
 constexpr u32 kFlatPad = 8;      // keys behind the last one (all ones)
@@ -1193,8 +1193,8 @@ struct FlatResult {
   u32 Q, H, sub;
 };
 
-template <int N, int R0>
-__device__ __forceinline__ void flat_rounds(const ScanParams& p, const FlatLevel& f, u32 wn, const u64* qw,
+template <bool kOut, int N, int R0>
+__device__ __forceinline__ void flat_rounds(const ScanParams& p, const FlatLevel& f, u32 wn, u64* qw,
                                             const unsigned short* qi, FlatResult& r) {
   const u32 lane = lane_id();
   u64 d[N];
@@ -1216,15 +1216,28 @@ __device__ __forceinline__ void flat_rounds(const ScanParams& p, const FlatLevel
     r.off[R0 + c] = off[c];
     r.H += __popcll(ballot(hit[c]));
   }
+  if constexpr (kOut) {
+    u64 nb[N];
+#pragma unroll
+    for (int c = 0; c < N; ++c) nb[c] = hit[c] ? p.new_base[n[c]] : 0;
+#pragma unroll
+    for (int c = 0; c < N; ++c) qw[c * 64 + lane] = hit[c] ? nb[c] + off[c] : d[c] + f.span_lo;
+  }
 }
 
-// Candidates with rank in [win, win + kFlatQ), in word order, to the queue.  Returns the sub-tile's
-// candidates.
-template <bool kHalf>
-__device__ __forceinline__ u32 flat_enqueue(const FlatLevel& f, const u64 (&w)[kWpl], u32 win, u64* qw,
-                                            unsigned short* qi) {
+// Which of the lane's eight words are candidates, one bit each.
+__device__ __forceinline__ u32 flat_candidates(const FlatLevel& f, const u64 (&w)[kWpl]) {
+  u32 mask = 0;
+#pragma unroll
+  for (int k = 0; k < kWpl; ++k) mask |= w[k] - f.span_lo < f.span_len ? 1u << k : 0u;
+  return mask;
+}
+
+// Calls visit(k, slot) for the lane's candidates (word k) with rank in [win, win + kFlatQ), ranks in
+// word order, slot = rank - win.  Returns the sub-tile's candidates.
+template <bool kHalf, typename Visit>
+__device__ __forceinline__ u32 flat_slots(u32 mask, u32 win, Visit visit) {
   constexpr int kPer = kHalf ? 4 : 2;
-  const u32 lane = lane_id();
   u32 Q = 0;
   wave_lds_fence();
 #pragma unroll
@@ -1232,47 +1245,54 @@ __device__ __forceinline__ u32 flat_enqueue(const FlatLevel& f, const u64 (&w)[k
     u32 rank = Q - win;  // of this lane's first candidate in the piece
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
-      const u64 m = ballot(w[kPer * k + j] - f.span_lo < f.span_len);
+      const u64 m = ballot((mask >> (kPer * k + j) & 1) != 0);
       rank = __builtin_amdgcn_mbcnt_hi((u32)(m >> 32), __builtin_amdgcn_mbcnt_lo((u32)m, rank));
       Q += __popcll(m);
     }
 #pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-      const u64 d = w[kPer * k + j] - f.span_lo;
-      if (d < f.span_len) {
-        if (rank < kFlatQ) {
-          qw[rank] = d;
-          qi[rank] = (unsigned short)pos_in_sub<kHalf>(kPer * k + j, lane);
-        }
+    for (int j = 0; j < kPer; ++j)
+      if (mask >> (kPer * k + j) & 1) {
+        if (rank < kFlatQ) visit(kPer * k + j, rank);
         ++rank;
       }
-    }
   }
   wave_lds_fence();
   return Q;
 }
 
-template <int kWin>
-__device__ __forceinline__ void flat_window(const ScanParams& p, const FlatLevel& f, const u64* qw,
+template <bool kOut, int kWin>
+__device__ __forceinline__ void flat_window(const ScanParams& p, const FlatLevel& f, u64* qw,
                                             const unsigned short* qi, FlatResult& r) {
   constexpr int R0 = kWin * (int)(kFlatQ / 64);
   const u32 left = r.Q - kWin * kFlatQ, wn = left < kFlatQ ? left : kFlatQ;
-  if (wn > 192) flat_rounds<4, R0>(p, f, wn, qw, qi, r);
-  else if (wn > 128) flat_rounds<3, R0>(p, f, wn, qw, qi, r);
-  else if (wn > 64) flat_rounds<2, R0>(p, f, wn, qw, qi, r);
-  else flat_rounds<1, R0>(p, f, wn, qw, qi, r);
+  if (wn > 192) flat_rounds<kOut, 4, R0>(p, f, wn, qw, qi, r);
+  else if (wn > 128) flat_rounds<kOut, 3, R0>(p, f, wn, qw, qi, r);
+  else if (wn > 64) flat_rounds<kOut, 2, R0>(p, f, wn, qw, qi, r);
+  else flat_rounds<kOut, 1, R0>(p, f, wn, qw, qi, r);
 }
 
-template <bool kHalf>
-__device__ __forceinline__ void flat_classify(const ScanParams& p, const FlatLevel& f, u32 sub, const u64 (&w)[kWpl],
+// kOut: hits among the lane's words are replaced by their rebased values (the search leaves every
+// candidate's final value in its queue slot).
+template <bool kHalf, bool kOut>
+__device__ __forceinline__ void flat_classify(const ScanParams& p, const FlatLevel& f, u32 sub, u64 (&w)[kWpl],
                                               u64* qw, unsigned short* qi, FlatResult& r) {
-  r.Q = flat_enqueue<kHalf>(f, w, 0, qw, qi);
+  const u32 mask = flat_candidates(f, w), lane = lane_id();
+  auto put = [&](int k, u32 slot) {
+    qw[slot] = w[k] - f.span_lo;
+    qi[slot] = (unsigned short)pos_in_sub<kHalf>(k, lane);
+  };
+  auto take = [&](int k, u32 slot) { w[k] = qw[slot]; };
+  r.Q = flat_slots<kHalf>(mask, 0, put);
   r.H = 0;
   r.sub = sub;
-  if (r.Q) flat_window<0>(p, f, qw, qi, r);
+  if (r.Q) {
+    flat_window<kOut, 0>(p, f, qw, qi, r);
+    if constexpr (kOut) flat_slots<kHalf>(mask, 0, take);
+  }
   if (r.Q > kFlatQ) {
-    flat_enqueue<kHalf>(f, w, kFlatQ, qw, qi);
-    flat_window<1>(p, f, qw, qi, r);
+    flat_slots<kHalf>(mask, kFlatQ, put);
+    flat_window<kOut, 1>(p, f, qw, qi, r);
+    if constexpr (kOut) flat_slots<kHalf>(mask, kFlatQ, take);
   }
   static_assert(2 * kFlatQ == kSub, "two windows hold every word");
 }
@@ -1304,11 +1324,11 @@ struct FlatTurn {
 };
 __device__ __forceinline__ FlatTurn flat_turn(const ScanParams& p, u32 turn) {
   const u64 max_words = p.prepared ? p.prepared[2] : p.n_words;
-  const u64 stride = chunk_state_bytes(max_words) / 8 * kFlatStateStride;
+  const u64 general = chunk_state_bytes(max_words) / 8, stride = general * kFlatStateStride;
   FlatTurn t;
   t.dirty = turn >> 1;
-  t.cstate = p.cstate + (turn & 1 ? stride : 0);
-  t.other = p.cstate + (turn & 1 ? 0 : stride);
+  t.cstate = p.cstate + general + (turn & 1 ? stride : 0);
+  t.other = p.cstate + general + (turn & 1 ? 0 : stride);
   return t;
 }
 __device__ __forceinline__ u32 flat_draw(const ScanParams& p, u32 turn, u32 last_draw) {
@@ -1322,7 +1342,7 @@ __device__ __forceinline__ u32 flat_draw(const ScanParams& p, u32 turn, u32 last
 
 // The ordered scan, as scan_kernel below: chunks (a sub-tile per wave) by ticket, the look-back
 // one round late, by one wave.
-template <int kW, bool kHalf>
+template <int kW, bool kHalf, bool kOut>
 __global__ __launch_bounds__((kW + 1) * 64) void scan_flat_kernel(ScanParams p) {
   constexpr u32 kThreads = (kW + 1) * 64;
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -1395,7 +1415,8 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_flat_kernel(ScanParams p) 
   u32 prev_before = 0, b = 1;
   bool have_prev = false;
   for (; chunk < p.n_chunks; b ^= 1) {
-    flat_classify<kHalf>(p, f, chunk * kW + wave, w, qw, qi, cur);
+    flat_classify<kHalf, kOut>(p, f, chunk * kW + wave, w, qw, qi, cur);
+    if constexpr (kOut) store_words<true>(p, chunk * kW + wave, w);
     if (lane == 0) s_cnt[b][wave] = cur.H;
     __syncthreads();  // counts, the next ticket and the previous chunk's prefix are visible
     const u32 nchunk = s_next[b];
@@ -1412,6 +1433,88 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_flat_kernel(ScanParams p) 
   if (have_prev) {
     __syncthreads();
     flat_write(p, prev, s_excl[b] + prev_before);
+  }
+}
+
+// Rebases the queue's first min(left, kFlatQ) candidates in place; returns the hits among them.
+template <int N>
+__device__ __forceinline__ u32 flat_rebase_round(const ScanParams& p, const FlatLevel& f, u32 wn, u64* qw) {
+  const u32 lane = lane_id();
+  u64 d[N], off[N], nb[N];
+  u32 n[N], H = 0;
+  bool hit[N];
+#pragma unroll
+  for (int c = 0; c < N; ++c) {
+    d[c] = qw[c * 64 + lane];
+    if (c == N - 1 && (u32)c * 64 + lane >= wn) d[c] = 0;
+  }
+  flat_search<N>(p, f, d, n, off, hit);
+#pragma unroll
+  for (int c = 0; c < N; ++c) nb[c] = hit[c] ? p.new_base[n[c]] : 0;
+#pragma unroll
+  for (int c = 0; c < N; ++c) {
+    qw[c * 64 + lane] = hit[c] ? nb[c] + off[c] : d[c] + f.span_lo;
+    H += __popcll(ballot(hit[c] && (u32)c * 64 + lane < wn));
+  }
+  return H;
+}
+__device__ __forceinline__ u32 flat_rebase_rounds(const ScanParams& p, const FlatLevel& f, u32 left, u64* qw) {
+  const u32 wn = left < kFlatQ ? left : kFlatQ;
+  if (wn > 192) return flat_rebase_round<4>(p, f, wn, qw);
+  if (wn > 128) return flat_rebase_round<3>(p, f, wn, qw);
+  if (wn > 64) return flat_rebase_round<2>(p, f, wn, qw);
+  return flat_rebase_round<1>(p, f, wn, qw);
+}
+
+// The unordered form (rebased words, no relocation table): no tickets and no look-back, waves
+// stride over the sub-tiles on their own.  A workgroup's hits and "one more is through" go to one
+// 64-bit counter in one addition (same-address additions are served one after the other, 12 ns
+// each: one per wave, as it was, is 25 us of them); the workgroup that finds itself last
+// publishes the sum and leaves the counter zero.
+template <int kW>
+__global__ __launch_bounds__(kW * 64) void rebase_flat_kernel(ScanParams p) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  __shared__ u32 s_hits[kW];
+  const u32 tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (!prepared_ok(p)) {  // every workgroup sees the same: nothing is read or written
+    if (blockIdx.x == 0 && tid == 0) raise_status(p.d_status, FDY_ST_BAD_PREPARED);
+    return;
+  }
+  const FlatLevel f = flat_stage<kW * 64>(p, smem_raw);
+  unsigned char* qb = smem_raw + flat_level_bytes(p.top_n, p.bucket_log2);
+  u64* qw = reinterpret_cast<u64*>(qb) + wave * kFlatQ;
+  const u32 stride = gridDim.x * kW;
+  u32 sub = blockIdx.x * kW + wave;
+  u64 w[kWpl];
+  load_words<false>(p, sub, f.span_lo, w);
+  __syncthreads();
+  u32 H = 0;
+  for (; sub < p.n_sub; sub += stride) {
+    u64 nw[kWpl];
+    load_words<false>(p, sub + stride, f.span_lo, nw);  // in flight during the search
+    const u32 mask = flat_candidates(f, w);
+    for (u32 win = 0;; win += kFlatQ) {
+      const u32 Q = flat_slots<false>(mask, win, [&](int k, u32 slot) { qw[slot] = w[k] - f.span_lo; });
+      if (win >= Q) break;
+      H += flat_rebase_rounds(p, f, Q - win, qw);
+      flat_slots<false>(mask, win, [&](int k, u32 slot) { w[k] = qw[slot]; });
+      if (Q - win <= kFlatQ) break;
+    }
+    store_words<true>(p, sub, w);
+#pragma unroll
+    for (int k = 0; k < kWpl; ++k) w[k] = nw[k];
+  }
+  if (lane == 0) s_hits[wave] = H;
+  __syncthreads();
+  if (tid == 0) {
+    constexpr int kDoneShift = 40;  // hits stay below 2^32, workgroups below 2^20
+    u64 mine = 1ull << kDoneShift;
+    for (int i = 0; i < kW; ++i) mine += s_hits[i];
+    const u64 sum = __hip_atomic_fetch_add(p.acc, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + mine;
+    if ((sum >> kDoneShift) == gridDim.x) {
+      *p.d_count = sum & ((1ull << kDoneShift) - 1);
+      __hip_atomic_store(p.acc, (u64)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
   }
 }
 
@@ -1807,7 +1910,7 @@ struct ScanInit {
   u32* top;
   unsigned short* bstart;
   u32 bucket_log2;
-  unsigned short* top16;
+  unsigned short* top16;  // null: not wanted by this call
   unsigned short* bstart16;
   u32 bucket16_log2;
   u32 levels;
@@ -1847,6 +1950,34 @@ __global__ void scan_leafmap_kernel(const uint4* cleaf, const u64* new_base, u32
   out[t] = v;
 }
 
+// First of the n sampled keys that is not below target, eight-way: a table cold in the caches costs
+// a round trip per step, and five steps of seven loads beat fourteen of one (7.2 -> 4.3 us for
+// 16,384 entries).
+__device__ __forceinline__ u32 sampled_lower_bound(const fdy_alloc* table, u32 sh0, u32 n, u64 span_lo, u32 key_shift,
+                                                   u64 target) {
+  u32 lo = 0, hi = n;
+  while (lo < hi) {
+    const u32 len = hi - lo;
+    u64 k[7];
+    u32 at[7];
+#pragma unroll
+    for (u32 i = 0; i < 7; ++i) {
+      at[i] = lo + (u32)(((u64)len * (i + 1)) >> 3);  // ascending; the same place twice in short ranges
+      k[i] = (table[(u64)at[i] << sh0].base - span_lo) >> key_shift;
+    }
+    u32 nlo = lo, nhi = hi;
+#pragma unroll
+    for (u32 i = 0; i < 7; ++i)
+      if (k[i] < target) nlo = at[i] + 1;
+#pragma unroll
+    for (int i = 6; i >= 0; --i)
+      if (k[i] >= target) nhi = at[i];
+    lo = nlo;
+    hi = nhi;
+  }
+  return lo;
+}
+
 // Builds the level-0 keys and the packed mid levels, clears the chunk states and counters.
 __global__ void scan_init_kernel(ScanInit a) {
   const u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1871,16 +2002,11 @@ __global__ void scan_init_kernel(ScanInit a) {
     if (i <= (1ull << a.bucket_log2)) {
       // bucket i starts at key value i << shift: how many level-0 keys lie below it
       const u64 target = i << bucket_shift_for(span_len, key_shift, a.bucket_log2);
-      u32 lo = 0, hi = a.sampled;
-      while (lo < hi) {
-        const u32 mid = lo + ((hi - lo) >> 1);
-        if (((a.table[(u64)mid << sh0].base - span_lo) >> key_shift) < target) lo = mid + 1;
-        else hi = mid;
-      }
+      const u32 lo = sampled_lower_bound(a.table, sh0, a.sampled, span_lo, key_shift, target);
       a.bstart[i] = (unsigned short)lo;
     }
   }
-  {
+  if (a.top16) {
     const u32 key_shift = key_shift_for(span_len, 16 + a.bucket16_log2);
     if (i < a.top_n) {
       const u64 j = i << sh0;
@@ -1888,12 +2014,7 @@ __global__ void scan_init_kernel(ScanInit a) {
     }
     if (i <= (1ull << a.bucket16_log2)) {
       const u64 target = i << bucket_shift_for(span_len, key_shift, a.bucket16_log2);
-      u32 lo = 0, hi = a.sampled;
-      while (lo < hi) {
-        const u32 mid = lo + ((hi - lo) >> 1);
-        if (((a.table[(u64)mid << sh0].base - span_lo) >> key_shift) < target) lo = mid + 1;
-        else hi = mid;
-      }
+      const u32 lo = sampled_lower_bound(a.table, sh0, a.sampled, span_lo, key_shift, target);
       a.bstart16[i] = (unsigned short)lo;
     }
   }
@@ -2097,9 +2218,10 @@ struct RunPlan {
 };
 
 constexpr size_t kStateHeader = 256;
-// Tables without packed levels have two sets of chunk states (see FlatTurn).
+// The general kernel's chunk states, and behind them, for tables without packed levels, the two
+// sets of the flat one (see FlatTurn).
 size_t state_bytes(u64 n_words, u32 levels) {
-  return kStateHeader + chunk_state_bytes(n_words) * (levels ? 1 : 2 * kFlatStateStride);
+  return kStateHeader + chunk_state_bytes(n_words) * (levels ? 1 : 1 + 2 * kFlatStateStride);
 }
 
 void plan_run(u64 n_words, RunPlan* rp) {
@@ -2119,8 +2241,16 @@ void plan_run(u64 n_words, RunPlan* rp) {
 // Workers per workgroup of the scans of tables without packed levels.  Measured (us, 7 / 15
 // workers, a quarter pointers, 4,096 allocations): 17 sub-tiles 6.0 / 9.0, 1,024 9.4 / 9.2, 1,536
 // 10.3 / 9.6, 2,048 12.9 / 10.4, 4,096 23 / 14.5, 16,384 50 / 33: many small workgroups start
-// sooner and share the staging's latency, but each chunk costs a ticket and a look-back.
-u32 flat_workers(u32 n_sub) { return n_sub < 1536 ? kFlatWorkers : kFlatWorkersBig; }
+// sooner and share the staging's latency, but each chunk costs a ticket and a look-back.  With
+// output 11 (170 registers per lane: with 15 the words in hand spill, 2 M words 17.5 against 14.7).
+u32 flat_workers(u32 n_sub, bool out) { return n_sub < 1536 ? kFlatWorkers : out ? kFlatWorkersOut : kFlatWorkersBig; }
+
+// Forms with output: from 16 Mi words on the general kernels take over.  A wave there has two
+// sub-tiles in hand, so that the acknowledgement of one's stores (which every later load waits
+// behind) is paid half as often.  us, flat / general, a quarter pointers, 4,096 allocations:
+// rebase 5 M words 22.7 / 45, 12 M 59.5 / 66, 33 M 154 / 143; scan with output 34 / 50, 65 / 75,
+// 161 / 165 (16,384 allocations: 182 / 175).
+constexpr u32 kFlatOutSubs = 32768;
 
 void fill_init(ScanInit* a, const fdy_alloc* d_table, u32 n_alloc, const TablePlan& tp, unsigned char* tb) {
   a->table = d_table;
@@ -2235,8 +2365,8 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
   if (!plan_table(n_alloc, &tp)) return FDY_ERR_INVALID_ARG;
   RunPlan rp;
   plan_run(n_words, &rp);
-  const bool flat = tp.levels == 0 && !d_out;  // every base has its key in LDS
-  const u32 flat_w = flat_workers(rp.n_sub);
+  const bool flat = tp.levels == 0 && (!d_out || rp.n_sub < kFlatOutSubs);  // every base has its key in LDS
+  const u32 flat_w = flat_workers(rp.n_sub, ordered_out);
   const u32 n_chunks = flat ? (rp.n_sub + flat_w - 1) / flat_w : rp.n_chunks;
   // where things lie
   unsigned char* ws = (unsigned char*)d_workspace;
@@ -2276,9 +2406,10 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
     }
   } else {
     a.header = (u32*)state;
-    a.cstate = (u64*)(state + kStateHeader);
+    a.cstate = (u64*)(state + kStateHeader + (flat ? chunk_state_bytes(n_words) : 0));
     a.n_chunks = flat ? n_chunks * kFlatStateStride : n_chunks;
     a.d_count = nothing ? (u64*)d_count : nullptr;
+    if (flat) a.top16 = nullptr;
     const u32 n_init = init_threads(tp, a.n_chunks);
     launch(FDY_PROF_SCAN_INIT, scan_init_kernel, dim3((n_init + 255) / 256), dim3(256), 0, stream, a);
     FDY_HIP_TRY(hipGetLastError());
@@ -2309,10 +2440,11 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
   p.prepared = (const u64*)d_prepared;
   p.top_log2 = (u32)fdy__tune_get(FDY_TUNE_SCAN_TOP_LOG2);
   // level 0 in the form this launch stages in LDS
-  p.top = ordered_out ? (const u32*)a.top16 : a.top;
-  p.bstart = ordered_out ? a.bstart16 : a.bstart;
-  p.bucket_log2 = ordered_out ? a.bucket16_log2 : a.bucket_log2;
-  p.key_bits = ordered_out ? 16 + a.bucket16_log2 : 31;
+  const bool k16 = ordered_out && !flat;
+  p.top = k16 ? (const u32*)a.top16 : a.top;
+  p.bstart = k16 ? a.bstart16 : a.bstart;
+  p.bucket_log2 = k16 ? a.bucket16_log2 : a.bucket_log2;
+  p.key_bits = k16 ? 16 + a.bucket16_log2 : 31;
   for (int j = 0; j < kMaxMid; ++j) p.mid[j] = a.mid[j];
   p.leaf = a.leaf;
   p.cmid = a.cmid;
@@ -2335,21 +2467,31 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
   p.new_base = (const u64*)d_new_base;
   p.out = (u64*)d_out;
 
+  if (flat && fused) {
+    const size_t lds = flat_level_bytes(tp.top_n, p.bucket_log2) + (size_t)kRebaseWaves * kFlatQ * 8;
+    const u32 fit = (u32)(160 * 1024 / (lds + 512)), room = 16u / kRebaseWaves;
+    const u32 want = (rp.n_sub + kRebaseWaves - 1) / kRebaseWaves;
+    u32 fgrid = (u32)n_cu * (fit < room ? fit : room);
+    if (fgrid > want) fgrid = want;
+    static std::atomic<u64> allowed;
+    if (const int rc = allow_full_lds(rebase_flat_kernel<kRebaseWaves>, dev, allowed)) return rc;
+    launch(FDY_PROF_SCAN_REBASE, rebase_flat_kernel<kRebaseWaves>, dim3(fgrid), dim3(kRebaseWaves * 64), lds, stream, p);
+    FDY_HIP_TRY(hipGetLastError());
+    return FDY_OK;
+  }
   if (flat) {
     const size_t lds = flat_level_bytes(tp.top_n, p.bucket_log2) + (size_t)flat_w * kFlatQ * 10;
     // as many workgroups as can be resident (128 registers per lane: 16 waves per compute unit)
     const u32 fit = (u32)(160 * 1024 / (lds + 512)), room = 16u / (flat_w + 1);
     u32 fgrid = (u32)n_cu * (fit < room ? fit : room);
     if (fgrid > p.n_chunks) fgrid = p.n_chunks;
-    auto form = [&](auto w_c) {
-      constexpr int kW = decltype(w_c)::value;
-      return half ? scan_flat_kernel<kW, true> : scan_flat_kernel<kW, false>;
-    };
-    const bool wide = flat_w == kFlatWorkersBig;
-    auto kern = wide ? form(std::integral_constant<int, kFlatWorkersBig>{}) : form(std::integral_constant<int, kFlatWorkers>{});
-    static std::atomic<u64> allowed[4];  // one per instance that form() can return
-    if (const int rc = allow_full_lds(kern, dev, allowed[(wide ? 2 : 0) + (half ? 1 : 0)])) return rc;
-    launch(FDY_PROF_SCAN_MAIN, kern, dim3(fgrid), dim3((flat_w + 1) * 64), lds, stream, p);
+    const bool few = flat_w == kFlatWorkers;
+    auto kern = ordered_out ? (few ? scan_flat_kernel<kFlatWorkers, false, true> : scan_flat_kernel<kFlatWorkersOut, false, true>)
+                : half      ? (few ? scan_flat_kernel<kFlatWorkers, true, false> : scan_flat_kernel<kFlatWorkersBig, true, false>)
+                            : (few ? scan_flat_kernel<kFlatWorkers, false, false> : scan_flat_kernel<kFlatWorkersBig, false, false>);
+    static std::atomic<u64> allowed[6];  // one per instance
+    if (const int rc = allow_full_lds(kern, dev, allowed[(few ? 0 : 3) + (ordered_out ? 0 : half ? 1 : 2)])) return rc;
+    launch(ordered_out ? FDY_PROF_SCAN_OUT : FDY_PROF_SCAN_MAIN, kern, dim3(fgrid), dim3((flat_w + 1) * 64), lds, stream, p);
     FDY_HIP_TRY(hipGetLastError());
     return FDY_OK;
   }

@@ -97,3 +97,39 @@ def test_prepared_states_take_turns():
         assert status == 0 and cnt == want and np.array_equal(got, ref), n
         assert bool((run.d_relocs[want * 16:] == 0xEE).all())
     torch.cuda.synchronize()
+
+
+def test_kernels_share_a_prepared_table():
+    """Scans with output of 16 Mi words and more go through the general kernel, smaller ones and
+    plain scans through the flat one; all use the same prepared table in turn."""
+    import paper_2604_06664_amd as fdy
+    from tests.support import session
+    from tests.test_gpu_parity import oracle_rebase
+
+    rng = np.random.default_rng(6)
+    t = table_of(rng, 300, "spread")
+    big = 32768 * SUB + 3
+    words = np.tile(words_of(rng, 1 << 20, t, 0.1), 17)[:big]
+    new_base = rng.integers(0, 1 << 64, len(t), dtype=np.uint64)
+    run = session.ScanPointersRebaseRun(words, t, new_base, prepared=True, staging=False)
+    ref, _ = orc.scan(words, t)
+    want, _ = oracle_rebase(orc, words, t, new_base)
+    for n, form in ((big, "out"), (5000, "scan"), (big, "out"), (9000, "out"), (big, "rebase"), (7000, "rebase"),
+                    (big, "scan"), (big, "out")):
+        cnt = int(np.searchsorted(ref["word"], n))
+        run.d_out.fill_(0xEE)
+        if form == "scan":
+            fdy.fdy_scan_pointers(run.d_words, n, run.d_table, run.n_alloc, run.d_relocs, run.capacity, run.d_count,
+                                  run.d_prepared, None, 0, run.d_status)
+        elif form == "out":
+            fdy.fdy_scan_pointers_rebase(run.d_words, n, run.d_table, run.n_alloc, run.d_relocs, run.capacity,
+                                         run.d_count, run.d_new_base, run.d_out, run.d_prepared, None, 0, run.d_status)
+        else:
+            fdy.fdy_scan_rebase(run.d_words, n, run.d_table, run.n_alloc, run.d_new_base, run.d_out, run.d_count,
+                                run.d_prepared, None, 0, run.d_status)
+        got, have, status, out = run.result()
+        assert status == 0 and have == cnt, (n, form)
+        if form != "rebase":
+            assert np.array_equal(got, ref[:cnt]), (n, form)
+        if form != "scan":
+            assert np.array_equal(out[:n], want[:n]), (n, form)
