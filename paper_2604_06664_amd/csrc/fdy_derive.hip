@@ -6,15 +6,20 @@
 // equal to s's half at the same place becomes an fdy_ovr32 {byte offset, value}, ascending
 // per graph, graphs in order: exactly the override lists fdy_materialize consumes.
 //
-//   prep  (one workgroup)    checks each graph against its template (index, word count) and
-//                            prefix-sums the graphs' tile counts (2048 words per tile);
-//   count (tile)             compares the tile with the template's, counts differing halves;
-//   scan  (one workgroup)    exclusive prefix over the tile counts -> each tile's output
-//                            position, each graph's offset, the total;
-//   write (tile)             compares again and writes the entries in order.
-// The archive is read twice (it is small next to what materialize writes from it: one
-// template and a list of scalars per graph); ordering inside a tile comes from ballots over
-// words in index order, low half before high half.
+//   tile  (tile of 2048 words) checks each graph against its template (index, word count) and
+//                            prefix-sums the graphs' tile counts in LDS; compares its tile with
+//                            the template's; leaves the tile's count and, if there are few, its
+//                            entries in the workspace;
+//   place (tile)             sums the counts of the tiles before it, moves the entries to their
+//                            place (a tile with more than kDerSlot of them is compared again)
+//                            and writes the offsets of the graphs that begin there.
+// Archives of more than 1,024 graphs take the per-graph sums from a launch of one workgroup
+// ahead (prep), those of more than kDerSelfTiles tiles the tiles' positions from one between
+// (scan).  What bounds the call is launches and the dependent loads in front of each tile's
+// words, not bytes: as prep, count, scan and write, each tile searching its graph in memory, the
+// MoE archive (3.7 M words, 12,032 entries) took 31 us, 17 now.  Entries are few (a handful per
+// tile), hence the slots: the archive is read once.  Ordering inside a tile comes from ballots
+// over words in index order, low half before high half.
 #include "fdy_device.hpp"
 #include "fdy_internal.h"
 
@@ -24,10 +29,18 @@ namespace {
 constexpr int kDerTile = 2048;  // words per tile
 constexpr int kDerBlock = 256;
 constexpr int kDerRounds = kDerTile / kDerBlock;  // words per thread
+constexpr u32 kDerSlot = 32;
+constexpr u32 kDerGrid = 2048;       // workgroups that compare, eight per compute unit: beyond, the sums are paid once each
+constexpr u32 kDerOwnGraphs = 1024;  // up to here every workgroup sums the graphs' tiles itself
+// Up to here every workgroup sums the counts before its own (4 bytes each, from L2): half the
+// square of them in all, 32 MiB at the limit.
+constexpr u32 kDerSelfTiles = 4096;
 
 struct DerWs {
   u64* tile_off;   // [G+1] first tile of each graph
   u32* tile_cnt;   // [max_tiles]
+  u32* tile_graph;  // [max_tiles]
+  fdy_ovr32* slot;  // [max_tiles][kDerSlot] entries of tiles with few
   u64* tile_pos;   // [max_tiles] entries before the tile
   u32* n_tiles;    // tiles in use
   u32 max_tiles;
@@ -48,44 +61,44 @@ struct DerParams {
   DerWs ws;
 };
 
-// Words of graph g that take part: 0 for a graph that cannot be compared (flagged).
-__device__ __forceinline__ u64 comparable_words(const DerParams& p, u32 g, u32* src, bool* bad_index,
-                                                bool* bad_size) {
+// Words of graph g that take part: 0 for a graph that cannot be compared (status bits in flag).
+struct DerGraph {
+  u64 words;
+  u32 src, flag;
+};
+__device__ __forceinline__ DerGraph comparable_words(const DerParams& p, u32 g) {
+  DerGraph r{0, 0xffffffffu, 0};
   const u32 t = p.graph_tmpl[g];
-  const u32 s = t < p.n_templates ? p.tmpl_graph[t] : 0xffffffffu;
-  *src = s;
-  if (s >= p.n_graphs) {
-    *bad_index = true;
-    return 0;
+  if (t < p.n_templates) r.src = p.tmpl_graph[t];
+  if (r.src >= p.n_graphs) {
+    r.flag = FDY_ST_BAD_INDEX;
+    return r;
   }
   const u64 nw = p.word_off[g + 1] - p.word_off[g];
-  if (p.word_off[s + 1] - p.word_off[s] != nw || (nw >> 29)) {  // byte offsets are 32-bit
-    *bad_size = true;
-    return 0;
-  }
-  return nw;
+  if (p.word_off[r.src + 1] - p.word_off[r.src] != nw || (nw >> 29)) r.flag = FDY_ST_BAD_SIZE;  // byte offsets are 32-bit
+  else r.words = nw;
+  return r;
 }
 
 __global__ __launch_bounds__(1024) void derive_prep_kernel(DerParams p) {
   __shared__ u64 s_buf[17];
   const u32 G = p.n_graphs;
   u64 carry = 0;
-  bool bad_index = false, bad_size = false;
+  u32 flags = 0;
   for (u32 g0 = 0; g0 < G; g0 += 1024) {
     const u32 g = g0 + threadIdx.x;
     u64 nt = 0;
     if (g < G) {
-      u32 s;
-      const u64 nw = comparable_words(p, g, &s, &bad_index, &bad_size);
-      nt = (nw + kDerTile - 1) / kDerTile;
+      const DerGraph q = comparable_words(p, g);
+      flags |= q.flag;
+      nt = (q.words + kDerTile - 1) / kDerTile;
     }
     u64 total;
     const u64 e = block_excl_scan(nt, s_buf, total);
     if (g < G) p.ws.tile_off[g] = carry + e;
     carry += total;
   }
-  if (bad_index) raise_status(p.d_status, FDY_ST_BAD_INDEX);
-  if (bad_size) raise_status(p.d_status, FDY_ST_BAD_SIZE);
+  if (flags) raise_status(p.d_status, flags);
   if (threadIdx.x == 0) {
     const bool ok = p.word_off[G] == p.n_words_total && carry <= p.ws.max_tiles;
     if (!ok) raise_status(p.d_status, FDY_ST_BAD_SIZE);
@@ -94,71 +107,180 @@ __global__ __launch_bounds__(1024) void derive_prep_kernel(DerParams p) {
   }
 }
 
-// kWrite = false: count the tile's differing halves; true: write them from tile_pos.
-template <bool kWrite>
-__global__ __launch_bounds__(kDerBlock) void derive_tile_kernel(DerParams p) {
-  __shared__ u32 s_cnt[kDerRounds][kDerBlock / 64];
-  const u32 j = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (j >= *p.ws.n_tiles) return;
-  // largest g with tile_off[g] <= j
-  u32 lo = 0, hi = p.n_graphs;  // answer in [lo, hi)
-  while (hi - lo > 1) {
-    const u32 mid = lo + (hi - lo) / 2;
-    if (p.ws.tile_off[mid] <= j) lo = mid;
-    else hi = mid;
-  }
-  const u32 g = lo;
-  const u32 s = p.tmpl_graph[p.graph_tmpl[g]];  // valid: a graph that failed the checks has no tiles
+// Where tile j lies.
+struct DerTile {
+  const u64 *a, *b;  // the graph's words and the template's
+  u64 k0;
+  u32 n;
+};
+__device__ __forceinline__ DerTile tile_at(const DerParams& p, u32 g, u32 s, u64 first_tile, u32 j) {
+  DerTile t;
   const u64 nw = p.word_off[g + 1] - p.word_off[g];
-  const u64 k0 = ((u64)j - p.ws.tile_off[g]) * kDerTile;
-  const u32 n = (u32)(nw - k0 < (u64)kDerTile ? nw - k0 : (u64)kDerTile);
-  const u64* a = p.words + p.word_off[g] + k0;
-  const u64* b = p.words + p.word_off[s] + k0;
-  const u64 lt = lanemask_lt();
+  t.k0 = ((u64)j - first_tile) * kDerTile;
+  t.n = (u32)(nw - t.k0 < (u64)kDerTile ? nw - t.k0 : (u64)kDerTile);
+  t.a = p.words + p.word_off[g] + t.k0;
+  t.b = p.words + p.word_off[s] + t.k0;
+  return t;
+}
+
+// Compares a tile and writes its entries, as far as `room` goes, to dst if there are at most
+// `most`; returns their number (the same in every thread).  Only the differences stay in
+// registers (64 per lane leave room for eight workgroups per compute unit, which cover the
+// latency of each other's words); the few words that differ are read again.
+struct DerCounts {
+  u32 n[kDerRounds][kDerBlock / 64];
+};
+__device__ __forceinline__ u32 compare_tile(const DerTile& t, DerCounts& s_cnt, fdy_ovr32* dst, u64 room, u32 most) {
+  static_assert(kDerBlock == 256, "a round's counts are four");
+  const u32 tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // words in index order: round i covers words [256 i, 256 i + 256), one per thread
-  u64 va[kDerRounds];
-  bool dlo[kDerRounds], dhi[kDerRounds];
-  u32 rank[kDerRounds];
+  u64 x[kDerRounds];
 #pragma unroll
   for (int i = 0; i < kDerRounds; ++i) {
     const u32 k = (u32)i * kDerBlock + tid;
-    va[i] = 0;
-    u64 vb = 0;
-    if (k < n) {
-      va[i] = a[k];
-      vb = b[k];
-    }
-    const u64 x = va[i] ^ vb;
-    dlo[i] = (u32)x != 0;
-    dhi[i] = (u32)(x >> 32) != 0;
-    const u64 blo = ballot(dlo[i]), bhi = ballot(dhi[i]);
-    rank[i] = __popcll(blo & lt) + __popcll(bhi & lt);
-    if (lane == 0) s_cnt[i][wave] = __popcll(blo) + __popcll(bhi);
+    x[i] = k < t.n ? t.a[k] ^ t.b[k] : 0;
   }
-  __syncthreads();
-  if (!kWrite) {
-    if (tid == 0) {
-      u32 c = 0;
-      for (int i = 0; i < kDerRounds; ++i)
-        for (int w = 0; w < kDerBlock / 64; ++w) c += s_cnt[i][w];
-      p.ws.tile_cnt[j] = c;
-    }
-    return;
-  }
-  const u64 pos0 = p.ws.tile_pos[j];
-  u32 before = 0;  // entries of the tile before this wave's share of round i
 #pragma unroll
   for (int i = 0; i < kDerRounds; ++i) {
-    u32 mine = before;
-    for (u32 w = 0; w < wave; ++w) mine += s_cnt[i][w];
-    const u32 byte_off = (u32)((k0 + (u64)i * kDerBlock + tid) * 8);
-    u64 at = pos0 + mine + rank[i];
-    if (dlo[i]) {
-      if (at < p.capacity) p.ovr[at] = fdy_ovr32{byte_off, (u32)va[i]};
-      ++at;
+    const u32 c = __popcll(ballot((u32)x[i] != 0)) + __popcll(ballot((u32)(x[i] >> 32) != 0));
+    if (lane == 0) s_cnt.n[i][wave] = c;
+  }
+  __syncthreads();
+  u32 total = 0;
+#pragma unroll
+  for (int i = 0; i < kDerRounds; ++i) {
+    const uint4 c = *reinterpret_cast<const uint4*>(s_cnt.n[i]);
+    total += c.x + c.y + c.z + c.w;
+  }
+  if (total == 0 || total > most) return total;
+  u32 before = 0;
+#pragma unroll
+  for (int i = 0; i < kDerRounds; ++i) {
+    const uint4 c = *reinterpret_cast<const uint4*>(s_cnt.n[i]);
+    const bool lo = (u32)x[i] != 0, hi = (u32)(x[i] >> 32) != 0;
+    const u64 blo = ballot(lo), bhi = ballot(hi);
+    if (lo || hi) {
+      const u32 k = (u32)i * kDerBlock + tid, byte_off = (u32)((t.k0 + k) * 8);
+      const u64 lt = lanemask_lt(), v = t.a[k];
+      u32 at = before + __popcll(blo & lt) + __popcll(bhi & lt);
+      at += (wave > 0 ? c.x : 0) + (wave > 1 ? c.y : 0) + (wave > 2 ? c.z : 0);
+      if (lo) {
+        if (at < room) dst[at] = fdy_ovr32{byte_off, (u32)v};
+        ++at;
+      }
+      if (hi && at < room) dst[at] = fdy_ovr32{byte_off + 4, (u32)(v >> 32)};
     }
-    if (dhi[i] && at < p.capacity) p.ovr[at] = fdy_ovr32{byte_off + 4, (u32)(va[i] >> 32)};
-    for (int w = 0; w < kDerBlock / 64; ++w) before += s_cnt[i][w];
+    before += c.x + c.y + c.z + c.w;
+  }
+  return total;
+}
+
+// kOwnSums: at most kDerOwnGraphs graphs; the per-graph sums are this workgroup's own, and the
+// first one leaves them in the workspace and reports what they show.
+template <bool kOwnSums>
+__global__ __launch_bounds__(kDerBlock, 8) void derive_tile_kernel(DerParams p) {
+  __shared__ __align__(16) DerCounts s_cnt;
+  __shared__ u64 s_buf[17];
+  __shared__ u32 s_first[kOwnSums ? kDerOwnGraphs + 1 : 1], s_src[kOwnSums ? kDerOwnGraphs : 1];
+  const u32 tid = threadIdx.x, G = p.n_graphs;
+  const bool reports = blockIdx.x == 0;
+  u32 n_tiles;
+  if constexpr (kOwnSums) {
+    u32 flags = 0;
+    u64 carry = 0;
+    for (u32 q0 = 0; q0 < G; q0 += kDerBlock) {
+      const u32 q = q0 + tid;
+      u64 nt = 0, total;
+      if (q < G) {
+        const DerGraph d = comparable_words(p, q);
+        flags |= d.flag;
+        nt = (d.words + kDerTile - 1) / kDerTile;
+        s_src[q] = d.src;
+      }
+      const u64 e = carry + block_excl_scan(nt, s_buf, total);
+      if (q < G) {
+        s_first[q] = (u32)e;
+        if (reports) p.ws.tile_off[q] = e;
+      }
+      carry += total;
+    }
+    const bool ok = p.word_off[G] == p.n_words_total && carry <= p.ws.max_tiles;
+    n_tiles = ok ? (u32)carry : 0u;
+    if (reports) {
+      if (flags) raise_status(p.d_status, flags);
+      if (tid == 0) {
+        if (!ok) raise_status(p.d_status, FDY_ST_BAD_SIZE);
+        p.ws.tile_off[G] = n_tiles;
+        *p.ws.n_tiles = n_tiles;
+      }
+    }
+    __syncthreads();
+  } else {
+    n_tiles = *p.ws.n_tiles;
+  }
+  for (u32 j = blockIdx.x; j < n_tiles; j += gridDim.x) {
+    // largest g whose first tile is not behind tile j
+    u32 g = 0, hi = G;  // answer in [g, hi)
+    while (hi - g > 1) {
+      const u32 mid = g + (hi - g) / 2;
+      if ((kOwnSums ? (u64)s_first[mid] : p.ws.tile_off[mid]) <= j) g = mid;
+      else hi = mid;
+    }
+    u32 s;
+    u64 first;
+    if constexpr (kOwnSums) {
+      first = s_first[g];
+      s = s_src[g];
+    } else {
+      first = p.ws.tile_off[g];
+      s = p.tmpl_graph[p.graph_tmpl[g]];  // valid: a graph that failed the checks has no tiles
+    }
+    u32 c = 0;
+    if (s != g) {  // (a template does not differ from itself)
+      c = compare_tile(tile_at(p, g, s, first, j), s_cnt, p.ws.slot + (u64)j * kDerSlot, kDerSlot, kDerSlot);
+      __syncthreads();  // the counts have been read
+    }
+    if (tid == 0) {
+      p.ws.tile_cnt[j] = c;
+      p.ws.tile_graph[j] = g;
+    }
+  }
+}
+
+// kSelf: at most kDerSelfTiles tiles; the position is this workgroup's own sum.
+template <bool kSelf>
+__global__ __launch_bounds__(kDerBlock, 6) void derive_place_kernel(DerParams p) {
+  __shared__ __align__(16) DerCounts s_cnt;
+  __shared__ u64 s_buf[17];
+  const u32 j = blockIdx.x, tid = threadIdx.x, G = p.n_graphs, n = *p.ws.n_tiles;
+  if (j >= n) {
+    if (j == 0)  // nothing to compare: every list is empty
+      for (u32 g = tid; g <= G; g += kDerBlock) p.ovr_off[g] = 0;
+    return;
+  }
+  const u32 c = p.ws.tile_cnt[j], g = p.ws.tile_graph[j], before = j ? p.ws.tile_graph[j - 1] : 0;
+  u64 pos;
+  if constexpr (kSelf) {
+    u64 sum = 0;
+    for (u32 i = tid; i < j; i += kDerBlock) sum += p.ws.tile_cnt[i];
+    (void)block_excl_scan(sum, s_buf, pos);
+  } else {
+    pos = p.ws.tile_pos[j];
+  }
+  // graphs that begin at this tile, those without tiles in front of them included
+  for (u32 q = (j ? before + 1 : 0) + tid; q <= g; q += kDerBlock) p.ovr_off[q] = pos;
+  if (j + 1 == n) {
+    for (u32 q = g + 1 + tid; q <= G; q += kDerBlock) p.ovr_off[q] = pos + c;
+    if (tid == 0 && pos + c > p.capacity) raise_status(p.d_status, FDY_ST_CAPACITY);
+  }
+  constexpr u64 kMost = 2 * kDerTile;  // entries of a tile
+  const u64 left = pos < p.capacity ? p.capacity - pos : 0;
+  const u32 room = (u32)(left < kMost ? left : kMost);
+  if (c <= kDerSlot) {
+    if (tid < c && tid < room) p.ovr[pos + tid] = p.ws.slot[(u64)j * kDerSlot + tid];
+  } else {
+    const u32 s = p.tmpl_graph[p.graph_tmpl[g]];
+    compare_tile(tile_at(p, g, s, p.ws.tile_off[g], j), s_cnt, p.ovr + pos, room, ~0u);
   }
 }
 
@@ -174,13 +296,6 @@ __global__ __launch_bounds__(1024) void derive_scan_kernel(DerParams p) {
     if (j < n) p.ws.tile_pos[j] = carry + e;
     carry += total;
   }
-  __syncthreads();  // this workgroup's own tile_pos stores are read back below
-  // a graph's offset: entries before its first tile (graphs without tiles included)
-  for (u32 g = threadIdx.x; g <= p.n_graphs; g += 1024) {
-    const u64 t = p.ws.tile_off[g];
-    p.ovr_off[g] = t < n ? p.ws.tile_pos[t] : carry;
-  }
-  if (threadIdx.x == 0 && carry > p.capacity) raise_status(p.d_status, FDY_ST_CAPACITY);
 }
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -197,6 +312,8 @@ size_t layout(u64 n_words_total, u32 n_graphs, unsigned char* base, DerWs* ws) {
   w.n_tiles = (u32*)take(4);
   w.tile_off = (u64*)take(((size_t)n_graphs + 1) * 8);
   w.tile_cnt = (u32*)take((size_t)max_tiles * 4);
+  w.tile_graph = (u32*)take((size_t)max_tiles * 4);
+  w.slot = (fdy_ovr32*)take((size_t)max_tiles * kDerSlot * sizeof(fdy_ovr32));
   w.tile_pos = (u64*)take((size_t)max_tiles * 8);
   w.max_tiles = (u32)max_tiles;
   if (ws) *ws = w;
@@ -244,17 +361,23 @@ extern "C" int fdy_derive_overrides(const uint64_t* d_words, uint64_t n_words_to
   layout(n_words_total, n_graphs, (unsigned char*)d_workspace, &p.ws);
   hipStream_t stream = (hipStream_t)hip_stream;
   (void)hipGetLastError();  // drop any stale error left by earlier, unrelated runtime calls
-  hipLaunchKernelGGL(derive_prep_kernel, dim3(1), dim3(1024), 0, stream, p);
-  FDY_HIP_TRY(hipGetLastError());
-  if (p.ws.max_tiles) {
-    hipLaunchKernelGGL(derive_tile_kernel<false>, dim3(p.ws.max_tiles), dim3(kDerBlock), 0, stream, p);
+  const u32 tiles = p.ws.max_tiles ? p.ws.max_tiles : 1;  // one workgroup at least: the checks, the offsets
+  const u32 resident = tiles < kDerGrid ? tiles : kDerGrid;
+  if (n_graphs > kDerOwnGraphs) {
+    hipLaunchKernelGGL(derive_prep_kernel, dim3(1), dim3(1024), 0, stream, p);
     FDY_HIP_TRY(hipGetLastError());
+    hipLaunchKernelGGL(derive_tile_kernel<false>, dim3(resident), dim3(kDerBlock), 0, stream, p);
+  } else {
+    hipLaunchKernelGGL(derive_tile_kernel<true>, dim3(resident), dim3(kDerBlock), 0, stream, p);
   }
-  hipLaunchKernelGGL(derive_scan_kernel, dim3(1), dim3(1024), 0, stream, p);
   FDY_HIP_TRY(hipGetLastError());
-  if (p.ws.max_tiles) {
-    hipLaunchKernelGGL(derive_tile_kernel<true>, dim3(p.ws.max_tiles), dim3(kDerBlock), 0, stream, p);
+  if (tiles > kDerSelfTiles) {
+    hipLaunchKernelGGL(derive_scan_kernel, dim3(1), dim3(1024), 0, stream, p);
     FDY_HIP_TRY(hipGetLastError());
+    hipLaunchKernelGGL(derive_place_kernel<false>, dim3(tiles), dim3(kDerBlock), 0, stream, p);
+  } else {
+    hipLaunchKernelGGL(derive_place_kernel<true>, dim3(tiles), dim3(kDerBlock), 0, stream, p);
   }
+  FDY_HIP_TRY(hipGetLastError());
   return FDY_OK;
 }
