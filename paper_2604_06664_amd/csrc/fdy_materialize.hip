@@ -37,6 +37,7 @@
 // The order of every list is verified on the way (FDY_ST_BAD_ORDER): the relocation lists
 // where main reads them, the short lists by blocks of the prep launch (or of main).
 #include <mutex>
+#include <type_traits>
 
 #include "fdy_device.hpp"
 #include "fdy_internal.h"
@@ -85,13 +86,12 @@ struct MatParams {
 
 // Word and node counts of output graph g (those of its template).  False, with zero counts, if
 // its template or the template's source graph is out of range or has 2^32 words or more.
-__device__ __forceinline__ bool graph_sizes(const MatParams& p, u32 g, u64& nw, u64& nn, u32* src_graph = nullptr) {
+__device__ __forceinline__ bool graph_sizes(const MatParams& p, u32 g, u64& nw, u64& nn) {
   const fdy_mat_desc& d = p.d;
   nw = 0;
   nn = 0;
   const u32 t = d.graph_tmpl[g];
   const u32 s = t < d.n_templates ? d.tmpl_graph[t] : 0xffffffffu;
-  if (src_graph) *src_graph = s;
   if (s >= d.n_src_graphs) return false;
   nw = d.src_word_off[s + 1] - d.src_word_off[s];
   if (p.out_dims) nn = d.src_node_off[s + 1] - d.src_node_off[s];
@@ -103,6 +103,83 @@ __device__ __forceinline__ bool graph_sizes(const MatParams& p, u32 g, u64& nw, 
   // a graph without words has no tile that would meet (and reject) its entries
   if (nw == 0 && (d.src_reloc_off[s + 1] != d.src_reloc_off[s] || d.ovr_off[g + 1] != d.ovr_off[g])) return false;
   return true;
+}
+
+// The same for the graphs i * 256 + threadIdx.x, i < kPer, of a workgroup of 256 threads, loads
+// of one step requested for all of them before the next step: three round trips (template, source
+// graph, offsets) however many graphs there are.  (One graph after the other they were twelve,
+// half of what the small launches took: prep of the MoE archive's 67 graphs 13.5 -> 11.2 us.)
+template <u32 kPer>
+__device__ __forceinline__ bool graphs_sizes(const MatParams& p, u64 (&nw)[kPer], u64 (&nn)[kPer], u32 (&src)[kPer]) {
+  const fdy_mat_desc& d = p.d;
+  const u32 G = d.n_graphs, tid = threadIdx.x;
+  u32 t[kPer];
+  u64 w0[kPer], w1[kPer], n0[kPer], n1[kPer];
+  bool bad = false;
+#pragma unroll
+  for (u32 i = 0; i < kPer; ++i) {
+    const u32 g = i * 256 + tid;
+    t[i] = g < G ? d.graph_tmpl[g] : 0xffffffffu;
+  }
+#pragma unroll
+  for (u32 i = 0; i < kPer; ++i) src[i] = t[i] < d.n_templates ? d.tmpl_graph[t[i]] : 0xffffffffu;
+#pragma unroll
+  for (u32 i = 0; i < kPer; ++i) {
+    w0[i] = w1[i] = n0[i] = n1[i] = 0;
+    if (src[i] < d.n_src_graphs) {
+      w0[i] = d.src_word_off[src[i]];
+      w1[i] = d.src_word_off[src[i] + 1];
+      if (p.out_dims) {
+        n0[i] = d.src_node_off[src[i]];
+        n1[i] = d.src_node_off[src[i] + 1];
+      }
+    }
+  }
+#pragma unroll
+  for (u32 i = 0; i < kPer; ++i) {
+    const u32 g = i * 256 + tid, s = src[i];
+    nw[i] = w1[i] - w0[i];
+    nn[i] = n1[i] - n0[i];
+    if (g >= G) continue;
+    if (s >= d.n_src_graphs) {
+      bad = true;
+    } else if (nw[i] >> 32) {  // a template must stay below 2^32 words
+      nw[i] = 0;
+      nn[i] = 0;
+      bad = true;
+    } else if (nw[i] == 0 && (d.src_reloc_off[s + 1] != d.src_reloc_off[s] || d.ovr_off[g + 1] != d.ovr_off[g])) {
+      bad = true;  // a graph without words has no tile that would meet (and reject) its entries
+    }
+  }
+  return bad;
+}
+
+// Exclusive scans of three values per thread at once over a workgroup of 256; s_buf: 12 u64.
+__device__ __forceinline__ void block_excl_scan3(u64 (&v)[3], u64 (&total)[3], u64* s_buf) {
+  const u32 l = lane_id(), w = threadIdx.x >> 6;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    u64 inc = v[k];
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const u64 o = __shfl_up(inc, d);
+      if (l >= (u32)d) inc += o;
+    }
+    if (l == 63) s_buf[k * 4 + w] = inc;
+    v[k] = inc - v[k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    total[k] = 0;
+#pragma unroll
+    for (u32 i = 0; i < 4; ++i) {
+      const u64 x = s_buf[k * 4 + i];
+      if (i < w) v[k] += x;
+      total[k] += x;
+    }
+  }
+  __syncthreads();
 }
 
 // Do the totals match what the caller sized the launch and the outputs for?
@@ -203,10 +280,12 @@ __device__ __forceinline__ void lane_lower_bound_pair(KeyA key_a, u32 lo_a, u32 
 
 // The per-graph prefix sums as the tile, patch and dims blocks read them: from the workspace
 // (written by mat_prep_graphs_kernel) or from the block's own LDS copy.
+template <bool kOwn>
 struct PrepView {
   const u64* out_word_off;  // [G+1]
   const u64* out_node_off;  // [G+1]
-  const u64* tile_off;      // [G+1]
+  const typename std::conditional<kOwn, u32, u64>::type* tile_off;  // [G+1]
+  const u32* src;           // [G] source graphs, own sums only
   u32 n_tiles;              // 0 if the totals do not match
   u32 ok;
 };
@@ -218,17 +297,18 @@ struct TileGeom {
   u64 k0, src_word;
   bool last;
 };
-__device__ __forceinline__ TileGeom tile_geometry(const MatParams& p, const PrepView& v, u32 j) {
+template <bool kOwn>
+__device__ __forceinline__ TileGeom tile_geometry(const MatParams& p, const PrepView<kOwn>& v, u32 j) {
   const fdy_mat_desc& d = p.d;
-  const u64* tile_off = v.tile_off;
   TileGeom q;
   // largest g with tile_off[g] <= j
-  q.g = lane_lower_bound([&](u32 i) { return tile_off[i]; }, 0u, d.n_graphs + 1u, (u64)j + 1) - 1;
+  q.g = lane_lower_bound([&](u32 i) { return (u64)v.tile_off[i]; }, 0u, d.n_graphs + 1u, (u64)j + 1) - 1;
   q.t = d.graph_tmpl[q.g];
-  q.s = d.tmpl_graph[q.t];  // valid: graphs with a bad template have no tiles
+  if constexpr (kOwn) q.s = v.src[q.g];
+  else q.s = d.tmpl_graph[q.t];  // valid: graphs with a bad template have no tiles
   const u64 w0 = d.src_word_off[q.s];
   const u64 nw = d.src_word_off[q.s + 1] - w0;
-  q.k0 = ((u64)j - tile_off[q.g]) * kMatTile;
+  q.k0 = ((u64)j - v.tile_off[q.g]) * kMatTile;
   q.n = (u32)((nw - q.k0) < (u64)kMatTile ? (nw - q.k0) : (u64)kMatTile);
   q.src_word = w0 + q.k0;
   q.last = q.k0 + q.n == nw;
@@ -244,7 +324,8 @@ __device__ __forceinline__ TileGeom tile_geometry(const MatParams& p, const Prep
 // size, so a malformed list can never index outside what mat_main_kernel reserves; entries
 // that do not belong to the tile are caught there.
 constexpr u32 kPrepTiles = 255;
-__device__ __forceinline__ void prep_tiles_block(const MatParams& p, const PrepView& v, u32 block, uint2* s_lo) {
+template <bool kOwn>
+__device__ __forceinline__ void prep_tiles_block(const MatParams& p, const PrepView<kOwn>& v, u32 block, uint2* s_lo) {
   const fdy_mat_desc& d = p.d;
   const u32 tid = threadIdx.x;
   const u32 j = block * kPrepTiles + tid;
@@ -298,7 +379,8 @@ __device__ __forceinline__ void prep_tiles_block(const MatParams& p, const PrepV
 
 // Thread i: (output tile, rank) pair i: the slice of the rank's patch list inside the tile.
 // Works from the tile's geometry, not from the tile table, which the same launch is writing.
-__device__ __forceinline__ void prep_patch(const MatParams& p, const PrepView& v, u64 i) {
+template <bool kOwn>
+__device__ __forceinline__ void prep_patch(const MatParams& p, const PrepView<kOwn>& v, u64 i) {
   const fdy_mat_desc& d = p.d;
   const u32 R = d.n_ranks;
   if (i >= (u64)v.n_tiles * R) return;
@@ -413,8 +495,12 @@ __device__ __forceinline__ void check_lists(const MatParams& p, u32 cb, u32 n_cb
   if (disorder) raise_status(p.d_status, FDY_ST_BAD_ORDER);
 }
 
-// Thread i: launch dimensions of output node i.
-__device__ __forceinline__ void write_dims(const MatParams& p, const PrepView& v, u64 i) {
+// Thread i: launch dimensions of output node i.  What it takes is its chain of dependent loads
+// (with own sums: source node offset, node, and the search among the graph's grid overrides).
+// The lanes of a wave search for neighbouring nodes, so eight-way steps touch the same lines and
+// cost one request each: 72 overrides are three steps, not seven.
+template <bool kOwn>
+__device__ __forceinline__ void write_dims(const MatParams& p, const PrepView<kOwn>& v, u64 i) {
   const fdy_mat_desc& d = p.d;
   if (!v.ok) return;
   if (i >= d.out_nodes_total) return;
@@ -428,17 +514,33 @@ __device__ __forceinline__ void write_dims(const MatParams& p, const PrepView& v
   }
   const u32 g = lo;
   const u32 n = (u32)(i - off[g]);
-  const u32 s = d.tmpl_graph[d.graph_tmpl[g]];
+  u32 s;
+  if constexpr (kOwn) s = v.src[g];
+  else s = d.tmpl_graph[d.graph_tmpl[g]];
   const fdy_node nd = d.src_nodes[d.src_node_off[s] + n];
   u32 gx = nd.grid[0], gy = nd.grid[1], gz = nd.grid[2];
-  // grid override of this node, if any (list ascending by node)
-  u64 a = d.govr_off[g], b = d.govr_off[g + 1];
+  // grid override of this node, if any (list ascending by node): the last entry not above it
+  const u64 a0 = d.govr_off[g], a1 = d.govr_off[g + 1];
+  u64 a = a0, b = a1;  // entries before a lie below n, those from b on do not
   while (a < b) {
-    const u64 mid = a + (b - a) / 2;
-    if (d.govr[mid].node < n) a = mid + 1;
-    else b = mid;
+    u64 at[7];
+    u32 key[7];
+#pragma unroll
+    for (u32 k = 0; k < 7; ++k) {
+      at[k] = a + (((b - a) * (k + 1)) >> 3);
+      key[k] = d.govr[at[k]].node;
+    }
+    u64 na = a, nb = b;
+#pragma unroll
+    for (u32 k = 0; k < 7; ++k)
+      if (key[k] < n) na = at[k] + 1;
+#pragma unroll
+    for (int k = 6; k >= 0; --k)
+      if (key[k] >= n) nb = at[k];
+    a = na;
+    b = nb > na ? nb : na;  // (a list out of order can cross them)
   }
-  if (a < d.govr_off[g + 1] && d.govr[a].node == n) {
+  if (a < a1 && d.govr[a].node == n) {
     gx = d.govr[a].grid[0];
     gy = d.govr[a].grid[1];
     gz = d.govr[a].grid[2];
@@ -489,35 +591,24 @@ __device__ __forceinline__ SelfSums self_sums(const MatParams& p, u64* buf, u64*
   r.off = buf + 1024;
   const u32 G = p.d.n_graphs, tid = threadIdx.x;
   constexpr u32 kPer = 1024 / kMatBlock;
-  u64 nw[kPer], nn[kPer], sum_w = 0, sum_n = 0, sum_t = 0;
+  static_assert(kMatBlock == 256, "graphs_sizes");
+  u64 nw[kPer], nn[kPer], tw = 0, tn = 0, tt = 0;
   u32 from[kPer];
-  bool bad = false;
+  const bool bad = graphs_sizes<kPer>(p, nw, nn, from);
 #pragma unroll
   for (u32 i = 0; i < kPer; ++i) {
-    const u32 g = tid * kPer + i;
-    nw[i] = 0;
-    nn[i] = 0;
-    from[i] = 0;
-    if (g < G && !graph_sizes(p, g, nw[i], nn[i], &from[i])) bad = true;
-    sum_w += nw[i];
-    sum_n += nn[i];
-    sum_t += (nw[i] + kMatTile - 1) / kMatTile;
-  }
-  u64 tw, tn, tt;
-  u64 ew = block_excl_scan(sum_w, s_buf, tw);
-  u64 en = block_excl_scan(sum_n, s_buf, tn);
-  u64 et = block_excl_scan(sum_t, s_buf, tt);
-#pragma unroll
-  for (u32 i = 0; i < kPer; ++i) {
-    const u32 g = tid * kPer + i;
+    if (i * kMatBlock >= G) break;  // uniform
+    const u32 g = i * kMatBlock + tid;
+    u64 e[3] = {nw[i], nn[i], (nw[i] + kMatTile - 1) / kMatTile}, sum[3];
+    block_excl_scan3(e, sum, s_buf);
     if (g < G) {
-      r.tile_off[g] = (u32)et;
+      r.tile_off[g] = (u32)(tt + e[2]);
       r.src[g] = from[i];
-      r.off[g] = nodes ? en : ew;
+      r.off[g] = nodes ? tn + e[1] : tw + e[0];
     }
-    ew += nw[i];
-    en += nn[i];
-    et += (nw[i] + kMatTile - 1) / kMatTile;
+    tw += sum[0];
+    tn += sum[1];
+    tt += sum[2];
   }
   if (tid == 0) {
     r.tile_off[G] = (u32)tt;
@@ -551,7 +642,8 @@ __global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 n_
       if (blockIdx.y) return;
       if (j < n_tile_blocks + nb_dims) {
         const SelfSums q = self_sums(p, buf, s_buf, true);
-        PrepView v;
+        PrepView<true> v;
+        v.src = q.src;
         v.out_word_off = nullptr;
         v.out_node_off = q.off;
         v.tile_off = nullptr;
@@ -840,56 +932,49 @@ __global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 n_
 constexpr u32 kOwnSumsMax = 1024;
 constexpr u32 kCheckBlocks = 96;
 template <bool kOwnSums>
-__global__ __launch_bounds__(256) void mat_prep_tiles_kernel(MatParams p, u32 nb_tiles, u32 nb_patch) {
+__global__ __launch_bounds__(256, 8) void mat_prep_tiles_kernel(MatParams p, u32 nb_tiles, u32 nb_patch) {
   if (blockIdx.x >= gridDim.x - kCheckBlocks) {  // the last blocks verify the order of the short lists
     check_lists(p, blockIdx.x - (gridDim.x - kCheckBlocks), kCheckBlocks);
     return;
   }
   __shared__ uint2 s_lo[256];
-  __shared__ u64 s_off[kOwnSums ? 3 : 1][kOwnSums ? kOwnSumsMax + 1 : 1];
+  // word offsets for the blocks that resolve tiles, node offsets for those that write dimensions
+  // (18 KiB of LDS in all: eight workgroups per compute unit)
+  __shared__ u64 s_off[kOwnSums ? kOwnSumsMax + 1 : 1];
+  __shared__ u32 s_tile[kOwnSums ? kOwnSumsMax + 1 : 1], s_src[kOwnSums ? kOwnSumsMax : 1];
   __shared__ u64 s_buf[17];
-  PrepView v;
+  PrepView<kOwnSums> v;
   if constexpr (kOwnSums) {
     const u32 G = p.d.n_graphs, tid = threadIdx.x;
+    const bool nodes = blockIdx.x >= nb_tiles + nb_patch;
     constexpr u32 kPer = kOwnSumsMax / 256;
-    u64 nw[kPer], nn[kPer], sum_w = 0, sum_n = 0, sum_t = 0;
-    bool bad = false;
+    u64 nw[kPer], nn[kPer], tw = 0, tn = 0, tt = 0;
+    u32 from[kPer];
+    const bool bad = graphs_sizes<kPer>(p, nw, nn, from);
 #pragma unroll
     for (u32 i = 0; i < kPer; ++i) {
-      const u32 g = tid * kPer + i;
-      nw[i] = 0;
-      nn[i] = 0;
-      if (g < G && !graph_sizes(p, g, nw[i], nn[i])) bad = true;
-      sum_w += nw[i];
-      sum_n += nn[i];
-      sum_t += (nw[i] + kMatTile - 1) / kMatTile;
-    }
-    u64 tw, tn, tt;
-    u64 ew = block_excl_scan(sum_w, s_buf, tw);
-    u64 en = block_excl_scan(sum_n, s_buf, tn);
-    u64 et = block_excl_scan(sum_t, s_buf, tt);
-#pragma unroll
-    for (u32 i = 0; i < kPer; ++i) {
-      const u32 g = tid * kPer + i;
+      if (i * 256 >= G) break;  // uniform
+      const u32 g = i * 256 + tid;
+      u64 e[3] = {nw[i], nn[i], (nw[i] + kMatTile - 1) / kMatTile}, sum[3];
+      block_excl_scan3(e, sum, s_buf);
       if (g < G) {
-        s_off[0][g] = ew;
-        s_off[1][g] = en;
-        s_off[2][g] = et;
+        s_off[g] = nodes ? tn + e[1] : tw + e[0];
+        s_tile[g] = (u32)(tt + e[2]);
+        s_src[g] = from[i];
       }
-      ew += nw[i];
-      en += nn[i];
-      et += (nw[i] + kMatTile - 1) / kMatTile;
+      tw += sum[0];
+      tn += sum[1];
+      tt += sum[2];
     }
     if (tid == 0) {
-      s_off[0][G] = tw;
-      s_off[1][G] = tn;
-      s_off[2][G] = tt;
+      s_off[G] = nodes ? tn : tw;
+      s_tile[G] = (u32)tt;
     }
     __syncthreads();
     const bool ok = totals_ok(p, tw, tn, tt);
-    v.out_word_off = s_off[0];
-    v.out_node_off = s_off[1];
-    v.tile_off = s_off[2];
+    v.out_word_off = v.out_node_off = s_off;
+    v.tile_off = s_tile;
+    v.src = s_src;
     v.n_tiles = ok ? (u32)tt : 0u;
     v.ok = ok ? 1u : 0u;
     if (blockIdx.x == 0) {
@@ -900,6 +985,7 @@ __global__ __launch_bounds__(256) void mat_prep_tiles_kernel(MatParams p, u32 nb
     v.out_word_off = p.ws.out_word_off;
     v.out_node_off = p.ws.out_node_off;
     v.tile_off = p.ws.tile_off;
+    v.src = nullptr;
     v.n_tiles = p.ws.hdr->n_tiles;
     v.ok = p.ws.hdr->ok;
   }
