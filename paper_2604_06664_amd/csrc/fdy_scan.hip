@@ -93,6 +93,7 @@
 
 #include "fdy_device.hpp"
 #include "fdy_internal.h"
+#include "fdy_level0.hpp"
 
 namespace fdy {
 namespace {
@@ -325,26 +326,6 @@ __device__ __forceinline__ void finish_and_reset(const ScanParams& p) {
     __hip_atomic_store(p.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(p.done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-}
-
-// Level-0 keys are (base - span_lo) >> shift with the smallest shift that makes every key of
-// the span fit key_bits bits (all-ones pads).  What the truncation leaves ambiguous is settled
-// on the exact bases, so the shift affects speed only.  Keys are kept in 32 bits (key_bits =
-// 31), or in 16 bits where LDS is needed for other things: then only a key's low half is
-// stored, key_bits = 16 + bucket_log2 makes a bucket at most 2^16 key values wide, and the keys
-// that a bucket's search compares all share their high half with the candidate.
-__device__ __forceinline__ u32 key_shift_for(u64 span_len, u32 key_bits) {
-  const u64 m = span_len - 1;
-  const u32 bits = m ? 64u - (u32)__clzll((long long)m) : 0u;
-  return bits > key_bits ? bits - key_bits : 0u;
-}
-
-// The level-0 key space is cut into 2^bucket_log2 equal buckets (key >> shift); the shift is the
-// smallest that maps the span's largest key below the bucket count.
-__device__ __forceinline__ u32 bucket_shift_for(u64 span_len, u32 key_shift, u32 bucket_log2) {
-  const u64 max_key = (span_len - 1) >> key_shift;
-  const u32 bits = max_key ? 64u - (u32)__clzll((long long)max_key) : 0u;
-  return bits > bucket_log2 ? bits - bucket_log2 : 0u;
 }
 
 // Bytes that the level-0 keys take in LDS, in front of the bucket index (kept 16-byte aligned).
@@ -1110,107 +1091,6 @@ __device__ __forceinline__ void write_round(const ScanParams& p, const RoundResu
 constexpr int kFlatWorkers = 7, kFlatWorkersBig = 15, kFlatWorkersOut = 11, kRebaseWaves = 8;
 constexpr u32 kFlatQ = 256;      // queue entries per wave
 constexpr int kFlatRounds = 8;   // rounds of 64 candidates per sub-tile: one sub-tile's words
-constexpr u32 kFlatPad = 8;      // keys behind the last one (all ones)
-
-// What a workgroup stages and knows before its first word.
-struct FlatLevel {
-  const unsigned char* keys;  // u32 keys, addressed in bytes
-  const unsigned short* bst;
-  u64 span_lo, span_len;
-  u32 key_shift, bucket_shift, last_at;  // last_at: byte offset of a key that is padding
-};
-__host__ __device__ __forceinline__ size_t flat_level_bytes(u32 top_n, u32 bucket_log2) {
-  return (((size_t)top_n * 4 + 15) & ~(size_t)15) + kFlatPad * 4 + ((((((size_t)1) << bucket_log2) + 1) * 2 + 15) & ~(size_t)15);
-}
-template <u32 kThreads>
-__device__ __forceinline__ FlatLevel flat_stage(const ScanParams& p, unsigned char* smem) {
-  FlatLevel f;
-  const u32 n_bst = (1u << p.bucket_log2) + 1, tid = threadIdx.x;
-  const u32 key_vec = (p.top_n + 3) / 4, bst_vec = (n_bst * 2 + 15) / 16;
-  uint4* dst = reinterpret_cast<uint4*>(smem);
-  const uint4 *ks = reinterpret_cast<const uint4*>(p.top), *bs = reinterpret_cast<const uint4*>(p.bstart);
-  for (u32 i = tid; i < key_vec; i += kThreads) dst[i] = ks[i];
-  for (u32 i = tid; i < bst_vec; i += kThreads) dst[key_vec + kFlatPad / 4 + i] = bs[i];
-  if (tid < kFlatPad / 4) dst[key_vec + tid] = make_uint4(~0u, ~0u, ~0u, ~0u);
-  f.keys = smem;
-  f.bst = reinterpret_cast<const unsigned short*>(smem + (size_t)(key_vec * 16 + kFlatPad * 4));
-  f.last_at = key_vec * 16;
-  f.span_lo = p.table[0].base;
-  f.span_len = p.table[p.n_alloc - 1].base + p.table[p.n_alloc - 1].size - f.span_lo;
-  f.key_shift = key_shift_for(f.span_len, 31);
-  f.bucket_shift = bucket_shift_for(f.span_len, f.key_shift, p.bucket_log2);
-  return f;
-}
-
-// Interval search of N distances d = word - span_lo per lane: region, and the offset inside it if
-// the entry holds the word (else any value at or above the entry's size: see hit).
-// The place among the keys of the bucket is found without branches: the step count is the one
-// that the fullest of the wave's buckets needs, a step that leads past the bucket meets keys
-// above the word's (keys ascend over the whole table) or the padding.
-template <int N>
-__device__ __forceinline__ void flat_search(const ScanParams& p, const FlatLevel& f, const u64 (&d)[N], u32 (&n)[N],
-                                            u64 (&off)[N], bool (&hit)[N]) {
-  u32 kw[N], at[N], most = 0;  // at: byte offset of the first key not known to be at or below the word's
-#pragma unroll
-  for (int c = 0; c < N; ++c) {
-    kw[c] = (u32)(d[c] >> f.key_shift);
-    const u32 bk = kw[c] >> f.bucket_shift;
-    const u32 lo = f.bst[bk], hi = f.bst[bk + 1];
-    at[c] = lo * 4;
-    most |= hi - lo;
-  }
-  u32 steps = 0;
-  while (ballot((most >> steps) != 0)) ++steps;  // 2^steps > every lane's count
-  for (; steps > 3; --steps) {
-    const u32 step = 4u << (steps - 1);
-    u32 k[N];
-#pragma unroll
-    for (int c = 0; c < N; ++c) k[c] = *reinterpret_cast<const u32*>(f.keys + min(at[c] + step - 4, f.last_at));
-#pragma unroll
-    for (int c = 0; c < N; ++c) at[c] += k[c] <= kw[c] ? step : 0u;
-  }
-  auto fixed = [&](auto step_c) {
-    constexpr u32 step = decltype(step_c)::value;
-    u32 k[N];
-#pragma unroll
-    for (int c = 0; c < N; ++c) k[c] = *reinterpret_cast<const u32*>(f.keys + at[c] + (step - 4));
-#pragma unroll
-    for (int c = 0; c < N; ++c) at[c] += k[c] <= kw[c] ? step : 0u;
-  };
-  if (steps >= 3) fixed(std::integral_constant<u32, 16>{});
-  if (steps >= 2) fixed(std::integral_constant<u32, 8>{});
-  if (steps >= 1) fixed(std::integral_constant<u32, 4>{});
-  const unsigned char* table = reinterpret_cast<const unsigned char*>(p.table);
-  u64x2 e[N];
-#pragma unroll
-  for (int c = 0; c < N; ++c) {
-    at[c] -= 4;  // the last key not above the word's; key 0 is 0
-    e[c] = *reinterpret_cast<const u64x2*>(table + at[c] * 4);
-  }
-  // a base with the word's own truncated key may still lie above the word: one entry back, or,
-  // where a run of blocks shares a key, a search among the exact bases
-#pragma unroll
-  for (int c = 0; c < N; ++c) {
-    const u64 w = d[c] + f.span_lo;
-    n[c] = at[c] >> 2;
-    for (u32 step = 0; e[c].x > w; ++step) {
-      if (step < 4) {
-        --n[c];
-      } else {
-        u32 a = 0, b = n[c];  // the last entry of [a, b) that is not above the word
-        while (b - a > 1) {
-          const u32 mid = a + ((b - a) >> 1);
-          if (p.table[mid].base <= w) a = mid;
-          else b = mid;
-        }
-        n[c] = a;
-      }
-      e[c] = *reinterpret_cast<const u64x2*>(&p.table[n[c]]);
-    }
-    off[c] = w - e[c].x;
-    hit[c] = off[c] < e[c].y;
-  }
-}
 
 // A wave's sub-tile: the candidates go to the wave's queue in word order, as distances from
 // the span's start, and are searched in dense rounds of 64.  Round r's lane l holds in tag / off
@@ -1236,7 +1116,7 @@ __device__ __forceinline__ void flat_rounds(const ScanParams& p, const FlatLevel
     idx[c] = qi[q];
     if (c == N - 1 && q >= wn) d[c] = 0;  // rounds before the last are full
   }
-  flat_search<N>(p, f, d, n, off, hit);
+  flat_search<N>(p, f, d, n, off, hit, [](bool b) { return ballot(b) != 0; });
 #pragma unroll
   for (int c = 0; c < N; ++c) {
     if (c == N - 1) hit[c] = hit[c] && (u32)c * 64 + lane < wn;
@@ -1392,7 +1272,7 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_flat_kernel(ScanParams p) 
     s_turn = turn;
     s_next[0] = flat_draw(p, turn, last_draw);
   }
-  const FlatLevel f = flat_stage<kThreads>(p, smem_raw);
+  const FlatLevel f = flat_stage<kThreads>(p, smem_raw, tid);
   __syncthreads();
   u32 chunk = s_next[0];
   const FlatTurn states = flat_turn(p, s_turn);
@@ -1476,7 +1356,7 @@ __device__ __forceinline__ u32 flat_rebase_round(const ScanParams& p, const Flat
     d[c] = qw[c * 64 + lane];
     if (c == N - 1 && (u32)c * 64 + lane >= wn) d[c] = 0;
   }
-  flat_search<N>(p, f, d, n, off, hit);
+  flat_search<N>(p, f, d, n, off, hit, [](bool b) { return ballot(b) != 0; });
 #pragma unroll
   for (int c = 0; c < N; ++c) nb[c] = hit[c] ? p.new_base[n[c]] : 0;
 #pragma unroll
@@ -1508,7 +1388,7 @@ __global__ __launch_bounds__(kW * 64) void rebase_flat_kernel(ScanParams p) {
     if (blockIdx.x == 0 && tid == 0) raise_status(p.d_status, FDY_ST_BAD_PREPARED);
     return;
   }
-  const FlatLevel f = flat_stage<kW * 64>(p, smem_raw);
+  const FlatLevel f = flat_stage<kW * 64>(p, smem_raw, tid);
   unsigned char* qb = smem_raw + flat_level_bytes(p.top_n, p.bucket_log2);
   u64* qw = reinterpret_cast<u64*>(qb) + wave * kFlatQ;
   const u32 stride = gridDim.x * kW;
@@ -1978,34 +1858,6 @@ __global__ void scan_leafmap_kernel(const uint4* cleaf, const u64* new_base, u32
   out[t] = v;
 }
 
-// First of the n sampled keys that is not below target, eight-way: a table cold in the caches costs
-// a round trip per step, and five steps of seven loads beat fourteen of one (7.2 -> 4.3 us for
-// 16,384 entries).
-__device__ __forceinline__ u32 sampled_lower_bound(const fdy_alloc* table, u32 sh0, u32 n, u64 span_lo, u32 key_shift,
-                                                   u64 target) {
-  u32 lo = 0, hi = n;
-  while (lo < hi) {
-    const u32 len = hi - lo;
-    u64 k[7];
-    u32 at[7];
-#pragma unroll
-    for (u32 i = 0; i < 7; ++i) {
-      at[i] = lo + (u32)(((u64)len * (i + 1)) >> 3);  // ascending; the same place twice in short ranges
-      k[i] = (table[(u64)at[i] << sh0].base - span_lo) >> key_shift;
-    }
-    u32 nlo = lo, nhi = hi;
-#pragma unroll
-    for (u32 i = 0; i < 7; ++i)
-      if (k[i] < target) nlo = at[i] + 1;
-#pragma unroll
-    for (int i = 6; i >= 0; --i)
-      if (k[i] >= target) nhi = at[i];
-    lo = nlo;
-    hi = nhi;
-  }
-  return lo;
-}
-
 // Builds the level-0 keys and the packed mid levels, clears the chunk states and counters.
 __global__ void scan_init_kernel(ScanInit a) {
   const u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x;
@@ -2023,10 +1875,7 @@ __global__ void scan_init_kernel(ScanInit a) {
   const u32 sh0 = 3 * a.levels + a.f0_log2;
   {
     const u32 key_shift = key_shift_for(span_len, 31);
-    if (i < a.top_n) {
-      const u64 j = i << sh0;
-      a.top[i] = j < a.n_alloc ? (u32)((a.table[j].base - span_lo) >> key_shift) : 0xffffffffu;
-    }
+    if (i < a.top_n) a.top[i] = level0_key(a.table, a.n_alloc, sh0, i, span_lo, key_shift);
     if (i <= (1ull << a.bucket_log2)) {
       // bucket i starts at key value i << shift: how many level-0 keys lie below it
       const u64 target = i << bucket_shift_for(span_len, key_shift, a.bucket_log2);
@@ -2148,12 +1997,6 @@ __global__ void reloc_segment_kernel(const fdy_reloc* relocs, const u64* d_count
   if (lane_id() == 0) reloc_off[s] = r;
 }
 
-u32 pow2_ceil(u32 v) {
-  u32 p = 1;
-  while (p < v) p <<= 1;
-  return p;
-}
-
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 // The search hierarchy of one table, as it lies in memory (a caller's prepared buffer or the
@@ -2185,7 +2028,7 @@ bool plan_table(u32 n_alloc, TablePlan* pl) {
   }
   if (levels > (u32)kMaxMid) return false;
   const u32 sampled = sampled_at(levels, f0_log2);
-  pl->top_n = pow2_ceil(sampled < 2 ? 2 : sampled);
+  pl->top_n = level0_entries(sampled);
   pl->levels = levels;
   pl->f0_log2 = f0_log2;
   pl->sampled = sampled;

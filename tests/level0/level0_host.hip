@@ -1,0 +1,147 @@
+// Level 0's keys, bucket index, staging and search (csrc/fdy_level0.hpp), compiled for the host and
+// run over small tables.  Built with AddressSanitizer: table, keys, buckets and the staged copy
+// lie in heap blocks of their exact sizes, so a read behind any of them is reported.  What the
+// library does not write (the rest of a 256-byte piece of the caller's buffer) holds `fill`.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <vector>
+
+#include "fdy_level0.hpp"
+
+using namespace fdy;
+
+namespace {
+
+struct Params {
+  const u32* top;
+  const unsigned short* bstart;
+  u32 top_n, bucket_log2, n_alloc;
+  const fdy_alloc* table;
+};
+
+u32 bucket_log2_for(u32 top_n) {  // as plan_table
+  u32 b = 0;
+  while ((2u << b) <= top_n && b < 14u) ++b;
+  return b;
+}
+
+size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
+
+struct Built {
+  std::vector<unsigned char> top, bst;
+  unsigned char* smem;  // 16-byte aligned, exactly flat_level_bytes long
+  fdy_alloc* table;
+  Params p;
+  FlatLevel f;
+
+  Built(const std::vector<fdy_alloc>& t, int fill) {
+    const u32 n = (u32)t.size();
+    table = (fdy_alloc*)aligned_alloc(16, n * sizeof(fdy_alloc));
+    memcpy(table, t.data(), n * sizeof(fdy_alloc));
+    p.n_alloc = n;
+    p.table = table;
+    p.top_n = level0_entries(n);
+    p.bucket_log2 = bucket_log2_for(p.top_n);
+    top.assign(align256((size_t)p.top_n * 4), (unsigned char)fill);
+    bst.assign(align256(((1u << p.bucket_log2) + 1) * 2), (unsigned char)fill);
+    p.top = (const u32*)top.data();
+    p.bstart = (const unsigned short*)bst.data();
+    // what scan_init_kernel writes
+    const u64 lo = t[0].base, len = t[n - 1].base + t[n - 1].size - lo;
+    const u32 ks = key_shift_for(len, 31);
+    for (u32 i = 0; i < p.top_n; ++i) ((u32*)top.data())[i] = level0_key(table, n, 0, i, lo, ks);
+    for (u32 i = 0; i <= (1u << p.bucket_log2); ++i)
+      ((unsigned short*)bst.data())[i] =
+          (unsigned short)sampled_lower_bound(table, 0, n, lo, ks, (u64)i << bucket_shift_for(len, ks, p.bucket_log2));
+    const size_t bytes = flat_level_bytes(p.top_n, p.bucket_log2);
+    smem = (unsigned char*)aligned_alloc(16, bytes);
+    memset(smem, fill, bytes);
+    for (u32 tid = 0; tid < 64; ++tid) f = flat_stage<64>(p, smem, tid);
+  }
+  ~Built() {
+    free(table);
+    free(smem);
+  }
+};
+
+int failures = 0;
+unsigned long long searches = 0;
+
+// Searches `words` four lanes' worth at a time (the step count is shared, as in a wave); `exact`:
+// compares with the definition, else only asks that a region is one of the table's.
+void check(const std::vector<fdy_alloc>& t, const std::vector<u64>& words, int fill, bool exact) {
+  Built b(t, fill);
+  std::vector<u64> cand;
+  for (u64 w : words)
+    if (w - b.f.span_lo < b.f.span_len) cand.push_back(w);
+  for (size_t i = 0; i < cand.size(); i += 4) {
+    u64 d[4], off[4];
+    u32 n[4];
+    bool hit[4];
+    for (int c = 0; c < 4; ++c) d[c] = (i + c < cand.size() ? cand[i + c] : b.f.span_lo) - b.f.span_lo;
+    flat_search<4>(b.p, b.f, d, n, off, hit, [](bool x) { return x; });
+    searches += 4;
+    for (int c = 0; c < 4; ++c) {
+      const u64 w = d[c] + b.f.span_lo;
+      bool ok = n[c] < t.size();
+      if (exact) {
+        u32 r = 0xffffffffu;
+        for (u32 k = 0; k < t.size(); ++k)
+          if (t[k].base <= w && w - t[k].base < t[k].size) r = k;
+        ok = ok && hit[c] == (r != 0xffffffffu) && (!hit[c] || (n[c] == r && off[c] == w - t[r].base));
+      }
+      if (!ok && ++failures <= 10) {
+        printf("word %llx in {", (unsigned long long)w);
+        for (auto& e : t) printf(" %llx+%llx", (unsigned long long)e.base, (unsigned long long)e.size);
+        printf(" }, fill %02x: hit %d region %u offset %llx\n", fill, hit[c], n[c], (unsigned long long)off[c]);
+      }
+    }
+  }
+}
+
+const int kFills[] = {0x00, 0x10, 0xA7, 0xFF};
+
+std::vector<u64> edges(const std::vector<fdy_alloc>& t) {
+  std::vector<u64> w;
+  for (auto& e : t)
+    for (u64 x : {e.base - 1, e.base, e.base + 1, e.base + e.size / 2, e.base + e.size - 1, e.base + e.size,
+                  e.base + e.size + 1})
+      w.push_back(x);
+  return w;
+}
+
+// Every table of 1 to 5 blocks with sizes and gaps of these, from three places.
+void valid_tables(u32 n, std::vector<fdy_alloc>& t, u64 at) {
+  static const u64 sizes[] = {1, 16, 4096, 1ull << 30}, gaps[] = {0, 1, 1ull << 21, 1ull << 33};
+  if (t.size() == n) {
+    const auto w = edges(t);
+    for (int fill : kFills) check(t, w, fill, true);
+    return;
+  }
+  for (u64 s : sizes)
+    for (u64 g : gaps) {
+      if (n > 3 && (s == 16 || g == 1)) continue;  // fewer of the larger tables
+      t.push_back(fdy_alloc{at + g, s});
+      valid_tables(n, t, at + g + s);
+      t.pop_back();
+    }
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  if (argc < 2) return 2;
+  if (!strcmp(argv[1], "valid")) {
+    for (u32 n = 1; n <= 5; ++n)
+      for (u64 at : {0ull, 0x7f0000000000ull, ~0ull - (1ull << 37)}) {
+        if (n > 3 && at != 0x7f0000000000ull) continue;
+        std::vector<fdy_alloc> t;
+        valid_tables(n, t, at);
+      }
+  } else {
+    return 2;
+  }
+  printf("%llu searches, %d wrong\n", searches, failures);
+  return failures ? 1 : 0;
+}
