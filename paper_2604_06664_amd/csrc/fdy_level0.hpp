@@ -155,12 +155,17 @@ __host__ __device__ __forceinline__ void flat_search(const P& p, const FlatLevel
     e[c] = *reinterpret_cast<const u64x2*>(table + at[c] * 4);
   }
   // a base with the word's own truncated key may still lie above the word: one entry back, or,
-  // where a run of blocks shares a key, a search among the exact bases
+  // where a run of blocks shares a key, a search among the exact bases.  A valid table's first
+  // base is never above a candidate; an invalid one's may be (a span that wraps): a miss.
 #pragma unroll
   for (int c = 0; c < N; ++c) {
     const u64 w = d[c] + f.span_lo;
     n[c] = at[c] >> 2;
     for (u32 step = 0; e[c].x > w; ++step) {
+      if (n[c] == 0) {
+        e[c].y = 0;
+        break;
+      }
       if (step < 4) {
         --n[c];
       } else {

@@ -2,6 +2,7 @@
 // run over small tables.  Built with AddressSanitizer: table, keys, buckets and the staged copy
 // lie in heap blocks of their exact sizes, so a read behind any of them is reported.  What the
 // library does not write (the rest of a 256-byte piece of the caller's buffer) holds `fill`.
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -128,6 +129,32 @@ void valid_tables(u32 n, std::vector<fdy_alloc>& t, u64 at) {
     }
 }
 
+u64 next(u64& s) {  // xorshift64
+  s ^= s << 13;
+  s ^= s >> 7;
+  return s ^= s << 17;
+}
+
+// Tables that fdy_table_validate refuses: any order, overlaps, spans that wrap.  What is found is
+// unspecified, but nothing outside the table may be read and every search ends.
+void invalid_tables() {
+  u64 s = 0x9e3779b97f4a7c15ull;
+  {  // ends below its first base: small integers lie in the span
+    std::vector<fdy_alloc> t{{0x7f0000000000ull, 16}, {4096, 16}};
+    check(t, {0, 1, 4095, 4096, 0x7f0000000000ull, ~0ull}, 0, false);
+  }
+  for (int round = 0; round < 60000; ++round) {
+    std::vector<fdy_alloc> t(1 + next(s) % (round % 50 ? 6 : 300));
+    const int bits = 1 + (int)(next(s) % 64);
+    for (auto& e : t) e = fdy_alloc{next(s) >> (64 - bits), next(s) >> (next(s) % 64)};
+    if (next(s) % 2) std::swap(t.front(), *std::max_element(t.begin(), t.end(), [](auto& a, auto& b) { return a.base < b.base; }));
+    auto w = edges(t);
+    if (w.size() > 64) w.resize(64);
+    for (int i = 0; i < 16; ++i) w.push_back(next(s) >> (next(s) % 64));
+    check(t, w, kFills[round % 4], false);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -139,6 +166,8 @@ int main(int argc, char** argv) {
         std::vector<fdy_alloc> t;
         valid_tables(n, t, at);
       }
+  } else if (!strcmp(argv[1], "invalid")) {
+    invalid_tables();
   } else {
     return 2;
   }

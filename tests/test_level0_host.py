@@ -29,3 +29,7 @@ def run(program, what):
 
 def test_small_tables(program):
     assert ", 0 wrong" in run(program, "valid")
+
+
+def test_invalid_tables_stay_in_bounds(program):
+    assert ", 0 wrong" in run(program, "invalid")
