@@ -211,8 +211,13 @@ int fdy_layout_replay(const fdy_alloc* h_recorded, uint32_t n, uint64_t recorded
  *                    per allocation beyond 16,384 of them: packed copies of the table, and
  *                    room for one new base per allocation beside them, which
  *                    fdy_scan_pointers_rebase fills per call) and 8 bytes per 4,096 words;
- *                    0 is returned for n_words beyond the limit above.
- *                    Optional staging area: where more than 3 words in 8 lie inside the
+ *                    0 is returned for n_words beyond the limit above.  Tables of up to
+ *                    16,384 allocations are answered up to 32 KiB more, with which their
+ *                    ordered scans are faster (up to a fifth); they run without as well, so a
+ *                    buffer sized for a table serves every smaller one.
+ *                    Optional staging area (tables of more than 16,384 allocations, and
+ *                    fdy_scan_pointers_rebase from 16 Mi words on; the other scans have no
+ *                    use for it): where more than 3 words in 8 lie inside the
  *                    table's span (word-dense inputs), the hits of such a stretch are either
  *                    staged (a workspace of fdy_scan_workspace_bytes() +
  *                    fdy_scan_staging_bytes() bytes or more: up to 160 MiB, independent of
@@ -235,7 +240,7 @@ int fdy_scan_pointers(const uint64_t* d_words, uint64_t n_words, const fdy_alloc
  * alone (its search hierarchy) can therefore be built once, into a device buffer that the
  * caller owns, and handed to every scan of that table as d_prepared; such a call launches
  * one kernel where it otherwise launches two.  The buffer also holds the scan's counters
- * (work ticket, per-chunk totals), which a scan leaves zeroed behind it:
+ * (work ticket, per-chunk totals), which a scan leaves ready for the next one:
  *   - calls that share a prepared table must not overlap in time (one stream, or ordered by
  *     events); read-only sharing is not possible;
  *   - after a call that returned FDY_ERR_HIP, or that raised FDY_ST_SPIN, prepare it again;
@@ -247,7 +252,8 @@ int fdy_scan_pointers(const uint64_t* d_words, uint64_t n_words, const fdy_alloc
  * builds the hierarchy into its workspace itself.
  *
  *   fdy_scan_table_bytes    size of the buffer for a table of n_alloc entries that serves
- *                           scans of up to max_words words (0: max_words out of range)
+ *                           scans of up to max_words words (0: max_words out of range); as
+ *                           with the workspace, the 32 KiB for small tables are optional
  *   fdy_scan_table_prepare  enqueues the build; d_prepared device, 256-byte aligned
  */
 size_t fdy_scan_table_bytes(uint32_t n_alloc, uint64_t max_words);

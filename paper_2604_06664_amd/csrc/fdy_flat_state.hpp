@@ -1,0 +1,121 @@
+// fdy_flat_state.hpp - chunk states of the ordered scans of small tables (scan_flat_kernel):
+// how many there are, where they lie and what a launch leaves for the next one.  Plain
+// arithmetic, also compiled for the host, where tests/level0/level0_host.hip runs sequences
+// of launches over it.
+#pragma once
+#include "fdy_device.hpp"
+
+namespace fdy {
+
+constexpr u32 kFlatWorkers = 7, kFlatWorkersBig = 15, kFlatWorkersOut = 11;
+
+// Forms with output: from 16 Mi words on the general kernels take over.  A wave there has two
+// sub-tiles in hand, so that the acknowledgement of one's stores (which every later load waits
+// behind) is paid half as often.  us, flat / general, a quarter pointers, 4,096 allocations:
+// rebase 5 M words 22.7 / 45, 12 M 59.5 / 66, 33 M 154 / 143; scan with output 34 / 50, 65 / 75,
+// 161 / 165 (16,384 allocations: 182 / 175).
+constexpr u32 kFlatOutSubs = 32768;
+
+// Workers per workgroup of the scans of tables without packed levels.  Measured (us, 7 / 15
+// workers, a quarter pointers, 4,096 allocations): 17 sub-tiles 6.0 / 9.0, 1,024 9.4 / 9.2, 1,536
+// 10.3 / 9.6, 2,048 12.9 / 10.4, 4,096 23 / 14.5, 16,384 50 / 33: many small workgroups start
+// sooner and share the staging's latency, but each chunk costs a ticket and a look-back.  With
+// output 11 (170 registers per lane: with 15 the words in hand spill, 2 M words 17.5 against 14.7).
+constexpr u32 kFlatFewSubs = 1536;
+__host__ __device__ __forceinline__ u32 flat_workers(u32 n_sub, bool out) {
+  return n_sub < kFlatFewSubs ? kFlatWorkers : out ? kFlatWorkersOut : kFlatWorkersBig;
+}
+__host__ __device__ __forceinline__ u32 flat_chunks(u32 n_sub, bool out) {
+  const u32 w = flat_workers(n_sub, out);
+  return (n_sub + w - 1) / w;
+}
+
+// Most chunks of a launch of up to max_sub sub-tiles.
+inline u32 flat_most_chunks(u32 max_sub) {
+  u32 most = flat_chunks(max_sub, max_sub < kFlatOutSubs);
+  if (max_sub >= kFlatFewSubs && flat_chunks(kFlatFewSubs - 1, false) > most) most = flat_chunks(kFlatFewSubs - 1, false);
+  if (max_sub >= kFlatOutSubs && flat_chunks(kFlatOutSubs - 1, true) > most) most = flat_chunks(kFlatOutSubs - 1, true);
+  return most;
+}
+
+// Neighbouring chunks' states are spread over 2^s lines of 64 bytes, eight to a line: every
+// workgroup in flight reads its predecessors', and states that lie closer are served by too few
+// memory channels.  State i lies at state_at(s, i) of blocks of 2^s * 8 states; s is the largest
+// for which `states` hold the blocks, at most kFlatSpread, and no larger than the chunks can use.
+// us with 16 allocations and 2 % pointers, in chunk_state_bytes (32, 128 and 128 lines) / 256
+// lines / 512 / a line for each: 0.76 M words 10.1 / 8.6 / 8.7 / 8.8, 5.8 M 22.2 / 20.1 / 19.5 /
+// 19.5, 16.8 M 46.6 / 41.0 / 40.5 / 41.0.
+constexpr u32 kFlatSpread = 9;
+__host__ __device__ __forceinline__ u32 flat_extent(u32 s, u32 n_chunks) {
+  return (n_chunks + (8u << s) - 1) >> (s + 3) << (s + 3);
+}
+__host__ __device__ __forceinline__ u32 flat_spread(u32 n_chunks, u32 states) {
+  u32 s = kFlatSpread;
+  while (s > 0 && (flat_extent(s, n_chunks) > states || (1u << (s - 1)) >= n_chunks)) --s;
+  return s;
+}
+
+// Bytes of chunk states that a launch of n_sub sub-tiles cannot do without: one state for eight
+// of them.  That is a state for each of the general kernel's small chunks, and enough for the
+// flat kernel's, closer together than it likes.
+inline size_t chunk_state_bytes(u32 n_sub) { return ((size_t)((n_sub + 7) / 8) * 8 + 255) & ~(size_t)255; }
+
+// Where the flat kernel's states lie, relative to the first chunk state of a buffer made for
+// max_sub sub-tiles with `bytes` of chunk states (at least chunk_state_bytes).  shared: a prepared
+// table, which launches of both kernels use in turn.  The general one has at least kFlatOutSubs
+// sub-tiles then and chunks of 32: its states come first, the flat kernel's behind them.
+// Otherwise nobody uses the 16-bit form of level 0 either: its `spare` bytes, in front of the
+// chunk states, are states as well.
+struct FlatRegion {
+  long long first;  // bytes from the first chunk state
+  u32 states;       // as many as the widest spread can use, at most
+};
+inline FlatRegion flat_region(u32 max_sub, u32 spare, bool shared, size_t bytes) {
+  FlatRegion r{-(long long)spare, 0};
+  if (shared && max_sub >= kFlatOutSubs) r.first = (long long)(((size_t)((max_sub + 31) / 32) * 8 + 255) & ~(size_t)255);
+  const u32 most = flat_most_chunks(max_sub), want = flat_extent(flat_spread(most, ~0u), most);
+  const size_t have = (size_t)((long long)bytes - r.first) / 8;
+  r.states = have < want ? (u32)have : want;
+  return r;
+}
+
+// Bytes of chunk states that let a launch of any size up to max_sub spread its states widest
+// (up to 32 KiB more than chunk_state_bytes).
+inline size_t flat_state_bytes(u32 max_sub, u32 spare, bool shared) {
+  const size_t least = chunk_state_bytes(max_sub);
+  const FlatRegion r = flat_region(max_sub, spare, shared, ~(size_t)0 >> 1);
+  const long long best = r.first + 8ll * r.states;
+  return best > (long long)least ? ((size_t)best + 255) & ~(size_t)255 : least;
+}
+
+__host__ __device__ __forceinline__ u32 state_at(u32 s, u32 i) {
+  return (i >> (s + 3) << (s + 3)) | ((i & ((1u << s) - 1)) << 3) | ((i >> s) & 7);
+}
+__host__ __device__ __forceinline__ u32 chunk_at(u32 s, u32 place) {  // the inverse
+  return (place >> (s + 3) << (s + 3)) | ((place >> 3) & ((1u << s) - 1)) | ((place & 7) << s);
+}
+
+// The states are left ready for the next launch without a count of the workgroups that are through
+// (256 additions to one address at 12 ns each, at the end of the launch where nothing hides
+// them): a state carries the parity of its launch, launches alternate, and a state of the other
+// parity counts as empty.  A launch writes the state of each of its chunks; those of the launch
+// before that it does not write itself it clears, so that the next but one finds its own parity
+// nowhere.  `turn`, kept from launch to launch: chunks of the launch before << 1 | parity of
+// the next.
+constexpr u64 kFlatParity = 1ull << 61;
+struct FlatTurn {
+  u32 s, parity;           // of this launch
+  u32 dirty, s_dirty;      // chunks of the launch before, and how their states are spread
+};
+__host__ __device__ __forceinline__ FlatTurn flat_turn(u32 turn, u32 n_chunks, u32 states) {
+  return FlatTurn{flat_spread(n_chunks, states), turn & 1, turn >> 1, flat_spread(turn >> 1, states)};
+}
+__host__ __device__ __forceinline__ u32 flat_next_turn(u32 turn, u32 n_chunks) { return n_chunks << 1 | (~turn & 1); }
+// Where chunk i of the launch before left its state, if this launch (n_chunks of its own) has to
+// clear it; else ~0.
+__host__ __device__ __forceinline__ u32 flat_to_clear(const FlatTurn& t, u32 i, u32 n_chunks) {
+  const u32 at = state_at(t.s_dirty, i);
+  return chunk_at(t.s, at) < n_chunks ? ~0u : at;
+}
+
+}  // namespace fdy

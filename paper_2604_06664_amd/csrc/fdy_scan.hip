@@ -78,8 +78,9 @@
 //
 // The table's part of all this (hierarchy, packed copies) depends on the table alone and can
 // be built once per archive (fdy_scan_table_prepare); the per-call state (ticket, chunk
-// states, counters) then lives in the same buffer and is zeroed again by the last workgroup
-// to finish, so that a scan is one launch.
+// states, counters) then lives in the same buffer and is left ready for the next call, so that a
+// scan is one launch: zeroed again by the last workgroup to finish, or, by the scans of tables
+// without packed levels, marked with the launch's parity (FlatTurn).
 //
 // Tickets are handed out in increasing order and a wave only ever waits for chunks with
 // smaller numbers, which are already owned by resident workgroups; the wait is bounded by a
@@ -92,6 +93,7 @@
 #include <type_traits>
 
 #include "fdy_device.hpp"
+#include "fdy_flat_state.hpp"
 #include "fdy_internal.h"
 #include "fdy_level0.hpp"
 
@@ -131,7 +133,6 @@ struct ScanParams {
   const uint4* leafmap;     // ordered scan with output: 128 bytes per 8 entries, the compact line and
                             // behind it the eight regions' new bases (null: not built)
   u64* cstate;     // [n_chunks] per-chunk totals / inclusive prefixes
-  u32* turn;       // tables without packed levels: whose turn the two sets of states are (see FlatTurn)
   u32* done;       // workgroups that have finished (the last one resets the state behind it)
   u64* acc;        // fused scan + rebase: hits so far
   u32 n_chunks;
@@ -149,18 +150,13 @@ struct ScanParams {
   const u64* new_base;  // with a rebased output only: [n_alloc]
   u64* out;             // with a rebased output only: [n_words]
   u32 key_bits;         // width of the level-0 keys: 31 (32-bit keys in LDS) or 16 + bucket_log2 (16-bit keys)
+  // tables without packed levels (behind what the general kernels read: with a field in its middle
+  // the 8 GiB-region scan took 234 us instead of 231, the code being the same but for offsets)
+  u32* turn;            // what the launch before left (see FlatTurn)
+  FlatRegion region;    // where its states lie (a prepared table's header says so itself)
 };
 
-// One state word per chunk, sized for the smallest chunks any launch uses.
-constexpr int kSmallestChunk = 7;
-// Chunk states of the flat scan lie 64 bytes apart (in words): read by every workgroup in flight,
-// packed ones are served by too few memory channels (5.8 M words: 30.8 us packed, 25.2 apart).
-constexpr u32 kFlatStateStride = 8;
 constexpr int kFlatLook = 2;  // 64-chunk blocks per look-back step (1: 26 us, 4: 26 us)
-__host__ __device__ __forceinline__ size_t chunk_state_bytes(u64 n_words) {
-  const u64 n_sub = (n_words + kSub - 1) / kSub;
-  return ((size_t)((n_sub + kSmallestChunk - 1) / kSmallestChunk) * 8 + 255) & ~(size_t)255;
-}
 
 constexpr u64 kFlagAgg = 1ull << 62;
 constexpr u64 kFlagInc = 2ull << 62;
@@ -228,14 +224,23 @@ __device__ __forceinline__ u64 chunk_exclusive_prefix(const u64* cstate, u32 chu
   return excl;
 }
 
+// The states of a launch of the flat scan.
+struct FlatStates {
+  u64* at;     // the region's first state
+  u32 s;       // spread (see state_at)
+  u64 parity;  // 0 or kFlatParity
+  __device__ __forceinline__ u64* place(u32 chunk) const { return &at[state_at(s, chunk)]; }
+  __device__ __forceinline__ void store(u32 chunk, u64 v) const { st_state(place(chunk), v ^ parity); }
+};
+
 // The 64 K states last, last - 1, ... (before chunk 0: prefix 0), as far as the first inclusive
 // prefix among them: their sum, and whether it ends in such a prefix.
 struct WindowSum {
   u64 sum;
   bool inc;
 };
-template <int K, u32 kStride>
-__device__ __forceinline__ WindowSum window_sum(const u64* cstate, int last, u32 spin_limit, u32* d_status) {
+template <int K>
+__device__ __forceinline__ WindowSum window_sum(const FlatStates& states, int last, u32 spin_limit, u32* d_status) {
   const u32 l = lane_id();
   u32 spins = 0;
   for (;;) {
@@ -243,35 +248,36 @@ __device__ __forceinline__ WindowSum window_sum(const u64* cstate, int last, u32
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       const int idx = last - k * 64 - (int)l;
-      v[k] = idx >= 0 ? ld_state(&cstate[(u64)idx * kStride]) : kFlagInc;
+      v[k] = idx >= 0 ? ld_state(states.place((u32)idx)) : kFlagInc ^ states.parity;
     }
     u64 mine = 0;
     bool inc = false, wait = false;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       if (inc || wait) break;
-      const u32 flag = (u32)(v[k] >> 62);
-      const u64 inc_mask = ballot(flag == 2);
-      const u64 empty_mask = ballot(flag == 0);
+      v[k] ^= states.parity;  // (not where it is loaded: the other load would wait for this one)
+      const u32 flag = (u32)(v[k] >> 61);  // the parity is the low bit: odd, another launch's
+      const u64 inc_mask = ballot(flag == (u32)(kFlagInc >> 61));
+      const u64 empty_mask = ballot(flag == 0 || (flag & 1));
       const u32 first_inc = inc_mask ? (u32)__ffsll((long long)inc_mask) - 1 : 64;
       const u64 need = first_inc >= 63 ? ~0ull : ((2ull << first_inc) - 1);  // lanes 0..first_inc
       wait = (empty_mask & need) != 0;
       inc = first_inc < 64;
-      mine += ((need >> l) & 1) ? (v[k] & kValMask) : 0;
+      mine += ((need >> l) & 1) ? (v[k] & (kFlatParity - 1)) : 0;
     }
     if (!wait) return WindowSum{wave_sum_u64(mine), inc};
     if (!spin_once(spins, spin_limit, d_status)) return WindowSum{0, true};
   }
 }
 
-// The same for the flat scan: K 64-chunk blocks per step, states kStride apart.  (As one function
-// for both, the general kernel lost 0.4 %: its time moves with the layout of its code.)
-template <int K, u32 kStride>
-__device__ __forceinline__ u64 flat_exclusive_prefix(const u64* cstate, u32 chunk, u32 spin_limit,
+// The same for the flat scan: K 64-chunk blocks per step.  (As one function for both, the general
+// kernel lost 0.4 %: its time moves with the layout of its code.)
+template <int K>
+__device__ __forceinline__ u64 flat_exclusive_prefix(const FlatStates& states, u32 chunk, u32 spin_limit,
                                                      u32* d_status) {
   u64 excl = 0;
   for (int pos = (int)chunk - 1; pos >= 0; pos -= 64 * K) {
-    const WindowSum s = window_sum<K, kStride>(cstate, pos, spin_limit, d_status);
+    const WindowSum s = window_sum<K>(states, pos, spin_limit, d_status);
     excl += s.sum;
     if (s.inc) break;
   }
@@ -288,13 +294,14 @@ __device__ __forceinline__ u64 wave_incl_scan_u64(u64 v) {
   return v;
 }
 
-// A prepared table: magic and what it was made for (four 64-bit words), then the hierarchy,
-// then the state.
+// A prepared table: magic, what it was made for and where the flat kernel's states lie (six 64-bit
+// words), then the counters, the hierarchy and the chunk states.
 struct PreparedHeader {
   u64 magic;
   u32 n_alloc, top_log2;
   u64 max_words;
   u64 table_ptr;
+  FlatRegion region;
 };
 constexpr u64 kPreparedMagic = 0x3159445f4c424154ull;  // "TABL_DY1"
 constexpr size_t kPreparedHeader = 256;
@@ -1084,11 +1091,11 @@ __device__ __forceinline__ void write_round(const ScanParams& p, const RoundResu
 //   - one wave of the workgroup, the clerk, owns no words: it draws the tickets and looks back
 //     for the chunk before while the others search, so that a round takes the longer of the two
 //     instead of their sum (36.6 -> 25.2 us with the states spread out);
-//   - chunk states 64 bytes apart, and reset without a count at the end (see FlatTurn).
+//   - chunk states spread over lines, and left ready without a count at the end (see FlatTurn).
 // The same input now takes 25.2 us, 3.7 M words against 16,384 allocations 20.9 (28.2), 0.76 M
 // words 10.6 (13.8); at 33 M words and a quarter pointers 101 us (116), 4.0 TB/s of words in and
 // relocations out.
-constexpr int kFlatWorkers = 7, kFlatWorkersBig = 15, kFlatWorkersOut = 11, kRebaseWaves = 8;
+constexpr int kRebaseWaves = 8;
 constexpr u32 kFlatQ = 256;      // queue entries per wave
 constexpr int kFlatRounds = 8;   // rounds of 64 candidates per sub-tile: one sub-tile's words
 
@@ -1220,30 +1227,13 @@ __device__ __forceinline__ void flat_write(const ScanParams& p, const FlatResult
   }
 }
 
-// The ordered scan's state is left ready for the next call without a count of the workgroups
-// that are through (256 additions to one address at 12 ns each, at the end of the launch where
-// nothing hides them): there are two sets of chunk states, launches take turns with them, and
-// each launch clears what the one before it wrote in the other set.  Ticket and turn are reset by
-// whoever makes the launch's last draw: every workgroup has read the turn before its first
-// draw, so nobody looks at either again.
-struct FlatTurn {
-  u64 *cstate, *other;  // this launch's states; those of the launch before
-  u32 dirty;            // states that the launch before has written
-};
-__device__ __forceinline__ FlatTurn flat_turn(const ScanParams& p, u32 turn) {
-  const u64 max_words = p.prepared ? p.prepared[2] : p.n_words;
-  const u64 general = chunk_state_bytes(max_words) / 8, stride = general * kFlatStateStride;
-  FlatTurn t;
-  t.dirty = turn >> 1;
-  t.cstate = p.cstate + general + (turn & 1 ? stride : 0);
-  t.other = p.cstate + general + (turn & 1 ? 0 : stride);
-  return t;
-}
+// Ticket and turn are reset by whoever makes the launch's last draw: every workgroup has read
+// the turn before its first draw, so nobody looks at either again.
 __device__ __forceinline__ u32 flat_draw(const ScanParams& p, u32 turn, u32 last_draw) {
   const u32 got = atomicAdd(p.ticket, 1u);
   if (got == last_draw) {
     __hip_atomic_store(p.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(p.turn, p.n_chunks << 1 | (~turn & 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(p.turn, flat_next_turn(turn, p.n_chunks), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   return got;
 }
@@ -1275,16 +1265,22 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_flat_kernel(ScanParams p) 
   const FlatLevel f = flat_stage<kThreads>(p, smem_raw, tid);
   __syncthreads();
   u32 chunk = s_next[0];
-  const FlatTurn states = flat_turn(p, s_turn);
   if (clerk) {
-    for (u32 i = blockIdx.x * 64 + lane; i < states.dirty; i += gridDim.x * 64) st_state(&states.other[(u64)i * kFlatStateStride], 0);
-    u64* const cstate = states.cstate;
+    FlatRegion region = p.region;
+    if (p.prepared) region = FlatRegion{(long long)p.prepared[4], (u32)p.prepared[5]};
+    const FlatTurn t = flat_turn(s_turn, p.n_chunks, region.states);
+    const FlatStates states{reinterpret_cast<u64*>(reinterpret_cast<unsigned char*>(p.cstate) + region.first), t.s,
+                            t.parity ? kFlatParity : 0ull};
+    for (u32 i = blockIdx.x * 64 + lane; i < t.dirty; i += gridDim.x * 64) {
+      const u32 at = flat_to_clear(t, i, p.n_chunks);
+      if (at != ~0u) st_state(&states.at[at], 0);
+    }
     u32 prev = 0, prev_total = 0, b = 1;
     // the exclusive prefix of the chunk before, for the workers that wait to write it
     auto close = [&](u32 slot) {
-      const u64 excl = flat_exclusive_prefix<kFlatLook, kFlatStateStride>(cstate, prev, p.spin_limit, p.d_status);
+      const u64 excl = flat_exclusive_prefix<kFlatLook>(states, prev, p.spin_limit, p.d_status);
       if (lane == 0) {
-        if (prev != 0) st_state(&cstate[(u64)prev * kFlatStateStride], kFlagInc | ((excl + prev_total) & kValMask));
+        if (prev != 0) states.store(prev, kFlagInc | (excl + prev_total));
         if (prev + 1 == p.n_chunks) {  // the last chunk: the grand total
           *p.d_count = excl + prev_total;
           if (excl + prev_total > p.capacity) raise_status(p.d_status, FDY_ST_CAPACITY);
@@ -1302,7 +1298,7 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_flat_kernel(ScanParams p) 
       u32 total = 0;
 #pragma unroll
       for (int i = 0; i < kW; ++i) total += s_cnt[b][i];
-      if (lane == 0) st_state(&cstate[(u64)chunk * kFlatStateStride], (chunk == 0 ? kFlagInc : kFlagAgg) | total);
+      if (lane == 0) states.store(chunk, (chunk == 0 ? kFlagInc : kFlagAgg) | total);
       prev = chunk;
       prev_total = total;
       have_prev = true;
@@ -1834,7 +1830,7 @@ struct ScanInit {
   u32 n_chunks;
   u32* header;   // the 64 counters in front of the chunk states
   u64* d_count;  // written 0 if not null (calls that find nothing to launch)
-  u64* prepared;  // a prepared table's first block: 32 words, the first four from hdr, the rest 0
+  u64* prepared;  // a prepared table's first block: 32 words, the first six from hdr, the rest 0
   PreparedHeader hdr;
 };
 
@@ -1865,8 +1861,9 @@ __global__ void scan_init_kernel(ScanInit a) {
   if (a.header && i < 64) a.header[i] = 0;
   if (a.d_count && i == 0) *a.d_count = 0;
   if (a.prepared && i < 32) {
-    const u64 h[4] = {a.hdr.magic, (u64)a.hdr.n_alloc | ((u64)a.hdr.top_log2 << 32), a.hdr.max_words, a.hdr.table_ptr};
-    a.prepared[i] = i < 4 ? h[i] : 0;
+    const u64 h[6] = {a.hdr.magic,     (u64)a.hdr.n_alloc | ((u64)a.hdr.top_log2 << 32), a.hdr.max_words,
+                      a.hdr.table_ptr, (u64)a.hdr.region.first,                          a.hdr.region.states};
+    a.prepared[i] = i < 6 ? h[i] : 0;
   }
   if (!a.build) return;
   const u64 span_lo = a.n_alloc ? a.table[0].base : 0;
@@ -2005,6 +2002,7 @@ struct TablePlan {
   u32 top_n, levels, f0_log2, sampled, bucket_log2, bucket16_log2;
   u32 mid_len[kMaxMid];
   u32 leaf_lines, cmid_nodes;
+  u32 spare;  // without packed levels: bytes of the 16-bit form of level 0, the plan's last arrays
   size_t off_top, off_bst, off_top16, off_bst16, off_mid[kMaxMid], off_leaf, off_cleaf, off_cmid, off_leafmap, bytes;
 };
 
@@ -2077,29 +2075,35 @@ bool plan_table(u32 n_alloc, TablePlan* pl) {
   pl->off_leafmap = off;
   off += align256((size_t)pl->leaf_lines * 128);
   pl->bytes = off;
+  pl->spare = levels ? 0 : (u32)(off - pl->off_top16);
   return true;
 }
 
-// What depends on the number of words: chunking, and the state that a launch counts in
-// (64 counters of 32 bits, then one state word per chunk; sized for the small chunks, which
-// are the more numerous).
+// What depends on the number of words: chunking, and the state that a launch counts in (64
+// counters of 32 bits in front of the hierarchy, the chunk states behind it).
 struct RunPlan {
   u32 n_sub, groups, g, n_chunks, stage_wgs;
   size_t stage_bytes;
 };
 
 constexpr size_t kStateHeader = 256;
-// The general kernel's chunk states, and behind them, for tables without packed levels, the two
-// sets of the flat one (see FlatTurn).
-size_t state_bytes(u64 n_words, u32 levels) {
-  return kStateHeader + chunk_state_bytes(n_words) * (levels ? 1 : 1 + 2 * kFlatStateStride);
+u32 sub_tiles(u64 n_words) { return (u32)((n_words + kSub - 1) / kSub); }
+// Counters, hierarchy and chunk states: the least a scan works with, and what it asks for.
+size_t least_bytes(u64 n_words, const TablePlan& tp) {
+  return kStateHeader + tp.bytes + chunk_state_bytes(sub_tiles(n_words));
+}
+size_t best_bytes(u64 n_words, const TablePlan& tp, bool shared) {
+  if (tp.levels) return least_bytes(n_words, tp);
+  return kStateHeader + tp.bytes + flat_state_bytes(sub_tiles(n_words), tp.spare, shared);
 }
 
-void plan_run(u64 n_words, RunPlan* rp) {
-  rp->n_sub = (u32)((n_words + kSub - 1) / kSub);
+// packed: the table has packed levels.  (Without them only launches of at least kFlatOutSubs
+// sub-tiles come here, and the room for chunk states counts on their large chunks: flat_region.)
+void plan_run(u64 n_words, bool packed, RunPlan* rp) {
+  rp->n_sub = sub_tiles(n_words);
   // measured crossover: from 4,096 sub-tiles (2 Mi words) on the large chunks win even though
   // they leave compute units without a chunk; below, more and smaller chunks do
-  const bool small = rp->n_sub < (1u << fdy__tune_get(FDY_TUNE_SCAN_SMALL_LOG2));
+  const bool small = packed && rp->n_sub < (1u << fdy__tune_get(FDY_TUNE_SCAN_SMALL_LOG2));
   rp->groups = small ? kGroupsSmall : kGroupsBig;
   rp->g = small ? kGSmall : kGBig;
   const u32 chunk = kWaves * rp->groups * rp->g;
@@ -2109,19 +2113,6 @@ void plan_run(u64 n_words, RunPlan* rp) {
   rp->stage_wgs = rp->n_chunks < kStageWgs ? rp->n_chunks : kStageWgs;
   rp->stage_bytes = align256((size_t)rp->stage_wgs * 2 * chunk * kSub * sizeof(fdy_reloc));
 }
-// Workers per workgroup of the scans of tables without packed levels.  Measured (us, 7 / 15
-// workers, a quarter pointers, 4,096 allocations): 17 sub-tiles 6.0 / 9.0, 1,024 9.4 / 9.2, 1,536
-// 10.3 / 9.6, 2,048 12.9 / 10.4, 4,096 23 / 14.5, 16,384 50 / 33: many small workgroups start
-// sooner and share the staging's latency, but each chunk costs a ticket and a look-back.  With
-// output 11 (170 registers per lane: with 15 the words in hand spill, 2 M words 17.5 against 14.7).
-u32 flat_workers(u32 n_sub, bool out) { return n_sub < 1536 ? kFlatWorkers : out ? kFlatWorkersOut : kFlatWorkersBig; }
-
-// Forms with output: from 16 Mi words on the general kernels take over.  A wave there has two
-// sub-tiles in hand, so that the acknowledgement of one's stores (which every later load waits
-// behind) is paid half as often.  us, flat / general, a quarter pointers, 4,096 allocations:
-// rebase 5 M words 22.7 / 45, 12 M 59.5 / 66, 33 M 154 / 143; scan with output 34 / 50, 65 / 75,
-// 161 / 165 (16,384 allocations: 182 / 175).
-constexpr u32 kFlatOutSubs = 32768;
 
 void fill_init(ScanInit* a, const fdy_alloc* d_table, u32 n_alloc, const TablePlan& tp, unsigned char* tb) {
   a->table = d_table;
@@ -2172,13 +2163,13 @@ extern "C" size_t fdy_scan_workspace_bytes(uint64_t n_words, uint32_t n_alloc) {
   if (n_words > kMaxWords) return 0;
   TablePlan tp;
   if (!plan_table(n_alloc, &tp)) return 0;
-  return state_bytes(n_words, tp.levels) + tp.bytes;
+  return best_bytes(n_words, tp, false);
 }
 
 extern "C" size_t fdy_scan_staging_bytes(uint64_t n_words) {
   if (n_words > kMaxWords) return 0;
   RunPlan rp;
-  plan_run(n_words, &rp);
+  plan_run(n_words, true, &rp);
   return rp.stage_bytes;
 }
 
@@ -2186,7 +2177,7 @@ extern "C" size_t fdy_scan_table_bytes(uint32_t n_alloc, uint64_t max_words) {
   if (max_words > kMaxWords) return 0;
   TablePlan tp;
   if (!plan_table(n_alloc, &tp)) return 0;
-  return kPreparedHeader + state_bytes(max_words, tp.levels) + tp.bytes;
+  return kPreparedHeader + best_bytes(max_words, tp, true);
 }
 
 extern "C" int fdy_scan_table_prepare(const fdy_alloc* d_table, uint32_t n_alloc, uint64_t max_words,
@@ -2195,22 +2186,34 @@ extern "C" int fdy_scan_table_prepare(const fdy_alloc* d_table, uint32_t n_alloc
   if (n_alloc && (!d_table || ((uintptr_t)d_table & 15))) return FDY_ERR_INVALID_ARG;
   TablePlan tp;
   if (!plan_table(n_alloc, &tp)) return FDY_ERR_INVALID_ARG;
-  const size_t need = kPreparedHeader + state_bytes(max_words, tp.levels) + tp.bytes;
+  const size_t need = kPreparedHeader + least_bytes(max_words, tp);
   if (!d_prepared || ((uintptr_t)d_prepared & 255) || prepared_bytes < need) return FDY_ERR_WORKSPACE;
   hipStream_t stream = (hipStream_t)hip_stream;
   (void)hipGetLastError();
   unsigned char* pb = (unsigned char*)d_prepared;
   ScanInit a;
-  fill_init(&a, d_table, n_alloc, tp, pb + kPreparedHeader);
+  fill_init(&a, d_table, n_alloc, tp, pb + kPreparedHeader + kStateHeader);
   a.prepared = (u64*)pb;
   a.hdr.magic = kPreparedMagic;
   a.hdr.n_alloc = n_alloc;
   a.hdr.top_log2 = (u32)fdy__tune_get(FDY_TUNE_SCAN_TOP_LOG2);
   a.hdr.max_words = max_words;
   a.hdr.table_ptr = (u64)(uintptr_t)d_table;
-  a.header = (u32*)(pb + kPreparedHeader + tp.bytes);
-  a.cstate = (u64*)(pb + kPreparedHeader + tp.bytes + kStateHeader);
-  a.n_chunks = (u32)((state_bytes(max_words, tp.levels) - kStateHeader) / 8);
+  a.header = (u32*)(pb + kPreparedHeader);
+  a.cstate = (u64*)(pb + kPreparedHeader + kStateHeader + tp.bytes);
+  a.n_chunks = (u32)(chunk_state_bytes(sub_tiles(max_words)) / 8);
+  if (tp.levels == 0) {
+    const FlatRegion region = flat_region(sub_tiles(max_words), tp.spare, true,
+                                          prepared_bytes - kPreparedHeader - kStateHeader - tp.bytes);
+    a.hdr.region = region;
+    if (region.first < 0) {  // over the 16-bit form of level 0
+      a.top16 = nullptr;
+      a.cstate += region.first / 8;
+      a.n_chunks = region.states;
+    } else if ((u32)(region.first / 8) + region.states > a.n_chunks) {
+      a.n_chunks = (u32)(region.first / 8) + region.states;
+    }
+  }
   a.d_count = nullptr;
   const u32 n_init = init_threads(tp, a.n_chunks);
   launch(FDY_PROF_SCAN_INIT, scan_init_kernel, dim3((n_init + 255) / 256), dim3(256), 0, stream, a);
@@ -2235,28 +2238,28 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
   TablePlan tp;
   if (!plan_table(n_alloc, &tp)) return FDY_ERR_INVALID_ARG;
   RunPlan rp;
-  plan_run(n_words, &rp);
+  plan_run(n_words, tp.levels != 0, &rp);
   const bool flat = tp.levels == 0 && (!d_out || rp.n_sub < kFlatOutSubs);  // every base has its key in LDS
   const u32 flat_w = flat_workers(rp.n_sub, ordered_out);
-  const u32 n_chunks = flat ? (rp.n_sub + flat_w - 1) / flat_w : rp.n_chunks;
+  const u32 n_chunks = flat ? flat_chunks(rp.n_sub, ordered_out) : rp.n_chunks;
   // where things lie
   unsigned char* ws = (unsigned char*)d_workspace;
-  unsigned char *state, *tb, *stage;
+  unsigned char *state, *stage;
   if (d_prepared) {
     // the caller vouches for the buffer (made by fdy_scan_table_prepare for this table and at
     // least this many words, under the same tuning); only the staging comes from the workspace
     unsigned char* pb = (unsigned char*)const_cast<void*>(d_prepared);
-    tb = pb + kPreparedHeader;
-    state = tb + tp.bytes;
+    state = pb + kPreparedHeader;
     if (ws && ((uintptr_t)ws & 255)) return FDY_ERR_WORKSPACE;
     stage = ws && workspace_bytes >= rp.stage_bytes ? ws : nullptr;
   } else {
-    const size_t need = state_bytes(n_words, tp.levels) + tp.bytes;
+    const size_t need = least_bytes(n_words, tp);
     if (!ws || ((uintptr_t)ws & 255) || workspace_bytes < need) return FDY_ERR_WORKSPACE;
     state = ws;
-    tb = ws + state_bytes(n_words, tp.levels);
-    stage = workspace_bytes >= need + rp.stage_bytes ? tb + tp.bytes : nullptr;
+    stage = workspace_bytes >= need + rp.stage_bytes ? ws + need : nullptr;
   }
+  unsigned char* const tb = state + kStateHeader;
+  u64* const cstate = (u64*)(tb + tp.bytes);
   hipStream_t stream = (hipStream_t)hip_stream;
   (void)hipGetLastError();  // drop any stale error left by earlier, unrelated runtime calls
   int dev = 0, n_cu = 256;
@@ -2266,6 +2269,7 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
   if (grid > rp.n_chunks) grid = rp.n_chunks;
   if (grid > rp.stage_wgs) grid = rp.stage_wgs;  // kStageWgs bounds every launch: the staging is sized for it
   const bool nothing = rp.n_sub == 0 || n_alloc == 0;  // no word can be a pointer
+  FlatRegion region{0, 0};
   ScanInit a;
   fill_init(&a, d_table, n_alloc, tp, tb);
   if (d_prepared) {
@@ -2277,10 +2281,18 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
     }
   } else {
     a.header = (u32*)state;
-    a.cstate = (u64*)(state + kStateHeader + (flat ? chunk_state_bytes(n_words) : 0));
-    a.n_chunks = flat ? n_chunks * kFlatStateStride : n_chunks;
+    if (flat) {
+      a.top16 = nullptr;
+      if (!fused) {
+        region = flat_region(rp.n_sub, tp.spare, false, workspace_bytes - kStateHeader - tp.bytes);
+        a.cstate = cstate + region.first / 8;
+        a.n_chunks = flat_extent(flat_spread(n_chunks, region.states), n_chunks);
+      }
+    } else {
+      a.cstate = cstate;
+      a.n_chunks = n_chunks;
+    }
     a.d_count = nothing ? (u64*)d_count : nullptr;
-    if (flat) a.top16 = nullptr;
     const u32 n_init = init_threads(tp, a.n_chunks);
     launch(FDY_PROF_SCAN_INIT, scan_init_kernel, dim3((n_init + 255) / 256), dim3(256), 0, stream, a);
     FDY_HIP_TRY(hipGetLastError());
@@ -2305,7 +2317,8 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
   p.done = (u32*)state + 1;
   p.acc = (u64*)state + 1;
   p.turn = d_prepared ? (u32*)const_cast<void*>(d_prepared) + kPreparedTurn / 4 : (u32*)state + 8;
-  p.cstate = (u64*)(state + kStateHeader);
+  p.region = region;
+  p.cstate = cstate;
   p.n_chunks = n_chunks;
   p.self_clean = d_prepared ? 1u : 0u;
   p.prepared = (const u64*)d_prepared;

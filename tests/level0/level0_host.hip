@@ -1,13 +1,15 @@
-// Level 0's keys, bucket index, staging and search (csrc/fdy_level0.hpp), compiled for the host and
-// run over small tables.  Built with AddressSanitizer: table, keys, buckets and the staged copy
-// lie in heap blocks of their exact sizes, so a read behind any of them is reported.  What the
-// library does not write (the rest of a 256-byte piece of the caller's buffer) holds `fill`.
+// Level 0's keys, bucket index, staging and search (csrc/fdy_level0.hpp) over small tables, and
+// the chunk states of launches in turn (csrc/fdy_flat_state.hpp), compiled for the host.  Built
+// with AddressSanitizer: table, keys, buckets and the staged copy lie in heap blocks of their
+// exact sizes, so a read behind any of them is reported.  What the library does not write (the
+// rest of a 256-byte piece of the caller's buffer) holds `fill`.
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <vector>
 
+#include "fdy_flat_state.hpp"
 #include "fdy_level0.hpp"
 
 using namespace fdy;
@@ -67,7 +69,7 @@ struct Built {
 };
 
 int failures = 0;
-unsigned long long searches = 0;
+unsigned long long runs = 0;
 
 // Searches `words` four lanes' worth at a time (the step count is shared, as in a wave); `exact`:
 // compares with the definition, else only asks that a region is one of the table's.
@@ -82,7 +84,7 @@ void check(const std::vector<fdy_alloc>& t, const std::vector<u64>& words, int f
     bool hit[4];
     for (int c = 0; c < 4; ++c) d[c] = (i + c < cand.size() ? cand[i + c] : b.f.span_lo) - b.f.span_lo;
     flat_search<4>(b.p, b.f, d, n, off, hit, [](bool x) { return x; });
-    searches += 4;
+    runs += 4;
     for (int c = 0; c < 4; ++c) {
       const u64 w = d[c] + b.f.span_lo;
       bool ok = n[c] < t.size();
@@ -155,6 +157,66 @@ void invalid_tables() {
   }
 }
 
+// Sequences of launches over the chunk states of one prepared table: every state lies inside its
+// region and is nobody else's, none looks written before its chunk writes it, and what the
+// launch clears it does not write.
+void chunk_states() {
+  u64 r = 0x2545f4914f6cdd1dull;
+  auto expect = [](bool ok, const char* what, u32 max_sub, u32 n_sub, u32 i) {
+    if (!ok && ++failures <= 10) printf("%s: max_sub %u n_sub %u chunk %u\n", what, max_sub, n_sub, i);
+  };
+  std::vector<u32> maxima{1, 2, 7, 8, 9, 255, 257, 1343, 1344, 1535, 1536, 1537, 1759, 1761, 2111, 2113, 20000,
+                          kFlatOutSubs - 1, kFlatOutSubs, kFlatOutSubs + 1, 44685, 300001};
+  for (int i = 0; i < 60; ++i) maxima.push_back(1 + (u32)(next(r) % (1u << (1 + next(r) % 17))));
+  for (u32 max_sub : maxima)
+    for (u32 spare : {512u, 6144u, 49408u})
+      for (int kind = 0; kind < 4; ++kind) {
+        const bool shared = kind & 1;
+        const size_t least = chunk_state_bytes(max_sub), best = flat_state_bytes(max_sub, spare, shared);
+        expect(best >= least && best <= least + 32768, "size", max_sub, 0, 0);
+        const size_t bytes = kind & 2 ? best : least;
+        const FlatRegion g = flat_region(max_sub, spare, shared, bytes);
+        expect(g.first >= -(long long)spare && g.first + 8ll * g.states <= (long long)bytes, "region", max_sub, 0, 0);
+        // general launches that share the buffer: chunks of 32 sub-tiles
+        if (shared && max_sub >= kFlatOutSubs) expect(g.first >= 8ll * ((max_sub + 31) / 32), "general", max_sub, 0, 0);
+        std::vector<u64> mem(g.states, 0);
+        std::vector<u32> mark(g.states, ~0u);
+        u32 turn = 0;
+        for (u32 launch = 0; launch < 12; ++launch) {
+          u32 n_sub = 1 + (u32)(next(r) % max_sub);
+          if (launch % 4 == 1) n_sub = max_sub;
+          if (launch % 4 == 3) n_sub = n_sub < 40 ? n_sub : 1 + (u32)(next(r) % 40);
+          const bool out = n_sub < kFlatOutSubs && next(r) % 2;
+          const u32 n = flat_chunks(n_sub, out);
+          const FlatTurn t = flat_turn(turn, n, g.states);
+          const u64 par = t.parity ? kFlatParity : 0;
+          expect(flat_extent(t.s, n) <= g.states, "extent", max_sub, n_sub, 0);
+          if (bytes == best) expect(t.s == flat_spread(n, ~0u), "spread", max_sub, n_sub, 0);
+          for (u32 i = 0; i < n; ++i) {
+            const u32 at = state_at(t.s, i);
+            if (at >= g.states || mark[at] == launch || chunk_at(t.s, at) != i) {
+              expect(false, "place", max_sub, n_sub, i);
+              continue;
+            }
+            mark[at] = launch;
+            const u64 flag = (mem[at] ^ par) >> 61;
+            expect(flag == 0 || (flag & 1), "looks written", max_sub, n_sub, i);
+          }
+          for (u32 i = 0; i < t.dirty; ++i) {
+            const u32 at = flat_to_clear(t, i, n);
+            if (at == ~0u) continue;
+            expect(at < g.states && mark[at] != launch, "clears its own", max_sub, n_sub, i);
+            if (at < g.states) mem[at] = 0;
+          }
+          for (u32 i = 0; i < n; ++i) mem[state_at(t.s, i)] = ((2ull << 62) | i) ^ par;
+          for (u32 i = 0; i < g.states; ++i)  // the next but one starts from this launch's parity
+            expect(mem[i] == 0 || ((mem[i] ^ par) >> 61) == 4, "left behind", max_sub, n_sub, i);
+          turn = flat_next_turn(turn, n);
+          ++runs;
+        }
+      }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -168,9 +230,11 @@ int main(int argc, char** argv) {
       }
   } else if (!strcmp(argv[1], "invalid")) {
     invalid_tables();
+  } else if (!strcmp(argv[1], "states")) {
+    chunk_states();
   } else {
     return 2;
   }
-  printf("%llu searches, %d wrong\n", searches, failures);
+  printf("%llu run, %d wrong\n", runs, failures);
   return failures ? 1 : 0;
 }

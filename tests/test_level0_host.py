@@ -1,5 +1,6 @@
-"""The interval search of small tables on the CPU: its own source (csrc/fdy_level0.hpp), compiled
-for the host under AddressSanitizer and compared with the definition over every small table."""
+"""The scan of small tables on the CPU, in its own source compiled for the host under
+AddressSanitizer: the interval search (csrc/fdy_level0.hpp) against the definition over every small
+table, and the chunk states (csrc/fdy_flat_state.hpp) over sequences of launches."""
 import os
 import subprocess
 
@@ -33,3 +34,7 @@ def test_small_tables(program):
 
 def test_invalid_tables_stay_in_bounds(program):
     assert ", 0 wrong" in run(program, "invalid")
+
+
+def test_chunk_states_of_launches_in_turn(program):
+    assert ", 0 wrong" in run(program, "states")
