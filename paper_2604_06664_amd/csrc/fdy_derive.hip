@@ -29,11 +29,16 @@ namespace {
 constexpr int kDerTile = 2048;  // words per tile
 constexpr int kDerBlock = 256;
 constexpr int kDerRounds = kDerTile / kDerBlock;  // words per thread
+// Entries of a tile that wait in the workspace (256 bytes per 16 KiB of words).  128 of them: 600
+// graphs of 20,480 words with 31 differing halves in a tile 50 us instead of 57, equal with 4.
 constexpr u32 kDerSlot = 32;
-constexpr u32 kDerGrid = 2048;       // workgroups that compare, eight per compute unit: beyond, the sums are paid once each
+// Workgroups that compare, eight per compute unit: beyond, the sums are paid once each (6,600
+// tiles: 39.8 us, one workgroup per tile 49.4).
+constexpr u32 kDerGrid = 2048;
 constexpr u32 kDerOwnGraphs = 1024;  // up to here every workgroup sums the graphs' tiles itself
 // Up to here every workgroup sums the counts before its own (4 bytes each, from L2): half the
-// square of them in all, 32 MiB at the limit.
+// square of them in all, 32 MiB at the limit.  us with the limit at 1,024 / 4,096 / 8,192: 2,000
+// tiles 24.4 / 22.4 / 22.4, 6,600 with 31 entries each 57.1 / 56.7 / 58.2.
 constexpr u32 kDerSelfTiles = 4096;
 
 struct DerWs {
@@ -124,21 +129,30 @@ __device__ __forceinline__ DerTile tile_at(const DerParams& p, u32 g, u32 s, u64
 }
 
 // Compares a tile and writes its entries, as far as `room` goes, to dst if there are at most
-// `most`; returns their number (the same in every thread).  Only the differences stay in
-// registers (64 per lane leave room for eight workgroups per compute unit, which cover the
-// latency of each other's words); the few words that differ are read again.
+// `most`; returns their number (the same in every thread).  kKeep false, for tiles with few
+// entries: only the differences stay in registers (64 per lane leave room for eight workgroups
+// per compute unit, which cover the latency of each other's words) and the few words that
+// differ are read again.  kKeep true: the words stay as well.  (Read again, 600 graphs of 20,480
+// words with 400 differing halves in a tile took 76 us instead of 64.)
 struct DerCounts {
   u32 n[kDerRounds][kDerBlock / 64];
 };
+template <bool kKeep>
 __device__ __forceinline__ u32 compare_tile(const DerTile& t, DerCounts& s_cnt, fdy_ovr32* dst, u64 room, u32 most) {
   static_assert(kDerBlock == 256, "a round's counts are four");
   const u32 tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // words in index order: round i covers words [256 i, 256 i + 256), one per thread
-  u64 x[kDerRounds];
+  u64 x[kDerRounds], va[kKeep ? kDerRounds : 1];
 #pragma unroll
   for (int i = 0; i < kDerRounds; ++i) {
     const u32 k = (u32)i * kDerBlock + tid;
-    x[i] = k < t.n ? t.a[k] ^ t.b[k] : 0;
+    u64 a = 0, b = 0;
+    if (k < t.n) {
+      a = t.a[k];
+      b = t.b[k];
+    }
+    x[i] = a ^ b;
+    if constexpr (kKeep) va[i] = a;
   }
 #pragma unroll
   for (int i = 0; i < kDerRounds; ++i) {
@@ -161,7 +175,7 @@ __device__ __forceinline__ u32 compare_tile(const DerTile& t, DerCounts& s_cnt, 
     const u64 blo = ballot(lo), bhi = ballot(hi);
     if (lo || hi) {
       const u32 k = (u32)i * kDerBlock + tid, byte_off = (u32)((t.k0 + k) * 8);
-      const u64 lt = lanemask_lt(), v = t.a[k];
+      const u64 lt = lanemask_lt(), v = kKeep ? va[kKeep ? i : 0] : t.a[k];
       u32 at = before + __popcll(blo & lt) + __popcll(bhi & lt);
       at += (wave > 0 ? c.x : 0) + (wave > 1 ? c.y : 0) + (wave > 2 ? c.z : 0);
       if (lo) {
@@ -237,7 +251,7 @@ __global__ __launch_bounds__(kDerBlock, 8) void derive_tile_kernel(DerParams p) 
     }
     u32 c = 0;
     if (s != g) {  // (a template does not differ from itself)
-      c = compare_tile(tile_at(p, g, s, first, j), s_cnt, p.ws.slot + (u64)j * kDerSlot, kDerSlot, kDerSlot);
+      c = compare_tile<false>(tile_at(p, g, s, first, j), s_cnt, p.ws.slot + (u64)j * kDerSlot, kDerSlot, kDerSlot);
       __syncthreads();  // the counts have been read
     }
     if (tid == 0) {
@@ -280,7 +294,7 @@ __global__ __launch_bounds__(kDerBlock, 6) void derive_place_kernel(DerParams p)
     if (tid < c && tid < room) p.ovr[pos + tid] = p.ws.slot[(u64)j * kDerSlot + tid];
   } else {
     const u32 s = p.tmpl_graph[p.graph_tmpl[g]];
-    compare_tile(tile_at(p, g, s, p.ws.tile_off[g], j), s_cnt, p.ovr + pos, room, ~0u);
+    compare_tile<true>(tile_at(p, g, s, p.ws.tile_off[g], j), s_cnt, p.ovr + pos, room, ~0u);
   }
 }
 
