@@ -165,6 +165,15 @@ def _current_stream():
     return _raw_stream()
 
 
+def _forget_stream():
+    """In a forked child torch refuses its parent's GPU (current_stream() raises): ask it again."""
+    global _raw_stream
+    _raw_stream = None
+
+
+os.register_at_fork(after_in_child=_forget_stream)
+
+
 def _stream(stream):
     if stream is None:
         return _current_stream()
