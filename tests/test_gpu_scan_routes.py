@@ -1,0 +1,96 @@
+"""What the flat kernels of small tables took away from older tests: word-dense inputs through the
+general kernels (small and large chunks, staged and searched twice), and the bounded wait of both
+ordered scans."""
+import numpy as np
+import pytest
+
+import oracle as orc
+from synth import layout as L
+
+pytestmark = pytest.mark.gpu
+
+SUB = 512
+
+
+def dense_input(n):
+    """301 touching 64-byte regions and one at the top of the address space; nearly every word a hit."""
+    rng = np.random.default_rng(5)
+    t = np.array([(0x1000 + 64 * i, 64) for i in range(300)] + [(2**64 - 0x100, 0xFF)], L.ALLOC)
+    w = (0x1000 + rng.integers(0, 64 * 300, n)).astype(np.uint64)
+    w[::97] = np.uint64(2**64 - 1)
+    w[1::97] = np.uint64(2**64 - 2)
+    w[2::97] = np.uint64(0xFFF)
+    return w, t, rng.integers(0, 1 << 64, len(t), dtype=np.uint64)
+
+
+def dense_with_gaps(n):
+    """The same with a stretch of the input without candidates, and one with some."""
+    w, t, nb = dense_input(n)
+    w[n // 3:n // 2] = np.arange(n // 2 - n // 3, dtype=np.uint64) % np.uint64(0x1000)
+    w[n // 2:n // 2 + n // 8:3] = np.uint64(7)
+    return w, t, nb
+
+
+@pytest.mark.parametrize("n", [9000, 70 * SUB + 1, 1 << 20, 4096 * SUB + 777])  # the last: large chunks
+@pytest.mark.parametrize("make", [dense_input, dense_with_gaps])
+def test_dense_words_through_the_general_kernels(n, make):
+    import paper_2604_06664_amd as fdy
+    from tests.support import session
+    from tests.test_gpu_parity import check_rebase, check_scan, check_scan_out, oracle_rebase
+
+    words, t, nb = make(n)
+    old = fdy.tune_get(fdy.TUNE_SCAN_TOP_LOG2)
+    try:
+        fdy.tune_set(fdy.TUNE_SCAN_TOP_LOG2, 4)  # 301 regions do not fit 16 keys: packed levels
+        check_scan(session, orc, words, t, tag="dense, general")
+        check_scan_out(session, orc, words, t, nb, tag="dense, general")
+        check_rebase(session, orc, words, t, nb, tag="dense, general")
+        units = words.view(np.uint32)[:n + 1 if n > 1 << 20 else 2 * n]
+        ref, cnt = orc.scan_stride4(units, t)
+        for prepared in (False, True):
+            for staging in (False, True):
+                got, have, status = session.scan_stride4(units, t, prepared=prepared, staging=staging)
+                assert status == 0 and have == cnt and np.array_equal(got, ref)
+    finally:
+        fdy.tune_set(fdy.TUNE_SCAN_TOP_LOG2, old)
+
+
+def test_dense_words_of_a_small_table_above_16_mi_words():
+    """With output such a launch takes the general kernel, without packed levels."""
+    from tests.support import session
+    from tests.test_gpu_parity import check_scan_out
+
+    words, t, nb = dense_with_gaps(32768 * SUB + 3)
+    check_scan_out(session, orc, words, t, nb, tag="dense, small table, large")
+
+
+@pytest.mark.parametrize("n_alloc", [300, 20000])  # flat, general
+@pytest.mark.parametrize("n", [200 * SUB, 1500 * SUB, 8000 * SUB])
+def test_bounded_wait_and_the_calls_after(n_alloc, n):
+    """With a spin limit of 0 a workgroup whose predecessor is not through gives up, says so and ends.
+    A small table's states are in order even then: calls on the same prepared table are exact
+    (the others are prepared again, as the interface asks)."""
+    import paper_2604_06664_amd as fdy
+    from tests.support import session
+    from tests.test_gpu_flat_scan import table_of, words_of
+
+    rng = np.random.default_rng(n_alloc)
+    t = table_of(rng, n_alloc, "spread")
+    words = words_of(rng, n, t, 0.25)
+    ref, cnt = orc.scan(words, t)
+    run = session.ScanRun(words, t, prepared=True)
+    for _ in range(2):
+        old = fdy.tune_set(fdy.TUNE_SCAN_SPIN_LIMIT, 0)
+        try:
+            run.launch()
+            _, _, status = run.result()
+        finally:
+            fdy.tune_set(fdy.TUNE_SCAN_SPIN_LIMIT, old)
+        assert status & ~(L.ST_SPIN | L.ST_CAPACITY) == 0
+        run.d_status.zero_()
+        if n_alloc > 16384:
+            run.prepare(n)
+        for _ in range(2):
+            run.launch()
+            got, have, status = run.result()
+            assert status == 0 and have == cnt and np.array_equal(got, ref)
