@@ -610,7 +610,7 @@ __device__ __forceinline__ void search(const ScanParams& p, const void* top_v, u
   const u64* nbl[N];  // base of the new-base array to index with the region: the line's own copy, if any
 #pragma unroll
   for (int c = 0; c < N; ++c) nbl[c] = nullptr;
-  if (p.levels == 0) {
+  if (kRecords && p.levels == 0) {  // (without output such tables have a kernel of their own)
 #pragma unroll
     for (int c = 0; c < N; ++c) e[c] = *reinterpret_cast<const u64x2*>(&p.table[n[c]]);
   } else if (cleaf) {
@@ -689,28 +689,25 @@ __device__ __forceinline__ void search(const ScanParams& p, const void* top_v, u
 // words are candidates, and each candidate's rank in word order (load k, lane, half).
 // Stages the level-0 keys and the bucket index in LDS with 16-byte copies.  Both arrays are
 // padded to 256 bytes in the workspace and to 16 bytes in LDS, so whole 16-byte pieces can be
-// copied past their last entry; a top level of two keys (8 bytes) is copied key by key.
+// copied past their last entry.
 __device__ __forceinline__ void stage_level0(const ScanParams& p, void* top_v, unsigned short* bst, u32 n_bst,
                                              bool k16 = false) {
   const u32 tid = threadIdx.x;
   u32* top = reinterpret_cast<u32*>(top_v);
-  if (k16) {  // 16-bit keys: top_n >= 2 of them, padded to 16 bytes in both places
+  if (k16) {  // 16-bit keys: top_n >= 4 of them, padded to 16 bytes in both places
     const uint4* src = reinterpret_cast<const uint4*>(p.top);
     uint4* dst = reinterpret_cast<uint4*>(top);
     for (u32 i = tid; i < (p.top_n * 2 + 15) / 16; i += kBlock) dst[i] = src[i];
     const uint4* bsrc = reinterpret_cast<const uint4*>(p.bstart);
     uint4* bdst = reinterpret_cast<uint4*>(bst);
     for (u32 i = tid; i < (n_bst * 2 + 15) / 16; i += kBlock) bdst[i] = bsrc[i];
-  } else if (p.top_n >= 4) {
+  } else {
     const uint4* src = reinterpret_cast<const uint4*>(p.top);
     uint4* dst = reinterpret_cast<uint4*>(top);
     for (u32 i = tid; i < p.top_n / 4; i += kBlock) dst[i] = src[i];
     const uint4* bsrc = reinterpret_cast<const uint4*>(p.bstart);
     uint4* bdst = reinterpret_cast<uint4*>(bst);
     for (u32 i = tid; i < (n_bst * 2 + 15) / 16; i += kBlock) bdst[i] = bsrc[i];
-  } else {
-    for (u32 i = tid; i < p.top_n; i += kBlock) top[i] = p.top[i];
-    for (u32 i = tid; i < n_bst; i += kBlock) bst[i] = p.bstart[i];
   }
 }
 
