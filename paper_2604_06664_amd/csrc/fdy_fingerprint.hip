@@ -228,10 +228,10 @@ __device__ void group_small(const u64* keys, u32 G, u32* template_id, u32* tmpl_
 }
 
 // The whole grouping by one workgroup of T threads, table in LDS: up to kLdsGraphs graphs.
-constexpr u32 kLdsGraphs = 8192, kLdsSlots = 2 * kLdsGraphs;
+constexpr u32 kLdsGraphs = 8192;
 template <int T>
 __device__ void group_in_lds(const u64* keys, u32 G, u32* template_id, u32* tmpl_graph, u32* n_templates,
-                             u32* table /* LDS, kLdsSlots */) {
+                             u32* table /* LDS, 2 * kLdsGraphs */) {
   if (G <= kSmallGraphs) {
     group_small<T>(keys, G, template_id, tmpl_graph, n_templates, table);
     return;

@@ -20,7 +20,7 @@ constexpr u32 kFlatOutSubs = 32768;
 // workers, a quarter pointers, 4,096 allocations): 17 sub-tiles 6.0 / 9.0, 1,024 9.4 / 9.2, 1,536
 // 10.3 / 9.6, 2,048 12.9 / 10.4, 4,096 23 / 14.5, 16,384 50 / 33: many small workgroups start
 // sooner and share the staging's latency, but each chunk costs a ticket and a look-back.  With
-// output 11 (170 registers per lane: with 15 the words in hand spill, 2 M words 17.5 against 14.7).
+// output 11 (145 registers per lane: 15 leave room for 128 and spill, 2 M words 17.5 against 14.7).
 constexpr u32 kFlatFewSubs = 1536;
 __host__ __device__ __forceinline__ u32 flat_workers(u32 n_sub, bool out) {
   return n_sub < kFlatFewSubs ? kFlatWorkers : out ? kFlatWorkersOut : kFlatWorkersBig;

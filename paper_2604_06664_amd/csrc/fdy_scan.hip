@@ -1082,7 +1082,7 @@ __device__ __forceinline__ void write_round(const ScanParams& p, const RoundResu
 // requests but the chains around them: with the general kernel below (two waves per SIMD, its
 // look-back in the way of a searching wave) 5.8 M words against 4,096 allocations took 41.5 us,
 // 14 us of which went when the look-back was left out.  Hence
-//   - 128 registers instead of 256: a wave has one sub-tile in hand, not two, and room for a
+//   - 128 registers (145 with output) instead of 256: a wave has one sub-tile in hand, not two, and room for a
 //     result per word (a queue of 256 candidates, refilled once if there are more): there is no
 //     dense case, no staging area and no second search, whatever the share of candidates;
 //   - one wave of the workgroup, the clerk, owns no words: it draws the tickets and looks back
@@ -2362,7 +2362,9 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
   }
   if (flat) {
     const size_t lds = flat_level_bytes(tp.top_n, p.bucket_log2) + (size_t)flat_w * kFlatQ * 10;
-    // as many workgroups as can be resident (128 registers per lane: 16 waves per compute unit)
+    // As many workgroups as can be resident: 16 waves per compute unit (128 registers per lane; 12
+    // with output, whose 145 registers and twelve waves are one workgroup as well).  Launches of
+    // the 8-wave form have fewer workgroups than there are compute units.
     const u32 fit = (u32)(160 * 1024 / (lds + 512)), room = 16u / (flat_w + 1);
     u32 fgrid = (u32)n_cu * (fit < room ? fit : room);
     if (fgrid > p.n_chunks) fgrid = p.n_chunks;
