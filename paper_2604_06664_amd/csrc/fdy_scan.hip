@@ -309,11 +309,15 @@ constexpr size_t kPreparedTurn = 128;  // byte offset of the turn (fdy_segment_f
 
 // Is the caller's prepared table one that was made for this table, this tuning and at least
 // this many words?  (The host cannot look into device memory without a round trip.)
+__device__ __forceinline__ bool prepared_ok(const u64* prepared, u32 n_alloc, u32 top_log2, u64 n_words,
+                                            const fdy_alloc* for_table) {
+  if (!prepared) return true;
+  const u64 magic = prepared[0], sizes = prepared[1], max_words = prepared[2], table = prepared[3];
+  return magic == kPreparedMagic && (u32)sizes == n_alloc && (u32)(sizes >> 32) == top_log2 &&
+         n_words <= max_words && table == (u64)(uintptr_t)for_table;
+}
 __device__ __forceinline__ bool prepared_ok(const ScanParams& p) {
-  if (!p.prepared) return true;
-  const u64 magic = p.prepared[0], sizes = p.prepared[1], max_words = p.prepared[2], table = p.prepared[3];
-  return magic == kPreparedMagic && (u32)sizes == p.n_alloc && (u32)(sizes >> 32) == p.top_log2 &&
-         p.n_words <= max_words && table == (u64)(uintptr_t)p.table;
+  return prepared_ok(p.prepared, p.n_alloc, p.top_log2, p.n_words, p.table);
 }
 
 // The scan's counters live in memory that outlasts the call when the caller prepared the table
@@ -1834,8 +1838,12 @@ struct ScanInit {
 // Line i of the compact table copy together with the new bases of its eight regions, in one
 // 128-byte memory line (32 bytes of it unused): built per call of the ordered scan with output,
 // from that call's base map.
-// One thread per 16-byte piece, so that reads and writes are whole lines.
-__global__ void scan_leafmap_kernel(const uint4* cleaf, const u64* new_base, u32 n_alloc, u32 lines, uint4* out) {
+// One thread per 16-byte piece, so that reads and writes are whole lines.  A prepared table that is
+// not this call's is left alone, as by the scan that follows (which reports it): its lines may lie
+// behind its end.
+__global__ void scan_leafmap_kernel(const uint4* cleaf, const u64* new_base, u32 n_alloc, u32 lines, uint4* out,
+                                    const u64* prepared, u32 top_log2, u64 n_words, const fdy_alloc* table) {
+  if (!prepared_ok(prepared, n_alloc, top_log2, n_words, table)) return;
   const u64 t = (u64)blockIdx.x * blockDim.x + threadIdx.x;
   const u64 i = t >> 3;
   const u32 piece = (u32)t & 7;
@@ -2334,7 +2342,8 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
   if ((ordered_out || fused) && tp.leaf_lines) {
     uint4* lm = (uint4*)(tb + tp.off_leafmap);
     launch(FDY_PROF_SCAN_RECORDS, scan_leafmap_kernel, dim3((u32)(((u64)tp.leaf_lines * 8 + 255) / 256)), dim3(256),
-           0, stream, (const uint4*)a.cleaf, (const u64*)d_new_base, n_alloc, tp.leaf_lines, lm);
+           0, stream, (const uint4*)a.cleaf, (const u64*)d_new_base, n_alloc, tp.leaf_lines, lm, p.prepared, p.top_log2,
+           p.n_words, p.table);
     FDY_HIP_TRY(hipGetLastError());
     p.leafmap = lm;
   }
