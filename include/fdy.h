@@ -207,23 +207,16 @@ int fdy_layout_replay(const fdy_alloc* h_recorded, uint32_t n, uint64_t recorded
  *                    written and FDY_ST_CAPACITY is raised)
  *   d_workspace      device, 256-byte aligned, at least fdy_scan_workspace_bytes() bytes;
  *                    contents on entry are irrelevant, contents on exit are unspecified.
- *                    The size is the search hierarchy built from the table (about 30 bytes
- *                    per allocation beyond 16,384 of them: packed copies of the table, and
- *                    room for one new base per allocation beside them, which
- *                    fdy_scan_pointers_rebase fills per call) and 8 bytes per 4,096 words;
- *                    0 is returned for n_words beyond the limit above.  Tables of up to
- *                    16,384 allocations are answered up to 32 KiB more, with which their
+ *                    The size is the search hierarchy built from the table (12 to 21 bytes
+ *                    per allocation beyond 16,384 of them: packed copies of the table, and from
+ *                    131,073 allocations on room for one new base per allocation beside them,
+ *                    which fdy_scan_pointers_rebase and fdy_scan_rebase fill per call) and 8 bytes
+ *                    per 4,096 words; 0 is returned for n_words beyond the limit above.  Tables of
+ *                    up to 16,384 allocations are answered up to 32 KiB more, with which their
  *                    ordered scans are faster (up to a fifth); they run without as well, so a
  *                    buffer sized for a table serves every smaller one.
- *                    Optional staging area (tables of more than 16,384 allocations, and
- *                    fdy_scan_pointers_rebase from 16 Mi words on; the other scans have no
- *                    use for it): where more than 3 words in 8 lie inside the
- *                    table's span (word-dense inputs), the hits of such a stretch are either
- *                    staged (a workspace of fdy_scan_workspace_bytes() +
- *                    fdy_scan_staging_bytes() bytes or more: up to 160 MiB, independent of
- *                    the table) or found by searching the stretch a second time (any smaller
- *                    workspace; about 1.6 times slower on inputs that are dense throughout).
- *                    Same results either way
+ *                    fdy_scan_staging_bytes() is what earlier versions could use on top for
+ *                    word-dense inputs; nothing uses it any more, and it may be left away
  *   d_prepared       NULL, or the table's prepared form (see fdy_scan_table_prepare below)
  *   d_status         device uint32_t or NULL
  */
@@ -247,8 +240,7 @@ int fdy_scan_pointers(const uint64_t* d_words, uint64_t n_words, const fdy_alloc
  *   - the buffer belongs to the table at d_table (same address and contents), to n_words <=
  *     max_words and to the process's tuning at the time; the device checks this and raises
  *     FDY_ST_BAD_PREPARED, writing nothing, when it does not hold.
- * With d_prepared the workspace only holds the optional staging area of dense inputs
- * (fdy_scan_staging_bytes; NULL or anything smaller: none).  d_prepared == NULL: the call
+ * With d_prepared the workspace is not used (it may be NULL).  d_prepared == NULL: the call
  * builds the hierarchy into its workspace itself.
  *
  *   fdy_scan_table_bytes    size of the buffer for a table of n_alloc entries that serves

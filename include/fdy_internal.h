@@ -17,12 +17,10 @@ extern "C" {
 
 enum {
   FDY_TUNE_SCAN_TOP_LOG2 = 0,   /* log2 of the most sampled bases staged in LDS           */
-  FDY_TUNE_SCAN_WG_PER_CU = 1,  /* persistent scan workgroups launched per compute unit    *
-                                 * (not by the kernels of small tables)                    */
+  FDY_TUNE_SCAN_WG_PER_CU = 1,  /* no effect (the scans launch what can be resident)         */
   FDY_TUNE_SCAN_SPIN_LIMIT = 2, /* polls of a predecessor tile before giving up            */
   FDY_TUNE_MAT_MAP_GROUP = 3,     /* base maps per materialize workgroup, 0 = automatic      */
-  FDY_TUNE_SCAN_SMALL_LOG2 = 4, /* inputs below 2^this sub-tiles use the small-chunk scan   *
-                                 * (tables of more than 2^SCAN_TOP_LOG2 allocations)       */
+  FDY_TUNE_SCAN_SMALL_LOG2 = 4, /* only in the answer of fdy_scan_staging_bytes             */
   FDY_TUNE_MAT_SELF_WGS = 5,    /* materialize launches of up to this many workgroups       *
                                  * resolve their tiles themselves (no prep launch); 0: none */
   FDY_TUNE_MAT_ONCE_TILES = 6,  /* a materialization of one map group over at least this many   *
@@ -52,7 +50,7 @@ enum {
   FDY_PROF_MAT_MAIN = 7,
   FDY_PROF_SCAN_OUT = 8,
   FDY_PROF_SCAN_REBASE = 9,
-  FDY_PROF_SCAN_RECORDS = 10, /* the launch ahead of the scan with output (scan_leafmap_kernel) */
+  FDY_PROF_SCAN_RECORDS = 10, /* the launch ahead of the scan with output (scan_records_kernel) */
   FDY_PROF_SLOTS = 11
 };
 int fdy__prof_enable(int n_records);

@@ -1,5 +1,4 @@
-// fdy_flat_state.hpp - chunk states of the ordered scans of small tables (scan_flat_kernel):
-// how many there are, where they lie and what a launch leaves for the next one.  Plain
+// fdy_flat_state.hpp - chunk states of the ordered scans: how many there are, where they lie and what a launch leaves for the next one.  Plain
 // arithmetic, also compiled for the host, where tests/level0/level0_host.hip runs sequences
 // of launches over it.
 #pragma once
@@ -7,23 +6,20 @@
 
 namespace fdy {
 
-constexpr u32 kFlatWorkers = 7, kFlatWorkersBig = 15, kFlatWorkersOut = 11;
+constexpr u32 kFlatWorkers = 7, kFlatWorkersBig = 15;
 
-// Forms with output: from 16 Mi words on the general kernels take over.  A wave there has two
-// sub-tiles in hand, so that the acknowledgement of one's stores (which every later load waits
-// behind) is paid half as often.  us, flat / general, a quarter pointers, 4,096 allocations:
-// rebase 5 M words 22.7 / 45, 12 M 59.5 / 66, 33 M 154 / 143; scan with output 34 / 50, 65 / 75,
-// 161 / 165 (16,384 allocations: 182 / 175).
+// From so many sub-tiles on a `shared` region leaves room in front (see flat_region).
 constexpr u32 kFlatOutSubs = 32768;
 
-// Workers per workgroup of the scans of tables without packed levels.  Measured (us, 7 / 15
+// Workers per workgroup.  Measured (us, 7 / 15
 // workers, a quarter pointers, 4,096 allocations): 17 sub-tiles 6.0 / 9.0, 1,024 9.4 / 9.2, 1,536
 // 10.3 / 9.6, 2,048 12.9 / 10.4, 4,096 23 / 14.5, 16,384 50 / 33: many small workgroups start
-// sooner and share the staging's latency, but each chunk costs a ticket and a look-back.  With
-// output 11 (145 registers per lane: 15 leave room for 128 and spill, 2 M words 17.5 against 14.7).
+// sooner and share the staging's latency, but each chunk costs a ticket and a look-back.  (`out`, a
+// form with output, makes no difference: 5 M words 32.1 us with 11 workers, 30.7 with 15.)
 constexpr u32 kFlatFewSubs = 1536;
 __host__ __device__ __forceinline__ u32 flat_workers(u32 n_sub, bool out) {
-  return n_sub < kFlatFewSubs ? kFlatWorkers : out ? kFlatWorkersOut : kFlatWorkersBig;
+  (void)out;
+  return n_sub < kFlatFewSubs ? kFlatWorkers : kFlatWorkersBig;
 }
 __host__ __device__ __forceinline__ u32 flat_chunks(u32 n_sub, bool out) {
   const u32 w = flat_workers(n_sub, out);
@@ -32,9 +28,8 @@ __host__ __device__ __forceinline__ u32 flat_chunks(u32 n_sub, bool out) {
 
 // Most chunks of a launch of up to max_sub sub-tiles.
 inline u32 flat_most_chunks(u32 max_sub) {
-  u32 most = flat_chunks(max_sub, max_sub < kFlatOutSubs);
+  u32 most = flat_chunks(max_sub, false);
   if (max_sub >= kFlatFewSubs && flat_chunks(kFlatFewSubs - 1, false) > most) most = flat_chunks(kFlatFewSubs - 1, false);
-  if (max_sub >= kFlatOutSubs && flat_chunks(kFlatOutSubs - 1, true) > most) most = flat_chunks(kFlatOutSubs - 1, true);
   return most;
 }
 
@@ -56,16 +51,13 @@ __host__ __device__ __forceinline__ u32 flat_spread(u32 n_chunks, u32 states) {
 }
 
 // Bytes of chunk states that a launch of n_sub sub-tiles cannot do without: one state for eight
-// of them.  That is a state for each of the general kernel's small chunks, and enough for the
-// flat kernel's, closer together than it likes.
+// of them, closer together than the scan likes.
 inline size_t chunk_state_bytes(u32 n_sub) { return ((size_t)((n_sub + 7) / 8) * 8 + 255) & ~(size_t)255; }
 
-// Where the flat kernel's states lie, relative to the first chunk state of a buffer made for
-// max_sub sub-tiles with `bytes` of chunk states (at least chunk_state_bytes).  shared: a prepared
-// table, which launches of both kernels use in turn.  The general one has at least kFlatOutSubs
-// sub-tiles then and chunks of 32: its states come first, the flat kernel's behind them.
-// Otherwise nobody uses the 16-bit form of level 0 either: its `spare` bytes, in front of the
-// chunk states, are states as well.
+// Where the states lie, relative to the first chunk state of a buffer made for max_sub sub-tiles with
+// `bytes` of chunk states (at least chunk_state_bytes).  The hierarchy's last `spare` bytes, in front
+// of the chunk states, are states as well; a `shared` region leaves a state for each 32 sub-tiles in
+// front to others instead (no scan asks for that any more).
 struct FlatRegion {
   long long first;  // bytes from the first chunk state
   u32 states;       // as many as the widest spread can use, at most

@@ -11,10 +11,7 @@ namespace fdy {
 
 // Level-0 keys are (base - span_lo) >> shift with the smallest shift that makes every key of
 // the span fit key_bits bits (all-ones pads).  What the truncation leaves ambiguous is settled
-// on the exact bases, so the shift affects speed only.  Keys are kept in 32 bits (key_bits =
-// 31), or in 16 bits where LDS is needed for other things: then only a key's low half is
-// stored, key_bits = 16 + bucket_log2 makes a bucket at most 2^16 key values wide, and the keys
-// that a bucket's search compares all share their high half with the candidate.
+// on the exact bases, so the shift affects speed only.
 __host__ __device__ __forceinline__ u32 key_shift_for(u64 span_len, u32 key_bits) {
   const u64 m = span_len - 1;
   const u32 bits = m ? 64u - (u32)__builtin_clzll(m) : 0u;
@@ -108,16 +105,15 @@ __host__ __device__ __forceinline__ FlatLevel flat_stage(const P& p, unsigned ch
   return f;
 }
 
-// Interval search of N distances d = word - span_lo per lane: region, and the offset inside it if
-// the entry holds the word (else any value at or above the entry's size: see hit).
+// Level 0 for N distances d = word - span_lo per lane: byte offset of the last key not above each
+// word's (key 0 is 0).
 // The place among the keys of the bucket is found without branches: the step count is the one
 // that the fullest of the wave's buckets needs, a step that leads past the bucket meets keys
 // above the word's (keys ascend over the whole table) or the padding.
 // any(b): whether b holds in some lane of the wave.
-template <int N, typename P, typename Any>
-__host__ __device__ __forceinline__ void flat_search(const P& p, const FlatLevel& f, const u64 (&d)[N], u32 (&n)[N],
-                                                     u64 (&off)[N], bool (&hit)[N], Any any) {
-  u32 kw[N], at[N], most = 0;  // at: byte offset of the first key not known to be at or below the word's
+template <int N, typename Any>
+__host__ __device__ __forceinline__ void flat_place(const FlatLevel& f, const u64 (&d)[N], u32 (&at)[N], Any any) {
+  u32 kw[N], most = 0;  // at: byte offset of the first key not known to be at or below the word's
 #pragma unroll
   for (int c = 0; c < N; ++c) {
     kw[c] = (u32)(d[c] >> f.key_shift);
@@ -147,13 +143,21 @@ __host__ __device__ __forceinline__ void flat_search(const P& p, const FlatLevel
   if (steps >= 3) fixed(std::integral_constant<u32, 16>{});
   if (steps >= 2) fixed(std::integral_constant<u32, 8>{});
   if (steps >= 1) fixed(std::integral_constant<u32, 4>{});
+#pragma unroll
+  for (int c = 0; c < N; ++c) at[c] -= 4;
+}
+
+// Interval search where every base has its key in level 0: region, and the offset inside it if
+// the entry holds the word (else any value at or above the entry's size: see hit).
+template <int N, typename P, typename Any>
+__host__ __device__ __forceinline__ void flat_search(const P& p, const FlatLevel& f, const u64 (&d)[N], u32 (&n)[N],
+                                                     u64 (&off)[N], bool (&hit)[N], Any any) {
+  u32 at[N];
+  flat_place<N>(f, d, at, any);
   const unsigned char* table = reinterpret_cast<const unsigned char*>(p.table);
   u64x2 e[N];
 #pragma unroll
-  for (int c = 0; c < N; ++c) {
-    at[c] -= 4;  // the last key not above the word's; key 0 is 0
-    e[c] = *reinterpret_cast<const u64x2*>(table + at[c] * 4);
-  }
+  for (int c = 0; c < N; ++c) e[c] = *reinterpret_cast<const u64x2*>(table + at[c] * 4);
   // a base with the word's own truncated key may still lie above the word: one entry back, or,
   // where a run of blocks shares a key, a search among the exact bases.  A valid table's first
   // base is never above a candidate; an invalid one's may be (a span that wraps): a miss.

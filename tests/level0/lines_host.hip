@@ -1,0 +1,172 @@
+// Lines and nodes of the table hierarchy (csrc/fdy_lines.hpp), compiled for the host under
+// AddressSanitizer: what is packed from a table is searched with words around every edge of it,
+// and the entry found is compared with the definition; tables that no valid layout has must not
+// lead outside the table.
+#include <algorithm>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <vector>
+
+#include "fdy_level0.hpp"
+#include "fdy_lines.hpp"
+
+using namespace fdy;
+
+namespace {
+
+u64 rng = 0x9e3779b97f4a7c15ull;
+u64 next() {  // xorshift64
+  rng ^= rng << 13;
+  rng ^= rng >> 7;
+  return rng ^= rng << 17;
+}
+u64 below(u64 n) { return next() % n; }
+u64 log_uniform(int lo, int hi) {  // between 2^lo and 2^hi
+  const int b = lo + (int)below(hi - lo + 1);
+  return (1ull << b) | (next() & ((1ull << b) - 1));
+}
+
+int failures = 0;
+unsigned long long runs = 0, compact_lines = 0, wide_lines = 0, nodes = 0;
+
+struct Table {
+  fdy_alloc* t;  // a heap block of its exact size
+  u32 n;
+  explicit Table(const std::vector<fdy_alloc>& v) : n((u32)v.size()) {
+    t = (fdy_alloc*)aligned_alloc(16, n * sizeof(fdy_alloc));
+    memcpy(t, v.data(), n * sizeof(fdy_alloc));
+  }
+  ~Table() { free(t); }
+};
+
+void report(const char* what, const Table& t, u64 w, u32 line) {
+  if (++failures <= 10) printf("%s: word %llx, line %u of %u entries\n", what, (unsigned long long)w, line, t.n);
+}
+
+// The last entry at or below w among the first n, by the definition (0 if there is none).
+u32 last_below(const Table& t, u32 n, u64 w) {
+  u32 want = 0;
+  for (u32 k = 0; k < n; ++k)
+    if (t.t[k].base <= w) want = k;
+  return want;
+}
+
+// The entry found in `line`, as the kernels do: the form asked for, the wide one, the table.
+void search_line(const Table& t, u32 line, u64 w, u64 told, bool valid) {
+  PackedLine l;
+  pack_line(t.t, (u64)line * 8, t.n, told, l);
+  uint4 c[2], q[4];
+  memcpy(c, l.compact, 32);
+  memcpy(q, l.wide, 64);
+  const u32 end = std::min(t.n, line * 8 + 8), want = last_below(t, end, w);
+  for (int form = 0; form < 2; ++form) {
+    u32 at = 99, n = line * 8;
+    u64x2 e{0, 0};
+    const bool got = form ? pick_wide_line(q, w, told, at, e) : pick_compact_line(c, w, told, at, e);
+    (form ? wide_lines : compact_lines) += got;
+    if (got) n += at;
+    else if (t.t[line * 8].base <= w) find_exact(t.t, line * 8, end, w, n, e);
+    else find_exact(t.t, 0, t.n, w, n, e);
+    ++runs;
+    if (n >= t.n || (got && at > 7)) report("outside", t, w, line);
+    else if (valid && w >= t.t[0].base && (n != want || e.x != t.t[n].base || e.y != t.t[n].size)) report("line", t, w, line);
+  }
+}
+
+// The node that holds entry i's line (step 8) or entry i itself (step 1), told all but `drop` low
+// bits of its key 0: the child chosen lies inside the table and is the last whose key is not
+// above w, but for bits that the node's shift loses; and the child's key is its own first base
+// but for bits that it can keep.
+void search_node(const Table& t, u32 i, u64 step, u64 w, u32 drop, bool valid) {
+  const u64 k0 = i / (8 * step) * (8 * step);
+  const u64 b0 = t.t[k0].base, told = (b0 - t.t[0].base) >> drop << drop;
+  PackedNode p;
+  pack_node(t.t, k0, step, t.n, t.t[0].base + told, p);
+  uint4 q[2];
+  memcpy(q, p.w, 32);
+  u32 at = 0;
+  u64 first = t.t[0].base + told;
+  ++runs;
+  if (!pick_node(q, w, at, first)) {
+    if (p.w[0] != kMarked) report("node refused", t, w, i);
+    return;
+  }
+  ++nodes;
+  if (at > 7 || k0 + step * at >= t.n) return report("node outside", t, w, i);
+  if (!valid || b0 > w) return;
+  const u32 s = p.w[0] & 31;
+  u32 want = 0;
+  for (u32 h = 1; h < 8 && k0 + step * h < t.n; ++h)
+    if ((t.t[k0 + step * h].base - b0) >> s <= (w - b0) >> s) want = h;
+  const u64 key = t.t[k0 + step * at].base;
+  if (at != want || key - first >= 1ull << s || first != told_of_child(t.t, k0, step, t.n, at)) report("node", t, w, i);
+}
+
+void search(const std::vector<fdy_alloc>& v, bool valid) {
+  const Table t(v);
+  const u64 lo = t.t[0].base;
+  // told in full, but for the bits that level 0 would drop, and for one more than can be kept
+  const u32 own = key_shift_for(t.t[t.n - 1].base + t.t[t.n - 1].size - lo, 31);
+  for (u32 i = 0; i < t.n; ++i)
+    for (u64 w : {t.t[i].base - 1, t.t[i].base, t.t[i].base + t.t[i].size / 2, t.t[i].base + t.t[i].size - 1,
+                  t.t[i].base + t.t[i].size}) {
+      for (u32 drop : {0u, own, 28u}) {
+        for (u32 line : {i / 8, (i + 7) / 8, (t.n - 1) / 8})
+          if (line * 8 < t.n) search_line(t, line, w, lo + ((t.t[line * 8].base - lo) >> drop << drop), valid);
+        for (u64 step : {1ull, 8ull}) search_node(t, i, step, w, drop, valid);
+      }
+    }
+}
+
+// Layouts of one granularity and a range of sizes, with a share of much larger blocks.
+std::vector<fdy_alloc> layout(u32 n, int granule, int size_granule, int hi, u32 big_every) {
+  std::vector<fdy_alloc> v;
+  u64 at = (next() & 0xffff) << granule;
+  for (u32 i = 0; i < n; ++i) {
+    u64 z = log_uniform(0, hi) >> size_granule << size_granule;
+    if (!z) z = 1ull << size_granule;
+    if (big_every && below(big_every) == 0) z = log_uniform(hi, hi + 8) >> 21 << 21;
+    if (!z) z = 1ull << 21;
+    v.push_back(fdy_alloc{at, z});
+    const u64 step = (z + (1ull << granule) - 1) >> granule << granule;
+    at += step + (below(4) << granule);
+  }
+  return v;
+}
+
+}  // namespace
+
+int main() {
+  for (int round = 0; round < 400; ++round) {
+    const u32 n = 1 + (u32)below(200);
+    const int g = (int)below(22), sg = (int)below(g + 1);
+    search(layout(n, g, sg, std::max(sg, 1) + (int)below(26), round % 3 ? 0 : 5), true);
+    search(layout(n, 21, 9, 26, round % 2 ? 12 : 0), true);  // 2 MiB granules, some gigabytes
+    search(layout(n, 4, 0, 26, 0), true);                    // a caching allocator's blocks
+    std::vector<fdy_alloc> v(n);                             // nothing that fdy_table_validate passes
+    const int bits = 1 + (int)below(64);
+    for (auto& e : v) e = fdy_alloc{next() >> (64 - bits), next() >> below(64)};
+    search(v, false);
+  }
+  {  // distances and sizes at the limits of the forms
+    for (int bits : {11, 12, 13, 17, 18, 19, 20, 25, 26, 27, 31, 32, 33})
+      for (int delta : {-1, 0, 1})
+        for (int s : {0, 9, 21, 31, 33}) {
+          if (bits + s > 58) continue;
+          const u64 x = ((1ull << bits) + delta) << s;
+          std::vector<fdy_alloc> a, b;
+          for (u32 i = 0; i < 8; ++i) a.push_back(fdy_alloc{(u64)i << s, 1ull << s});
+          a[7].base = x;
+          if (a[7].base > a[6].base) search(a, true);
+          for (u32 i = 0; i < 8; ++i) b.push_back(fdy_alloc{(u64)i << (bits + s + 1), i == 4 ? x : 1ull << s});
+          search(b, true);
+          std::vector<fdy_alloc> c;
+          for (u32 i = 0; i < 64; ++i) c.push_back(fdy_alloc{(u64)i << s, 1ull << s});
+          for (u32 i = 56; i < 64; ++i) c[i].base = x + ((u64)i << s);
+          search(c, true);
+        }
+  }
+  printf("%llu run (%llu compact lines, %llu wide, %llu nodes), %d wrong\n", runs, compact_lines, wide_lines, nodes, failures);
+  return failures ? 1 : 0;
+}
