@@ -17,12 +17,11 @@
 //                            begin; they end where the next tile's begin).  Patch blocks (one
 //                            thread per tile and rank) do the same for each rank's patch list.
 //                            Dims blocks (one thread per node) write the launch dimensions of
-//                            the template with the graph's grid overrides.  Plain per-lane
-//                            binary searches: tens of thousands of them run side by side, and
-//                            one request per halving is what the memory system serves best;
-//                            the kernel's time is its longest chain of dependent loads.  One
-//                            launch rather than four because small archives are bound by
-//                            launch latency.
+//                            the template with the graph's grid overrides.  The kernel's time is
+//                            its longest chain of dependent loads: up to 2,048 tiles several lanes
+//                            search for each end of a slice together; beyond, per-lane searches,
+//                            tens of thousands side by side.  One launch rather than four because
+//                            small archives are bound by launch latency.
 //   main  (tile x map group) stages the template tile in LDS and the tile's relocation entries
 //                            in registers once, then per base map of its group scatters c2
 //                            rebased pointers (new_base[m][region] + offset), c3 32-bit
@@ -278,6 +277,26 @@ __device__ __forceinline__ void lane_lower_bound_pair(KeyA key_a, u32 lo_a, u32 
   res_b = lo_b;
 }
 
+// Lower bound by K neighbouring lanes together (a power of two; each K of a wave search for their own
+// target, all lanes of the wave call): K probes a step, so that a list of n entries takes log K n
+// round trips, where one lane alone takes log2 n.  For launches whose searches leave most of the
+// chip's lanes idle.
+template <u32 K, typename KeyFn>
+__device__ __forceinline__ u32 group_lower_bound(KeyFn key, u32 lo, u32 hi, u64 target) {
+  static_assert(K >= 2 && K < 64 && (K & (K - 1)) == 0, "lanes of one search");
+  const u32 l = lane_id(), i = l & (K - 1);
+  if (hi < lo) hi = lo;  // (offsets that decrease)
+  while (ballot(lo < hi)) {
+    const u32 n = hi - lo, stride = (n + K - 1) / K, at = lo + (i + 1) * stride - 1;
+    const u64 k = n && at < hi ? key(at) : ~0ull;  // past the end: never below
+    const u32 below = __popcll(ballot(k < target) >> (l & ~(K - 1)) & ((1ull << K) - 1));  // a prefix
+    const u32 nlo = min(lo + below * stride, hi);
+    hi = n ? nlo + min(stride - 1, hi - nlo) : hi;
+    lo = n ? nlo : lo;
+  }
+  return lo;
+}
+
 // The per-graph prefix sums as the tile, patch and dims blocks read them: from the workspace
 // (written by mat_prep_graphs_kernel) or from the block's own LDS copy.
 template <bool kOwn>
@@ -375,6 +394,84 @@ __device__ __forceinline__ void prep_tiles_block(const MatParams& p, const PrepV
   e.reloc_seg = rl0;
   e.pad[0] = e.pad[1] = e.pad[2] = 0;
   *ent = e;
+}
+
+// The same with half a wave per tile, eight lanes for each of its four ends: what the kernel takes is
+// its longest chain of dependent loads, and 13,400 relocations and 1,880 patches are five and six
+// steps, not seven and 22.  For up to kGroupTiles tiles; with more, the workgroups that this takes
+// (each repeats the per-graph sums) cost what the steps save.  us, a thread per tile / half a wave:
+// 1,870 tiles and 8 ranks 12.9 / 10.1, 446 tiles 8.5 / 7.6, 3,391 tiles 13.7 / 15.6.
+constexpr u32 kGroupTiles = 2048;
+template <bool kOwn>
+__device__ __forceinline__ void prep_tile_group(const MatParams& p, const PrepView<kOwn>& v, u32 j) {
+  const fdy_mat_desc& d = p.d;
+  const u32 l = lane_id() & 31;
+  if (v.n_tiles == 0) {  // (the same for all; no tile has a place)
+    if (l == 0 && j < p.ws.max_tiles) p.ws.tiles[j].n_words = 0;
+    return;
+  }
+  const bool valid = j < v.n_tiles;
+  const TileGeom q = tile_geometry(p, v, valid ? j : 0);
+  const u32 rl0 = (u32)d.src_reloc_off[q.s], rl1 = (u32)d.src_reloc_off[q.s + 1];
+  const u32 ov0 = (u32)d.ovr_off[q.g], ov1 = (u32)d.ovr_off[q.g + 1];
+  // lanes 0..15: the relocation list, its entries from the tile's first word on, and from behind its
+  // last; lanes 16..31: the overrides
+  const bool of_ovr = l & 16, end = l & 8;
+  const fdy_reloc* relocs = d.relocs;
+  const fdy_ovr32* ovr = d.ovr;
+  const u64 target = of_ovr ? (q.k0 + (end ? q.n : 0u)) * 8 : q.src_word + (end ? q.n : 0u);
+  const u32 lo = of_ovr ? ov0 : rl0, hi = of_ovr ? ov1 : rl1;
+  const u32 found = group_lower_bound<8>([&](u32 i) { return of_ovr ? (u64)ovr[i].byte_off : (u64)relocs[i].word; },
+                                          !valid || (q.last && end) ? hi : lo, hi, target);
+  MatTile e;
+  e.src_word = q.src_word;
+  e.out_word = v.out_word_off[q.g] + q.k0;
+  e.n_words = q.n;
+  e.g = q.g;
+  e.tmpl = q.t;
+  e.k0 = (u32)q.k0;
+  const u32 at = lane_id() & 32;
+  e.reloc_lo = __shfl(found, at);
+  e.reloc_hi = max((u32)__shfl(found, at + 8), e.reloc_lo);  // (a list out of order can cross them)
+  e.ovr_lo = __shfl(found, at + 16);
+  e.ovr_hi = max((u32)__shfl(found, at + 24), e.ovr_lo);
+  e.reloc_seg = rl0;
+  e.pad[0] = e.pad[1] = e.pad[2] = 0;
+  if (l != 0 || j >= p.ws.max_tiles) return;
+  MatTile* ent = &p.ws.tiles[j];
+  if (!valid) {
+    ent->n_words = 0;
+    return;
+  }
+  if (e.reloc_hi - e.reloc_lo > q.n) {  // strictly ascending: at most one entry per word
+    e.reloc_hi = e.reloc_lo + q.n;
+    raise_status(p.d_status, FDY_ST_BAD_ORDER);
+  }
+  if (q.k0 == 0 && e.reloc_lo != rl0) raise_status(p.d_status, FDY_ST_BAD_INDEX);
+  *ent = e;
+}
+
+// A slice of a rank's patch list by eight lanes, four for either end: up to kGroupPairs pairs of
+// tile and rank.
+constexpr u32 kGroupPairs = 65536;
+template <bool kOwn>
+__device__ __forceinline__ void prep_patch_group(const MatParams& p, const PrepView<kOwn>& v, u32 i) {
+  const fdy_mat_desc& d = p.d;
+  const u32 R = d.n_ranks;
+  const bool valid = i < v.n_tiles * R;  // (at most kGroupPairs)
+  const fdy_patch* patch = d.patch;
+  u32 p0 = 0, p1 = 0;
+  u64 target = 0;
+  if (valid) {
+    const TileGeom e = tile_geometry(p, v, i / R);
+    const u64 row = (u64)e.t * R + i % R;
+    p0 = (u32)d.patch_off[row];
+    p1 = (u32)d.patch_off[row + 1];
+    target = e.k0 + ((lane_id() & 4) ? e.n : 0u);
+  }
+  const u32 found = group_lower_bound<4>([&](u32 q) { return (u64)patch[q].word; }, p0, p1, target);
+  const u32 lo = __shfl(found, lane_id() & ~7u), hi = __shfl(found, lane_id() | 4u);
+  if (valid && (lane_id() & 7) == 0) p.ws.tile_patch[i] = make_uint2(lo, max(lo, hi));
 }
 
 // Thread i: (output tile, rank) pair i: the slice of the rank's patch list inside the tile.
@@ -931,8 +1028,10 @@ __global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 n_
 // is then not needed at all.  Block 0 reports what that kernel would have reported.
 constexpr u32 kOwnSumsMax = 1024;
 constexpr u32 kCheckBlocks = 96;
+// group_tiles, group_patch: the tiles' and patch slices' ends by several lanes each.
 template <bool kOwnSums>
-__global__ __launch_bounds__(256, 8) void mat_prep_tiles_kernel(MatParams p, u32 nb_tiles, u32 nb_patch) {
+__global__ __launch_bounds__(256, 8) void mat_prep_tiles_kernel(MatParams p, u32 nb_tiles, u32 nb_patch, bool group_tiles,
+                                                                bool group_patch) {
   if (blockIdx.x >= gridDim.x - kCheckBlocks) {  // the last blocks verify the order of the short lists
     check_lists(p, blockIdx.x - (gridDim.x - kCheckBlocks), kCheckBlocks);
     return;
@@ -990,9 +1089,15 @@ __global__ __launch_bounds__(256, 8) void mat_prep_tiles_kernel(MatParams p, u32
     v.ok = p.ws.hdr->ok;
   }
   const u32 b = blockIdx.x;
-  if (b < nb_tiles) prep_tiles_block(p, v, b, s_lo);
-  else if (b < nb_tiles + nb_patch) prep_patch(p, v, (u64)(b - nb_tiles) * 256 + threadIdx.x);
-  else write_dims(p, v, (u64)(b - nb_tiles - nb_patch) * 256 + threadIdx.x);
+  if (b < nb_tiles) {
+    if (group_tiles) prep_tile_group(p, v, b * 8 + (threadIdx.x >> 5));
+    else prep_tiles_block(p, v, b, s_lo);
+  } else if (b < nb_tiles + nb_patch) {
+    if (group_patch) prep_patch_group(p, v, (b - nb_tiles) * 32 + (threadIdx.x >> 3));
+    else prep_patch(p, v, (u64)(b - nb_tiles) * 256 + threadIdx.x);
+  } else {
+    write_dims(p, v, (u64)(b - nb_tiles - nb_patch) * 256 + threadIdx.x);
+  }
 }
 
 bool desc_ok(const fdy_mat_desc* d) {
@@ -1134,14 +1239,16 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
     launch(FDY_PROF_MAT_PREP_GRAPHS, mat_prep_graphs_kernel, dim3(1), dim3(1024), 0, stream, p);
     FDY_HIP_TRY(hipGetLastError());
   }
-  u32 nb_tiles = (p.ws.max_tiles + kPrepTiles - 1) / kPrepTiles;
-  const u32 nb_patch = p.d.map_rank ? (u32)(((u64)p.ws.max_tiles * p.d.n_ranks + 255) / 256) : 0;
+  const u64 pairs = (u64)p.ws.max_tiles * p.d.n_ranks;  // (0 ranks without a rank map)
+  const bool group_tiles = p.ws.max_tiles <= kGroupTiles, group_patch = pairs <= kGroupPairs;
+  u32 nb_tiles = group_tiles ? (p.ws.max_tiles + 7) / 8 : (p.ws.max_tiles + kPrepTiles - 1) / kPrepTiles;
+  const u32 nb_patch = (u32)(group_patch ? (pairs + 31) / 32 : (pairs + 255) / 256);
   const u32 nb_dims = (d_out_dims && d.out_nodes_total) ? (u32)((d.out_nodes_total + 255) / 256) : 0;
   if (own_sums && nb_tiles + nb_patch + nb_dims == 0) nb_tiles = 1;  // someone has to verify the totals
   if (nb_tiles + nb_patch + nb_dims) {
     const u32 nb = nb_tiles + nb_patch + nb_dims + kCheckBlocks;
     launch(FDY_PROF_MAT_PREP_TILES, own_sums ? mat_prep_tiles_kernel<true> : mat_prep_tiles_kernel<false>, dim3(nb),
-           dim3(256), 0, stream, p, nb_tiles, nb_patch);
+           dim3(256), 0, stream, p, nb_tiles, nb_patch, group_tiles, group_patch);
     FDY_HIP_TRY(hipGetLastError());
   }
   if (p.ws.max_tiles) {

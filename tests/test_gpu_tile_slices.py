@@ -1,0 +1,41 @@
+"""The slices of relocations, overrides and rank patches that fall into an output tile: lists of lengths
+around the steps of a search by four or eight lanes, and tile counts on both sides of the one (2,048)
+from which a thread looks for a tile's ends alone."""
+import numpy as np
+import pytest
+
+import oracle as orc
+from synth import MatProblem
+from synth import layout as L
+
+pytestmark = pytest.mark.gpu
+TILE = 2048
+
+
+def places(rng, n, k):
+    return np.sort(rng.choice(n, min(n, k), replace=False))
+
+
+@pytest.mark.parametrize("tiles", [1, 2, 9, 300, 2046, 2047, 2049])
+@pytest.mark.parametrize("entries", [0, 1, 8, 9, 65, 4097, 200_000])
+def test_slices(tiles, entries):
+    from tests.support import session
+    from tests.test_gpu_parity import check_mat
+
+    rng = np.random.default_rng(tiles * 7 + entries)
+    n, regions, ranks = tiles * TILE - 5, 100, 3
+    r = np.zeros(min(n, entries), L.RELOC)
+    r["word"], r["region"], r["offset"] = places(rng, n, entries), rng.integers(0, regions, len(r)), rng.integers(0, 1 << 40, len(r))
+    ovr = np.zeros(min(2 * n, entries), L.OVR32)
+    ovr["byte_off"], ovr["value"] = places(rng, 2 * n, entries) * 4, rng.integers(0, 1 << 32, len(ovr))
+    lists = []
+    for k in (entries, entries // 3, 5):
+        e = np.zeros(min(n, k), L.PATCH)
+        e["word"], e["value"] = places(rng, n, k), rng.integers(0, 1 << 63, len(e))
+        lists.append(e)
+    mp = MatProblem(src_words=rng.integers(0, 1 << 63, n, dtype=np.uint64), src_word_off=[0, n], src_nodes=np.zeros(0, L.NODE),
+                    src_node_off=[0, 0], relocs=r, src_reloc_off=[0, len(r)], tmpl_graph=[0], graph_tmpl=[0], ovr=ovr,
+                    ovr_off=[0, len(ovr)], govr=np.zeros(0, L.GRID_OVR), govr_off=[0, 0],
+                    new_base=rng.integers(0, 1 << 63, (3, regions), dtype=np.uint64), map_rank=[1, 0, 2], n_ranks=ranks,
+                    patch=np.concatenate(lists), patch_off=np.cumsum([0] + [len(e) for e in lists]).astype(np.uint64))
+    check_mat(session, orc, mp, tag=f"{tiles} tiles, {entries} entries")
