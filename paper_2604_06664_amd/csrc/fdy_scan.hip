@@ -206,7 +206,8 @@ struct PreparedHeader {
 };
 constexpr u64 kPreparedMagic = 0x3159445f4c424154ull;  // "TABL_DY1"
 constexpr size_t kPreparedHeader = 256;
-constexpr size_t kPreparedTurn = 128;  // byte offset of the turn (fdy_segment_fingerprint's counter lies at 64)
+constexpr size_t kPreparedTurn = 128;  // byte offset of the turn (fdy_segment_fingerprint's counters lie at 64, 192, 196, 320
+                                       // and 448: the last two behind the scan's own)
 
 // Is the caller's prepared table one that was made for this table, this tuning and at least
 // this many words?  (The host cannot look into device memory without a round trip.)
