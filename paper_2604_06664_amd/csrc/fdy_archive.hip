@@ -94,17 +94,30 @@ extern "C" uint32_t fdy_archive_elem_bytes(uint32_t kind) {
 extern "C" uint64_t fdy_archive_sum(const void* h_bytes, size_t n) {
   const unsigned char* p = static_cast<const unsigned char*>(h_bytes);
   const size_t k = n / 8;
-  // four independent accumulators keep the multiplier pipeline full
-  uint64_t s0 = 0, s1 = 0, s2 = 0, s3 = 0;
-  size_t i = 0;
-  for (; i + 4 <= k; i += 4) {
-    uint64_t w[4];
-    memcpy(w, p + i * 8, 32);
-    s0 += w[0] * (2 * (uint64_t)i + 1);
-    s1 += w[1] * (2 * (uint64_t)i + 3);
-    s2 += w[2] * (2 * (uint64_t)i + 5);
-    s3 += w[3] * (2 * (uint64_t)i + 7);
+  // Word i counts 2 i + 1 times.  In rows of kLanes words that takes no multiplication: with S the sum
+  // of a column's words so far and T the sum of those S, a column of R rows has T = sum of (R - m) times
+  // its word of row m.  Columns side by side are vector additions (16 bytes: what every host of
+  // this library has), where a 64-bit product per word was bound by the multiplier: opening 11 MB
+  // from the page cache took 301 us, 131 now.  (All pages mapped ahead by MADV_POPULATE_READ: 152.)
+  typedef uint64_t pair __attribute__((vector_size(16)));
+  constexpr size_t kPairs = 4, kLanes = 2 * kPairs;
+  pair S[kPairs] = {}, T[kPairs] = {};
+  const size_t rows = k / kLanes;
+  for (size_t m = 0; m < rows; ++m) {
+#pragma unroll
+    for (size_t j = 0; j < kPairs; ++j) {
+      pair w;
+      memcpy(&w, p + (m * kPairs + j) * sizeof w, sizeof w);
+      S[j] += w;
+      T[j] += S[j];
+    }
   }
+  uint64_t s0 = 0;
+  for (size_t j = 0; j < kLanes; ++j) {
+    const uint64_t sum = S[j / 2][j % 2];
+    s0 += 2 * kLanes * (rows * sum - T[j / 2][j % 2]) + (2 * j + 1) * sum;
+  }
+  size_t i = rows * kLanes;
   for (; i < k; ++i) {
     uint64_t w;
     memcpy(&w, p + i * 8, 8);
@@ -115,7 +128,7 @@ extern "C" uint64_t fdy_archive_sum(const void* h_bytes, size_t n) {
     memcpy(&w, p + k * 8, n % 8);
     s0 += w * (2 * (uint64_t)k + 1);
   }
-  return s0 + s1 + s2 + s3;
+  return s0;
 }
 
 namespace {
