@@ -189,6 +189,27 @@ __host__ __device__ __forceinline__ bool pick_node(const uint4 (&q)[2], u64 w, u
   return q[0].x != kMarked;
 }
 
+// What became of a candidate, in 64 bits: {word of the sub-tile (9 bits), region, offset (the rest)}, all
+// ones if no hit (no region is as large as its field).  An offset that does not fit (for 2^20
+// allocations 16 GiB and more into a region) has a field of ones: whoever writes the entry takes
+// word and base from memory.
+struct Entries {
+  u32 off_bits;
+  __host__ __device__ __forceinline__ u64 none() const { return (1ull << off_bits) - 1; }
+  __host__ __device__ __forceinline__ u64 pack(u32 word, u32 region, u64 off) const {
+    return (u64)word << 55 | (u64)region << off_bits | (off < none() ? off : none());
+  }
+  __host__ __device__ __forceinline__ u32 word(u64 e) const { return (u32)(e >> 55); }
+  __host__ __device__ __forceinline__ u32 region(u64 e) const { return (u32)(e << 9 >> 9 >> off_bits); }
+  __host__ __device__ __forceinline__ u64 off(u64 e) const { return e & none(); }
+};
+// The most bits that the regions of a table leave: n_alloc < 2^(55 - off_bits).
+inline u32 entry_off_bits(u64 n_alloc) {
+  u32 bits = 55;
+  while (n_alloc >> (55 - bits)) --bits;
+  return bits;
+}
+
 // In the table itself, for the rare candidate whose line or a node above it is marked or begins above
 // w: the last entry at or below w among [lo, hi).
 __host__ __device__ __forceinline__ void find_exact(const fdy_alloc* table, u32 lo, u32 hi, u64 w, u32& n, u64x2& e) {

@@ -113,7 +113,7 @@ struct ScanParams {
   u32 n_chunks;
   const u64* prepared;  // the caller's prepared table (its header is checked on the device), or null
   u32 top_log2;         // the tuning that the hierarchy's layout depends on
-  u32 off_bits;         // see Entries
+  u32 off_bits;         // see Entries (fdy_lines.hpp)
   u32 n_sub;            // sub-tiles
   u32* d_status;
   u32 spin_limit;
@@ -559,17 +559,6 @@ __device__ __forceinline__ u32 flat_draw(const ScanParams& p, u32 turn, u32 last
   return got;
 }
 
-// What became of a candidate, in 64 bits: {word of the sub-tile (9 bits), region, offset (the rest)}, all
-// ones if no hit (no region is as large as its field).  An offset that does not fit (for 2^20
-// allocations 16 GiB and more into a region) has a field of ones: whoever writes the entry takes
-// word and base from memory.
-struct Entries {
-  u32 off_bits;
-  __device__ __forceinline__ u64 none() const { return (1ull << off_bits) - 1; }
-  __device__ __forceinline__ u64 pack(u32 word, u32 region, u64 off) const {
-    return (u64)word << 55 | (u64)region << off_bits | (off < none() ? off : none());
-  }
-};
 // A worker's sub-tile: round k's lane l has candidate 64 k + l.
 struct Results {
   u64 e[kRounds];
@@ -744,8 +733,8 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_kernel(ScanParams p) {
         const bool hit = e != ~0ull;
         const u64 bl = ballot(hit);
         if (hit) {
-          const u32 word = wbase + (u32)(e >> 55), region = (u32)(e << 9 >> 9 >> pk.off_bits);
-          u64 off = e & pk.none();
+          const u32 word = wbase + pk.word(e), region = pk.region(e);
+          u64 off = pk.off(e);
           if (off == pk.none()) off = word_at<kHalf>(p, word) - p.table[region].base;
           store_reloc(p, pos + __builtin_amdgcn_mbcnt_hi((u32)(bl >> 32), __builtin_amdgcn_mbcnt_lo((u32)bl, 0)), word, region,
                       off);
@@ -1334,8 +1323,7 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
     p.records = rec;
   }
   p.n_sub = n_sub;
-  p.off_bits = 55;
-  while (n_alloc >> (55 - p.off_bits)) --p.off_bits;  // n_alloc < 2^(55 - off_bits)
+  p.off_bits = entry_off_bits(n_alloc);
   p.d_status = d_status;
   p.spin_limit = (u32)fdy__tune_get(FDY_TUNE_SCAN_SPIN_LIMIT);
   p.new_base = (const u64*)d_new_base;

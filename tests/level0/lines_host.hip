@@ -135,9 +135,27 @@ std::vector<fdy_alloc> layout(u32 n, int granule, int size_granule, int hi, u32 
   return v;
 }
 
+// Tables of every size that an entry point takes, up to 2^32 - 1 allocations: there are bits for every region, and
+// what is packed comes back.
+void packed_entries() {
+  for (u64 n : std::vector<u64>{1, 2, 3, 16384, 1 << 20, (1ull << 31) - 1, 1ull << 31, (1ull << 31) + 1, (1ull << 32) - 1}) {
+    const Entries pk{entry_off_bits(n)};
+    bool ok = pk.off_bits <= 55 && n < 1ull << (55 - pk.off_bits) && (pk.off_bits == 55 || n >= 1ull << (54 - pk.off_bits));
+    for (u64 region : std::vector<u64>{0, n / 2, n - 1})
+      for (u32 word : {0u, 1u, 511u})
+        for (u64 off : std::vector<u64>{0, 1, pk.none() - 1, pk.none(), ~0ull}) {
+          const u64 e = pk.pack(word, (u32)region, off);
+          ok = ok && e != ~0ull && pk.word(e) == word && pk.region(e) == region && pk.off(e) == std::min(off, pk.none());
+          ++runs;
+        }
+    if (!ok && ++failures <= 10) printf("entries of %llu allocations: %u bits\n", (unsigned long long)n, pk.off_bits);
+  }
+}
+
 }  // namespace
 
 int main() {
+  packed_entries();
   for (int round = 0; round < 400; ++round) {
     const u32 n = 1 + (u32)below(200);
     const int g = (int)below(22), sg = (int)below(g + 1);
