@@ -210,6 +210,9 @@ inline u32 entry_off_bits(u64 n_alloc) {
   return bits;
 }
 
+// One behind the last entry of the line at entry lo (lo + 8 need not fit 32 bits).
+__host__ __device__ __forceinline__ u32 line_end(u32 lo, u32 n_alloc) { return n_alloc - lo < 8u ? n_alloc : lo + 8u; }
+
 // In the table itself, for the rare candidate whose line or a node above it is marked or begins above
 // w: the last entry at or below w among [lo, hi).
 __host__ __device__ __forceinline__ void find_exact(const fdy_alloc* table, u32 lo, u32 hi, u64 w, u32& n, u64x2& e) {

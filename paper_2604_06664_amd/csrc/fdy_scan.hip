@@ -446,7 +446,7 @@ __device__ __forceinline__ void deep_search(const ScanParams& p, const FlatLevel
     // (a marked line, also the last one: among its own entries if it begins at or below w)
     const u32 lo = line[c] * 8;
     const bool own = !lost[c] && p.table[lo].base <= w[c];
-    find_exact(p.table, own ? lo : 0u, own ? min(lo + 8u, p.n_alloc) : p.n_alloc, w[c], n[c], e[c]);
+    find_exact(p.table, own ? lo : 0u, own ? line_end(lo, p.n_alloc) : p.n_alloc, w[c], n[c], e[c]);
   };
   if (m.lines) {
     const uint4* a = kDepth == 2 && p.records ? p.records : p.cleaf;

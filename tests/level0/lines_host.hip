@@ -59,7 +59,7 @@ void search_line(const Table& t, u32 line, u64 w, u64 told, bool valid) {
   uint4 c[2], q[4];
   memcpy(c, l.compact, 32);
   memcpy(q, l.wide, 64);
-  const u32 end = std::min(t.n, line * 8 + 8), want = last_below(t, end, w);
+  const u32 end = line_end(line * 8, t.n), want = last_below(t, end, w);
   for (int form = 0; form < 2; ++form) {
     u32 at = 99, n = line * 8;
     u64x2 e{0, 0};
@@ -135,6 +135,15 @@ std::vector<fdy_alloc> layout(u32 n, int granule, int size_granule, int hi, u32 
   return v;
 }
 
+// The last line of a table, also where its places are the last that 32 bits number.
+void line_ends() {
+  for (u64 n : std::vector<u64>{1, 7, 8, 9, 16, (1ull << 32) - 17, (1ull << 32) - 9, (1ull << 32) - 8, (1ull << 32) - 7, (1ull << 32) - 1})
+    for (u64 lo : std::vector<u64>{0, (n - 1) / 8 * 8}) {
+      ++runs;
+      if (line_end((u32)lo, (u32)n) != std::min(lo + 8, n) && ++failures <= 10) printf("end of the line at %llu of %llu\n", (unsigned long long)lo, (unsigned long long)n);
+    }
+}
+
 // Tables of every size that an entry point takes, up to 2^32 - 1 allocations: there are bits for every region, and
 // what is packed comes back.
 void packed_entries() {
@@ -156,6 +165,7 @@ void packed_entries() {
 
 int main() {
   packed_entries();
+  line_ends();
   for (int round = 0; round < 400; ++round) {
     const u32 n = 1 + (u32)below(200);
     const int g = (int)below(22), sg = (int)below(g + 1);
