@@ -1042,7 +1042,9 @@ bool plan_table(u32 n_alloc, TablePlan* pl) {
   off += align256((((size_t)1 << pl->bucket_log2) + 1) * 2);
   pl->n_runs = f0_log2 ? sampled << f0_log2 : 0;
   pl->off_runs = off;
-  off += align256((size_t)pl->n_runs * 8);
+  // (a buffer for a table serves every smaller one: from three levels on with room for the longest runs, which end
+  // where a level takes their place)
+  off += align256((levels >= 3 ? (size_t)top_cap * 4 : (size_t)pl->n_runs) * 8);
   for (u32 j = 1; j <= (u32)kMaxNodeLevels; ++j) {
     pl->n_nodes[j - 1] = j < levels ? (u32)(((u64)n_alloc + (8ull << 3 * j) - 1) >> (3 * j + 3)) : 0;
     pl->off_nodes[j - 1] = off;

@@ -7,7 +7,9 @@ import pytest
 import oracle as orc
 from synth import layout as L
 
-ALLOCS = [0, 1, 2, 3, 16, 255, 1000, 4096, 16383, 16384, 16385, 20000, 65536, 1 << 20]
+ALLOCS = [0, 1, 2, 3, 16, 255, 1000, 4096, 16383, 16384, 16385, 20000, 65536, 131072, 131073, 1 << 20, (1 << 20) + 1,
+          1 << 21, (1 << 21) + 1, 1 << 22, (1 << 22) + 1, 1 << 23, (1 << 23) + 1, 1 << 25, (1 << 25) + 1, 1 << 28,
+          (1 << 28) + 1, (1 << 31) - 1, 1 << 31, (1 << 32) - 1]
 WORDS = [0, 1, 511, 4096, 100_000, 786_431, 1 << 20, (1 << 24) - 1, 1 << 24, 1 << 27, (1 << 32) - 256]
 
 
