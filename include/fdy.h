@@ -425,8 +425,9 @@ int fdy_derive_overrides(const uint64_t* d_words, uint64_t n_words_total, const 
  * Each reloc / override / grid-override / patch list is strictly ascending by location (the
  * slices of a list that fall into an output tile are found by binary search).  The device
  * verifies it for every list it reads: a list out of order, or with a location twice, raises
- * FDY_ST_BAD_ORDER and leaves the output unspecified, without any out-of-bounds access.  The
- * lists of a template that no output graph uses are not read.
+ * FDY_ST_BAD_ORDER and leaves the output unspecified, without any out-of-bounds access; so does
+ * a relocation list that ends before it begins (src_reloc_off decreasing).  The lists of a
+ * template that no output graph uses are not read.
  *
  * Output layout: d_out_words is [n_maps][out_words_per_map], map-major; inside a map the
  * graphs follow in order g = 0..n_graphs-1, each with the word count of its template.

@@ -373,6 +373,10 @@ __device__ __forceinline__ void prep_tiles_block(const MatParams& p, const PrepV
   // a tile that is not its graph's last is followed by a tile of the same graph (j + 1 < n_tiles)
   u32 reloc_hi = q.last ? rl1 : s_lo[tid + 1].x;
   const u32 ovr_hi = q.last ? ov1 : s_lo[tid + 1].y;
+  if (rl1 < rl0) {  // offsets that decrease: no list
+    reloc_hi = reloc_lo;
+    raise_status(p.d_status, FDY_ST_BAD_ORDER);
+  }
   // the list is strictly ascending by word: at most n entries fall inside the tile, and none
   // lies before the template's first word
   if (reloc_hi - reloc_lo > q.n) {
@@ -447,6 +451,7 @@ __device__ __forceinline__ void prep_tile_group(const MatParams& p, const PrepVi
     e.reloc_hi = e.reloc_lo + q.n;
     raise_status(p.d_status, FDY_ST_BAD_ORDER);
   }
+  if (rl1 < rl0) raise_status(p.d_status, FDY_ST_BAD_ORDER);  // offsets that decrease: no list
   if (q.k0 == 0 && e.reloc_lo != rl0) raise_status(p.d_status, FDY_ST_BAD_INDEX);
   *ent = e;
 }
@@ -824,6 +829,7 @@ __global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 n_
       ent.reloc_hi = ent.reloc_lo + n_here;
       if (blockIdx.y == 0) raise_status(p.d_status, FDY_ST_BAD_ORDER);
     }
+    if (rl1 < rl0 && blockIdx.y == 0) raise_status(p.d_status, FDY_ST_BAD_ORDER);  // offsets that decrease: no list
     if (k0 == 0 && ent.reloc_lo != rl0 && blockIdx.y == 0) raise_status(p.d_status, FDY_ST_BAD_INDEX);
   } else {
     ent = p.ws.tiles[j];

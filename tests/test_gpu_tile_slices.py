@@ -12,6 +12,16 @@ pytestmark = pytest.mark.gpu
 TILE = 2048
 
 
+def problem(n, relocs, src_reloc_off, regions, rng, ranks=0, **lists):
+    """One graph of n words that is its own template, three base maps."""
+    kw = dict(src_words=rng.integers(0, 1 << 63, n, dtype=np.uint64), src_word_off=[0, n], src_nodes=np.zeros(0, L.NODE),
+              src_node_off=[0, 0], relocs=relocs, src_reloc_off=src_reloc_off, tmpl_graph=[0], graph_tmpl=[0],
+              ovr=np.zeros(0, L.OVR32), ovr_off=[0, 0], govr=np.zeros(0, L.GRID_OVR), govr_off=[0, 0],
+              new_base=rng.integers(0, 1 << 63, (3, regions), dtype=np.uint64), map_rank=None, n_ranks=ranks,
+              patch=np.zeros(0, L.PATCH), patch_off=[0])
+    return MatProblem(**(kw | lists))
+
+
 def places(rng, n, k):
     return np.sort(rng.choice(n, min(n, k), replace=False))
 
@@ -33,9 +43,22 @@ def test_slices(tiles, entries):
         e = np.zeros(min(n, k), L.PATCH)
         e["word"], e["value"] = places(rng, n, k), rng.integers(0, 1 << 63, len(e))
         lists.append(e)
-    mp = MatProblem(src_words=rng.integers(0, 1 << 63, n, dtype=np.uint64), src_word_off=[0, n], src_nodes=np.zeros(0, L.NODE),
-                    src_node_off=[0, 0], relocs=r, src_reloc_off=[0, len(r)], tmpl_graph=[0], graph_tmpl=[0], ovr=ovr,
-                    ovr_off=[0, len(ovr)], govr=np.zeros(0, L.GRID_OVR), govr_off=[0, 0],
-                    new_base=rng.integers(0, 1 << 63, (3, regions), dtype=np.uint64), map_rank=[1, 0, 2], n_ranks=ranks,
-                    patch=np.concatenate(lists), patch_off=np.cumsum([0] + [len(e) for e in lists]).astype(np.uint64))
+    mp = problem(n, r, [0, len(r)], regions, rng, ranks, ovr=ovr, ovr_off=[0, len(ovr)], map_rank=[1, 0, 2],
+                 patch=np.concatenate(lists), patch_off=np.cumsum([0] + [len(e) for e in lists]).astype(np.uint64))
     check_mat(session, orc, mp, tag=f"{tiles} tiles, {entries} entries")
+
+
+@pytest.mark.parametrize("tiles", [1, 9, 2047, 2049])  # (with 9 also resolved by the main kernel itself)
+def test_offsets_that_decrease_are_reported(tiles):
+    """A relocation list that ends before it begins: no entry applies, and the status says so."""
+    from tests.support import session
+
+    rng = np.random.default_rng(tiles)
+    n = tiles * TILE - 5
+    r = np.zeros(n, L.RELOC)
+    r["word"] = np.arange(n)
+    for lo, hi in ((n // 2, 7), (n // 2, n // 2 - 1), (1, 0)):
+        _, _, status = session.materialize(problem(n, r, [lo, hi], 1, rng))
+        assert status & L.ST_BAD_ORDER, (lo, hi)
+    _, _, status = session.materialize(problem(n, r, [0, n], 1, rng))
+    assert status == 0
