@@ -207,7 +207,7 @@ int fdy_layout_replay(const fdy_alloc* h_recorded, uint32_t n, uint64_t recorded
  *                    written and FDY_ST_CAPACITY is raised)
  *   d_workspace      device, 256-byte aligned, at least fdy_scan_workspace_bytes() bytes;
  *                    contents on entry are irrelevant, contents on exit are unspecified.
- *                    The size is the search hierarchy built from the table (12 to 21 bytes
+ *                    The size is the search hierarchy built from the table (14 to 22 bytes
  *                    per allocation beyond 16,384 of them: packed copies of the table, and from
  *                    131,073 allocations on room for one new base per allocation beside them,
  *                    which fdy_scan_pointers_rebase and fdy_scan_rebase fill per call) and 8 bytes

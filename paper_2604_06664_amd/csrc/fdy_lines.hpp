@@ -10,10 +10,67 @@
 // between a third.
 #pragma once
 #include "fdy_device.hpp"
+#include "fdy_level0.hpp"
 
 namespace fdy {
 
 constexpr u32 kMarked = 0xffffffffu;  // first word of a line that does not fit its form
+
+// ---- units: what a level-0 key stands for, a line or the nodes above 8^k of them.  Keys are truncated: the last unit
+// whose key is not above a word's may begin above the word, and so may several where units share the key (blocks of a
+// few KiB and one region 2^46 bytes away: a key spans 64 KiB).  Exact first bases settle it, among the units with
+// that key and the one before them.  us, 8.4 M words, a quarter pointers to blocks of 512 B to 8 KiB, one region
+// 2^47 bytes away, whole table searched / settled: 100,000 blocks 156 / 76, 10^6 blocks 189 / 75.
+
+// Whether the unit before u has the key of distance d as well: more than u may begin above the word.
+__host__ __device__ __forceinline__ bool units_share(const FlatLevel& f, u64 d, u32 u) {
+  return u && reinterpret_cast<const u32*>(f.keys)[u - 1] == (u32)(d >> f.key_shift);
+}
+
+// The last unit at or below u that begins at or below the word (0 if there is none), u being the last whose key is
+// not above the word's.  units: exact first bases, and kUnitWindow more that may hold anything.  A power of four says
+// how far back the units with the word's key reach at most, each request divides that by four, and the last is for
+// neighbours, 32 bytes in a row (as four requests: 76 us above become 81).
+constexpr u32 kUnitWindow = 4;
+__host__ __device__ __forceinline__ u32 settle_unit(const FlatLevel& f, const u64* units, u64 d, u32 u) {
+  const u64 w = d + f.span_lo;
+  u32 reach = kUnitWindow;
+  while (reach < u && reinterpret_cast<const u32*>(f.keys)[u - reach] == (u32)(d >> f.key_shift)) reach <<= 2;
+  u32 r = u > reach ? u - reach : 0u;
+  u64 b[kUnitWindow];
+  for (u32 s = reach >> 2; s > 1; s >>= 2) {
+    u32 m[4];
+#pragma unroll
+    for (u32 h = 0; h < 4; ++h) {
+      m[h] = r + (h + 1) * s < u ? r + (h + 1) * s : u;
+      b[h] = units[m[h]];
+    }
+#pragma unroll
+    for (u32 h = 0; h < 4; ++h)
+      if (b[h] <= w) r = m[h];
+  }
+  const u32 from = r + 1;
+#pragma unroll
+  for (u32 h = 0; h < kUnitWindow; ++h) b[h] = units[from + h];
+#pragma unroll
+  for (u32 h = 0; h < kUnitWindow; ++h)
+    if (b[h] <= w && from + h <= u) r = from + h;
+  return r;
+}
+
+// The same in few instructions, where it is rare: u itself is known to begin above the word.
+__host__ __device__ __forceinline__ u32 settle_unit_rare(const FlatLevel& f, const u64* units, u64 d, u32 u) {
+  const u64 w = d + f.span_lo;
+  u32 reach = 4;
+  while (reach < u && reinterpret_cast<const u32*>(f.keys)[u - reach] == (u32)(d >> f.key_shift)) reach <<= 1;
+  u32 r = u > reach ? u - reach : 0u;
+  while (u - r > 1) {
+    const u32 mid = r + ((u - r) >> 1);
+    if (units[mid] <= w) r = mid;
+    else u = mid;
+  }
+  return r;
+}
 
 // ---- wide line: {distance >> s, size >> s} of each entry, 32 bits each, s the trailing zeros common to
 // all sixteen (at most 31; allocators hand out aligned blocks, so regions far beyond 4 GiB fit).

@@ -15,6 +15,7 @@
 //   3. searches the hierarchy: level 0 in LDS (truncated keys of sampled bases behind a bucket
 //      index, fdy_level0.hpp), nodes in global memory for the largest tables only, then one line of
 //      eight entries (fdy_lines.hpp), or the table entry itself where level 0 has every base;
+//      where truncated keys lead a word too far, exact bases of what the keys stand for settle it;
 //      what became of a candidate stays in registers, 64 bits each;
 //   4. posts its hits; one barrier per chunk makes them and the next ticket visible.
 // The sixteenth wave, the clerk, owns no words: it draws the tickets and finds the chunk's output
@@ -102,6 +103,7 @@ struct ScanParams {
   u32 top_n;        // level-0 keys, rounded up to whole 16-byte pieces
   u32 levels;       // 8-ary levels below level 0, the table line included
   u32 f0_log2;      // level 0 samples every (2^f0_log2 * 8^levels)-th base
+  const u64* units;         // levels >= 1: the first base of what each level-0 key stands for
   const u64* runs;          // f0_log2 > 0: every 8^levels-th base, padded with ~0
   const uint4* nodes[kMaxNodeLevels];  // nodes[j-1]: level j's, of every 8^j-th base (levels >= 2)
   const uint4* leaf;        // the table's lines in their wide form (levels >= 1)
@@ -331,6 +333,7 @@ __device__ __forceinline__ void store_reloc(const ScanParams& p, u64 at, u32 wor
 // What a launch's hierarchy is read through (one per wave; kDepth 0 has no use for it).
 struct Forms {
   bool lines;            // compact lines
+  bool settle;           // kDepth 1: lines share keys, so that a line is settled before it is fetched
   u32 marked, searched;  // marked lines met by this wave's candidates; its candidates
   u64 nb_from;           // records: a code stands for nb_from + (code << nb_shift)
   u32 nb_shift;
@@ -342,9 +345,16 @@ __device__ __forceinline__ bool mostly_packed(const uint4* lines, u32 n) {
   const u64 i = ((u64)lane_id() * n) >> 6;
   return __popcll(ballot(lines[i * 2].x == kMarked)) <= 16;
 }
+// Whether lines share level-0 keys, in any of 64 evenly spaced pairs of neighbours.  (100,000 blocks of 512 B to 8 KiB,
+// 5 % of the pairs share a key, settled before / after a line was fetched in vain: 70 / 78 us.)
+__device__ __forceinline__ bool units_share_keys(const FlatLevel& f, u32 n) {
+  const u32 i = (u32)(((u64)lane_id() * n) >> 6);
+  const u32* keys = reinterpret_cast<const u32*>(f.keys);
+  return ballot(keys[i] == keys[i + 1]) != 0;
+}
 template <int kDepth>
 __device__ __forceinline__ Forms pick_forms(const ScanParams& p) {
-  Forms m{false, 0, 0, 0, 0};
+  Forms m{false, false, 0, 0, 0, 0};
   if constexpr (kDepth >= 1) m.lines = mostly_packed(p.cleaf, p.n_lines);
   if constexpr (kDepth >= 2) {
     if (p.records) {
@@ -380,9 +390,25 @@ __device__ __forceinline__ void deep_search(const ScanParams& p, const FlatLevel
     w[c] = d[c] + f.span_lo;
     line[c] = at[c] >> 2;
   }
+  auto told = [&](u32 unit) {  // what its key says of a unit's first base
+    return f.span_lo + ((u64)reinterpret_cast<const u32*>(f.keys)[unit] << f.key_shift);
+  };
+  if constexpr (kDepth == 1) {
+    if (m.settle) {
 #pragma unroll
-  for (int c = 0; c < N; ++c)
-    first[c] = f.span_lo + ((u64) * reinterpret_cast<const u32*>(f.keys + at[c]) << f.key_shift);
+      for (int c = 0; c < N; ++c)
+        if (reinterpret_cast<const u32*>(f.keys)[line[c]] == (u32)(d[c] >> f.key_shift))
+          line[c] = settle_unit(f, p.units, d[c], line[c]);
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < N; ++c) first[c] = told(line[c]);
+  // The unit for a word that its own unit begins above.  (After the fact: looked for ahead of every search, as
+  // Forms.settle has it, tables whose units lie far apart lose 1 to 5 %.)
+  auto settled = [&](int c, u32 unit) __attribute__((always_inline)) {
+    if (!units_share(f, d[c], unit)) return unit - 1;
+    return kDepth == 1 ? settle_unit_rare(f, p.units, d[c], unit) : settle_unit(f, p.units, d[c], unit);
+  };
   bool lost[N];  // the way down ended at a node
 #pragma unroll
   for (int c = 0; c < N; ++c) lost[c] = false;
@@ -403,6 +429,19 @@ __device__ __forceinline__ void deep_search(const ScanParams& p, const FlatLevel
           }
         }
       }
+#pragma unroll
+      for (int c = 0; c < N; ++c)
+        if (first[c] > w[c] && line[c]) {
+          line[c] = settled(c, line[c] >> p.f0_log2) << p.f0_log2;
+          first[c] = p.runs[line[c]];
+          for (u32 step = 1u << (p.f0_log2 - 1); step; step >>= 1) {
+            const u64 b = p.runs[line[c] + step];
+            if (b <= w[c] && b != ~0ull) {
+              line[c] += step;
+              first[c] = b;
+            }
+          }
+        }
     }
     for (u32 j = p.levels - 1; j >= 1; --j) {
       const uint4* a = p.nodes[j - 1];
@@ -413,6 +452,16 @@ __device__ __forceinline__ void deep_search(const ScanParams& p, const FlatLevel
         q[c][1] = a[(u64)line[c] * 2 + 1];
       }
       __builtin_amdgcn_sched_barrier(0);
+      if (j + 1 == p.levels && !p.f0_log2) {
+#pragma unroll
+        for (int c = 0; c < N; ++c)
+          if (first[c] + (q[c][0].x >> 5) > w[c] && line[c]) {
+            line[c] = settled(c, line[c]);
+            first[c] = told(line[c]);
+            q[c][0] = a[(u64)line[c] * 2];
+            q[c][1] = a[(u64)line[c] * 2 + 1];
+          }
+      }
 #pragma unroll
       for (int c = 0; c < N; ++c) {
         u32 h = 0;
@@ -429,16 +478,16 @@ __device__ __forceinline__ void deep_search(const ScanParams& p, const FlatLevel
     const bool ok = pick_wide_line(q, w[c], first[c], h, e[c]);
     n[c] += h;
     if (ok & !lost[c]) return;
-    // most often the word lies below the line's first base with the same truncated key (the end of the
-    // region before, for one): the line before, at the cost of one request more and not of a search
+    // the word lies below the line's first base, with the same truncated key (the end of the region before, for
+    // one): most often in the line before, at the cost of one request more and not of a search
     if (!lost[c] && q[0].x != kMarked && line[c]) {
-      const u32 before = line[c] - 1;
+      const u32 l = kDepth == 1 ? settled(c, line[c]) : line[c] - 1;
       uint4 r[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) r[i] = p.leaf[(u64)before * 4 + i];
-      const u64 b = p.table[(u64)before * 8].base;
-      n[c] = before * 8;
-      if (pick_wide_line(r, w[c], b - (r[0].x >> 5), h, e[c])) {
+      for (int i = 0; i < 4; ++i) r[i] = p.leaf[(u64)l * 4 + i];
+      const u64 b = kDepth == 1 ? told(l) : p.table[(u64)l * 8].base - (r[0].x >> 5);
+      n[c] = l * 8;
+      if (pick_wide_line(r, w[c], b, h, e[c])) {
         n[c] += h;
         return;
       }
@@ -744,6 +793,7 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_kernel(ScanParams p) {
     }
   };
   Forms m = pick_forms<kDepth>(p);
+  if constexpr (kDepth == 1) m.settle = units_share_keys(f, p.n_lines);
   u64 w[kWpl];
   load_words<kHalf>(p, chunk * kW + wave, f.span_lo, w);
   Results cur, prev;
@@ -808,6 +858,7 @@ __global__ __launch_bounds__(kRebaseWaves * 64) void scan_rebase_kernel(ScanPara
   load_words<false>(p, sub, f.span_lo, w);
   Forms m = pick_forms<kDepth>(p);
   __syncthreads();
+  if constexpr (kDepth == 1) m.settle = units_share_keys(f, p.n_lines);
   u32 H = 0;
   for (; sub < p.n_sub; sub += stride) {
     Results r;  // (nobody asks for the entries)
@@ -849,7 +900,9 @@ struct ScanInit {
   u32 bucket_log2;
   u32 levels;
   u32 f0_log2;
-  u64* runs;  // see ScanParams
+  u64* units;  // see ScanParams
+  u32 n_units;
+  u64* runs;
   u32 n_runs;
   uint4* nodes[kMaxNodeLevels];
   u32 n_nodes[kMaxNodeLevels];
@@ -950,6 +1003,10 @@ __global__ void scan_init_kernel(ScanInit a) {
     a.bstart[i] = (unsigned short)sampled_lower_bound(a.table, sh0, a.sampled, span_lo, key_shift, target);
   }
   if constexpr (!kLines) return;
+  if (i < a.n_units) {
+    const u64 j = i << sh0;
+    a.units[i] = j < a.n_alloc ? a.table[j].base : ~0ull;
+  }
   if (i < a.n_runs) {
     const u64 j = i << (3 * a.levels);
     a.runs[i] = j < a.n_alloc ? a.table[j].base : ~0ull;
@@ -1000,9 +1057,9 @@ size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 // front of a workspace).  Offsets are relative to the block's start.
 struct TablePlan {
   u32 top_n, levels, f0_log2, sampled, bucket_log2;
-  u32 n_runs, n_nodes[kMaxNodeLevels], leaf_lines;
+  u32 n_units, n_runs, n_nodes[kMaxNodeLevels], leaf_lines;
   u32 spare;  // bytes for chunk states, the plan's last
-  size_t off_top, off_bst, off_runs, off_nodes[kMaxNodeLevels], off_leaf, off_cleaf, off_records, bytes;
+  size_t off_top, off_bst, off_units, off_runs, off_nodes[kMaxNodeLevels], off_leaf, off_cleaf, off_records, bytes;
 };
 
 // From so many sub-tiles on a base map is laid beside the lines of a table with nodes, a launch of 5 to
@@ -1040,10 +1097,13 @@ bool plan_table(u32 n_alloc, TablePlan* pl) {
   while ((2u << pl->bucket_log2) <= pl->top_n && pl->bucket_log2 < 13u) ++pl->bucket_log2;
   pl->off_bst = off;
   off += align256((((size_t)1 << pl->bucket_log2) + 1) * 2);
+  // (a buffer for a table serves every smaller one: where a level takes the place of longer arrays, these keep
+  // the room of their longest)
+  pl->n_units = levels ? sampled + kUnitWindow : 0;
+  pl->off_units = off;
+  off += align256((size_t)(levels >= 2 ? top_cap + kUnitWindow : pl->n_units) * 8);
   pl->n_runs = f0_log2 ? sampled << f0_log2 : 0;
   pl->off_runs = off;
-  // (a buffer for a table serves every smaller one: from three levels on with room for the longest runs, which end
-  // where a level takes their place)
   off += align256((levels >= 3 ? (size_t)top_cap * 4 : (size_t)pl->n_runs) * 8);
   for (u32 j = 1; j <= (u32)kMaxNodeLevels; ++j) {
     pl->n_nodes[j - 1] = j < levels ? (u32)(((u64)n_alloc + (8ull << 3 * j) - 1) >> (3 * j + 3)) : 0;
@@ -1089,6 +1149,8 @@ void fill_init(ScanInit* a, const fdy_alloc* d_table, u32 n_alloc, const TablePl
   a->bucket_log2 = tp.bucket_log2;
   a->levels = tp.levels;
   a->f0_log2 = tp.f0_log2;
+  a->units = (u64*)(tb + tp.off_units);
+  a->n_units = tp.n_units;
   a->runs = (u64*)(tb + tp.off_runs);
   a->n_runs = tp.n_runs;
   for (int j = 0; j < kMaxNodeLevels; ++j) {
@@ -1310,6 +1372,7 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
   p.top_n = (tp.sampled + 3) & ~3u;
   p.levels = tp.levels;
   p.f0_log2 = tp.f0_log2;
+  p.units = a.units;
   p.runs = a.runs;
   for (int j = 0; j < kMaxNodeLevels; ++j) p.nodes[j] = a.nodes[j];
   p.leaf = a.leaf;

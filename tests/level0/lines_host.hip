@@ -135,6 +135,56 @@ std::vector<fdy_alloc> layout(u32 n, int granule, int size_granule, int hi, u32 
   return v;
 }
 
+// Level-0 keys of units of 2^sh entries each: from the last unit whose key is not above a word's to the last that
+// begins at or below the word.
+void settle_units(const std::vector<fdy_alloc>& v, u32 sh, bool valid) {
+  const Table t(v);
+  const u32 n = (t.n + (1u << sh) - 1) >> sh;
+  FlatLevel f{};
+  f.span_lo = t.t[0].base;
+  f.span_len = t.t[t.n - 1].base + t.t[t.n - 1].size - f.span_lo;
+  f.key_shift = key_shift_for(f.span_len, 31);
+  u32* keys = (u32*)malloc(n * 4);  // heap blocks of their exact sizes
+  u64* units = (u64*)malloc((n + kUnitWindow) * 8);
+  memset(units, (int)below(256), (n + kUnitWindow) * 8);
+  for (u32 i = 0; i < n; ++i) {
+    keys[i] = level0_key(t.t, t.n, sh, i, f.span_lo, f.key_shift);
+    units[i] = t.t[(u64)i << sh].base;
+  }
+  f.keys = (const unsigned char*)keys;
+  for (u32 i = 0; i < t.n; i += 1 + (t.n > 300 ? (u32)below(40) : 0))
+    for (u64 w : {t.t[i].base - 1, t.t[i].base, t.t[i].base + t.t[i].size / 2, t.t[i].base + t.t[i].size}) {
+      const u64 d = w - f.span_lo;
+      if (d >= f.span_len) continue;
+      u32 u = 0, want = 0;
+      for (u32 k = 0; k < n; ++k) {
+        if (keys[k] <= (u32)(d >> f.key_shift)) u = k;
+        if (units[k] <= w) want = k;
+      }
+      ++runs;
+      const u32 got = settle_unit(f, units, d, u);
+      const bool share = units_share(f, d, u);
+      if (got > u || (valid && (got != want || (!share && got + 1 < u)))) report("unit", t, w, u);
+      if (u == 0 || (valid && units[u] <= w)) continue;
+      const u32 rare = settle_unit_rare(f, units, d, u);
+      if (rare > u || (valid && rare != want)) report("unit, rare", t, w, u);
+    }
+  free(keys);
+  free(units);
+}
+
+// Blocks of up to 2^hi bytes in a few places far apart, so that many share a key.
+std::vector<fdy_alloc> clusters(u32 n, int hi) {
+  std::vector<fdy_alloc> v;
+  u64 at = next() & 0xffff0;
+  for (u32 i = 0; i < n; ++i) {
+    v.push_back(fdy_alloc{at, log_uniform(3, hi)});
+    at += v.back().size + (below(3) ? 0 : 16);
+    if (below(n) < 2) at += 1ull << (40 + below(7));
+  }
+  return v;
+}
+
 // The last line of a table, also where its places are the last that 32 bits number.
 void line_ends() {
   for (u64 n : std::vector<u64>{1, 7, 8, 9, 16, (1ull << 32) - 17, (1ull << 32) - 9, (1ull << 32) - 8, (1ull << 32) - 7, (1ull << 32) - 1})
@@ -170,12 +220,14 @@ int main() {
     const u32 n = 1 + (u32)below(200);
     const int g = (int)below(22), sg = (int)below(g + 1);
     search(layout(n, g, sg, std::max(sg, 1) + (int)below(26), round % 3 ? 0 : 5), true);
+    settle_units(clusters(1 + (u32)below(round % 20 ? 300 : 9000), 4 + (int)below(14)), (u32)below(4), true);
     search(layout(n, 21, 9, 26, round % 2 ? 12 : 0), true);  // 2 MiB granules, some gigabytes
     search(layout(n, 4, 0, 26, 0), true);                    // a caching allocator's blocks
     std::vector<fdy_alloc> v(n);                             // nothing that fdy_table_validate passes
     const int bits = 1 + (int)below(64);
     for (auto& e : v) e = fdy_alloc{next() >> (64 - bits), next() >> below(64)};
     search(v, false);
+    settle_units(v, (u32)below(4), false);
   }
   {  // distances and sizes at the limits of the forms
     for (int bits : {11, 12, 13, 17, 18, 19, 20, 25, 26, 27, 31, 32, 33})

@@ -74,6 +74,35 @@ def test_rounds(density):
     check_all_forms(words_of(rng, 90 * SUB + 300, t, density), t, rng)
 
 
+def pools_of(rng, n, largest):
+    """Pools of small blocks, 2^43 bytes and more apart: lines and nodes share level-0 keys, in some pools by the
+    hundred; between them regions of their own."""
+    size = rng.integers(1, largest // 16 + 1, n).astype(np.uint64) * np.uint64(16)
+    step = size + rng.choice([0, 0, 16], n).astype(np.uint64)
+    step[[n // 3, n // 3 + 1, n // 2]] += np.uint64(1 << 43)
+    step[-2] += np.uint64(1 << 46)
+    t = np.zeros(n, L.ALLOC)
+    t["base"], t["size"] = np.uint64(0x10000000) + np.cumsum(step) - step, size
+    assert orc.table_validate(t)[0] == 0
+    return t
+
+
+# one level and two, runs of two and four nodes to a key, three levels
+@pytest.mark.parametrize("top_log2,n_alloc", [(14, 16385), (14, 131072), (14, 131073), (14, 300007), (5, 150), (5, 1500), (5, 3000),
+                                              (5, 5000), (5, 20000)])
+@pytest.mark.parametrize("largest", [16, 512, 8192])
+def test_pools_of_small_blocks(top_log2, n_alloc, largest):
+    import paper_2604_06664_amd as fdy
+
+    rng = np.random.default_rng(n_alloc + largest)
+    t = pools_of(rng, n_alloc, largest)
+    old = fdy.tune_set(fdy.TUNE_SCAN_TOP_LOG2, top_log2)
+    try:
+        check_all_forms(words_of(rng, 60 * SUB + 5, t, 0.4), t, rng)
+    finally:
+        fdy.tune_set(fdy.TUNE_SCAN_TOP_LOG2, old)
+
+
 @pytest.mark.parametrize("top_log2,n_alloc", [(14, 5), (2, 40), (1, 40)])
 def test_offsets_beyond_a_packed_result(top_log2, n_alloc):
     import paper_2604_06664_amd as fdy

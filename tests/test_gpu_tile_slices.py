@@ -62,3 +62,23 @@ def test_offsets_that_decrease_are_reported(tiles):
         assert status & L.ST_BAD_ORDER, (lo, hi)
     _, _, status = session.materialize(problem(n, r, [0, n], 1, rng))
     assert status == 0
+
+
+@pytest.mark.parametrize("ranks", [1, 1598, 1599])  # 41 tiles: 65,518 and 65,559 pairs; beyond 65,536 a thread searches alone
+@pytest.mark.parametrize("entries", [1, 9, 700])
+def test_slices_of_many_ranks(ranks, entries):
+    from tests.support import session
+    from tests.test_gpu_parity import check_mat
+
+    rng = np.random.default_rng(ranks + entries)
+    n = 40 * TILE - 5
+    lens = rng.integers(0, 3, ranks)
+    lens[[0, ranks // 2, ranks - 1]] = entries
+    patch = np.zeros(int(lens.sum()), L.PATCH)
+    patch["word"] = np.concatenate([places(rng, n, k) for k in lens])
+    patch["value"] = rng.integers(0, 1 << 63, len(patch))
+    r = np.zeros(n // 3, L.RELOC)
+    r["word"], r["region"] = np.arange(n // 3) * 3, rng.integers(0, 50, n // 3)
+    mp = problem(n, r, [0, len(r)], 50, rng, ranks, map_rank=[ranks - 1, 0, ranks // 2], patch=patch,
+                 patch_off=np.cumsum(np.r_[0, lens]).astype(np.uint64))
+    check_mat(session, orc, mp, tag=f"{ranks} ranks, {entries} entries")
