@@ -8,10 +8,11 @@
 // Work decomposition.  Persistent workgroups, one per compute unit, stage the top level of the
 // table's hierarchy in LDS once.  Words come in sub-tiles of 512; a chunk is a sub-tile for each
 // of the workgroup's 15 (small inputs: 7) workers, handed out by an atomic ticket.  A worker
-//   1. takes its 8 words per lane (16-byte coalesced non-temporal loads), keeps a copy of the
-//      sub-tile in LDS (the stash) and rejects every word outside the table's span;
-//   2. queues the places of the surviving candidates in LDS, in word order (ballot ranks), so
-//      that the interval search runs on dense rounds of 64 lanes;
+//   1. takes its 8 words per lane (16-byte coalesced non-temporal loads) and rejects every word
+//      outside the table's span;
+//   2. queues the surviving candidates and their places in LDS, in word order (ballot ranks), so
+//      that the interval search runs on dense rounds of 64 lanes; with a rebased output, where the
+//      sub-tile goes out again, LDS holds a copy of it (the stash) in place of the candidates;
 //   3. searches the hierarchy: level 0 in LDS (truncated keys of sampled bases behind a bucket
 //      index, fdy_level0.hpp), nodes in global memory for the largest tables only, then one line of
 //      eight entries (fdy_lines.hpp), or the table entry itself where level 0 has every base;
@@ -614,7 +615,8 @@ struct Results {
   u32 Q, H, sub;
 };
 
-// Candidates [64 R0, 64 (R0 + N)) of the words in `stash`.
+// Candidates [64 R0, 64 (R0 + N)).  stash: with output the sub-tile's words, else the candidates alone: read through
+// their places, 26.8 M positions at 4-byte stride with 2 to 20 % candidates took 2 to 3 % longer.
 template <int kDepth, bool kOut, int N, int R0>
 __device__ __forceinline__ void search_rounds(const ScanParams& p, const FlatLevel& f, Forms& m, Entries pk, u64* stash,
                                             const unsigned short* places, Results& r) {
@@ -627,7 +629,7 @@ __device__ __forceinline__ void search_rounds(const ScanParams& p, const FlatLev
 #pragma unroll
   for (int c = 0; c < N; ++c) {
     const bool valid = c < N - 1 || (u32)(R0 + c) * 64 + lane < r.Q;  // rounds before the last are full
-    d[c] = valid ? stash[idx[c]] - f.span_lo : 0;
+    d[c] = valid ? stash[kOut ? idx[c] : (u32)(R0 + c) * 64 + lane] - f.span_lo : 0;
   }
   any_search<kDepth, N>(p, f, m, d, n, off, hit);
 #pragma unroll
@@ -670,6 +672,16 @@ __device__ __forceinline__ void search_all(const ScanParams& p, const FlatLevel&
     if (r.Q <= R0 * 64) return;
     if constexpr (kDepth == 2 && R0 == 0) {
       if (r.Q > 64 && r.Q <= kFewCandidates) return search_rounds<kDepth, kOut, 2, 0>(p, f, m, pk, stash, places, r);
+    }
+    // Four rounds, seven and eight: four at once, where three would leave one or two alone.  (Not with output, whose
+    // chains hold new bases as well.)  us, three / four at once: 13.4 M words, 4,096 allocations, 43 % candidates 51.0 /
+    // 48.4; twice as many 4-byte positions 80 % dense 84.8 / 78.1, 100 % 88.8 / 84.2; 16,384 allocations, 100 % of 13.4 M
+    // words 93.3 / 94.9.  Five rounds as four and one instead of three and two: 66.3 -> 68.7.
+    if constexpr (kDepth == 0 && !kOut && R0 % 4 == 0) {
+      if (const u32 left = r.Q - R0 * 64; left > 192 && (left <= 256 || left > 384)) {
+        search_rounds<kDepth, kOut, 4, R0>(p, f, m, pk, stash, places, r);
+        return search_all<kDepth, kOut, R0 + 4>(p, f, m, pk, stash, places, r);
+      }
     }
     constexpr int N = kDepth == 0 ? 3 : kDepth == 1 ? 2 : 1;
     search_step<kDepth, kOut, N, R0>(p, f, m, pk, stash, places, r);
@@ -802,9 +814,10 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_kernel(ScanParams p) {
   for (; chunk < p.n_chunks; b ^= 1) {
     cur.sub = chunk * kW + wave;
     cur.H = 0;
-    stash_words<kHalf>(stash, w);
+    if constexpr (kOut) stash_words<kHalf>(stash, w);
     cur.Q = rank_candidates<kHalf>(flat_candidates(f, w), [&](int k, u32 rank) {
       places[rank] = (unsigned short)pos_in_sub<kHalf>(k, lane);
+      if constexpr (!kOut) stash[rank] = w[k];
     });
     search_all<kDepth, kOut>(p, f, m, pk, stash, places, cur);
     if constexpr (kDepth != 0) count_marked(m, cur.Q);

@@ -78,6 +78,34 @@ def test_candidates_and_tables(n_alloc, shape, density):
     check_all_forms(words_of(rng, 20 * SUB + 5, t, density), t, rng)
 
 
+@pytest.mark.parametrize("each", [1, 64, 65, 192, 193, 256, 257, 320, 384, 385, 448, 449, 511, 512])
+@pytest.mark.parametrize("n_alloc", [1, 300])
+def test_candidates_of_a_sub_tile(n_alloc, each):
+    """Exactly so many candidates in every sub-tile, of words and of 4-byte positions: rounds one by one, two to four at
+    a time."""
+    from tests.support import session
+
+    rng = np.random.default_rng(each)
+    t = np.zeros(n_alloc, L.ALLOC)
+    t["base"] = np.uint64(0x7F000000 << 32) + np.arange(n_alloc, dtype=np.uint64) * np.uint64(1 << 34)
+    t["size"] = np.uint64(1 << 34) - rng.integers(0, 1 << 33, n_alloc, dtype=np.uint64)
+    t["size"][-1] = np.uint64(1 << 34)
+    n = 20 * SUB
+    chosen = np.concatenate([s * SUB + rng.choice(SUB, each, replace=False) for s in range(20)])
+    for stride4 in (False, True):
+        units = rng.integers(1, 1 << 20, n + 1 if stride4 else 2 * n).astype(np.uint32)
+        high = chosen + 1 if stride4 else 2 * chosen + 1  # the half of a candidate that makes it one
+        units[high] = (0x7F000000 + rng.integers(0, 4 * n_alloc, len(high))).astype(np.uint32)
+        if stride4:
+            ref, cnt = orc.scan_stride4(units, t)
+            got, have, status = session.scan_stride4(units, t, prepared=True)
+        else:
+            ref, cnt = orc.scan(units.view(np.uint64), t)
+            got, have, status = session.scan(units.view(np.uint64), t, prepared=True)
+        assert 0 < cnt <= 20 * each
+        assert status == 0 and have == cnt and np.array_equal(got, ref), stride4
+
+
 def test_prepared_states_take_turns():
     import torch
 
