@@ -402,9 +402,11 @@ __device__ __forceinline__ void prep_tiles_block(const MatParams& p, const PrepV
 
 // The same with half a wave per tile, eight lanes for each of its four ends: what the kernel takes is
 // its longest chain of dependent loads, and 13,400 relocations and 1,880 patches are five and six
-// steps, not seven and 22.  For up to kGroupTiles tiles; with more, the workgroups that this takes
-// (each repeats the per-graph sums) cost what the steps save.  us, a thread per tile / half a wave:
-// 1,870 tiles and 8 ranks 12.9 / 10.1, 446 tiles 8.5 / 7.6, 3,391 tiles 13.7 / 15.6.
+// steps, not seven and 22.  For up to kGroupTiles tiles: each workgroup that this takes repeats the
+// per-graph sums, and beside as many that write dimensions they come to cost what the steps save.  us
+// of the launch, a thread per tile / half a wave: 1,870 tiles and 8 ranks 12.9 / 10.1, 446 tiles 8.5 / 7.6; 3,391
+// tiles of 512 graphs with 295,000 dimensions 13.7 / 15.6; without dimensions 8 to 512 graphs gain 2 to 3 everywhere
+// from 1,100 to 3,400 tiles (9.4 to 10.7 / 6.2 to 8.4) and nothing from 4,100 on.
 constexpr u32 kGroupTiles = 2048;
 template <bool kOwn>
 __device__ __forceinline__ void prep_tile_group(const MatParams& p, const PrepView<kOwn>& v, u32 j) {
@@ -457,8 +459,11 @@ __device__ __forceinline__ void prep_tile_group(const MatParams& p, const PrepVi
 }
 
 // A slice of a rank's patch list by eight lanes, four for either end: up to kGroupPairs pairs of
-// tile and rank.
-constexpr u32 kGroupPairs = 65536;
+// tile and rank, beyond which the workgroups that this takes cost what the steps save.  us of the launch, a
+// thread per slice / eight lanes, 8 templates with 20, 300 and 1,880 patches to a rank: 9,648 pairs 6.2 / 6.3,
+// 7.9 / 6.2, 9.5 / 6.6; 32,096 pairs 6.9 / 7.3, 8.7 / 8.0, 10.3 / 9.2 (30 templates 7.0 / 7.1, 10.1 / 11.0,
+// 21.1 / 23.1); 38,592 pairs 6.7 / 7.2, 8.6 / 9.0, 12.5 / 14.9; 64,192 pairs 7.0 / 10.2, 9.0 / 12.8, 13.7 / 21.0.
+constexpr u32 kGroupPairs = 32768;
 template <bool kOwn>
 __device__ __forceinline__ void prep_patch_group(const MatParams& p, const PrepView<kOwn>& v, u32 i) {
   const fdy_mat_desc& d = p.d;

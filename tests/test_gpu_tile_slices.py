@@ -64,7 +64,7 @@ def test_offsets_that_decrease_are_reported(tiles):
     assert status == 0
 
 
-@pytest.mark.parametrize("ranks", [1, 1598, 1599])  # 41 tiles: 65,518 and 65,559 pairs; beyond 65,536 a thread searches alone
+@pytest.mark.parametrize("ranks", [1, 799, 800, 1599])  # 41 tiles: beyond 32,768 pairs a thread searches alone
 @pytest.mark.parametrize("entries", [1, 9, 700])
 def test_slices_of_many_ranks(ranks, entries):
     from tests.support import session
