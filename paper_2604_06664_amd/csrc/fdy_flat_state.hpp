@@ -1,6 +1,6 @@
-// fdy_flat_state.hpp - chunk states of the ordered scans: how many there are, where they lie and what a launch leaves for the next one.  Plain
-// arithmetic, also compiled for the host, where tests/level0/level0_host.hip runs sequences
-// of launches over it.
+// fdy_flat_state.hpp - chunk states of the ordered scans: how many there are, where they lie and
+// what a launch leaves for the next one.  Plain arithmetic, also compiled for the host, where
+// tests/level0/level0_host.hip runs sequences of launches over it.
 #pragma once
 #include "fdy_device.hpp"
 
@@ -8,28 +8,23 @@ namespace fdy {
 
 constexpr u32 kFlatWorkers = 7, kFlatWorkersBig = 15;
 
-// From so many sub-tiles on a `shared` region leaves room in front (see flat_region).
-constexpr u32 kFlatOutSubs = 32768;
-
 // Workers per workgroup.  Measured (us, 7 / 15
 // workers, a quarter pointers, 4,096 allocations): 17 sub-tiles 6.0 / 9.0, 1,024 9.4 / 9.2, 1,536
 // 10.3 / 9.6, 2,048 12.9 / 10.4, 4,096 23 / 14.5, 16,384 50 / 33: many small workgroups start
-// sooner and share the staging's latency, but each chunk costs a ticket and a look-back.  (`out`, a
-// form with output, makes no difference: 5 M words 32.1 us with 11 workers, 30.7 with 15.)
+// sooner and share the staging's latency, but each chunk costs a ticket and a look-back.
 constexpr u32 kFlatFewSubs = 1536;
-__host__ __device__ __forceinline__ u32 flat_workers(u32 n_sub, bool out) {
-  (void)out;
+__host__ __device__ __forceinline__ u32 flat_workers(u32 n_sub) {
   return n_sub < kFlatFewSubs ? kFlatWorkers : kFlatWorkersBig;
 }
-__host__ __device__ __forceinline__ u32 flat_chunks(u32 n_sub, bool out) {
-  const u32 w = flat_workers(n_sub, out);
+__host__ __device__ __forceinline__ u32 flat_chunks(u32 n_sub) {
+  const u32 w = flat_workers(n_sub);
   return (n_sub + w - 1) / w;
 }
 
 // Most chunks of a launch of up to max_sub sub-tiles.
 inline u32 flat_most_chunks(u32 max_sub) {
-  u32 most = flat_chunks(max_sub, false);
-  if (max_sub >= kFlatFewSubs && flat_chunks(kFlatFewSubs - 1, false) > most) most = flat_chunks(kFlatFewSubs - 1, false);
+  u32 most = flat_chunks(max_sub);
+  if (max_sub >= kFlatFewSubs && flat_chunks(kFlatFewSubs - 1) > most) most = flat_chunks(kFlatFewSubs - 1);
   return most;
 }
 
@@ -56,15 +51,13 @@ inline size_t chunk_state_bytes(u32 n_sub) { return ((size_t)((n_sub + 7) / 8) *
 
 // Where the states lie, relative to the first chunk state of a buffer made for max_sub sub-tiles with
 // `bytes` of chunk states (at least chunk_state_bytes).  The hierarchy's last `spare` bytes, in front
-// of the chunk states, are states as well; a `shared` region leaves a state for each 32 sub-tiles in
-// front to others instead (no scan asks for that any more).
+// of the chunk states, are states as well.
 struct FlatRegion {
   long long first;  // bytes from the first chunk state
   u32 states;       // as many as the widest spread can use, at most
 };
-inline FlatRegion flat_region(u32 max_sub, u32 spare, bool shared, size_t bytes) {
+inline FlatRegion flat_region(u32 max_sub, u32 spare, size_t bytes) {
   FlatRegion r{-(long long)spare, 0};
-  if (shared && max_sub >= kFlatOutSubs) r.first = (long long)(((size_t)((max_sub + 31) / 32) * 8 + 255) & ~(size_t)255);
   const u32 most = flat_most_chunks(max_sub), want = flat_extent(flat_spread(most, ~0u), most);
   const size_t have = (size_t)((long long)bytes - r.first) / 8;
   r.states = have < want ? (u32)have : want;
@@ -73,9 +66,9 @@ inline FlatRegion flat_region(u32 max_sub, u32 spare, bool shared, size_t bytes)
 
 // Bytes of chunk states that let a launch of any size up to max_sub spread its states widest
 // (up to 32 KiB more than chunk_state_bytes).
-inline size_t flat_state_bytes(u32 max_sub, u32 spare, bool shared) {
+inline size_t flat_state_bytes(u32 max_sub, u32 spare) {
   const size_t least = chunk_state_bytes(max_sub);
-  const FlatRegion r = flat_region(max_sub, spare, shared, ~(size_t)0 >> 1);
+  const FlatRegion r = flat_region(max_sub, spare, ~(size_t)0 >> 1);
   const long long best = r.first + 8ll * r.states;
   return best > (long long)least ? ((size_t)best + 255) & ~(size_t)255 : least;
 }

@@ -1148,7 +1148,7 @@ size_t least_bytes(u64 n_words, const TablePlan& tp) {
 }
 size_t best_bytes(u64 n_words, const TablePlan& tp) {
   if (tp.levels) return least_bytes(n_words, tp);
-  return kStateHeader + tp.bytes + flat_state_bytes(sub_tiles(n_words), tp.spare, false);
+  return kStateHeader + tp.bytes + flat_state_bytes(sub_tiles(n_words), tp.spare);
 }
 
 void fill_init(ScanInit* a, const fdy_alloc* d_table, u32 n_alloc, const TablePlan& tp, unsigned char* tb) {
@@ -1238,7 +1238,7 @@ extern "C" int fdy_scan_table_prepare(const fdy_alloc* d_table, uint32_t n_alloc
   a.hdr.max_words = max_words;
   a.hdr.table_ptr = (u64)(uintptr_t)d_table;
   a.header = (u32*)(pb + kPreparedHeader);
-  const FlatRegion region = flat_region(sub_tiles(max_words), tp.spare, false,
+  const FlatRegion region = flat_region(sub_tiles(max_words), tp.spare,
                                         prepared_bytes - kPreparedHeader - kStateHeader - tp.bytes);
   a.hdr.region = region;
   a.cstate = (u64*)(pb + kPreparedHeader + kStateHeader + tp.bytes + region.first);
@@ -1311,7 +1311,7 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
   TablePlan tp;
   if (!plan_table(n_alloc, &tp)) return FDY_ERR_INVALID_ARG;
   const u32 n_sub = sub_tiles(n_words);
-  const u32 workers = flat_workers(n_sub, ordered_out), n_chunks = flat_chunks(n_sub, ordered_out);
+  const u32 workers = flat_workers(n_sub), n_chunks = flat_chunks(n_sub);
   // where things lie
   unsigned char* ws = (unsigned char*)d_workspace;
   unsigned char* state;
@@ -1345,7 +1345,7 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
   } else {
     a.header = (u32*)state;
     if (!fused) {
-      region = flat_region(n_sub, tp.spare, false, workspace_bytes - kStateHeader - tp.bytes);
+      region = flat_region(n_sub, tp.spare, workspace_bytes - kStateHeader - tp.bytes);
       a.cstate = cstate + region.first / 8;
       a.n_states = flat_extent(flat_spread(n_chunks, region.states), n_chunks);
     }

@@ -166,19 +166,16 @@ void chunk_states() {
     if (!ok && ++failures <= 10) printf("%s: max_sub %u n_sub %u chunk %u\n", what, max_sub, n_sub, i);
   };
   std::vector<u32> maxima{1, 2, 7, 8, 9, 255, 257, 1343, 1344, 1535, 1536, 1537, 1759, 1761, 2111, 2113, 20000,
-                          kFlatOutSubs - 1, kFlatOutSubs, kFlatOutSubs + 1, 44685, 300001};
+                          32767, 32768, 32769, 44685, 300001};
   for (int i = 0; i < 60; ++i) maxima.push_back(1 + (u32)(next(r) % (1u << (1 + next(r) % 17))));
   for (u32 max_sub : maxima)
     for (u32 spare : {512u, 6144u, 49408u})
-      for (int kind = 0; kind < 4; ++kind) {
-        const bool shared = kind & 1;
-        const size_t least = chunk_state_bytes(max_sub), best = flat_state_bytes(max_sub, spare, shared);
+      for (const bool tight : {false, true}) {
+        const size_t least = chunk_state_bytes(max_sub), best = flat_state_bytes(max_sub, spare);
         expect(best >= least && best <= least + 32768, "size", max_sub, 0, 0);
-        const size_t bytes = kind & 2 ? best : least;
-        const FlatRegion g = flat_region(max_sub, spare, shared, bytes);
+        const size_t bytes = tight ? least : best;
+        const FlatRegion g = flat_region(max_sub, spare, bytes);
         expect(g.first >= -(long long)spare && g.first + 8ll * g.states <= (long long)bytes, "region", max_sub, 0, 0);
-        // general launches that share the buffer: chunks of 32 sub-tiles
-        if (shared && max_sub >= kFlatOutSubs) expect(g.first >= 8ll * ((max_sub + 31) / 32), "general", max_sub, 0, 0);
         std::vector<u64> mem(g.states, 0);
         std::vector<u32> mark(g.states, ~0u);
         u32 turn = 0;
@@ -186,8 +183,7 @@ void chunk_states() {
           u32 n_sub = 1 + (u32)(next(r) % max_sub);
           if (launch % 4 == 1) n_sub = max_sub;
           if (launch % 4 == 3) n_sub = n_sub < 40 ? n_sub : 1 + (u32)(next(r) % 40);
-          const bool out = n_sub < kFlatOutSubs && next(r) % 2;
-          const u32 n = flat_chunks(n_sub, out);
+          const u32 n = flat_chunks(n_sub);
           const FlatTurn t = flat_turn(turn, n, g.states);
           const u64 par = t.parity ? kFlatParity : 0;
           expect(flat_extent(t.s, n) <= g.states, "extent", max_sub, n_sub, 0);

@@ -204,7 +204,7 @@ extern "C" int install_scale_check(uint32_t n_nodes, uint32_t n_graphs, uint32_t
   DevBuf<uint32_t> d_status, d_tmpl_graph, d_graph_tmpl, d_n_tmpl, d_dims;
   DevBuf<fdy_ovr32> d_ovr;
   DevBuf<fdy_grid_ovr> d_govr;
-  DevBuf<unsigned char> d_ws_scan, d_ws_mat, d_ws_derive, d_prepared;
+  DevBuf<unsigned char> d_ws_mat, d_ws_derive, d_prepared;
   CK(d_words.alloc(n_words + 2));
   CK(hipMemcpy(d_words.p, captured.data(), n_words * 8, hipMemcpyHostToDevice));
   CK(d_table.upload(table));
@@ -215,10 +215,8 @@ extern "C" int install_scale_check(uint32_t n_nodes, uint32_t n_graphs, uint32_t
   const size_t prep_bytes = fdy_scan_table_bytes(n_buf, n_words);
   CK(d_prepared.alloc(prep_bytes));
   FD(fdy_scan_table_prepare(d_table.p, n_buf, n_words, d_prepared.p, prep_bytes, stream));
-  const size_t ws_scan = fdy_scan_staging_bytes(n_words);
-  CK(d_ws_scan.alloc(ws_scan));
   FD(fdy_scan_pointers(d_words.p, n_words, d_table.p, n_buf, d_relocs.p, n_words, d_count.p, d_prepared.p,
-                       d_ws_scan.p, ws_scan, d_status.p, stream));
+                       nullptr, 0, d_status.p, stream));
   CK(d_word_off.upload(word_off));
   CK(d_reloc_off.alloc(n_graphs + 1));
   CK(d_recs.upload(recs));
