@@ -30,9 +30,11 @@
 // from memory, some 600 vector instructions per sub-tile, and, once a table outgrows the 4 MiB
 // L2 of an XCD, the lines that candidates pull through the fabric.  None of these alone is at
 // its limit: what counts is how much of them overlaps, so the kernel is built for sixteen waves
-// per compute unit.  Hence 128 registers: a stash in LDS in place of the words, 64 bits per result,
-// wide lines one chain at a time, and no window, staging area or second search for dense stretches
-// (eight rounds hold a whole sub-tile).  Measured on the way (us; 2^27 words, 2^20 allocations, with
+// per compute unit.  Hence 128 registers: candidates (or the stash) in LDS in place of the words,
+// 64 bits per result, wide lines one chain at a time, and no window, staging area or second search for
+// dense stretches (eight rounds hold a whole sub-tile).  They are just enough: with nodes and an output
+// four values are spilled (20 bytes of scratch a lane), and the instances for tables with lines keep
+// 20 to 50 scalars in lanes of vector registers.  Measured on the way (us; 2^27 words, 2^20 allocations, with
 // output / 12.3 M words, 65,537 byte-granular allocations, with output / 33.5 M words, 300,007
 // allocations with 8 GiB regions, without):
 //   eight waves of 256 registers, two sub-tiles in hand, tables read through up to two nodes   758 / 95 / 227
@@ -663,7 +665,13 @@ __device__ __forceinline__ void search_step(const ScanParams& p, const FlatLevel
 // nodes, the others' rounds go one by one: sixteen waves cover each other's latency, and more chains
 // per lane only thrash the vector L1 between a line's two halves.  2^27 words with 15 % candidates,
 // 2^20 allocations: 685 us with the two rounds at once, 728 one by one; 16.8 M words with 25 %
-// and 8 GiB regions: 160 and 145.
+// and 8 GiB regions: 160 and 145.  Where the line lies depends on table and form: us one by one / at once, 8.4 M words
+// with exactly so many candidates in each sub-tile,
+//                                  80            90            96            102           112
+//   200,000 allocations            37.2 / 34.8   37.8 / 35.7   37.9 / 36.3   38.3 / 36.9   38.8 / 38.0
+//   200,000, with output           49.4 / 47.1   50.1 / 49.2   50.7 / 50.5   51.6 / 51.9   53.6 / 54.1
+//   2^20                           45.9 / 42.3   46.3 / 44.1   46.7 / 45.2   47.4 / 46.7   48.9 / 49.3
+//   2^20, with output              70.6 / 70.6   74.2 / 75.4   76.9 / 78.3   79.6 / 81.2   84.4 / 85.9
 constexpr u32 kFewCandidates = 96;
 template <int kDepth, bool kOut, int R0 = 0>
 __device__ __forceinline__ void search_all(const ScanParams& p, const FlatLevel& f, Forms& m, Entries pk, u64* stash,
@@ -843,9 +851,13 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_kernel(ScanParams p) {
 
 // The unordered form (fdy_scan_rebase: rebased words, no relocation table): no tickets and no look-back,
 // waves stride over the sub-tiles on their own, with the next words in flight during a search (no
-// barrier lines the waves up here).  Eight waves a workgroup: 12 take 26.4 instead of 24.9 us for 5 M
-// words and 16,384 allocations, 87 instead of 76 for 16.8 M and 100,000, but 126 instead of 139 for
-// 33 M and 4,096.  A workgroup's hits and "one more is through" go to one
+// barrier lines the waves up here).  Eight waves a workgroup, two workgroups a compute unit: how many are best moves
+// with the rounds that a size takes (us with 8 / 10 / 12 / 15 waves, sub-tiles per compute unit, a quarter candidates):
+//   16,384 allocations   20  15.2 / 14.6 / 14.3 / 14.2   32  20.8 / 22.4 / 21.1 / 24.9   64  39.0 / 40.0 / 41.7 / 44.7
+//                        256  139 / 136 / 144 / 155
+//   300,000              20  23.8 / 20.9 / 21.6 / 25.2   32  29.8 / 37.2 / 31.8 / 39.3   64  57.3 / 61.2 / 61.4 / 64.9
+//                        256  219 / 213 / 211 / 217
+// and eight are seldom far from the best.  A workgroup's hits and "one more is through" go to one
 // 64-bit counter in one addition (same-address additions are served one after the other, 12 ns
 // each: one per wave is 25 us of them); the workgroup that finds itself last publishes the sum and
 // leaves the counter zero.  out may be the input array itself: a wave has read a sub-tile
@@ -1076,8 +1088,15 @@ struct TablePlan {
 };
 
 // From so many sub-tiles on a base map is laid beside the lines of a table with nodes, a launch of 5 to
-// 8 us.  us without / with, a quarter candidates, 200,000 allocations: 4 M words 45 / 47, 12 M 87 /
-// 91, 32 M 197 / 194; 600,000: 54 / 59, 114 / 113, 260 / 245; 2^20: 60 / 65, 131 / 126, 306 / 276.
+// 8 us.  us without / with, a fifth candidates, 2 MiB granules:
+//   allocations     4 Mi words    8 Mi          12 Mi         16 Mi         32 Mi
+//   140,000         31.4 / 37.0   49.5 / 56.7   68.3 / 75.5   87.1 / 94.2   163 / 172
+//   200,000         33.8 / 38.2   52.2 / 57.4   71.5 / 76.7   90.3 / 95.4   169 / 173
+//   300,000         36.3 / 40.9   57.5 / 60.5   78.8 / 80.0   99.5 / 99.4   187 / 180
+//   450,000         39.1 / 44.0   62.9 / 64.5   86.1 / 85.1   110 / 106     208 / 192
+//   2^20            48.0 / 51.1   80.1 / 75.8   112 / 100     143 / 124     271 / 224
+// So the line that would fit depends on the table: this one, for all, is where most tables gain; below 300,000
+// allocations it costs up to a tenth.
 constexpr u32 kRecordSubs = 24576;
 
 bool plan_table(u32 n_alloc, TablePlan* pl) {
@@ -1203,8 +1222,8 @@ extern "C" size_t fdy_scan_workspace_bytes(uint64_t n_words, uint32_t n_alloc) {
 
 extern "C" size_t fdy_scan_staging_bytes(uint64_t n_words) {
   if (n_words > kMaxWords) return 0;
-  // No scan has a use for it any more (dense stretches are searched in windows).  The answer stays what it
-  // was, so that a caller's sizes do not move.
+  // No scan has a use for it any more (a worker's registers hold the results of a whole sub-tile).  The answer stays
+  // what it was, so that a caller's sizes do not move.
   constexpr u32 kStageWgs = 320;
   const u32 n_sub = sub_tiles(n_words), chunk = n_sub < (1u << fdy__tune_get(FDY_TUNE_SCAN_SMALL_LOG2)) ? 8 : 32;
   const u32 n_chunks = (n_sub + chunk - 1) / chunk;

@@ -18,7 +18,7 @@ def _status_tensor():
 
 
 def _scan_ws_bytes(n_words, n_alloc, staging=True):
-    """Workspace of a scan: hierarchy and state, plus (staging) the optional staging area."""
+    """Workspace of a scan: hierarchy and state, plus (staging) as much again as earlier versions could use."""
     return fdy.fdy_scan_workspace_bytes(n_words, n_alloc) + (fdy.fdy_scan_staging_bytes(n_words) if staging else 0)
 
 

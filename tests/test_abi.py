@@ -87,8 +87,8 @@ def test_table_validate_agrees_with_oracle(fdy, oracle):
 def test_workspace_sizes(fdy):
     assert fdy.fdy_scan_workspace_bytes(0, 0) >= 256
     a = fdy.fdy_scan_workspace_bytes(1 << 27, 1 << 20)
-    # table hierarchy (about 14 MiB for 2^20 allocations) and chunk states; the staging area of
-    # dense inputs is optional, queried apart, and bounded by the workgroups in flight (160 MiB)
+    # table hierarchy (about 21 MiB for 2^20 allocations) and chunk states; what earlier versions could
+    # use beside it for dense inputs is queried apart (up to 160 MiB)
     assert 0 < a < 32 << 20 and a % 256 == 0
     assert 0 < fdy.fdy_scan_staging_bytes(1 << 27) <= 160 << 20
     assert fdy.fdy_scan_staging_bytes(1 << 31) == fdy.fdy_scan_staging_bytes(1 << 27)

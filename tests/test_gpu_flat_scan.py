@@ -78,12 +78,23 @@ def test_candidates_and_tables(n_alloc, shape, density):
     check_all_forms(words_of(rng, 20 * SUB + 5, t, density), t, rng)
 
 
-@pytest.mark.parametrize("each", [1, 64, 65, 192, 193, 256, 257, 320, 384, 385, 448, 449, 511, 512])
-@pytest.mark.parametrize("n_alloc", [1, 300])
-def test_candidates_of_a_sub_tile(n_alloc, each):
+@pytest.mark.parametrize("each", [1, 64, 65, 96, 97, 128, 192, 193, 256, 257, 320, 384, 385, 448, 449, 511, 512])
+@pytest.mark.parametrize("top_log2,n_alloc", [(14, 1), (14, 300), (5, 200), (5, 1024)])  # level 0 alone, lines, nodes
+def test_candidates_of_a_sub_tile(top_log2, n_alloc, each):
     """Exactly so many candidates in every sub-tile, of words and of 4-byte positions: rounds one by one, two to four at
     a time."""
+    import paper_2604_06664_amd as fdy
+
+    old = fdy.tune_set(fdy.TUNE_SCAN_TOP_LOG2, top_log2)
+    try:
+        candidates_of_a_sub_tile(n_alloc, each)
+    finally:
+        fdy.tune_set(fdy.TUNE_SCAN_TOP_LOG2, old)
+
+
+def candidates_of_a_sub_tile(n_alloc, each):
     from tests.support import session
+    from tests.test_gpu_parity import oracle_rebase
 
     rng = np.random.default_rng(each)
     t = np.zeros(n_alloc, L.ALLOC)
@@ -92,7 +103,7 @@ def test_candidates_of_a_sub_tile(n_alloc, each):
     t["size"][-1] = np.uint64(1 << 34)
     n = 20 * SUB
     chosen = np.concatenate([s * SUB + rng.choice(SUB, each, replace=False) for s in range(20)])
-    for stride4 in (False, True):
+    for stride4 in (True, False):
         units = rng.integers(1, 1 << 20, n + 1 if stride4 else 2 * n).astype(np.uint32)
         high = chosen + 1 if stride4 else 2 * chosen + 1  # the half of a candidate that makes it one
         units[high] = (0x7F000000 + rng.integers(0, 4 * n_alloc, len(high))).astype(np.uint32)
@@ -104,6 +115,12 @@ def test_candidates_of_a_sub_tile(n_alloc, each):
             got, have, status = session.scan(units.view(np.uint64), t, prepared=True)
         assert 0 < cnt <= 20 * each
         assert status == 0 and have == cnt and np.array_equal(got, ref), stride4
+    words, nb = units.view(np.uint64), rng.integers(0, 1 << 63, n_alloc, dtype=np.uint64)  # (of the words' turn)
+    want, _ = oracle_rebase(orc, words, t, nb)
+    run = session.ScanPointersRebaseRun(words, t, nb, prepared=True, staging=False)
+    run.launch()
+    got, have, status, out = run.result()
+    assert status == 0 and have == cnt and np.array_equal(got, ref) and np.array_equal(out, want)
 
 
 def test_prepared_states_take_turns():
@@ -127,9 +144,8 @@ def test_prepared_states_take_turns():
     torch.cuda.synchronize()
 
 
-def test_kernels_share_a_prepared_table():
-    """Scans with output of 16 Mi words and more go through the general kernel, smaller ones and
-    plain scans through the flat one; all use the same prepared table in turn."""
+def test_forms_share_a_prepared_table():
+    """Launches of every form, of 16 Mi words and of a few thousand, on one prepared table in turn."""
     import paper_2604_06664_amd as fdy
     from tests.support import session
     from tests.test_gpu_parity import oracle_rebase

@@ -33,7 +33,8 @@ def say(msg):
     print(msg, flush=True)
 
 
-MODES = ((False, True), (True, True), (False, False), (True, False))  # (prepared table, staging area)
+# (prepared table, a workspace larger than asked for by fdy_scan_staging_bytes, which nothing uses)
+MODES = ((False, True), (True, False))
 
 
 # ------------------------------------------------------------------------------------ scan
@@ -41,7 +42,7 @@ def check_scan(hip, oracle, words, table, capacity=None, tag=""):
     say(f"[scan] {tag} W={len(words)} A={len(table)} cap={capacity}")
     ref, rcnt = oracle.scan(words, table, capacity)
     cap = len(words) if capacity is None else capacity
-    # hierarchy built by the call / by fdy_scan_table_prepare; dense groups staged / searched twice
+    # hierarchy built by the call / by fdy_scan_table_prepare
     for prepared, staging in MODES:
         got, cnt, status = hip.scan(words, table, capacity, prepared=prepared, staging=staging)
         assert cnt == rcnt
@@ -129,12 +130,10 @@ def test_scan_truncated_key_ambiguity(hip, oracle):
 
 
 def test_scan_large_input_dense_groups_and_wide_lines(hip, oracle):
-    """The large-input kernel variant (two groups of two sub-tiles per wave) on an input long
-    enough to select it, with everything that variant handles specially: stretches where every
-    word is a pointer (groups beyond the register-resident limit: windowed two-pass path),
-    moderate and zero density elsewhere, a ragged tail, and a 200,000-entry table read through
-    its packed copy in which some 8-entry lines cannot be packed (an allocation of 5 GiB, a
-    gap of 6 GiB) and the last line is partial."""
+    """An input of 1,101 chunks with stretches where every word is a pointer (eight rounds of
+    candidates), moderate and zero density elsewhere, a ragged tail, and a 200,003-entry table read
+    through nodes and lines, some of which have no compact form (an allocation of 5 GiB, a gap of
+    6 GiB) and the last of which is partial."""
     rng = np.random.default_rng(77)
     A = 200_003
     size = rng.integers(16, 1 << 16, A).astype(np.uint64)
@@ -160,7 +159,7 @@ def test_scan_large_input_dense_groups_and_wide_lines(hip, oracle):
         words[idx[kind == 3]] = table["base"][reg[kind == 3]] - np.uint64(1)    # one below
 
     plant(0, 2_000_000, 0.30)
-    plant(2_000_000, 2_600_000, 1.0)     # dense: every group overflows the register path
+    plant(2_000_000, 2_600_000, 1.0)     # dense
     plant(2_600_000, 2_600_700, 0.0)
     plant(3_000_000, 3_001_536, 1.0)     # a dense island of three sub-tiles
     plant(5_000_000, W, 0.12)
@@ -375,7 +374,7 @@ def test_scan_stride4_edge_cases(hip, oracle):
     # no table: nothing is a pointer
     got, cnt, status = hip.scan_stride4(u, t[:0])
     assert cnt == 0 and status == 0
-    # (nearly) every position a hit: the windowed path
+    # (nearly) every position a hit
     wide = mk_table([(0, 1 << 63), (1 << 63, (1 << 63) - 1)])
     check_scan4(hip, oracle, rng.integers(0, 1 << 32, 9001, dtype=np.uint32), wide, tag="all hits")
     old = fdy.tune_get(fdy.TUNE_SCAN_TOP_LOG2)
@@ -446,7 +445,7 @@ def test_scan_rebase_edge_cases(hip, oracle):
     # no table: a plain copy
     got, cnt, status = hip.scan_rebase(ar.words[:5000], ar.table[:0], nb[:0])
     assert cnt == 0 and status == 0 and np.array_equal(got, ar.words[:5000])
-    # every word a hit (groups beyond the queue: windowed path), touching intervals, extremes,
+    # every word a hit, touching intervals, extremes,
     # sums that wrap mod 2^64
     dense = mk_table([(0x1000 + 64 * i, 64) for i in range(300)] + [(2**64 - 0x100, 0xFF)])
     rng = np.random.default_rng(5)
@@ -536,7 +535,7 @@ def test_scan_pointers_rebase_edge_cases(hip, oracle):
         check_scan_out(hip, oracle, ar.words[:n], ar.table, nb, tag="ragged")
     check_scan_out(hip, oracle, ar.words[:5000], ar.table[:0], nb[:0], tag="no table: a plain copy")
     check_scan_out(hip, oracle, ar.words[:300000], ar.table, nb, capacity=1000, tag="capacity exceeded")
-    # every word a hit (dense groups: windowed path with staged entries), touching intervals,
+    # every word a hit, touching intervals,
     # extremes, sums that wrap mod 2^64
     dense = mk_table([(0x1000 + 64 * i, 64) for i in range(300)] + [(2**64 - 0x100, 0xFF)])
     rng = np.random.default_rng(5)

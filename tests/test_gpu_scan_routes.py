@@ -1,6 +1,5 @@
-"""What the flat kernels of small tables took away from older tests: word-dense inputs through the
-general kernels (small and large chunks, staged and searched twice), and the bounded wait of both
-ordered scans."""
+"""Word-dense inputs through lines and nodes (a small table beyond a level 0 made smaller), through level 0
+alone at a size where workgroups take many chunks, and the bounded wait of the ordered scan."""
 import numpy as np
 import pytest
 
@@ -31,9 +30,9 @@ def dense_with_gaps(n):
     return w, t, nb
 
 
-@pytest.mark.parametrize("n", [9000, 70 * SUB + 1, 1 << 20, 4096 * SUB + 777])  # the last: large chunks
+@pytest.mark.parametrize("n", [9000, 70 * SUB + 1, 1 << 20, 4096 * SUB + 777])  # the last two: fifteen workers
 @pytest.mark.parametrize("make", [dense_input, dense_with_gaps])
-def test_dense_words_through_the_general_kernels(n, make):
+def test_dense_words_of_a_table_with_nodes(n, make):
     import paper_2604_06664_amd as fdy
     from tests.support import session
     from tests.test_gpu_parity import check_rebase, check_scan, check_scan_out, oracle_rebase
@@ -41,22 +40,21 @@ def test_dense_words_through_the_general_kernels(n, make):
     words, t, nb = make(n)
     old = fdy.tune_get(fdy.TUNE_SCAN_TOP_LOG2)
     try:
-        fdy.tune_set(fdy.TUNE_SCAN_TOP_LOG2, 4)  # 301 regions do not fit 16 keys: packed levels
-        check_scan(session, orc, words, t, tag="dense, general")
-        check_scan_out(session, orc, words, t, nb, tag="dense, general")
-        check_rebase(session, orc, words, t, nb, tag="dense, general")
+        fdy.tune_set(fdy.TUNE_SCAN_TOP_LOG2, 4)  # 301 regions do not fit 16 keys: lines and nodes
+        check_scan(session, orc, words, t, tag="dense, nodes")
+        check_scan_out(session, orc, words, t, nb, tag="dense, nodes")
+        check_rebase(session, orc, words, t, nb, tag="dense, nodes")
         units = words.view(np.uint32)[:n + 1 if n > 1 << 20 else 2 * n]
         ref, cnt = orc.scan_stride4(units, t)
         for prepared in (False, True):
-            for staging in (False, True):
-                got, have, status = session.scan_stride4(units, t, prepared=prepared, staging=staging)
-                assert status == 0 and have == cnt and np.array_equal(got, ref)
+            got, have, status = session.scan_stride4(units, t, prepared=prepared, staging=False)
+            assert status == 0 and have == cnt and np.array_equal(got, ref)
     finally:
         fdy.tune_set(fdy.TUNE_SCAN_TOP_LOG2, old)
 
 
 def test_dense_words_of_a_small_table_above_16_mi_words():
-    """With output such a launch takes the general kernel, without packed levels."""
+    """2,185 chunks, with output."""
     from tests.support import session
     from tests.test_gpu_parity import check_scan_out
 
@@ -64,12 +62,11 @@ def test_dense_words_of_a_small_table_above_16_mi_words():
     check_scan_out(session, orc, words, t, nb, tag="dense, small table, large")
 
 
-@pytest.mark.parametrize("n_alloc", [300, 20000])  # flat, general
+@pytest.mark.parametrize("n_alloc", [300, 20000, 140000])  # level 0 alone, lines, nodes
 @pytest.mark.parametrize("n", [200 * SUB, 1500 * SUB, 8000 * SUB])
 def test_bounded_wait_and_the_calls_after(n_alloc, n):
     """With a spin limit of 0 a workgroup whose predecessor is not through gives up, says so and ends.
-    A small table's states are in order even then: calls on the same prepared table are exact
-    (the others are prepared again, as the interface asks)."""
+    The chunk states are in order even then: calls on the same prepared table are exact."""
     import paper_2604_06664_amd as fdy
     from tests.support import session
     from tests.test_gpu_flat_scan import table_of, words_of
@@ -88,8 +85,6 @@ def test_bounded_wait_and_the_calls_after(n_alloc, n):
             fdy.tune_set(fdy.TUNE_SCAN_SPIN_LIMIT, old)
         assert status & ~(L.ST_SPIN | L.ST_CAPACITY) == 0
         run.d_status.zero_()
-        if n_alloc > 16384:
-            run.prepare(n)
         for _ in range(2):
             run.launch()
             got, have, status = run.result()
