@@ -27,7 +27,7 @@
 //
 // What bounds it.  A compute unit's vector L1 takes one divergent lane per clock and its
 // searches' chains of dependent requests cost 0.6-0.8 us a step; beside them stand the words
-// from memory, some 600 vector instructions per sub-tile, and, once a table outgrows the 4 MiB
+// from memory, 300 to 700 vector instructions per sub-tile, and, once a table outgrows the 4 MiB
 // L2 of an XCD, the lines that candidates pull through the fabric.  None of these alone is at
 // its limit: what counts is how much of them overlaps, so the kernel is built for sixteen waves
 // per compute unit.  Hence 128 registers: candidates (or the stash) in LDS in place of the words,
