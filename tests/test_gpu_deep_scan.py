@@ -118,15 +118,17 @@ def test_offsets_beyond_a_packed_result(top_log2, n_alloc):
         fdy.tune_set(fdy.TUNE_SCAN_TOP_LOG2, old)
 
 
-@pytest.mark.parametrize("bases", ["moved", "random", "some odd"])
-def test_base_map_beside_the_lines(bases):
-    """From 24,576 sub-tiles on, with nodes: codes, and new bases that have none."""
+@pytest.mark.parametrize("bases,n_alloc,subs", [("moved", 131073, 24577), ("random", 131073, 24577), ("some odd", 131073, 24577),
+                                                ("some odd", 131073, 24575), ("some odd", (1 << 20) + 9, 24576)])
+def test_base_map_beside_the_lines(bases, n_alloc, subs):
+    """From 24,576 sub-tiles on, with nodes (and, beyond 2^20 allocations, two of them to a key): codes, and new bases
+    that have none."""
     from tests.support import session
     from tests.test_gpu_parity import oracle_rebase
 
     rng = np.random.default_rng(24)
-    t = table_of(rng, 131073, "granule")
-    n = 24576 * SUB + 1
+    t = table_of(rng, n_alloc, "granule")
+    n = (subs - 1) * SUB + 1
     words = np.tile(words_of(rng, 1 << 18, t, 0.2), 49)[:n]
     nb = t["base"] + np.uint64(0x5000_0000_0000)
     if bases == "random":
