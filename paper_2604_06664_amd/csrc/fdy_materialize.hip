@@ -26,7 +26,7 @@
 //                            in registers once, then per base map of its group scatters c2
 //                            rebased pointers (new_base[m][region] + offset), c3 32-bit
 //                            overrides and c4 64-bit rank patches into LDS in that order and
-//                            streams the tile out with coalesced stores.  Templates,
+//                            streams the tile out by whole memory lines.  Templates,
 //                            relocation lists and base maps are re-read per group from L2 /
 //                            Infinity Cache; only the output is compulsory HBM traffic.
 //   small launches           (every workgroup of main resident at once): no prep launch at
@@ -44,19 +44,26 @@
 namespace fdy {
 namespace {
 
-constexpr int kMatTile = 2048;  // words per tile (16 KiB)
 constexpr int kMatBlock = 256;
+constexpr int kMatBuf = 2048;             // words of a workgroup's tile buffer (16 KiB)
+constexpr int kLine = 16;                 // words of a 128-byte memory line
+// Words per tile.  A wave stores whole 128-byte lines, wherever the tile begins: a store that straddles two more lines
+// than it fills cost the launch 3 to 5 % (us per pass: 67 graphs to 8 ranks, 240 MB, 93.6 -> 91.2; to 256 maps, 1.56 GB,
+// 297 -> 287).  A line less than the buffer, so that a tile and the words in front of it in its first line are four
+// 16-byte stores per thread: with a fifth for a few lanes, or with assignments that wrap, the gain went into registers.
+// The lines that two tiles share are left (without them 88.9 and 285).
+constexpr int kMatTile = kMatBuf - kLine;
 
-struct __attribute__((aligned(16))) MatTile {  // 64 B
+struct __attribute__((aligned(16))) MatTile {  // 48 B
   u64 src_word;  // index into src_words of the tile's first word
   u64 out_word;  // word offset of the tile inside one map's output
   u32 n_words;   // 0: unused entry
-  u32 g, tmpl, k0;
+  u32 k0;
   u32 reloc_lo, reloc_hi, ovr_lo, ovr_hi;
   u32 reloc_seg;  // first entry of the template's relocation list (order checks stop there)
-  u32 pad[3];
+  u32 pad;
 };
-static_assert(sizeof(MatTile) == 64, "MatTile");
+static_assert(sizeof(MatTile) == 48, "MatTile");
 
 struct MatHeader {
   u32 n_tiles;
@@ -388,15 +395,13 @@ __device__ __forceinline__ void prep_tiles_block(const MatParams& p, const PrepV
   e.src_word = q.src_word;
   e.out_word = v.out_word_off[q.g] + q.k0;
   e.n_words = q.n;
-  e.g = q.g;
-  e.tmpl = q.t;
   e.k0 = (u32)q.k0;
   e.reloc_lo = reloc_lo;
   e.reloc_hi = reloc_hi;
   e.ovr_lo = ovr_lo;
   e.ovr_hi = ovr_hi;
   e.reloc_seg = rl0;
-  e.pad[0] = e.pad[1] = e.pad[2] = 0;
+  e.pad = 0;
   *ent = e;
 }
 
@@ -433,8 +438,6 @@ __device__ __forceinline__ void prep_tile_group(const MatParams& p, const PrepVi
   e.src_word = q.src_word;
   e.out_word = v.out_word_off[q.g] + q.k0;
   e.n_words = q.n;
-  e.g = q.g;
-  e.tmpl = q.t;
   e.k0 = (u32)q.k0;
   const u32 at = lane_id() & 32;
   e.reloc_lo = __shfl(found, at);
@@ -442,7 +445,7 @@ __device__ __forceinline__ void prep_tile_group(const MatParams& p, const PrepVi
   e.ovr_lo = __shfl(found, at + 16);
   e.ovr_hi = max((u32)__shfl(found, at + 24), e.ovr_lo);
   e.reloc_seg = rl0;
-  e.pad[0] = e.pad[1] = e.pad[2] = 0;
+  e.pad = 0;
   if (l != 0 || j >= p.ws.max_tiles) return;
   MatTile* ent = &p.ws.tiles[j];
   if (!valid) {
@@ -525,7 +528,7 @@ __device__ __forceinline__ void stage_tile(u64* buf, const u64* src, u64 src_wor
 
 // The same in two steps, so that other work can sit between the loads and their use (the
 // self-resolving form of the main kernel searches its slices meanwhile).
-constexpr int kTileChunks = kMatTile / (2 * kMatBlock);
+constexpr int kTileChunks = kMatBuf / (2 * kMatBlock);
 struct TileRegs {
   u64x2 v[kTileChunks];
   u64 first, last;
@@ -665,8 +668,8 @@ __device__ __forceinline__ void write_dims(const MatParams& p, const PrepView<kO
 // and the store of the tile repeat.  Relocations and overrides hit the same words for every
 // map, so the LDS copy needs no refresh between maps; rank patches differ per map, so the
 // words the previous map's rank patched are given their template values back first.
-constexpr int kMatPre = kMatTile / kMatBlock;
-constexpr int kMatStore = kMatTile / (2 * kMatBlock);  // 16-byte chunks per thread
+constexpr int kMatPre = kMatBuf / kMatBlock;
+constexpr int kMatStore = kMatBuf / (2 * kMatBlock);  // 16-byte chunks per thread
 constexpr int kMatOvrPre = 2;                          // overrides of the tile a thread keeps in registers
 
 //
@@ -729,7 +732,7 @@ __device__ __forceinline__ SelfSums self_sums(const MatParams& p, u64* buf, u64*
 
 template <bool kSelf>
 __global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 n_tile_blocks, u32 nb_dims) {
-  __shared__ __align__(16) u64 buf[kMatTile];
+  __shared__ __align__(16) u64 buf[kMatBuf];
   __shared__ u64 s_buf[kSelf ? 17 : 1];
   __shared__ u32 s_found[kSelf ? 4 + 2 * kSelfMaxGroup : 1];
   typedef u64 v2u64 __attribute__((ext_vector_type(2)));
@@ -820,8 +823,6 @@ __global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 n_
     ent.src_word = src_word;
     ent.out_word = out_word;
     ent.n_words = n_here;
-    ent.g = g;
-    ent.tmpl = t;
     ent.k0 = k0;
     ent.reloc_lo = s_found[0];
     ent.reloc_hi = s_found[1];
@@ -989,19 +990,19 @@ __global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 n_
     __syncthreads();
     // stream the tile out: LDS -> registers, then 16-byte non-temporal stores (the output is
     // written once and not read again here; keeping it out of L2 leaves the templates, lists
-    // and base maps there).  The barrier sits between the LDS reads and the global stores so
+    // and base maps there: with plain stores 256 maps take 407 us, not 287).  The barrier sits between the LDS reads and the global stores so
     // that the next map's scatter can start while the stores drain.
     const u64 out_at = (u64)m * d.out_words_per_map + ent.out_word;
     u64* out = p.out_words + out_at;
-    const u32 head = (u32)(out_at & 1);
-    const u32 pairs = (n - head) >> 1;
+    const u32 behind = (u32)((uintptr_t)out >> 3) & (kLine - 1);  // words of the first line in front of the tile
+    const u32 at = 2 * tid - behind;                               // (wraps below the tile's first word)
     v2u64 v[kMatStore];
 #pragma unroll
     for (int c = 0; c < kMatStore; ++c) {
-      const u32 i = tid + (u32)c * kMatBlock;
-      if (i < pairs) {
-        v[c].x = buf[head + 2 * i];
-        v[c].y = buf[head + 2 * i + 1];
+      const u32 i = at + (u32)c * 2 * kMatBlock;
+      if (i < n - 1) {
+        v[c].x = buf[i];
+        v[c].y = buf[i + 1];
       }
     }
     const u64 first = buf[0], last = buf[n - 1];
@@ -1021,11 +1022,11 @@ __global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 n_
     }
 #pragma unroll
     for (int c = 0; c < kMatStore; ++c) {
-      const u32 i = tid + (u32)c * kMatBlock;
-      if (i < pairs) __builtin_nontemporal_store(v[c], reinterpret_cast<v2u64*>(out + head + 2 * i));
+      const u32 i = at + (u32)c * 2 * kMatBlock;
+      if (i < n - 1) __builtin_nontemporal_store(v[c], reinterpret_cast<v2u64*>(out + i));
     }
-    if (tid == 0 && head) __builtin_nontemporal_store(first, out);
-    if (tid == 0 && head + 2 * pairs < n) __builtin_nontemporal_store(last, out + n - 1);
+    if (tid == 0 && (behind & 1)) __builtin_nontemporal_store(first, out);
+    if (tid == 0 && ((behind + n) & 1)) __builtin_nontemporal_store(last, out + n - 1);
   }
   if (bad) raise_status(p.d_status, FDY_ST_BAD_INDEX);
   if (disorder) raise_status(p.d_status, FDY_ST_BAD_ORDER);
@@ -1143,6 +1144,19 @@ size_t layout(const fdy_mat_desc* d, unsigned char* base, MatWs* ws) {
   return off;
 }
 
+// The size that is asked for: that of tables for tiles of 2,048 words and 64-byte entries, as ever, so that a caller's
+// sizes do not move, or what the tables take where that is more (248 ranks and more: up to 0.8 %, and an entry per rank).
+size_t asked_bytes(const fdy_mat_desc* d) {
+  const u64 tiles = (d->out_words_per_map + 2047) / 2048 + d->n_graphs;
+  const size_t per_graph = align256(((size_t)d->n_graphs + 1) * 8);
+  return align256(sizeof(MatHeader)) + 3 * per_graph + align256((size_t)tiles * 64) +
+         align256((size_t)tiles * (d->map_rank ? d->n_ranks : 0) * sizeof(uint2));
+}
+size_t workspace_need(const fdy_mat_desc* d) {
+  const size_t asked = asked_bytes(d), need = layout(d, nullptr, nullptr);
+  return asked > need ? asked : need;
+}
+
 }  // namespace
 }  // namespace fdy
 
@@ -1150,14 +1164,16 @@ using namespace fdy;
 
 extern "C" size_t fdy_materialize_workspace_bytes(const fdy_mat_desc* h_desc) {
   if (!desc_ok(h_desc)) return 0;
-  return layout(h_desc, nullptr, nullptr);
+  return workspace_need(h_desc);
 }
 
 // Scratch of the entry point that allocates nothing (fdy_materialize_static): the tile table and
 // the other per-call tables of a materialization, in device memory that belongs to the loaded
 // library.  Each GPU holds its own copy at its own address, found once per device with
 // hipGetSymbolAddress; host code uses that address, never the array's name.
-constexpr size_t kStaticScratchBytes = 4u << 20;
+// (The limit is on what is asked for; the tables themselves can take half as much again where thousands of ranks
+// patch a graph of three tiles that would have been two of 2,048 words.)
+constexpr size_t kStaticLimitBytes = 4u << 20, kStaticScratchBytes = 6u << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words, uint32_t* d_out_dims,
@@ -1170,12 +1186,12 @@ extern "C" int fdy_materialize(const fdy_mat_desc* h_desc, uint64_t* d_out_words
   return materialize_launch(h_desc, d_out_words, d_out_dims, d_workspace, workspace_bytes, d_status, hip_stream);
 }
 
-extern "C" size_t fdy_materialize_static_limit(void) { return kStaticScratchBytes; }
+extern "C" size_t fdy_materialize_static_limit(void) { return kStaticLimitBytes; }
 
 extern "C" int fdy_materialize_static(const fdy_mat_desc* h_desc, uint64_t* d_out_words, uint32_t* d_out_dims,
                                       uint32_t* d_status, void* hip_stream) {
   if (!desc_ok(h_desc)) return FDY_ERR_INVALID_ARG;
-  if (layout(h_desc, nullptr, nullptr) > kStaticScratchBytes) return FDY_ERR_WORKSPACE;  // beyond the fixed scratch
+  if (asked_bytes(h_desc) > kStaticLimitBytes) return FDY_ERR_WORKSPACE;  // beyond the fixed scratch
   constexpr int kMaxDevices = 64;
   static void* ptr_of_device[kMaxDevices] = {};
   static std::mutex mu;
@@ -1217,7 +1233,7 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
   p.d = d;
   if (!d.map_rank) p.d.n_ranks = 0;
   if (!d_out_dims) p.d.out_nodes_total = 0;
-  const size_t need = layout(&d, nullptr, nullptr);
+  const size_t need = workspace_need(&d);
   if (!d_workspace || ((uintptr_t)d_workspace & 255) || workspace_bytes < need) return FDY_ERR_WORKSPACE;
   layout(&d, (unsigned char*)d_workspace, &p.ws);
   p.out_words = (u64*)d_out_words;

@@ -1,0 +1,76 @@
+"""Output tiles against the 128-byte lines that they are stored by: template lengths around a tile, an output
+that begins at each 16-byte place of a line, and maps of an odd number of words, so that tiles begin everywhere."""
+import numpy as np
+import pytest
+
+import oracle as orc
+from synth import MatProblem
+from synth import layout as L
+
+pytestmark = pytest.mark.gpu
+TILE = 2032
+
+
+@pytest.mark.parametrize("place", range(8))
+def test_tiles_at_every_place_of_a_line(place):
+    import paper_2604_06664_amd as fdy
+    from tests.support import session
+
+    rng = np.random.default_rng(place)
+    lens = [1, 2, 15, 16, 17, TILE - 1, TILE, TILE + 1, TILE + 16, 2 * TILE, 2 * TILE + 1, 0]
+    off = np.cumsum([0] + lens).astype(np.uint64)
+    W, regions = int(off[-1]), 50
+    words = np.sort(rng.choice(W, W // 2, replace=False))
+    r = np.zeros(len(words), L.RELOC)
+    r["word"], r["region"], r["offset"] = words, rng.integers(0, regions, len(r)), rng.integers(0, 1 << 40, len(r))
+    tmpl = rng.permutation(np.r_[np.arange(len(lens)), np.arange(len(lens)), 0]).astype(np.uint32)
+    ovr, ovr_off = [], [0]
+    for t in tmpl:  # the first and the last half of each tile
+        at = sorted({b for k in range(0, lens[t], TILE) for b in (2 * k, 2 * min(k + TILE, lens[t]) - 1)})
+        o = np.zeros(len(at), L.OVR32)
+        o["byte_off"], o["value"] = np.array(at, np.uint32) * 4, rng.integers(0, 1 << 32, len(at))
+        ovr.append(o)
+        ovr_off.append(ovr_off[-1] + len(o))
+    mp = MatProblem(
+        src_words=rng.integers(0, 1 << 63, W, dtype=np.uint64), src_word_off=off, src_nodes=np.zeros(0, L.NODE),
+        src_node_off=np.zeros(len(lens) + 1), relocs=r, src_reloc_off=np.searchsorted(words, off.astype(np.int64)),
+        tmpl_graph=np.arange(len(lens)), graph_tmpl=tmpl, ovr=np.concatenate(ovr), ovr_off=ovr_off,
+        govr=np.zeros(0, L.GRID_OVR), govr_off=np.zeros(len(tmpl) + 1),
+        new_base=rng.integers(0, 1 << 63, (17, regions), dtype=np.uint64), map_rank=None, n_ranks=0,
+        patch=np.zeros(0, L.PATCH), patch_off=[0])
+    wpm = mp.out_words_per_map()
+    assert wpm % 2 == 1
+    want, _ = orc.materialize(mp)
+    default = fdy.tune_get(fdy.TUNE_MAT_SELF_WGS)
+    try:
+        for self_wgs in (0, default):  # tiles resolved by a launch ahead / by the workgroups themselves
+            fdy.tune_set(fdy.TUNE_MAT_SELF_WGS, self_wgs)
+            n = 17 * wpm * 8
+            room = fdy.device_bytes(n + 512, fill=0xCD)
+            lo = (-room.data_ptr()) % 128 + 128 + 16 * place
+            run = session.MatRun(mp, want_dims=False, out=room[lo:lo + n])
+            run.launch()
+            got, _, status = run.result()
+            assert status == 0 and np.array_equal(got, want)
+            host = room.cpu().numpy()
+            assert (host[:lo] == 0xCD).all() and (host[lo + n:] == 0xCD).all()
+    finally:
+        fdy.tune_set(fdy.TUNE_MAT_SELF_WGS, default)
+
+
+@pytest.mark.parametrize("n", [1023 * TILE, 1023 * TILE + 1, 2047 * TILE, 2047 * TILE + 1])
+def test_slices_at_the_lines_between_launch_forms(n):
+    """1,024 tiles (with the one that is reserved) are the last that a launch resolves by itself, 2,048 the last
+    whose ends several lanes look for."""
+    from tests.support import session
+    from tests.test_gpu_parity import check_mat
+    from tests.test_gpu_tile_slices import places, problem
+
+    rng = np.random.default_rng(n)
+    r = np.zeros(n // 4, L.RELOC)
+    r["word"], r["region"], r["offset"] = places(rng, n, n // 4), rng.integers(0, 100, len(r)), rng.integers(0, 1 << 40, len(r))
+    ovr = np.zeros(5000, L.OVR32)
+    ovr["byte_off"], ovr["value"] = places(rng, 2 * n, 5000) * 4, rng.integers(0, 1 << 32, len(ovr))
+    mp = problem(n, r, [0, len(r)], 100, rng, ovr=ovr, ovr_off=[0, len(ovr)])
+    mp.new_base = mp.new_base[:1].copy()
+    check_mat(session, orc, mp, tag=f"{n} words")
