@@ -33,6 +33,9 @@
 //                            all; each workgroup of main resolves its own tile first, and
 //                            extra blocks of the same launch write the dimensions and check
 //                            the short lists.  Same results, one launch less.
+// What bounds main is round trips to memory in front of a workgroup's first store, as far as the
+// workgroups of a compute unit (five, by 96 registers; more registers at once than that cost more than
+// they hide) do not cover each other's, and the rate of the stores beyond: hence loads without branches.
 // The order of every list is verified on the way (FDY_ST_BAD_ORDER): the relocation lists
 // where main reads them, the short lists by blocks of the prep launch (or of main).
 #include <mutex>
@@ -504,70 +507,48 @@ __device__ __forceinline__ void prep_patch(const MatParams& p, const PrepView<kO
   p.ws.tile_patch[i] = make_uint2(lo, hi);
 }
 
-// Stage the template tile in LDS: 16-byte global loads from the first even word on.
-__device__ __forceinline__ void stage_tile(u64* buf, const u64* src, u64 src_word, u32 n, u32 tid, bool once) {
-  typedef u64 v2u64 __attribute__((ext_vector_type(2)));
-  const u32 head = (u32)(src_word & 1);  // words before 16-byte alignment (n >= 1 here)
-  const u32 pairs = (n - head) >> 1;
-  if (tid == 0 && head) buf[0] = src[0];
-  if (once) {
-    for (u32 i = tid; i < pairs; i += kMatBlock) {
-      const v2u64 v = __builtin_nontemporal_load(reinterpret_cast<const v2u64*>(src + head + 2 * i));
-      buf[head + 2 * i] = v.x;
-      buf[head + 2 * i + 1] = v.y;
-    }
-  } else {
-    for (u32 i = tid; i < pairs; i += kMatBlock) {
-      const u64x2 v = *reinterpret_cast<const u64x2*>(src + head + 2 * i);
-      buf[head + 2 * i] = v.x;
-      buf[head + 2 * i + 1] = v.y;
-    }
-  }
-  if (tid == 0 && head + 2 * pairs < n) buf[n - 1] = src[n - 1];
+// Buffer accesses: lanes whose offset is not below the descriptor's bytes read zero and store nothing, so that
+// loads and stores need no branches around them and stay together (see mat_main_kernel).
+typedef u32 v4u32 __attribute__((ext_vector_type(4)));
+typedef u32 v2u32 __attribute__((ext_vector_type(2)));
+constexpr int kNonTemporal = 2;            // cache policy of a buffer access
+constexpr u32 kNowhere = 0x80000000u;      // an offset behind every descriptor's end
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const void* base, u32 bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
 }
+__device__ __forceinline__ u64 pair64(u32 lo, u32 hi) { return (u64)lo | (u64)hi << 32; }
 
-// The same in two steps, so that other work can sit between the loads and their use (the
-// self-resolving form of the main kernel searches its slices meanwhile).
+// The template tile on its way to LDS: 16-byte loads from the first even word on.
 constexpr int kTileChunks = kMatBuf / (2 * kMatBlock);
 struct TileRegs {
-  u64x2 v[kTileChunks];
+  v4u32 v[kTileChunks];
   u64 first, last;
 };
-__device__ __forceinline__ void tile_load(TileRegs& r, const u64* src, u64 src_word, u32 n, u32 tid, bool once) {
-  typedef u64 v2u64 __attribute__((ext_vector_type(2)));
+template <int kPolicy>
+__device__ __forceinline__ void tile_load(TileRegs& r, const u64* src, u64 src_word, u32 n, u32 tid) {
   const u32 head = (u32)(src_word & 1);  // words before 16-byte alignment (n >= 1 here)
-  const u32 pairs = (n - head) >> 1;
-  r.first = r.last = 0;
-  if (tid == 0 && head) r.first = src[0];
+  const __amdgpu_buffer_rsrc_t from = buffer(src + head, (n - head) >> 1 << 4);
 #pragma unroll
-  for (int c = 0; c < kTileChunks; ++c) {
-    const u32 i = tid + (u32)c * kMatBlock;
-    r.v[c] = u64x2{0, 0};
-    if (i < pairs) {
-      if (once) {
-        const v2u64 v = __builtin_nontemporal_load(reinterpret_cast<const v2u64*>(src + head + 2 * i));
-        r.v[c].x = v.x;
-        r.v[c].y = v.y;
-      } else {
-        r.v[c] = *reinterpret_cast<const u64x2*>(src + head + 2 * i);
-      }
-    }
-  }
-  if (tid == 0 && head + 2 * pairs < n) r.last = src[n - 1];
+  for (int c = 0; c < kTileChunks; ++c)
+    r.v[c] = __builtin_amdgcn_raw_buffer_load_b128(from, (tid + (u32)c * kMatBlock) * 16, 0, kPolicy);
+  r.first = src[0];
+  r.last = src[n - 1];
 }
 __device__ __forceinline__ void tile_store(u64* buf, const TileRegs& r, u64 src_word, u32 n, u32 tid) {
   const u32 head = (u32)(src_word & 1);
   const u32 pairs = (n - head) >> 1;
-  if (tid == 0 && head) buf[0] = r.first;
 #pragma unroll
   for (int c = 0; c < kTileChunks; ++c) {
     const u32 i = tid + (u32)c * kMatBlock;
     if (i < pairs) {
-      buf[head + 2 * i] = r.v[c].x;
-      buf[head + 2 * i + 1] = r.v[c].y;
+      buf[head + 2 * i] = pair64(r.v[c].x, r.v[c].y);
+      buf[head + 2 * i + 1] = pair64(r.v[c].z, r.v[c].w);
     }
   }
-  if (tid == 0 && head + 2 * pairs < n) buf[n - 1] = r.last;
+  if (tid == 0) {  // what lies outside the pairs, or the same again
+    buf[0] = r.first;
+    buf[n - 1] = r.last;
+  }
 }
 
 // Order of the short lists (overrides, grid overrides, rank patches): every entry against the
@@ -670,6 +651,7 @@ __device__ __forceinline__ void write_dims(const MatParams& p, const PrepView<kO
 // words the previous map's rank patched are given their template values back first.
 constexpr int kMatPre = kMatBuf / kMatBlock;
 constexpr int kMatStore = kMatBuf / (2 * kMatBlock);  // 16-byte chunks per thread
+constexpr u32 kMatMostMaps = 64;                       // base maps of a workgroup: a lane each keeps their patch slices
 constexpr int kMatOvrPre = 2;                          // overrides of the tile a thread keeps in registers
 
 //
@@ -735,7 +717,6 @@ __global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 n_
   __shared__ __align__(16) u64 buf[kMatBuf];
   __shared__ u64 s_buf[kSelf ? 17 : 1];
   __shared__ u32 s_found[kSelf ? 4 + 2 * kSelfMaxGroup : 1];
-  typedef u64 v2u64 __attribute__((ext_vector_type(2)));
   const fdy_mat_desc& d = p.d;
   const u32 j = blockIdx.x, tid = threadIdx.x;
   const u32 m0 = blockIdx.y * p.map_group;
@@ -747,6 +728,7 @@ __global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 n_
   // whoever reads them next.
   const bool once = p.stream_once != 0;
   MatTile ent;
+  TileRegs tile;
   if constexpr (kSelf) {
     if (j >= n_tile_blocks) {  // launch dimensions, then the order of the short lists
       if (blockIdx.y) return;
@@ -789,8 +771,9 @@ __global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 n_
     const u32 rl0 = (u32)d.src_reloc_off[s_graph], rl1 = (u32)d.src_reloc_off[s_graph + 1];
     const u32 ov0 = (u32)d.ovr_off[g], ov1 = (u32)d.ovr_off[g + 1];
     __syncthreads();  // everyone has read the sums; the buffer is free for the tile
-    TileRegs tile;
-    tile_load(tile, d.src_words + src_word, src_word, n_here, tid, once);  // in flight during the searches
+    // in flight during the searches
+    if (once) tile_load<kNonTemporal>(tile, d.src_words + src_word, src_word, n_here, tid);
+    else tile_load<0>(tile, d.src_words + src_word, src_word, n_here, tid);
     {
       // one cooperative search per wave: where the tile's slices of the template's relocation
       // list and of the graph's override list begin and end; then the patch slices of the
@@ -824,10 +807,10 @@ __global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 n_
     ent.out_word = out_word;
     ent.n_words = n_here;
     ent.k0 = k0;
-    ent.reloc_lo = s_found[0];
-    ent.reloc_hi = s_found[1];
-    ent.ovr_lo = s_found[2];
-    ent.ovr_hi = s_found[3];
+    ent.reloc_lo = __builtin_amdgcn_readfirstlane(s_found[0]);
+    ent.reloc_hi = __builtin_amdgcn_readfirstlane(s_found[1]);
+    ent.ovr_lo = __builtin_amdgcn_readfirstlane(s_found[2]);
+    ent.ovr_hi = __builtin_amdgcn_readfirstlane(s_found[3]);
     ent.reloc_seg = rl0;
     if (ent.reloc_hi < ent.reloc_lo) ent.reloc_hi = ent.reloc_lo;  // (a list out of order can cross them)
     if (ent.ovr_hi < ent.ovr_lo) ent.ovr_hi = ent.ovr_lo;
@@ -843,119 +826,146 @@ __global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 n_
   const u32 n = ent.n_words;
   if (n == 0) return;
   const u64* src = d.src_words + ent.src_word;
-  if constexpr (!kSelf) stage_tile(buf, src, ent.src_word, n, tid, once);  // c1
+  const u32 lane = tid & 63;
+  const u32 n_rel = ent.reloc_hi - ent.reloc_lo;  // (at most n, see where entries are made)
+  const u32 n_ovr = ent.ovr_hi > ent.ovr_lo ? ent.ovr_hi - ent.ovr_lo : 0u;  // (a list out of order can cross them)
+  const bool has_ovr = n_ovr != 0;
+  const bool has_patch = d.map_rank != nullptr;
   bool bad = false, disorder = false;
-  u32 rk[kMatPre], rr[kMatPre];
+  // Everything that depends on the tile's entry alone is requested before any of it is looked at, in buffer loads that
+  // need no branches: with a loop that waits for each piece of the template, a wait per register of relocation
+  // entries, one more for the word in front of it, and two for an override, a workgroup spent a dozen round trips in a
+  // row here.  us of main: 512 graphs, 5.9 M words to one map 22.3 -> 15.1, 67 graphs to 8 ranks 54.8 -> 50.2, to 256 maps
+  // (of which most is the fill's 245) 281 -> 251; 67 graphs to one map, tiles resolved here, 10.6 -> 9.1.
+  v4u32 raw[kMatPre];
+  auto request = [&](auto policy) __attribute__((always_inline)) {
+    constexpr int kPolicy = decltype(policy)::value;
+    if constexpr (!kSelf) tile_load<kPolicy>(tile, src, ent.src_word, n, tid);
+    const __amdgpu_buffer_rsrc_t from = buffer(d.relocs + ent.reloc_lo, n_rel * 16);
+#pragma unroll
+    for (int i = 0; i < kMatPre; ++i)
+      if ((u32)i * kMatBlock < n_rel)
+        raw[i] = __builtin_amdgcn_raw_buffer_load_b128(from, (tid + (u32)i * kMatBlock) * 16, 0, kPolicy);
+  };
+  if (once) request(std::integral_constant<int, kNonTemporal>{});
+  else request(std::integral_constant<int, 0>{});
+  // lane i: the word in front of what this wave has of the slice in its registers i
+  u32 in_front = 0;
+  {
+    const u32 q = ent.reloc_lo + lane * kMatBlock + (tid & ~63u);
+    if (lane < (u32)kMatPre && q < ent.reloc_hi && q > ent.reloc_seg) in_front = d.relocs[q - 1].word;
+  }
+  // the tile's overrides (the same for every map), kMatOvrPre per thread; longer lists take the rest from memory
+  v2u32 ov[kMatOvrPre];
+  {
+    const __amdgpu_buffer_rsrc_t from = buffer(d.ovr + ent.ovr_lo, min(n_ovr, (u32)(kMatOvrPre * kMatBlock)) * 8);
+#pragma unroll
+    for (int i = 0; i < kMatOvrPre; ++i)
+      ov[i] = __builtin_amdgcn_raw_buffer_load_b64(from, (tid + (u32)i * kMatBlock) * 8, 0, 0);
+  }
+  // lane i: the slice of map (m0 + i)'s rank inside this tile; empty for a bad rank
+  uint2 slices = make_uint2(0, 0);
+  if (const u32 m = m0 + lane; has_patch && m < m1) {
+    if constexpr (kSelf) {
+      const u32 lo = s_found[4 + 2 * lane], hi = s_found[5 + 2 * lane];
+      slices = make_uint2(lo, lo == 0xffffffffu ? 0u : max(hi, lo));
+    } else {
+      const u32 rk_m = d.map_rank[m];
+      slices = rk_m < d.n_ranks ? p.ws.tile_patch[(u64)j * d.n_ranks + rk_m] : make_uint2(0xffffffffu, 0);
+    }
+  }
+  auto patch_slice = [&](u32 m) __attribute__((always_inline)) {
+    return make_uint2(__builtin_amdgcn_readlane(slices.x, m - m0), __builtin_amdgcn_readlane(slices.y, m - m0));
+  };
+  // this thread's patch entry of a slice (zero behind its end)
+  auto patch_entry = [&](uint2 pr) __attribute__((always_inline)) {
+    const u32 c = pr.x != 0xffffffffu ? min(pr.y - pr.x, (u32)kMatBlock) : 0u;
+    return __builtin_amdgcn_raw_buffer_load_b128(buffer(d.patch + pr.x, c * 16), tid * 16, 0, 0);
+  };
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (!kSelf) tile_store(buf, tile, ent.src_word, n, tid);  // c1
+  u32 rk[kMatPre / 2], rr[kMatPre];  // words of the tile in 16 bits each (all ones: none); regions
   u64 ro[kMatPre];
 #pragma unroll
   for (int i = 0; i < kMatPre; ++i) {
-    const u32 q = ent.reloc_lo + tid + (u32)i * kMatBlock;
-    rk[i] = 0xffffffffu;
+    if (i % 2 == 0) rk[i / 2] = 0xffffffffu;
     rr[i] = 0;
     ro[i] = 0;
-    u32 word_q = 0;
-    if (q < ent.reloc_hi) {
-      u64x2 raw;
-      if (once) {
-        typedef u64 v2u64 __attribute__((ext_vector_type(2)));
-        const v2u64 r = __builtin_nontemporal_load(reinterpret_cast<const v2u64*>(&d.relocs[q]));
-        raw.x = r.x;
-        raw.y = r.y;
-      } else {
-        raw = *reinterpret_cast<const u64x2*>(&d.relocs[q]);
-      }
-      const u32 word = (u32)raw.x, region = (u32)(raw.x >> 32);
-      word_q = word;
-      const u64 k = (u64)word - ent.src_word;
-      if (k < n && region < d.n_alloc) {
-        rk[i] = (u32)k;
-        rr[i] = region;
-        ro[i] = raw.y;
-      } else {
-        bad = true;
-      }
+    if ((u32)i * kMatBlock >= n_rel) continue;  // uniform
+    const u32 q = ent.reloc_lo + tid + (u32)i * kMatBlock;
+    const u32 word = raw[i].x, region = raw[i].y;
+    const u64 k = (u64)word - ent.src_word;
+    const bool mine = q < ent.reloc_hi;
+    if (mine && k < n && region < d.n_alloc) {
+      rk[i / 2] = i % 2 ? (rk[i / 2] & 0xffffu) | (u32)k << 16 : 0xffff0000u | (u32)k;
+      rr[i] = region;
+    } else if (mine) {
+      bad = true;
     }
+    ro[i] = pair64(raw[i].z, raw[i].w);
     // Strictly ascending by word: every entry of the slice against the one before it in the
-    // template's list (the lower lane holds it; a wave's first lane reads it).  The slices of a
+    // template's list (the lower lane holds it; a wave's first lane has read it).  The slices of a
     // template's tiles cover its list, so a list that passes everywhere is in order, which is
     // what the slices themselves (found by binary search) rely on.
-    u32 before = __shfl_up(word_q, 1);
-    if (q < ent.reloc_hi && q > ent.reloc_seg) {
-      if (lane_id() == 0) before = d.relocs[q - 1].word;
-      if (before >= word_q) disorder = true;
-    }
+    u32 before = __shfl_up(word, 1);
+    const u32 of_first = __builtin_amdgcn_readlane(in_front, i);
+    if (lane == 0) before = of_first;
+    if (mine && q > ent.reloc_seg && before >= word) disorder = true;
   }
-  const bool has_ovr = ent.ovr_lo < ent.ovr_hi;
-  const bool has_patch = d.map_rank != nullptr;
-  // What repeats per map is kept off the chain of dependent loads as far as it goes: the
-  // tile's overrides (the same for every map) wait in registers, kMatOvrPre per thread; a map's
-  // patch slice is looked up one map ahead; its entries are requested together with the base-map
-  // gathers, one per thread; and a patched word gets back what it held before the patch (the
-  // template's value, or a rebased or overridden one that the next map's c2 / c3 write again
-  // anyway) from a register instead of from the template in memory.  Lists longer than the
-  // registers hold take their surplus from memory, in the same stage.
-  u32 ov_at[kMatOvrPre], ov_val[kMatOvrPre];
-  if (has_ovr) {
+  u32 ov_at[kMatOvrPre];
 #pragma unroll
-    for (int i = 0; i < kMatOvrPre; ++i) {
-      const u32 q = ent.ovr_lo + tid + (u32)i * kMatBlock;
-      ov_at[i] = 0xffffffffu;
-      ov_val[i] = 0;
-      if (q < ent.ovr_hi) {
-        const fdy_ovr32 o = d.ovr[q];
-        const u64 b = (u64)o.byte_off - (u64)ent.k0 * 8;
-        if ((b >> 3) < n && (b & 3) == 0) {
-          ov_at[i] = (u32)(b >> 2);
-          ov_val[i] = o.value;
-        } else {
-          bad = true;
-        }
-      }
-    }
+  for (int i = 0; i < kMatOvrPre; ++i) {
+    const u64 b = (u64)ov[i].x - (u64)ent.k0 * 8;
+    const bool mine = tid + (u32)i * kMatBlock < n_ovr, fits = (b >> 3) < n && (b & 3) == 0;
+    ov_at[i] = mine && fits ? (u32)(b >> 2) : 0xffffffffu;
+    if (mine && !fits) bad = true;
   }
-  auto patch_slice = [&](u32 m) {  // the slice of map m's rank inside this tile; empty for a bad rank
-    if constexpr (kSelf) {
-      const u32 lo = s_found[4 + 2 * (m - m0)], hi = s_found[5 + 2 * (m - m0)];
-      return make_uint2(lo, lo == 0xffffffffu ? 0u : max(hi, lo));
-    } else {
-      const u32 rk_m = d.map_rank[m];
-      return rk_m < d.n_ranks ? p.ws.tile_patch[(u64)j * d.n_ranks + rk_m] : make_uint2(0xffffffffu, 0);
-    }
+  // The base-map gathers of a map (c2).
+  auto gather = [&](u32 m, u64 (&base)[kMatPre]) __attribute__((always_inline)) {
+    const u64* nb = d.n_alloc ? d.new_base + (u64)m * d.n_alloc : d.src_word_off;  // (no allocations: no entry is valid)
+#pragma unroll
+    for (int i = 0; i < kMatPre; ++i)
+      if ((u32)i * kMatBlock < n_rel) base[i] = nb[rr[i]];
   };
-  // this thread's patch entry of a slice (none: word index all ones)
-  auto patch_entry = [&](uint2 pr) {
-    u64x2 e = u64x2{~0ull, 0};
-    if (pr.x != 0xffffffffu && pr.x + tid < pr.y) e = *reinterpret_cast<const u64x2*>(&d.patch[pr.x + tid]);
-    return e;
+  auto add_offsets = [&](u64 (&base)[kMatPre]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < kMatPre; ++i)
+      if ((u32)i * kMatBlock < n_rel) base[i] += ro[i];
   };
-  uint2 pr_next = has_patch ? patch_slice(m0) : make_uint2(0, 0);
-  u64x2 pe_next = has_patch ? patch_entry(pr_next) : u64x2{~0ull, 0};
+  u64 base[kMatPre];
+#pragma unroll
+  for (int i = 0; i < kMatPre; ++i) base[i] = 0;
+  uint2 pr = make_uint2(0, 0);
+  v4u32 pe = v4u32{0, 0, 0, 0};
+  if (has_patch) {
+    pr = patch_slice(m0);
+    pe = patch_entry(pr);
+  }
+  gather(m0, base);
+  add_offsets(base);
   __syncthreads();
   for (u32 m = m0; m < m1; ++m) {
-    const uint2 pr = pr_next;
-    const u64x2 pe = pe_next;
-    if (has_patch && m + 1 < m1) {
-      pr_next = patch_slice(m + 1);
-      pe_next = patch_entry(pr_next);
-    }
-    // requests of this map: the base-map gathers (c2); its patch entry (c4) came a map ahead
-    const u64* nb = d.new_base + (u64)m * d.n_alloc;
-    u64 base[kMatPre];
-#pragma unroll
-    for (int i = 0; i < kMatPre; ++i) base[i] = rk[i] != 0xffffffffu ? nb[rr[i]] : 0;
-    const bool my_patch = has_patch && (u32)pe.x != 0xffffffffu;
-    if (has_patch && pr.x == 0xffffffffu) bad = true;
+    const bool more = m + 1 < m1;
     // c2: rebase
 #pragma unroll
     for (int i = 0; i < kMatPre; ++i)
-      if (rk[i] != 0xffffffffu) buf[rk[i]] = base[i] + ro[i];
+      if ((u32)i * kMatBlock < n_rel) {
+        asm volatile("" : "+v"(rk[i / 2]));  // (neither address nor comparison is kept across maps)
+        const u32 k = i % 2 ? rk[i / 2] >> 16 : rk[i / 2] & 0xffffu;
+        if (k != 0xffffu) buf[k] = base[i];
+      }
+    // What the next map needs is requested here, ahead of this map's stores, and taken behind them: a wave's
+    // memory operations are waited for in order, and a gather behind the stores would wait for all of them.
+    if (more) gather(m + 1, base);
     // c3: 32-bit overrides
     if (has_ovr) {
       __syncthreads();
       u32* buf32 = reinterpret_cast<u32*>(buf);
 #pragma unroll
-      for (int i = 0; i < kMatOvrPre; ++i)
-        if (ov_at[i] != 0xffffffffu) buf32[ov_at[i]] = ov_val[i];
+      for (int i = 0; i < kMatOvrPre; ++i) {
+        asm volatile("" : "+v"(ov_at[i]));
+        if (ov_at[i] != 0xffffffffu) buf32[ov_at[i]] = ov[i].y;
+      }
       for (u32 q = ent.ovr_lo + tid + kMatOvrPre * kMatBlock; q < ent.ovr_hi; q += kMatBlock) {
         const fdy_ovr32 o = d.ovr[q];
         const u64 b = (u64)o.byte_off - (u64)ent.k0 * 8;
@@ -963,50 +973,54 @@ __global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 n_
         else bad = true;
       }
     }
-    // c4: rank patches; what the patched word held goes to a register for the way back
+    // c4: rank patches; what the patched word held goes to a register for the way back (the template's value, or a
+    // rebased or overridden one that the next map's c2 / c3 write again anyway)
     u32 undo_at = 0xffffffffu;
     u64 undo_val = 0;
-    const bool long_slice = has_patch && pr.x != 0xffffffffu && pr.y - pr.x > (u32)kMatBlock;
+    const u32 n_patch = pr.x != 0xffffffffu ? pr.y - pr.x : 0u;
+    const bool long_slice = n_patch > (u32)kMatBlock;
     if (has_patch) {
+      if (pr.x == 0xffffffffu) bad = true;
       __syncthreads();
-      if (my_patch) {
-        const u64 k = (u64)(u32)pe.x - ent.k0;
+      if (tid < n_patch) {
+        const u64 k = (u64)pe.x - ent.k0;
         if (k < n) {
           undo_at = (u32)k;
           undo_val = buf[k];
-          buf[k] = pe.y;
+          buf[k] = pair64(pe.z, pe.w);
         } else {
           bad = true;
         }
       }
       if (long_slice)
         for (u32 q = pr.x + tid + kMatBlock; q < pr.y; q += kMatBlock) {
-          const u64x2 raw = *reinterpret_cast<const u64x2*>(&d.patch[q]);
-          const u64 k = (u64)(u32)raw.x - ent.k0;
-          if (k < n) buf[k] = raw.y;
+          const u64x2 e = *reinterpret_cast<const u64x2*>(&d.patch[q]);
+          const u64 k = (u64)(u32)e.x - ent.k0;
+          if (k < n) buf[k] = e.y;
           else bad = true;
         }
     }
     __syncthreads();
     // stream the tile out: LDS -> registers, then 16-byte non-temporal stores (the output is
     // written once and not read again here; keeping it out of L2 leaves the templates, lists
-    // and base maps there: with plain stores 256 maps take 407 us, not 287).  The barrier sits between the LDS reads and the global stores so
-    // that the next map's scatter can start while the stores drain.
-    const u64 out_at = (u64)m * d.out_words_per_map + ent.out_word;
-    u64* out = p.out_words + out_at;
+    // and base maps there: with plain stores 256 maps take 407 us, not 287).  The barrier sits between the LDS reads and
+    // the global stores so that the next map's scatter can start while the stores drain.
+    u64* out = p.out_words + (u64)m * d.out_words_per_map + ent.out_word;
     const u32 behind = (u32)((uintptr_t)out >> 3) & (kLine - 1);  // words of the first line in front of the tile
-    const u32 at = 2 * tid - behind;                               // (wraps below the tile's first word)
-    v2u64 v[kMatStore];
+    u32 twice = 2 * tid;
+    asm volatile("" : "+v"(twice));  // (what follows from it is not kept across maps)
+    const u32 at = twice - behind;  // (wraps below the tile's first word)
+    u64 v[2 * kMatStore];
 #pragma unroll
     for (int c = 0; c < kMatStore; ++c) {
-      const u32 i = at + (u32)c * 2 * kMatBlock;
-      if (i < n - 1) {
-        v[c].x = buf[i];
-        v[c].y = buf[i + 1];
-      }
+      const u32 i = at + (u32)c * 2 * kMatBlock, k = i < n - 1 ? i : 0u;
+      v[2 * c] = buf[k];
+      v[2 * c + 1] = buf[k + 1];
     }
-    const u64 first = buf[0], last = buf[n - 1];
-    if (m + 1 < m1) {
+    const uint2 pr_next = more && has_patch ? patch_slice(m + 1) : make_uint2(0, 0);
+    if (more && has_patch) pe = patch_entry(pr_next);
+    const u64 edge = buf[tid == 0 ? 0u : n - 1];  // thread 0: the tile's first word, thread 1: its last
+    if (more) {
       __syncthreads();
       if (has_patch) {
         // the patched words get back what they held (the surplus of a long slice: the template's
@@ -1020,13 +1034,24 @@ __global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 n_
         __syncthreads();
       }
     }
+    const u32 odd_end = (behind + n) & 1;
+    const __amdgpu_buffer_rsrc_t pairs = buffer(out - behind, (behind + n - odd_end) * 8);
+    const __amdgpu_buffer_rsrc_t words = buffer(out - behind, (behind + n) * 8);
 #pragma unroll
     for (int c = 0; c < kMatStore; ++c) {
-      const u32 i = at + (u32)c * 2 * kMatBlock;
-      if (i < n - 1) __builtin_nontemporal_store(v[c], reinterpret_cast<v2u64*>(out + i));
+      const v4u32 o = v4u32{(u32)v[2 * c], (u32)(v[2 * c] >> 32), (u32)v[2 * c + 1], (u32)(v[2 * c + 1] >> 32)};
+      const u32 to = c == 0 && twice < behind ? kNowhere : twice * 8 + (u32)c * (kMatBlock * 16);
+      __builtin_amdgcn_raw_buffer_store_b128(o, pairs, to, 0, kNonTemporal);
     }
-    if (tid == 0 && (behind & 1)) __builtin_nontemporal_store(first, out);
-    if (tid == 0 && ((behind + n) & 1)) __builtin_nontemporal_store(last, out + n - 1);
+    if (tid < 64) {
+      const u32 to = tid == 0 && (behind & 1) ? behind * 8 : tid == 1 && odd_end ? (behind + n - 1) * 8 : kNowhere;
+      __builtin_amdgcn_raw_buffer_store_b64(v2u32{(u32)edge, (u32)(edge >> 32)}, words, to, 0, kNonTemporal);
+    }
+    if (more) {
+      add_offsets(base);
+      pr = pr_next;
+      asm volatile("" : "+v"(pe));
+    }
   }
   if (bad) raise_status(p.d_status, FDY_ST_BAD_INDEX);
   if (disorder) raise_status(p.d_status, FDY_ST_BAD_ORDER);
@@ -1243,12 +1268,19 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
   hipStream_t stream = (hipStream_t)hip_stream;
   (void)hipGetLastError();  // drop any stale error left by earlier, unrelated runtime calls
 
-  // Base maps per workgroup.  Measured on MI355X, groups above 2 (4 with rank patches) lose
-  // more to the coarser tail of the launch than they save in repeated loads.
+  // Base maps per workgroup: two.  A workgroup writes each of its maps in turn, and the further apart the maps that are
+  // written at a time lie, the slower.  us of main with 1 / 2 / 3 / 4 / 8 maps: 67 graphs to 8 ranks 55.6 / 50.2 / 49.3 /
+  // 50.0 / 52.1, 67 graphs to 256 maps 329 / 252 / 279 / 285 / 294.
   u32 mg = (u32)fdy__tune_get(FDY_TUNE_MAT_MAP_GROUP);
-  if (mg == 0) mg = d.map_rank ? 4 : 2;
+  if (mg == 0) mg = 2;
+  if (mg > kMatMostMaps) mg = kMatMostMaps;
   p.map_group = mg < d.n_maps ? mg : d.n_maps;
   const u32 n_groups = (d.n_maps + p.map_group - 1) / p.map_group;
+  // Where many maps are written, unused LDS keeps a compute unit to four workgroups instead of five: fewer places are
+  // written at a time.  us of main with five / four: 772,000 words to 16 maps (8 groups) 20.5 / 21.0, 32 37.0 / 35.2, 64
+  // 69.9 / 65.2, 128 133 / 126, 256 266 / 251; 5.9 M words to 8 maps 65.4 / 66.2, 32 maps 269 / 246; 3.7 M words to 32
+  // maps 157 / 158, with rank patches, whose barriers need the fifth, 175 / 183.
+  const size_t unused_lds = n_groups > 8 && !d.map_rank ? 160 * 1024 / 4 - kMatBuf * 8 - 512 : 0;
   p.stream_once = n_groups == 1 && p.ws.max_tiles >= (u32)fdy__tune_get(FDY_TUNE_MAT_ONCE_TILES) ? 1u : 0u;
   const u32 nb_dims_all = (d_out_dims && d.out_nodes_total) ? (u32)((d.out_nodes_total + 255) / 256) : 0;
   // A launch small enough that all its workgroups run side by side resolves its tiles itself.
@@ -1279,8 +1311,8 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
     FDY_HIP_TRY(hipGetLastError());
   }
   if (p.ws.max_tiles) {
-    launch(FDY_PROF_MAT_MAIN, mat_main_kernel<false>, dim3(p.ws.max_tiles, n_groups), dim3(kMatBlock), 0, stream, p,
-           p.ws.max_tiles, 0u);
+    launch(FDY_PROF_MAT_MAIN, mat_main_kernel<false>, dim3(p.ws.max_tiles, n_groups), dim3(kMatBlock), unused_lds,
+           stream, p, p.ws.max_tiles, 0u);
     FDY_HIP_TRY(hipGetLastError());
   }
   return FDY_OK;

@@ -74,3 +74,36 @@ def test_slices_at_the_lines_between_launch_forms(n):
     mp = problem(n, r, [0, len(r)], 100, rng, ovr=ovr, ovr_off=[0, len(ovr)])
     mp.new_base = mp.new_base[:1].copy()
     check_mat(session, orc, mp, tag=f"{n} words")
+
+
+@pytest.mark.parametrize("ranks", [0, 3])
+@pytest.mark.parametrize("maps,group", [(1, 0), (2, 0), (16, 0), (17, 0), (63, 64), (64, 64), (65, 64), (130, 100)])
+def test_maps_around_the_lines_of_a_group(maps, group, ranks):
+    """Two maps to a workgroup by themselves, 64 at most; from nine groups on fewer workgroups to a compute unit (the
+    others' launches are resolved by the workgroups themselves as well, up to eight maps each)."""
+    import paper_2604_06664_amd as fdy
+    from tests.support import session
+    from tests.test_gpu_parity import check_mat
+    from tests.test_gpu_tile_slices import places, problem
+
+    rng = np.random.default_rng(maps * 5 + ranks)
+    n = 3 * TILE + 77
+    r = np.zeros(n // 2, L.RELOC)  # up to six registers of entries per thread, none in the second tile
+    r["word"] = np.sort(np.r_[places(rng, TILE, 1500), 2 * TILE + places(rng, TILE + 77, len(r) - 1500)])
+    r["region"], r["offset"] = rng.integers(0, 100, len(r)), rng.integers(0, 1 << 40, len(r))
+    ovr = np.zeros(1100, L.OVR32)  # more than two to a thread in one tile
+    ovr["byte_off"], ovr["value"] = places(rng, 2 * TILE, len(ovr)) * 4, rng.integers(0, 1 << 32, len(ovr))
+    lists = []
+    for k in range(ranks):
+        e = np.zeros((5, 600, 0)[k], L.PATCH)  # none, a few, more than one to a thread
+        e["word"], e["value"] = places(rng, TILE, len(e)), rng.integers(0, 1 << 63, len(e))
+        lists.append(e)
+    mp = problem(n, r, [0, len(r)], 100, rng, ranks, ovr=ovr, ovr_off=[0, len(ovr)],
+                 **(dict(map_rank=rng.integers(0, ranks, maps).astype(np.uint32), patch=np.concatenate(lists),
+                         patch_off=np.cumsum([0] + [len(e) for e in lists]).astype(np.uint64)) if ranks else {}))
+    mp.new_base = rng.integers(0, 1 << 63, (maps, 100), dtype=np.uint64)
+    try:
+        fdy.tune_set(fdy.TUNE_MAT_MAP_GROUP, group)
+        check_mat(session, orc, mp, tag=f"{maps} maps by {group}, {ranks} ranks")
+    finally:
+        fdy.tune_set(fdy.TUNE_MAT_MAP_GROUP, 0)
