@@ -12,6 +12,8 @@
 // caller supplies a counter for that (fdy_segment_fingerprint with a prepared table), else by
 // a second, single-workgroup launch; archives of more than 8,192 graphs use a table in the
 // caller's workspace.
+#include <type_traits>
+
 #include "fdy_device.hpp"
 #include "fdy_internal.h"
 
@@ -34,11 +36,17 @@ __device__ __forceinline__ u64 mix(u64 x) {
   return x;
 }
 
-__device__ __forceinline__ u64 node_hash(const fdy_node* n, u32 mask) {
-  // 40-byte record read as five 8-byte words: kernel_id | grid.x,grid.y | grid.z,block.x |
-  // block.y,block.z | blob_len,flags
+// A 40-byte record read as five 8-byte words: kernel_id | grid.x,grid.y | grid.z,block.x |
+// block.y,block.z | blob_len,flags
+struct NodeWords {
+  u64 w[5];
+};
+__device__ __forceinline__ NodeWords load_node(const fdy_node* n) {
   const u64* q = reinterpret_cast<const u64*>(n);
-  u64 w0 = q[0], w1 = q[1], w2 = q[2], w3 = q[3], w4 = q[4];
+  return NodeWords{{q[0], q[1], q[2], q[3], q[4]}};
+}
+__device__ __forceinline__ u64 node_hash(const NodeWords& n, u32 mask) {
+  u64 w0 = n.w[0], w1 = n.w[1], w2 = n.w[2], w3 = n.w[3], w4 = n.w[4];
   const u64 lo = 0x00000000ffffffffull, hi = 0xffffffff00000000ull;
   if (!(mask & FDY_FP_KERNEL_ID)) w0 = 0;
   w1 &= ((mask & FDY_FP_GRID_X) ? lo : 0) | ((mask & FDY_FP_GRID_Y) ? hi : 0);
@@ -258,8 +266,8 @@ struct FpArgs {
   u32* template_id;
   u32* tmpl_graph;
   u32* n_templates;
-  // relocation segmentation in the same launch (null relocs_off: none): block g answers
-  // boundary g, the last block boundary G as well
+  u32 n_graphs;
+  // relocation segmentation in the same launch (null reloc_off: none), by blocks of its own behind the graphs'
   const fdy_reloc* relocs;
   const u64* d_count;
   u64 capacity;
@@ -292,13 +300,33 @@ __device__ __forceinline__ void reset_counters(u32* counter, u32 G) {
   zero(counter + kLastCounter);
 }
 
-// One block per graph.  A launch of one block (an archive of a single graph) also writes the
-// grouping: the graph is its own template.
+// (a2) lower bound of graph b's first word among the relocation words (b = G: the end of the last graph), by a wave.
+// The first boundary is word 0 and the last lies behind every word: both are answered without the search's
+// dependent round trips.
+__device__ __forceinline__ void find_boundary(const FpArgs& a, u32 b) {
+  if (b > a.n_graphs) return;
+  u64 n = *a.d_count;
+  if (n > a.capacity) n = a.capacity;
+  const fdy_reloc* relocs = a.relocs;
+  const u64 target = a.word_off[b];
+  u32 r = 0;
+  if (target != 0 && n != 0)
+    r = b == a.n_graphs && (u64)relocs[n - 1].word < target
+            ? (u32)n
+            : wave_lower_bound([&](u32 i) { return (u64)relocs[i].word; }, 0u, (u32)n, target);
+  if (lane_id() == 0) a.reloc_off[b] = r;
+}
+
+// One block per graph, then blocks with a boundary to each wave.  (Searched by a wave of the graph's own block, a
+// boundary's four round trips stood behind that wave's nodes: us of the launch before / now, 512 graphs of 576 nodes
+// 9.5 / 8.2, 67 of them 6.2 / 5.5, 67 graphs of 2,632 nodes, which the mixes bound, 8.1 / 8.0.)  A launch of one graph also writes the grouping: the
+// graph is its own template.
 __global__ __launch_bounds__(kFpBlock) void fp_key_kernel(FpArgs a) {
   __shared__ Seg s_seg[kFpBlock / 64];
   __shared__ u32 s_last;
   extern __shared__ __align__(16) u32 s_table[];  // grouping in this launch only
-  const u32 g = blockIdx.x, tid = threadIdx.x, G = gridDim.x;
+  const u32 g = blockIdx.x, tid = threadIdx.x, G = a.n_graphs;
+  if (g >= G) return find_boundary(a, (g - G) * (kFpBlock / 64) + (tid >> 6));
   const u64 n0 = a.node_off[g], N = a.node_off[g + 1] - n0;
   // contiguous chunk per thread, in thread order
   const u64 chunk = (N + kFpBlock - 1) / kFpBlock;
@@ -307,16 +335,25 @@ __global__ __launch_bounds__(kFpBlock) void fp_key_kernel(FpArgs a) {
   if (hi > N) hi = N;
   Seg s{0, 1};
   u64 i = lo;
-  for (; i + 4 <= hi; i += 4) {  // four nodes' loads and mixes side by side, folded in order
-    const u64 h0 = node_hash(a.nodes + n0 + i, a.mask), h1 = node_hash(a.nodes + n0 + i + 1, a.mask);
-    const u64 h2 = node_hash(a.nodes + n0 + i + 2, a.mask), h3 = node_hash(a.nodes + n0 + i + 3, a.mask);
-    s.v = (((s.v * kP + h0) * kP + h1) * kP + h2) * kP + h3;
-    s.p *= kP * kP * kP * kP;
-  }
-  for (; i < hi; ++i) {
-    s.v = s.v * kP + node_hash(a.nodes + n0 + i, a.mask);
-    s.p *= kP;
-  }
+  // four nodes' loads and mixes side by side, then two, folded in order
+  auto fold = [&](auto count) __attribute__((always_inline)) {
+    constexpr int N = decltype(count)::value;
+    NodeWords n[N];
+    u64 h[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) n[k] = load_node(a.nodes + n0 + i + k);
+#pragma unroll
+    for (int k = 0; k < N; ++k) h[k] = node_hash(n[k], a.mask);
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      s.v = s.v * kP + h[k];
+      s.p *= kP;
+    }
+    i += N;
+  };
+  while (i + 4 <= hi) fold(std::integral_constant<int, 4>{});
+  if (i + 2 <= hi) fold(std::integral_constant<int, 2>{});
+  if (i < hi) fold(std::integral_constant<int, 1>{});
   // ordered reduction inside the wave: lane l absorbs lane l+d (its right neighbour block)
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
@@ -326,27 +363,6 @@ __global__ __launch_bounds__(kFpBlock) void fp_key_kernel(FpArgs a) {
     if ((lane_id() & (2 * d - 1)) == 0) s = combine(s, r);
   }
   if (lane_id() == 0) s_seg[tid >> 6] = s;
-  if (a.reloc_off) {
-    // (a2) lower bound of this graph's first word among the relocation words, by the block's
-    // last waves while the first one folds the partial hashes
-    const u32 w = tid >> 6;
-    const bool extra = g + 1 == G && w == kFpBlock / 64 - 2;  // boundary G: the end of the last graph
-    if (w == kFpBlock / 64 - 1 || extra) {
-      const u32 b = extra ? G : g;
-      u64 n = *a.d_count;
-      if (n > a.capacity) n = a.capacity;
-      const fdy_reloc* relocs = a.relocs;
-      const u64 target = a.word_off[b];
-      // the first boundary is word 0 and the last lies behind every word: both are answered
-      // without the search's dependent round trips
-      u32 r = 0;
-      if (target != 0 && n != 0)
-        r = (u64)relocs[n - 1].word < target
-                ? (u32)n
-                : wave_lower_bound([&](u32 i) { return (u64)relocs[i].word; }, 0u, (u32)n, target);
-      if (lane_id() == 0) a.reloc_off[b] = r;
-    }
-  }
   __syncthreads();
   Seg t{0, 1};
   if (tid < 64) {  // the waves' segments, again as a tree (one after the other 0.4 us longer)
@@ -426,7 +442,7 @@ extern "C" size_t fdy_fingerprint_workspace_bytes(uint32_t n_graphs) {
   return n_graphs > kLdsGraphs ? (size_t)table_slots(n_graphs) * 4 : 256;
 }
 
-static int fingerprint_launch(FpArgs a, uint32_t n_graphs, uint32_t n_boundaries, void* d_workspace,
+static int fingerprint_launch(FpArgs a, uint32_t n_graphs, void* d_workspace,
                               size_t workspace_bytes, hipStream_t stream) {
   const bool big = n_graphs > kLdsGraphs;
   if (big && (!d_workspace || ((uintptr_t)d_workspace & 255) || workspace_bytes < (size_t)table_slots(n_graphs) * 4))
@@ -442,7 +458,8 @@ static int fingerprint_launch(FpArgs a, uint32_t n_graphs, uint32_t n_boundaries
       if (const int rc = current_device(&dev, &n_cu)) return rc;
       if (const int rc = allow_full_lds(fp_key_kernel, dev, allowed)) return rc;
     }
-    launch(FDY_PROF_FP_KEYS, fp_key_kernel, dim3(n_graphs), dim3(kFpBlock), lds, stream, a);
+    const u32 boundaries = a.reloc_off ? n_graphs + 1 : 0, per_block = kFpBlock / 64;
+    launch(FDY_PROF_FP_KEYS, fp_key_kernel, dim3(n_graphs + (boundaries + per_block - 1) / per_block), dim3(kFpBlock), lds, stream, a);
     FDY_HIP_TRY(hipGetLastError());
     if (n_graphs == 1 || a.counter) return FDY_OK;  // the key kernel has written the grouping too
   }
@@ -489,7 +506,8 @@ extern "C" int fdy_fingerprint(const fdy_node* d_nodes, const uint64_t* d_node_o
   a.template_id = d_template_id;
   a.tmpl_graph = d_tmpl_graph;
   a.n_templates = d_n_templates;
-  return fingerprint_launch(a, n_graphs, 0, d_workspace, workspace_bytes, (hipStream_t)hip_stream);
+  a.n_graphs = n_graphs;
+  return fingerprint_launch(a, n_graphs, d_workspace, workspace_bytes, (hipStream_t)hip_stream);
 }
 
 extern "C" int fdy_segment_fingerprint(const fdy_reloc* d_relocs, const uint64_t* d_count, uint64_t reloc_capacity,
@@ -517,6 +535,7 @@ extern "C" int fdy_segment_fingerprint(const fdy_reloc* d_relocs, const uint64_t
   a.template_id = d_template_id;
   a.tmpl_graph = d_tmpl_graph;
   a.n_templates = d_n_templates;
+  a.n_graphs = n_graphs;
   a.relocs = d_relocs;
   a.d_count = (const u64*)d_count;
   a.capacity = reloc_capacity;
@@ -524,5 +543,5 @@ extern "C" int fdy_segment_fingerprint(const fdy_reloc* d_relocs, const uint64_t
   a.reloc_off = (u64*)d_reloc_off;
   // the prepared table's first 512 bytes hold counters for this call (zero between calls)
   a.counter = d_prepared ? (u32*)((unsigned char*)d_prepared + 64) : nullptr;
-  return fingerprint_launch(a, n_graphs, n_graphs + 1, d_workspace, workspace_bytes, (hipStream_t)hip_stream);
+  return fingerprint_launch(a, n_graphs, d_workspace, workspace_bytes, (hipStream_t)hip_stream);
 }
