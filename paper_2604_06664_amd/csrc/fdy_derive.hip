@@ -120,11 +120,12 @@ struct DerTile {
 };
 __device__ __forceinline__ DerTile tile_at(const DerParams& p, u32 g, u32 s, u64 first_tile, u32 j) {
   DerTile t;
-  const u64 nw = p.word_off[g + 1] - p.word_off[g];
-  t.k0 = ((u64)j - first_tile) * kDerTile;
+  const u64 a = uniform((u64)p.word_off[g]), b = uniform((u64)p.word_off[s]);
+  const u64 nw = uniform((u64)p.word_off[g + 1]) - a;
+  t.k0 = ((u64)j - uniform(first_tile)) * kDerTile;
   t.n = (u32)(nw - t.k0 < (u64)kDerTile ? nw - t.k0 : (u64)kDerTile);
-  t.a = p.words + p.word_off[g] + t.k0;
-  t.b = p.words + p.word_off[s] + t.k0;
+  t.a = p.words + a + t.k0;
+  t.b = p.words + b + t.k0;
   return t;
 }
 
@@ -141,17 +142,22 @@ template <bool kKeep>
 __device__ __forceinline__ u32 compare_tile(const DerTile& t, DerCounts& s_cnt, fdy_ovr32* dst, u64 room, u32 most) {
   static_assert(kDerBlock == 256, "a round's counts are four");
   const u32 tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // words in index order: round i covers words [256 i, 256 i + 256), one per thread
+  // All words are requested before one is looked at, in buffer loads without branches (3.7 M words: 0.5 us of 45.5 per
+  // scan, fingerprint and derivation).  Words in index order: round i covers words [256 i, 256 i + 256), one per thread
   u64 x[kDerRounds], va[kKeep ? kDerRounds : 1];
+  const __amdgpu_buffer_rsrc_t from_a = buffer(t.a, t.n * 8), from_b = buffer(t.b, t.n * 8);
+  v2u32 ra[kDerRounds], rb[kDerRounds];
+  u32 at = tid * 8;
+  asm volatile("" : "+v"(at));  // (the eight offsets are not kept from tile to tile)
 #pragma unroll
   for (int i = 0; i < kDerRounds; ++i) {
-    const u32 k = (u32)i * kDerBlock + tid;
-    u64 a = 0, b = 0;
-    if (k < t.n) {
-      a = t.a[k];
-      b = t.b[k];
-    }
-    x[i] = a ^ b;
+    ra[i] = __builtin_amdgcn_raw_buffer_load_b64(from_a, at + (u32)i * kDerBlock * 8, 0, 0);
+    rb[i] = __builtin_amdgcn_raw_buffer_load_b64(from_b, at + (u32)i * kDerBlock * 8, 0, 0);
+  }
+#pragma unroll
+  for (int i = 0; i < kDerRounds; ++i) {
+    const u64 a = pair64(ra[i].x, ra[i].y);
+    x[i] = a ^ pair64(rb[i].x, rb[i].y);
     if constexpr (kKeep) va[i] = a;
   }
 #pragma unroll
@@ -176,13 +182,13 @@ __device__ __forceinline__ u32 compare_tile(const DerTile& t, DerCounts& s_cnt, 
     if (lo || hi) {
       const u32 k = (u32)i * kDerBlock + tid, byte_off = (u32)((t.k0 + k) * 8);
       const u64 lt = lanemask_lt(), v = kKeep ? va[kKeep ? i : 0] : t.a[k];
-      u32 at = before + __popcll(blo & lt) + __popcll(bhi & lt);
-      at += (wave > 0 ? c.x : 0) + (wave > 1 ? c.y : 0) + (wave > 2 ? c.z : 0);
+      u32 to = before + __popcll(blo & lt) + __popcll(bhi & lt);
+      to += (wave > 0 ? c.x : 0) + (wave > 1 ? c.y : 0) + (wave > 2 ? c.z : 0);
       if (lo) {
-        if (at < room) dst[at] = fdy_ovr32{byte_off, (u32)v};
-        ++at;
+        if (to < room) dst[to] = fdy_ovr32{byte_off, (u32)v};
+        ++to;
       }
-      if (hi && at < room) dst[at] = fdy_ovr32{byte_off + 4, (u32)(v >> 32)};
+      if (hi && to < room) dst[to] = fdy_ovr32{byte_off + 4, (u32)(v >> 32)};
     }
     before += c.x + c.y + c.z + c.w;
   }

@@ -36,6 +36,22 @@ struct __attribute__((aligned(16))) u64x2 {
   u64 x, y;
 };
 
+// Buffer accesses: lanes whose offset is not below the descriptor's bytes read zero and store nothing, so that
+// loads and stores need no branches around them and stay together.  (Accesses lie wholly inside or wholly outside:
+// what one does that straddles the end is not relied upon.)
+typedef u32 v4u32 __attribute__((ext_vector_type(4)));
+typedef u32 v2u32 __attribute__((ext_vector_type(2)));
+constexpr int kNonTemporal = 2;        // cache policy of a buffer access
+constexpr u32 kNowhere = 0x80000000u;  // an offset behind every descriptor's end
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const void* base, u32 bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ u64 pair64(u32 lo, u32 hi) { return (u64)lo | (u64)hi << 32; }
+// A value that is the same in all lanes, where the compiler cannot see that it is (a descriptor made of others is
+// looped over).
+__device__ __forceinline__ u32 uniform(u32 v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ u64 uniform(u64 v) { return pair64(uniform((u32)v), uniform((u32)(v >> 32))); }
+
 __device__ __forceinline__ void raise_status(u32* d_status, u32 bit) {
   if (d_status) atomicOr(d_status, bit);
 }

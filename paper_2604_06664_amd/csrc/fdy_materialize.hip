@@ -507,17 +507,6 @@ __device__ __forceinline__ void prep_patch(const MatParams& p, const PrepView<kO
   p.ws.tile_patch[i] = make_uint2(lo, hi);
 }
 
-// Buffer accesses: lanes whose offset is not below the descriptor's bytes read zero and store nothing, so that
-// loads and stores need no branches around them and stay together (see mat_main_kernel).
-typedef u32 v4u32 __attribute__((ext_vector_type(4)));
-typedef u32 v2u32 __attribute__((ext_vector_type(2)));
-constexpr int kNonTemporal = 2;            // cache policy of a buffer access
-constexpr u32 kNowhere = 0x80000000u;      // an offset behind every descriptor's end
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const void* base, u32 bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
-}
-__device__ __forceinline__ u64 pair64(u32 lo, u32 hi) { return (u64)lo | (u64)hi << 32; }
-
 // The template tile on its way to LDS: 16-byte loads from the first even word on.
 constexpr int kTileChunks = kMatBuf / (2 * kMatBlock);
 struct TileRegs {
@@ -631,10 +620,14 @@ __device__ __forceinline__ void write_dims(const MatParams& p, const PrepView<kO
     a = na;
     b = nb > na ? nb : na;  // (a list out of order can cross them)
   }
-  if (a < a1 && d.govr[a].node == n) {
-    gx = d.govr[a].grid[0];
-    gy = d.govr[a].grid[1];
-    gz = d.govr[a].grid[2];
+  if (a < a1) {
+    u32 node = d.govr[a].node, x = d.govr[a].grid[0], y = d.govr[a].grid[1], z = d.govr[a].grid[2];
+    asm volatile("" : "+v"(node), "+v"(x), "+v"(y), "+v"(z));  // (one round trip, not the grid's behind the node's)
+    if (node == n) {
+      gx = x;
+      gy = y;
+      gz = z;
+    }
   }
   uint2* o = reinterpret_cast<uint2*>(p.out_dims + i * 6);
   o[0] = make_uint2(gx, gy);
@@ -807,10 +800,10 @@ __global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 n_
     ent.out_word = out_word;
     ent.n_words = n_here;
     ent.k0 = k0;
-    ent.reloc_lo = __builtin_amdgcn_readfirstlane(s_found[0]);
-    ent.reloc_hi = __builtin_amdgcn_readfirstlane(s_found[1]);
-    ent.ovr_lo = __builtin_amdgcn_readfirstlane(s_found[2]);
-    ent.ovr_hi = __builtin_amdgcn_readfirstlane(s_found[3]);
+    ent.reloc_lo = uniform(s_found[0]);
+    ent.reloc_hi = uniform(s_found[1]);
+    ent.ovr_lo = uniform(s_found[2]);
+    ent.ovr_hi = uniform(s_found[3]);
     ent.reloc_seg = rl0;
     if (ent.reloc_hi < ent.reloc_lo) ent.reloc_hi = ent.reloc_lo;  // (a list out of order can cross them)
     if (ent.ovr_hi < ent.ovr_lo) ent.ovr_hi = ent.ovr_lo;
