@@ -84,16 +84,39 @@ __host__ __device__ __forceinline__ size_t flat_level_bytes(u32 top_n, u32 bucke
   return (size_t)top_n * 4 + kFlatPad * 4 + ((((((size_t)1) << bucket_log2) + 1) * 2 + 15) & ~(size_t)15);
 }
 
-// P: the launch's parameters (top, bstart, top_n, bucket_log2, table, n_alloc).
-template <u32 kThreads, typename P>
+// P: the launch's parameters (top, bstart, top_n, bucket_log2, table, n_alloc).  kAtOnce: all pieces of up to 16,384
+// keys and their index are requested before the first arrives, and not each behind the one before: 5.0 M words rebased,
+// 16,384 allocations, eight waves 24.4 -> 22.8 us.  (The ordered scan's waves wait for their workgroup's ticket anyway;
+// with it 0.4 us longer on 8,439 words, 1 us of 63 on 12.3 M words with lines, 1 us of 154 shorter with nodes.)
+template <u32 kThreads, bool kAtOnce = true, typename P>
 __host__ __device__ __forceinline__ FlatLevel flat_stage(const P& p, unsigned char* smem, u32 tid) {
   FlatLevel f;
   const u32 n_bst = (1u << p.bucket_log2) + 1;
   const u32 key_vec = p.top_n / 4, bst_vec = (n_bst * 2 + 15) / 16;
   uint4* dst = reinterpret_cast<uint4*>(smem);
   const uint4 *ks = reinterpret_cast<const uint4*>(p.top), *bs = reinterpret_cast<const uint4*>(p.bstart);
-  for (u32 i = tid; i < key_vec; i += kThreads) dst[i] = ks[i];
-  for (u32 i = tid; i < bst_vec; i += kThreads) dst[key_vec + kFlatPad / 4 + i] = bs[i];
+  if constexpr (kAtOnce) {
+    constexpr u32 kBatch = (16384 / 4 + 8192 / 8 + 1 + kThreads - 1) / kThreads;
+    const u32 pieces = key_vec + bst_vec;
+    typedef u32 piece_t __attribute__((ext_vector_type(4)));
+    const piece_t *kp = reinterpret_cast<const piece_t*>(p.top), *bp = reinterpret_cast<const piece_t*>(p.bstart);
+    for (u32 i0 = 0; i0 < pieces; i0 += kBatch * kThreads) {
+      piece_t v[kBatch];
+#pragma unroll
+      for (u32 c = 0; c < kBatch; ++c) {  // (beyond the last piece: the last again, no branch around the load)
+        const u32 at = i0 + c * kThreads + tid, i = at < pieces ? at : pieces - 1;
+        v[c] = *(i < key_vec ? kp + i : bp + (i - key_vec));
+      }
+#pragma unroll
+      for (u32 c = 0; c < kBatch; ++c) {
+        const u32 i = i0 + c * kThreads + tid;
+        if (i < pieces) reinterpret_cast<piece_t*>(dst)[i < key_vec ? i : i + kFlatPad / 4] = v[c];
+      }
+    }
+  } else {
+    for (u32 i = tid; i < key_vec; i += kThreads) dst[i] = ks[i];
+    for (u32 i = tid; i < bst_vec; i += kThreads) dst[key_vec + kFlatPad / 4 + i] = bs[i];
+  }
   if (tid < kFlatPad / 4) dst[key_vec + tid] = make_uint4(~0u, ~0u, ~0u, ~0u);
   f.keys = smem;
   f.bst = reinterpret_cast<const unsigned short*>(smem + (size_t)(key_vec * 16 + kFlatPad * 4));

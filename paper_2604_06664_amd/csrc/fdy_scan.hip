@@ -741,7 +741,7 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_kernel(ScanParams p) {
     s_turn = turn;
     s_next[0] = flat_draw(p, turn, last_draw);
   }
-  const FlatLevel f = flat_stage<kThreads>(p, smem_raw, tid);
+  const FlatLevel f = flat_stage<kThreads, false>(p, smem_raw, tid);
   __syncthreads();
   u32 chunk = s_next[0];
   if (clerk) {
@@ -872,7 +872,7 @@ __global__ __launch_bounds__(kRebaseWaves * 64) void scan_rebase_kernel(ScanPara
     if (blockIdx.x == 0 && tid == 0) raise_status(p.d_status, FDY_ST_BAD_PREPARED);
     return;
   }
-  const FlatLevel f = flat_stage<kW * 64>(p, smem_raw, tid);
+  const FlatLevel f = flat_stage<kW * 64, true>(p, smem_raw, tid);
   unsigned char* qb = smem_raw + flat_level_bytes(p.top_n, p.bucket_log2);
   u64* stash = reinterpret_cast<u64*>(qb) + wave * kSub;
   unsigned short* places = reinterpret_cast<unsigned short*>(qb + (size_t)kW * kSub * 8) + wave * kSub;
