@@ -118,8 +118,14 @@ __device__ __forceinline__ bool graph_sizes(const MatParams& p, u32 g, u64& nw, 
 // of one step requested for all of them before the next step: three round trips (template, source
 // graph, offsets) however many graphs there are.  (One graph after the other they were twelve,
 // half of what the small launches took: prep of the MoE archive's 67 graphs 13.5 -> 11.2 us.)
+// rows: null, or where else a graph's words and lists lie (requested with the offsets).
+struct GraphRow {
+  u64 src_word;
+  u32 rl0, rl1, ov0, ov1;
+};
 template <u32 kPer>
-__device__ __forceinline__ bool graphs_sizes(const MatParams& p, u64 (&nw)[kPer], u64 (&nn)[kPer], u32 (&src)[kPer]) {
+__device__ __forceinline__ bool graphs_sizes(const MatParams& p, u64 (&nw)[kPer], u64 (&nn)[kPer], u32 (&src)[kPer],
+                                             GraphRow* rows = nullptr, u32* tmpl = nullptr) {
   const fdy_mat_desc& d = p.d;
   const u32 G = d.n_graphs, tid = threadIdx.x;
   u32 t[kPer];
@@ -142,7 +148,19 @@ __device__ __forceinline__ bool graphs_sizes(const MatParams& p, u64 (&nw)[kPer]
         n0[i] = d.src_node_off[src[i]];
         n1[i] = d.src_node_off[src[i] + 1];
       }
+      if (rows) {
+        const u32 g = i * 256 + tid;
+        rows[i].rl0 = (u32)d.src_reloc_off[src[i]];
+        rows[i].rl1 = (u32)d.src_reloc_off[src[i] + 1];
+        rows[i].ov0 = (u32)d.ovr_off[g];
+        rows[i].ov1 = (u32)d.ovr_off[g + 1];
+      }
     }
+  }
+#pragma unroll
+  for (u32 i = 0; i < kPer; ++i) {
+    if (rows) rows[i].src_word = w0[i];
+    if (tmpl) tmpl[i] = t[i];
   }
 #pragma unroll
   for (u32 i = 0; i < kPer; ++i) {
@@ -655,31 +673,26 @@ constexpr int kMatOvrPre = 2;                          // overrides of the tile 
 // is mat_prep_tiles_kernel's work without its launch: the model-shaped archives are bound by
 // launches, and an extra 4 us of prologue in workgroups that all run side by side is less than
 // the 10 us the launch costs.
-constexpr u32 kSelfGraphs = 1000;   // offsets of up to 1,024 graphs fit the tile buffer
+constexpr u32 kSelfGraphs = 1000;   // four graphs to a thread; their node offsets fit the tile buffer
 constexpr u32 kSelfMaxGroup = 8;    // most base maps per workgroup in this mode
 
-// Per-graph sums of a kSelf block, in the 16 KiB tile buffer: tile_off u32[1024] | source graph
-// u32[1024] | out_word_off (or, for the blocks that write dimensions, out_node_off) u64[1024].
-// Returns whether the totals match what the caller sized the launch for; `bad` reports an
-// output graph without a valid template.
+// Per-graph sums of a kSelf block that writes dimensions, in the 16 KiB tile buffer: source graph u32[1024] |
+// out_node_off u64[1024].
 struct SelfSums {
-  u32* tile_off;
   u32* src;
   u64* off;
-  u32 n_tiles;
-  bool ok, bad;
+  bool ok;  // the totals match what the caller sized the launch for
 };
-__device__ __forceinline__ SelfSums self_sums(const MatParams& p, u64* buf, u64* s_buf, bool nodes) {
+__device__ __forceinline__ SelfSums self_sums(const MatParams& p, u64* buf, u64* s_buf) {
   SelfSums r;
-  r.tile_off = reinterpret_cast<u32*>(buf);
-  r.src = r.tile_off + 1024;
-  r.off = buf + 1024;
+  r.src = reinterpret_cast<u32*>(buf);
+  r.off = buf + 512;
   const u32 G = p.d.n_graphs, tid = threadIdx.x;
   constexpr u32 kPer = 1024 / kMatBlock;
   static_assert(kMatBlock == 256, "graphs_sizes");
   u64 nw[kPer], nn[kPer], tw = 0, tn = 0, tt = 0;
   u32 from[kPer];
-  const bool bad = graphs_sizes<kPer>(p, nw, nn, from);
+  graphs_sizes<kPer>(p, nw, nn, from);
 #pragma unroll
   for (u32 i = 0; i < kPer; ++i) {
     if (i * kMatBlock >= G) break;  // uniform
@@ -687,22 +700,63 @@ __device__ __forceinline__ SelfSums self_sums(const MatParams& p, u64* buf, u64*
     u64 e[3] = {nw[i], nn[i], (nw[i] + kMatTile - 1) / kMatTile}, sum[3];
     block_excl_scan3(e, sum, s_buf);
     if (g < G) {
-      r.tile_off[g] = (u32)(tt + e[2]);
       r.src[g] = from[i];
-      r.off[g] = nodes ? tn + e[1] : tw + e[0];
+      r.off[g] = tn + e[1];
     }
     tw += sum[0];
     tn += sum[1];
     tt += sum[2];
   }
-  if (tid == 0) {
-    r.tile_off[G] = (u32)tt;
-    r.off[G] = nodes ? tn : tw;
-  }
+  if (tid == 0) r.off[G] = tn;
   r.ok = totals_ok(p, tw, tn, tt);
-  r.n_tiles = r.ok ? (u32)tt : 0u;
-  r.bad = __syncthreads_or(bad);
+  __syncthreads();
   return r;
+}
+
+// Output tile j for a kSelf block that resolves it: the thread that has its graph in hand leaves it in LDS.  (With all
+// graphs' sums in LDS, a search among them and the graph's offsets read behind it 1 us longer.)
+struct SelfTile {
+  u64 src_word, out_word;
+  u32 n, k0, tmpl, last;
+  GraphRow row;
+};
+__device__ __forceinline__ bool self_tile(const MatParams& p, u32 j, u64* s_buf, SelfTile* s_tile, bool reports) {
+  const u32 G = p.d.n_graphs;
+  constexpr u32 kPer = 1024 / kMatBlock;
+  u64 nw[kPer], nn[kPer], tw = 0, tn = 0, tt = 0;
+  u32 from[kPer], tmpl[kPer];
+  GraphRow rows[kPer];
+  const bool bad = graphs_sizes<kPer>(p, nw, nn, from, rows, tmpl);
+#pragma unroll
+  for (u32 i = 0; i < kPer; ++i) {
+    if (i * kMatBlock >= G) break;  // uniform
+    const u64 tiles = (nw[i] + kMatTile - 1) / kMatTile;
+    u64 e[3] = {nw[i], nn[i], tiles}, sum[3];
+    block_excl_scan3(e, sum, s_buf);
+    const u64 k = j - (tt + e[2]);  // (wraps where the graph begins behind tile j)
+    if (k < tiles) {
+      const u64 k0 = k * kMatTile, left = nw[i] - k0;
+      SelfTile q;
+      q.src_word = rows[i].src_word + k0;
+      q.out_word = tw + e[0] + k0;
+      q.n = left < (u64)kMatTile ? (u32)left : (u32)kMatTile;
+      q.k0 = (u32)k0;
+      q.tmpl = tmpl[i];
+      q.last = left <= (u64)kMatTile;
+      q.row = rows[i];
+      *s_tile = q;
+    }
+    tw += sum[0];
+    tn += sum[1];
+    tt += sum[2];
+  }
+  const bool ok = totals_ok(p, tw, tn, tt);
+  if (reports) {  // what the prep launch reports
+    if (bad) raise_status(p.d_status, FDY_ST_BAD_INDEX);
+    if (threadIdx.x == 0 && !ok) raise_status(p.d_status, FDY_ST_BAD_SIZE);
+  }
+  __syncthreads();
+  return ok && j < tt;
 }
 
 template <bool kSelf>
@@ -710,6 +764,7 @@ __global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 n_
   __shared__ __align__(16) u64 buf[kMatBuf];
   __shared__ u64 s_buf[kSelf ? 17 : 1];
   __shared__ u32 s_found[kSelf ? 4 + 2 * kSelfMaxGroup : 1];
+  __shared__ typename std::conditional<kSelf, SelfTile, char>::type s_tile;
   const fdy_mat_desc& d = p.d;
   const u32 j = blockIdx.x, tid = threadIdx.x;
   const u32 m0 = blockIdx.y * p.map_group;
@@ -726,13 +781,13 @@ __global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 n_
     if (j >= n_tile_blocks) {  // launch dimensions, then the order of the short lists
       if (blockIdx.y) return;
       if (j < n_tile_blocks + nb_dims) {
-        const SelfSums q = self_sums(p, buf, s_buf, true);
+        const SelfSums q = self_sums(p, buf, s_buf);
         PrepView<true> v;
         v.src = q.src;
         v.out_word_off = nullptr;
         v.out_node_off = q.off;
         v.tile_off = nullptr;
-        v.n_tiles = q.n_tiles;
+        v.n_tiles = 0;
         v.ok = q.ok ? 1u : 0u;
         write_dims(p, v, (u64)(j - n_tile_blocks) * kMatBlock + tid);
       } else {
@@ -740,30 +795,12 @@ __global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 n_
       }
       return;
     }
-    const SelfSums q = self_sums(p, buf, s_buf, false);
-    if (j == 0 && blockIdx.y == 0) {  // what the prep launch reports
-      if (q.bad) raise_status(p.d_status, FDY_ST_BAD_INDEX);
-      if (tid == 0 && !q.ok) raise_status(p.d_status, FDY_ST_BAD_SIZE);
-    }
-    if (j >= q.n_tiles) return;
-    // the tile's graph: the last one whose first tile is not behind tile j
-    u32 glo = 0, ghi = d.n_graphs;  // answer in [glo, ghi)
-    while (ghi - glo > 1) {
-      const u32 mid = glo + (ghi - glo) / 2;
-      if (q.tile_off[mid] <= j) glo = mid;
-      else ghi = mid;
-    }
-    const u32 g = glo, s_graph = q.src[g];
-    const u32 k0 = (j - q.tile_off[g]) * (u32)kMatTile;
-    const u64 out_word = q.off[g] + k0;
-    const u32 nw = (u32)(q.off[g + 1] - q.off[g]);  // a template stays below 2^32 words
-    const u32 n_here = min(nw - k0, (u32)kMatTile);
-    const bool last = k0 + n_here == nw;
-    const u32 t = d.graph_tmpl[g];
-    const u64 src_word = d.src_word_off[s_graph] + k0;
-    const u32 rl0 = (u32)d.src_reloc_off[s_graph], rl1 = (u32)d.src_reloc_off[s_graph + 1];
-    const u32 ov0 = (u32)d.ovr_off[g], ov1 = (u32)d.ovr_off[g + 1];
-    __syncthreads();  // everyone has read the sums; the buffer is free for the tile
+    if (!self_tile(p, j, s_buf, &s_tile, j == 0 && blockIdx.y == 0)) return;
+    const u32 k0 = uniform(s_tile.k0), n_here = uniform(s_tile.n), t = uniform(s_tile.tmpl);
+    const u64 src_word = uniform(s_tile.src_word), out_word = uniform(s_tile.out_word);
+    const bool last = uniform(s_tile.last);
+    const u32 rl0 = uniform(s_tile.row.rl0), rl1 = uniform(s_tile.row.rl1);
+    const u32 ov0 = uniform(s_tile.row.ov0), ov1 = uniform(s_tile.row.ov1);
     // in flight during the searches
     if (once) tile_load<kNonTemporal>(tile, d.src_words + src_word, src_word, n_here, tid);
     else tile_load<0>(tile, d.src_words + src_word, src_word, n_here, tid);
