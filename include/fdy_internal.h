@@ -25,6 +25,8 @@ enum {
                                  * resolve their tiles themselves (no prep launch); 0: none */
   FDY_TUNE_MAT_ONCE_TILES = 6,  /* a materialization of one map group over at least this many   *
                                  * tiles streams templates and relocation lists past the L2s  */
+  FDY_TUNE_MAT_MOST_BLOCKS = 7, /* most blocks that a materialize launch has for tiles, and    *
+                                 * for patch slices; more take further launches, or rounds    */
   FDY_TUNE_COUNT = 8
 };
 

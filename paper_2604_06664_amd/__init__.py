@@ -28,6 +28,7 @@ TUNE_SCAN_TOP_LOG2, TUNE_SCAN_WG_PER_CU, TUNE_SCAN_SPIN_LIMIT, TUNE_MAT_MAP_GROU
 TUNE_SCAN_SMALL_LOG2 = 4
 TUNE_MAT_SELF_WGS = 5
 TUNE_MAT_ONCE_TILES = 6
+TUNE_MAT_MOST_BLOCKS = 7
 
 
 class FdyError(RuntimeError):

@@ -760,13 +760,13 @@ __device__ __forceinline__ bool self_tile(const MatParams& p, u32 j, u64* s_buf,
 }
 
 template <bool kSelf>
-__global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 n_tile_blocks, u32 nb_dims) {
+__global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 first_tile, u32 n_tile_blocks, u32 nb_dims) {
   __shared__ __align__(16) u64 buf[kMatBuf];
   __shared__ u64 s_buf[kSelf ? 17 : 1];
   __shared__ u32 s_found[kSelf ? 4 + 2 * kSelfMaxGroup : 1];
   __shared__ typename std::conditional<kSelf, SelfTile, char>::type s_tile;
   const fdy_mat_desc& d = p.d;
-  const u32 j = blockIdx.x, tid = threadIdx.x;
+  const u32 j = first_tile + blockIdx.x, tid = threadIdx.x;
   const u32 m0 = blockIdx.y * p.map_group;
   const u32 m1 = min(m0 + p.map_group, d.n_maps);
   // Template words and relocation entries that no other map group reads again, in an archive
@@ -1161,9 +1161,13 @@ __global__ __launch_bounds__(256, 8) void mat_prep_tiles_kernel(MatParams p, u32
     else prep_tiles_block(p, v, b, s_lo);
   } else if (b < nb_tiles + nb_patch) {
     if (group_patch) prep_patch_group(p, v, (b - nb_tiles) * 32 + (threadIdx.x >> 3));
-    else prep_patch(p, v, (u64)(b - nb_tiles) * 256 + threadIdx.x);
-  } else {
-    write_dims(p, v, (u64)(b - nb_tiles - nb_patch) * 256 + threadIdx.x);
+    else
+      for (u64 i = (u64)(b - nb_tiles) * 256; i < (u64)v.n_tiles * p.d.n_ranks; i += (u64)nb_patch * 256)
+        prep_patch(p, v, i + threadIdx.x);
+  } else if (v.ok) {
+    const u32 nb_dims = gridDim.x - kCheckBlocks - nb_tiles - nb_patch;
+    for (u64 i = (u64)(b - nb_tiles - nb_patch) * 256; i < p.d.out_nodes_total; i += (u64)nb_dims * 256)
+      write_dims(p, v, i + threadIdx.x);
   }
 }
 
@@ -1312,13 +1316,17 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
   // maps 157 / 158, with rank patches, whose barriers need the fifth, 175 / 183.
   const size_t unused_lds = n_groups > 8 && !d.map_rank ? 160 * 1024 / 4 - kMatBuf * 8 - 512 : 0;
   p.stream_once = n_groups == 1 && p.ws.max_tiles >= (u32)fdy__tune_get(FDY_TUNE_MAT_ONCE_TILES) ? 1u : 0u;
-  const u32 nb_dims_all = (d_out_dims && d.out_nodes_total) ? (u32)((d.out_nodes_total + 255) / 256) : 0;
+  // A grid of 2^32 threads in one dimension and more is cut to its low 32 bits, and no error says so (16,778,216 blocks
+  // of 256: 1,000 run).  Main goes out in several launches beyond this many tiles, 136 GB of output to a map; the prep
+  // launch's blocks of patch slices and of launch dimensions take several rounds.
+  const u32 most = (u32)fdy__tune_get(FDY_TUNE_MAT_MOST_BLOCKS);
+  const u64 nb_dims_all = (d_out_dims && d.out_nodes_total) ? (d.out_nodes_total + 255) / 256 : 0;
   // A launch small enough that all its workgroups run side by side resolves its tiles itself.
   const u64 self_limit = (u64)fdy__tune_get(FDY_TUNE_MAT_SELF_WGS);
   if (d.n_graphs <= kSelfGraphs && p.map_group <= kSelfMaxGroup && p.ws.max_tiles &&
-      (u64)p.ws.max_tiles * n_groups <= self_limit) {
-    launch(FDY_PROF_MAT_MAIN, mat_main_kernel<true>, dim3(p.ws.max_tiles + nb_dims_all + kCheckBlocks, n_groups),
-           dim3(kMatBlock), 0, stream, p, p.ws.max_tiles, nb_dims_all);
+      (u64)p.ws.max_tiles * n_groups <= self_limit && p.ws.max_tiles <= most && nb_dims_all <= most / 2) {
+    launch(FDY_PROF_MAT_MAIN, mat_main_kernel<true>, dim3(p.ws.max_tiles + (u32)nb_dims_all + kCheckBlocks, n_groups),
+           dim3(kMatBlock), 0, stream, p, 0u, p.ws.max_tiles, (u32)nb_dims_all);
     FDY_HIP_TRY(hipGetLastError());
     return FDY_OK;
   }
@@ -1331,8 +1339,9 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
   const u64 pairs = (u64)p.ws.max_tiles * p.d.n_ranks;  // (0 ranks without a rank map)
   const bool group_tiles = p.ws.max_tiles <= kGroupTiles, group_patch = pairs <= kGroupPairs;
   u32 nb_tiles = group_tiles ? (p.ws.max_tiles + 7) / 8 : (p.ws.max_tiles + kPrepTiles - 1) / kPrepTiles;
-  const u32 nb_patch = (u32)(group_patch ? (pairs + 31) / 32 : (pairs + 255) / 256);
-  const u32 nb_dims = (d_out_dims && d.out_nodes_total) ? (u32)((d.out_nodes_total + 255) / 256) : 0;
+  const u64 nb_patch_all = group_patch ? (pairs + 31) / 32 : (pairs + 255) / 256;
+  const u32 nb_patch = !group_patch && nb_patch_all > most ? most : (u32)nb_patch_all;
+  const u32 nb_dims = nb_dims_all > most / 2 ? (most + 1) / 2 : (u32)nb_dims_all;
   if (own_sums && nb_tiles + nb_patch + nb_dims == 0) nb_tiles = 1;  // someone has to verify the totals
   if (nb_tiles + nb_patch + nb_dims) {
     const u32 nb = nb_tiles + nb_patch + nb_dims + kCheckBlocks;
@@ -1340,10 +1349,12 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
            dim3(256), 0, stream, p, nb_tiles, nb_patch, group_tiles, group_patch);
     FDY_HIP_TRY(hipGetLastError());
   }
-  if (p.ws.max_tiles) {
-    launch(FDY_PROF_MAT_MAIN, mat_main_kernel<false>, dim3(p.ws.max_tiles, n_groups), dim3(kMatBlock), unused_lds,
-           stream, p, p.ws.max_tiles, 0u);
+  for (u32 first = 0; first < p.ws.max_tiles;) {
+    const u32 n = p.ws.max_tiles - first < most ? p.ws.max_tiles - first : most;
+    launch(FDY_PROF_MAT_MAIN, mat_main_kernel<false>, dim3(n, n_groups), dim3(kMatBlock), unused_lds, stream, p, first,
+           0u, 0u);
     FDY_HIP_TRY(hipGetLastError());
+    first += n;
   }
   return FDY_OK;
 }
