@@ -84,34 +84,44 @@ __host__ __device__ __forceinline__ size_t flat_level_bytes(u32 top_n, u32 bucke
   return (size_t)top_n * 4 + kFlatPad * 4 + ((((((size_t)1) << bucket_log2) + 1) * 2 + 15) & ~(size_t)15);
 }
 
-// P: the launch's parameters (top, bstart, top_n, bucket_log2, table, n_alloc).  kAtOnce: all pieces of up to 16,384
-// keys and their index are requested before the first arrives, and not each behind the one before: 5.0 M words rebased,
-// 16,384 allocations, eight waves 24.4 -> 22.8 us.  (The ordered scan's waves wait for their workgroup's ticket anyway;
-// with it 0.4 us longer on 8,439 words, 1 us of 63 on 12.3 M words with lines, 1 us of 154 shorter with nodes.)
-template <u32 kThreads, bool kAtOnce = true, typename P>
-__host__ __device__ __forceinline__ FlatLevel flat_stage(const P& p, unsigned char* smem, u32 tid) {
+// The largest level 0 that is staged (plan_table keeps to it).
+constexpr u32 kMostTopLog2 = 14, kMostBucketLog2 = 13;
+
+// P: the launch's parameters (top, bstart, top_n, bucket_log2, table, n_alloc).  at_once: all pieces of the keys and
+// their index are requested before the first arrives, and not each behind the one before.  For keys that a launch just
+// before has written, which come from afar: us of a rebase with its preparation, piece by piece / at once, 16,384
+// allocations, 100,003 words 11.7 / 10.2, 1.0 M 14.5 / 13.2, 5.0 M 26.9 / 25.4; 1,024 allocations 8.6 / 8.4, 11.4 / 11.3.  Keys of
+// a table prepared before, which the caches hold, are better piece by piece below nodes: 1.0 M words, 4,096 allocations
+// 8.8 / 9.05, 16,384 10.2 / 10.5, 5.0 M and 1,024 17.4 / 18.2; with nodes above the lines it is at once again, 1.0 M
+// words and 10^6 allocations 18.8 / 17.9, 5.0 M and 300,000 34.9 / 34.1.  (The ordered scan's waves wait for their
+// workgroup's ticket anyway: with all at once 0.4 us longer on 8,439 words, 1 us of 63 on 12.3 M words with lines, 1 us
+// of 154 shorter with nodes.)
+template <u32 kThreads, typename P>
+__host__ __device__ __forceinline__ FlatLevel flat_stage(const P& p, unsigned char* smem, u32 tid, bool at_once) {
   FlatLevel f;
   const u32 n_bst = (1u << p.bucket_log2) + 1;
   const u32 key_vec = p.top_n / 4, bst_vec = (n_bst * 2 + 15) / 16;
   uint4* dst = reinterpret_cast<uint4*>(smem);
   const uint4 *ks = reinterpret_cast<const uint4*>(p.top), *bs = reinterpret_cast<const uint4*>(p.bstart);
-  if constexpr (kAtOnce) {
-    constexpr u32 kBatch = (16384 / 4 + 8192 / 8 + 1 + kThreads - 1) / kThreads;
+  if (at_once) {
+    constexpr u32 kMostPieces = (1u << kMostTopLog2) / 4 + (1u << kMostBucketLog2) / 8 + 1;
+    constexpr u32 kBatch = (kMostPieces + kThreads - 1) / kThreads;
     const u32 pieces = key_vec + bst_vec;
     typedef u32 piece_t __attribute__((ext_vector_type(4)));
     const piece_t *kp = reinterpret_cast<const piece_t*>(p.top), *bp = reinterpret_cast<const piece_t*>(p.bstart);
-    for (u32 i0 = 0; i0 < pieces; i0 += kBatch * kThreads) {
-      piece_t v[kBatch];
+    piece_t v[kBatch];
 #pragma unroll
-      for (u32 c = 0; c < kBatch; ++c) {  // (beyond the last piece: the last again, no branch around the load)
-        const u32 at = i0 + c * kThreads + tid, i = at < pieces ? at : pieces - 1;
-        v[c] = *(i < key_vec ? kp + i : bp + (i - key_vec));
-      }
+    for (u32 c = 0; c < kBatch; ++c) {
+      if (c * kThreads >= pieces) break;  // (the same for all threads)
+      // (beyond the last piece: the last again, no branch around the load)
+      const u32 at = c * kThreads + tid, i = at < pieces ? at : pieces - 1;
+      v[c] = *(i < key_vec ? kp + i : bp + (i - key_vec));
+    }
 #pragma unroll
-      for (u32 c = 0; c < kBatch; ++c) {
-        const u32 i = i0 + c * kThreads + tid;
-        if (i < pieces) reinterpret_cast<piece_t*>(dst)[i < key_vec ? i : i + kFlatPad / 4] = v[c];
-      }
+    for (u32 c = 0; c < kBatch; ++c) {
+      if (c * kThreads >= pieces) break;
+      const u32 i = c * kThreads + tid;
+      if (i < pieces) reinterpret_cast<piece_t*>(dst)[i < key_vec ? i : i + kFlatPad / 4] = v[c];
     }
   } else {
     for (u32 i = tid; i < key_vec; i += kThreads) dst[i] = ks[i];

@@ -741,7 +741,7 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_kernel(ScanParams p) {
     s_turn = turn;
     s_next[0] = flat_draw(p, turn, last_draw);
   }
-  const FlatLevel f = flat_stage<kThreads, false>(p, smem_raw, tid);
+  const FlatLevel f = flat_stage<kThreads>(p, smem_raw, tid, false);
   __syncthreads();
   u32 chunk = s_next[0];
   if (clerk) {
@@ -872,7 +872,7 @@ __global__ __launch_bounds__(kRebaseWaves * 64) void scan_rebase_kernel(ScanPara
     if (blockIdx.x == 0 && tid == 0) raise_status(p.d_status, FDY_ST_BAD_PREPARED);
     return;
   }
-  const FlatLevel f = flat_stage<kW * 64, true>(p, smem_raw, tid);
+  const FlatLevel f = flat_stage<kW * 64>(p, smem_raw, tid, kDepth == 2 || !p.prepared);
   unsigned char* qb = smem_raw + flat_level_bytes(p.top_n, p.bucket_log2);
   u64* stash = reinterpret_cast<u64*>(qb) + wave * kSub;
   unsigned short* places = reinterpret_cast<unsigned short*>(qb + (size_t)kW * kSub * 8) + wave * kSub;
@@ -1100,7 +1100,7 @@ struct TablePlan {
 constexpr u32 kRecordSubs = 24576;
 
 bool plan_table(u32 n_alloc, TablePlan* pl) {
-  const u32 top_cap = 1u << fdy__tune_get(FDY_TUNE_SCAN_TOP_LOG2);
+  const u32 top_log2 = (u32)fdy__tune_get(FDY_TUNE_SCAN_TOP_LOG2), top_cap = 1u << (top_log2 < kMostTopLog2 ? top_log2 : kMostTopLog2);
   // smallest sampling stride 2^f0_log2 * 8^levels for which the sampled bases fit the LDS level.
   // Strides between 8 and 64 are left out: the line's first base would have to be found among two
   // or four with a request of its own, and one more whole node costs no more.
@@ -1126,7 +1126,7 @@ bool plan_table(u32 n_alloc, TablePlan* pl) {
   pl->off_top = off;
   off += align256((size_t)pl->top_n * 4);
   pl->bucket_log2 = 0;
-  while ((2u << pl->bucket_log2) <= pl->top_n && pl->bucket_log2 < 13u) ++pl->bucket_log2;
+  while ((2u << pl->bucket_log2) <= pl->top_n && pl->bucket_log2 < kMostBucketLog2) ++pl->bucket_log2;
   pl->off_bst = off;
   off += align256((((size_t)1 << pl->bucket_log2) + 1) * 2);
   // (a buffer for a table serves every smaller one: where a level takes the place of longer arrays, these keep

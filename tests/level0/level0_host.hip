@@ -25,7 +25,7 @@ struct Params {
 
 u32 bucket_log2_for(u32 top_n) {  // as plan_table
   u32 b = 0;
-  while ((2u << b) <= top_n && b < 14u) ++b;
+  while ((2u << b) <= top_n && b < kMostBucketLog2) ++b;
   return b;
 }
 
@@ -60,7 +60,7 @@ struct Built {
     const size_t bytes = flat_level_bytes(p.top_n, p.bucket_log2);
     smem = (unsigned char*)aligned_alloc(16, bytes);
     memset(smem, fill, bytes);
-    for (u32 tid = 0; tid < 64; ++tid) f = flat_stage<64>(p, smem, tid);
+    for (u32 tid = 0; tid < 64; ++tid) f = flat_stage<64>(p, smem, tid, false);
   }
   ~Built() {
     free(table);
@@ -135,6 +135,34 @@ u64 next(u64& s) {  // xorshift64
   s ^= s << 13;
   s ^= s >> 7;
   return s ^= s << 17;
+}
+
+// The two ways to stage a table, and by how many threads, leave the same bytes: sizes around whole batches of pieces,
+// up to the largest level 0.
+template <u32 kThreads>
+void stage_again(const Built& b, int fill, bool at_once) {
+  const size_t bytes = flat_level_bytes(b.p.top_n, b.p.bucket_log2);
+  unsigned char* again = (unsigned char*)aligned_alloc(16, bytes);
+  memset(again, fill, bytes);
+  for (u32 tid = 0; tid < kThreads; ++tid) flat_stage<kThreads>(b.p, again, tid, at_once);
+  ++runs;
+  if (memcmp(again, b.smem, bytes) && ++failures <= 10)
+    printf("%u allocations, %u threads%s: staged differently\n", b.p.n_alloc, kThreads, at_once ? " at once" : "");
+  free(again);
+}
+void staging() {
+  for (u32 n : {1u, 4u, 5u, 64u, 255u, 256u, 257u, 1000u, 1024u, 2048u, 4096u, 8192u, 1u << kMostTopLog2}) {
+    std::vector<fdy_alloc> t(n);
+    for (u32 i = 0; i < n; ++i) t[i] = fdy_alloc{0x7f0000000000ull + ((u64)i << 21), 4096};
+    for (int fill : kFills) {
+      Built b(t, fill);
+      for (bool at_once : {false, true}) {
+        stage_again<64>(b, fill, at_once);
+        stage_again<512>(b, fill, at_once);
+        stage_again<1024>(b, fill, at_once);
+      }
+    }
+  }
 }
 
 // Tables that fdy_table_validate refuses: any order, overlaps, spans that wrap.  What is found is
@@ -226,6 +254,8 @@ int main(int argc, char** argv) {
       }
   } else if (!strcmp(argv[1], "invalid")) {
     invalid_tables();
+  } else if (!strcmp(argv[1], "staging")) {
+    staging();
   } else if (!strcmp(argv[1], "states")) {
     chunk_states();
   } else {

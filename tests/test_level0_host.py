@@ -36,5 +36,9 @@ def test_invalid_tables_stay_in_bounds(program):
     assert ", 0 wrong" in run(program, "invalid")
 
 
+def test_both_ways_to_stage_leave_the_same(program):
+    assert ", 0 wrong" in run(program, "staging")
+
+
 def test_chunk_states_of_launches_in_turn(program):
     assert ", 0 wrong" in run(program, "states")
