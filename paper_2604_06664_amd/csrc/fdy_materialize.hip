@@ -1303,10 +1303,34 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
   (void)hipGetLastError();  // drop any stale error left by earlier, unrelated runtime calls
 
   // Base maps per workgroup: two.  A workgroup writes each of its maps in turn, and the further apart the maps that are
-  // written at a time lie, the slower.  us of main with 1 / 2 / 3 / 4 / 8 maps: 67 graphs to 8 ranks 55.6 / 50.2 / 49.3 /
-  // 50.0 / 52.1, 67 graphs to 256 maps 329 / 252 / 279 / 285 / 294.
+  // written at a time lie, the slower.  us of main with 1 / 2 / 3 / 4 / 8 maps: 67 graphs to 256 maps 329 / 252 / 279 / 285 /
+  // 294; of the call, 1,937 tiles to 8 ranks with 2 / 3 / 4 / 8 60.6 / 60.8 / 61.5 / 65.3.
+  //
+  // With rank patches, whose maps cost a workgroup three barriers each, a larger group is worth it where it lets the
+  // launch resolve its own tiles, up to 4,608 tiles of all maps and sixteen maps: us of the call with two in two launches / more
+  // in one, 449 tiles to 5, 6, 8 ranks 16.3 / 14.5 (four), 17.4 / 15.6 (four), 21.2 / 20.1 (four); 867 to 3, 4, 5 19.1 / 16.7,
+  // 21.6 / 19.2 (four), 23.4 / 22.6 (eight), but to 8 30.3 / 31.8; 267 to 16 maps 22.0 / 20.7 (eight).  Beyond
+  // sixteen maps only once groups of two are more workgroups than run at a time, and four at most: 24 tiles to 96 maps
+  // 14.0 / 16.1, to 160 19.0 / 17.7, 7 to 512 18.4 / 19.9; 160 to 24 20.8 / 19.9, to 32 24.3 / 25.2 (six).  In two launches
+  // four are better up to five maps (1,001 tiles to 3, 4, 5 ranks 20.4 / 19.3, 22.3 / 22.0, 26.6 / 24.7; 1,937 33.1 / 31.5,
+  // 38.9 / 38.2, 44.5 / 43.6; to 8 60.6 / 61.5), and where full groups of four all run at a time (667 to 8 26.3 / 25.5, 449 to
+  // 12 maps 26.2 / 25.3; to 10 22.5 / 23.2).
+  const u64 self_limit = (u64)fdy__tune_get(FDY_TUNE_MAT_SELF_WGS);
+  auto resolves_itself = [&](u32 group) {
+    return d.n_graphs <= kSelfGraphs && group <= kSelfMaxGroup && p.ws.max_tiles &&
+           (u64)p.ws.max_tiles * ((d.n_maps + group - 1) / group) <= self_limit;
+  };
   u32 mg = (u32)fdy__tune_get(FDY_TUNE_MAT_MAP_GROUP);
-  if (mg == 0) mg = 2;
+  if (mg == 0) {
+    mg = 2;
+    if (d.map_rank && !resolves_itself(2)) {
+      const u64 tiles = p.ws.max_tiles - d.n_graphs;  // at least (the entries in reserve aside)
+      const bool few = d.n_maps <= 16, one_launch = (u64)p.ws.max_tiles * d.n_maps <= 4608;
+      if (d.n_maps <= 5 || (few && d.n_maps % 4 == 0 && tiles * (d.n_maps / 4) <= 1200)) mg = 4;
+      if (one_launch && few && resolves_itself(8)) mg = 8;
+      if (one_launch && (few || (d.n_maps <= 256 && tiles * ((d.n_maps + 1) / 2) >= 1280)) && resolves_itself(4)) mg = 4;
+    }
+  }
   if (mg > kMatMostMaps) mg = kMatMostMaps;
   p.map_group = mg < d.n_maps ? mg : d.n_maps;
   const u32 n_groups = (d.n_maps + p.map_group - 1) / p.map_group;
@@ -1322,9 +1346,7 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
   const u32 most = (u32)fdy__tune_get(FDY_TUNE_MAT_MOST_BLOCKS);
   const u64 nb_dims_all = (d_out_dims && d.out_nodes_total) ? (d.out_nodes_total + 255) / 256 : 0;
   // A launch small enough that all its workgroups run side by side resolves its tiles itself.
-  const u64 self_limit = (u64)fdy__tune_get(FDY_TUNE_MAT_SELF_WGS);
-  if (d.n_graphs <= kSelfGraphs && p.map_group <= kSelfMaxGroup && p.ws.max_tiles &&
-      (u64)p.ws.max_tiles * n_groups <= self_limit && p.ws.max_tiles <= most && nb_dims_all <= most / 2) {
+  if (resolves_itself(p.map_group) && p.ws.max_tiles <= most && nb_dims_all <= most / 2) {
     launch(FDY_PROF_MAT_MAIN, mat_main_kernel<true>, dim3(p.ws.max_tiles + (u32)nb_dims_all + kCheckBlocks, n_groups),
            dim3(kMatBlock), 0, stream, p, 0u, p.ws.max_tiles, (u32)nb_dims_all);
     FDY_HIP_TRY(hipGetLastError());

@@ -1,0 +1,50 @@
+"""Rank patches: how many base maps a workgroup takes, and so whether a launch resolves its own tiles, on both sides of
+each line of the rule; results against the oracle."""
+import numpy as np
+import pytest
+
+import oracle as orc
+from synth import layout as L
+
+pytestmark = pytest.mark.gpu
+TILE = 2032
+
+
+# tiles (one more is reserved), maps, launches
+@pytest.mark.parametrize("tiles,maps,launches", [
+    (448, 4, 1), (448, 5, 1), (448, 6, 1), (448, 8, 1), (448, 9, 1), (448, 10, 1), (448, 11, 2),  # 449 * 11 > 4,608
+    (866, 3, 1), (866, 5, 1), (866, 6, 2),
+    (1000, 3, 1), (1023, 4, 1), (1024, 3, 2), (1024, 5, 2), (1024, 6, 2),
+    (266, 16, 1), (270, 17, 2),
+    (159, 23, 1), (159, 32, 2),
+    (23, 84, 1), (23, 96, 2), (23, 112, 1), (40, 62, 2), (40, 64, 1), (10, 256, 1), (10, 257, 2)])
+def test_launches(tiles, maps, launches):
+    import paper_2604_06664_amd as fdy
+    from tests.support import session
+    from tests.test_gpu_tile_slices import places, problem
+
+    rng = np.random.default_rng(tiles * maps)
+    n, ranks = tiles * TILE - 7, 3
+    r = np.zeros(n // 50, L.RELOC)
+    r["word"], r["region"], r["offset"] = places(rng, n, n // 50), rng.integers(0, 60, len(r)), rng.integers(0, 1 << 40, len(r))
+    ovr = np.zeros(300, L.OVR32)
+    ovr["byte_off"], ovr["value"] = places(rng, 2 * n, 300) * 4, rng.integers(0, 1 << 32, 300)
+    lists = []
+    for k in (700, 3, 260):
+        e = np.zeros(k, L.PATCH)
+        e["word"], e["value"] = places(rng, min(n, 4 * TILE), k), rng.integers(0, 1 << 63, k)
+        lists.append(e)
+    mp = problem(n, r, [0, len(r)], 60, rng, ranks, ovr=ovr, ovr_off=[0, len(ovr)],
+                 map_rank=rng.integers(0, ranks, maps).astype(np.uint32), patch=np.concatenate(lists),
+                 patch_off=np.cumsum([0] + [len(e) for e in lists]).astype(np.uint64))
+    mp.new_base = rng.integers(0, 1 << 63, (maps, 60), dtype=np.uint64)
+    run = session.MatRun(mp, want_dims=False)
+    fdy.prof_enable(8)
+    try:
+        run.launch()
+        timed = fdy.prof_read()
+    finally:
+        fdy.prof_enable(0)
+    out, _, status = run.result()
+    assert status == 0 and np.array_equal(out, orc.materialize(mp, False)[0])
+    assert sum(v["n"] for v in timed.values()) == launches, timed
