@@ -675,6 +675,10 @@ constexpr int kMatOvrPre = 2;                          // overrides of the tile 
 // the 10 us the launch costs.
 constexpr u32 kSelfGraphs = 1000;   // four graphs to a thread; their node offsets fit the tile buffer
 constexpr u32 kSelfMaxGroup = 8;    // most base maps per workgroup in this mode
+// Most groups of maps: the blocks for dimensions and list order stand idle in each group but the first, and a prep launch
+// comes to cost less.  us of the call resolving its tiles / with a prep launch: 7 tiles to 128 maps (64 groups) 11.1 / 11.3,
+// 160 11.8 / 11.7, 256 14.8 / 12.4; 8 to 128 11.7 / 11.9, 224 16.1 / 13.0; 5 to 400 17.1 / 12.5; 21 to 90 (45 groups) 12.9 / 13.7.
+constexpr u32 kSelfGroups = 64;
 
 // Per-graph sums of a kSelf block that writes dimensions, in the 16 KiB tile buffer: source graph u32[1024] |
 // out_node_off u64[1024].
@@ -1317,8 +1321,9 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
   // 12 maps 26.2 / 25.3; to 10 22.5 / 23.2).
   const u64 self_limit = (u64)fdy__tune_get(FDY_TUNE_MAT_SELF_WGS);
   auto resolves_itself = [&](u32 group) {
-    return d.n_graphs <= kSelfGraphs && group <= kSelfMaxGroup && p.ws.max_tiles &&
-           (u64)p.ws.max_tiles * ((d.n_maps + group - 1) / group) <= self_limit;
+    const u32 groups = (d.n_maps + group - 1) / group;
+    return d.n_graphs <= kSelfGraphs && group <= kSelfMaxGroup && groups <= kSelfGroups && p.ws.max_tiles &&
+           (u64)p.ws.max_tiles * groups <= self_limit;
   };
   u32 mg = (u32)fdy__tune_get(FDY_TUNE_MAT_MAP_GROUP);
   if (mg == 0) {
@@ -1328,7 +1333,7 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
       const bool few = d.n_maps <= 16, one_launch = (u64)p.ws.max_tiles * d.n_maps <= 4608;
       if (d.n_maps <= 5 || (few && d.n_maps % 4 == 0 && tiles * (d.n_maps / 4) <= 1200)) mg = 4;
       if (one_launch && few && resolves_itself(8)) mg = 8;
-      if (one_launch && (few || (d.n_maps <= 256 && tiles * ((d.n_maps + 1) / 2) >= 1280)) && resolves_itself(4)) mg = 4;
+      if (one_launch && (few || tiles * ((d.n_maps + 1) / 2) >= 1280) && resolves_itself(4)) mg = 4;
     }
   }
   if (mg > kMatMostMaps) mg = kMatMostMaps;

@@ -1,5 +1,5 @@
-"""Rank patches: how many base maps a workgroup takes, and so whether a launch resolves its own tiles, on both sides of
-each line of the rule; results against the oracle."""
+"""How many base maps a workgroup takes under rank patches, and so whether a launch resolves its own tiles, on both sides
+of each line of the rule; and the most groups of maps with which one does.  Results against the oracle."""
 import numpy as np
 import pytest
 
@@ -18,7 +18,7 @@ TILE = 2032
     (266, 16, 1), (270, 17, 2),
     (159, 23, 1), (159, 32, 2),
     (23, 84, 1), (23, 96, 2), (23, 112, 1), (40, 62, 2), (40, 64, 1), (10, 256, 1), (10, 257, 2)])
-def test_launches(tiles, maps, launches):
+def test_launches_under_patches(tiles, maps, launches):
     import paper_2604_06664_amd as fdy
     from tests.support import session
     from tests.test_gpu_tile_slices import places, problem
@@ -37,6 +37,30 @@ def test_launches(tiles, maps, launches):
     mp = problem(n, r, [0, len(r)], 60, rng, ranks, ovr=ovr, ovr_off=[0, len(ovr)],
                  map_rank=rng.integers(0, ranks, maps).astype(np.uint32), patch=np.concatenate(lists),
                  patch_off=np.cumsum([0] + [len(e) for e in lists]).astype(np.uint64))
+    mp.new_base = rng.integers(0, 1 << 63, (maps, 60), dtype=np.uint64)
+    run = session.MatRun(mp, want_dims=False)
+    fdy.prof_enable(8)
+    try:
+        run.launch()
+        timed = fdy.prof_read()
+    finally:
+        fdy.prof_enable(0)
+    out, _, status = run.result()
+    assert status == 0 and np.array_equal(out, orc.materialize(mp, False)[0])
+    assert sum(v["n"] for v in timed.values()) == launches, timed
+
+
+@pytest.mark.parametrize("maps,launches", [(127, 1), (128, 1), (129, 2), (300, 2)])
+def test_launches_by_groups_of_maps(maps, launches):
+    import paper_2604_06664_amd as fdy
+    from tests.support import session
+    from tests.test_gpu_tile_slices import places, problem
+
+    rng = np.random.default_rng(maps)
+    n = 3 * TILE + 100
+    r = np.zeros(n // 3, L.RELOC)
+    r["word"], r["region"], r["offset"] = places(rng, n, n // 3), rng.integers(0, 60, len(r)), rng.integers(0, 1 << 40, len(r))
+    mp = problem(n, r, [0, len(r)], 60, rng)
     mp.new_base = rng.integers(0, 1 << 63, (maps, 60), dtype=np.uint64)
     run = session.MatRun(mp, want_dims=False)
     fdy.prof_enable(8)
