@@ -1342,8 +1342,13 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
   // Where many maps are written, unused LDS keeps a compute unit to four workgroups instead of five: fewer places are
   // written at a time.  us of main with five / four: 772,000 words to 16 maps (8 groups) 20.5 / 21.0, 32 37.0 / 35.2, 64
   // 69.9 / 65.2, 128 133 / 126, 256 266 / 251; 5.9 M words to 8 maps 65.4 / 66.2, 32 maps 269 / 246; 3.7 M words to 32
-  // maps 157 / 158, with rank patches, whose barriers need the fifth, 175 / 183.
-  const size_t unused_lds = n_groups > 8 && !d.map_rank ? 160 * 1024 / 4 - kMatBuf * 8 - 512 : 0;
+  // maps 157 / 158, with rank patches, whose barriers need the fifth, 175 / 183.  Not where five hold all workgroups at
+  // a time and four do not: us of the call with five / four, 16 tiles to 124 maps (992 workgroups) 14.4 / 14.1, 128 (1,024, and
+  // the entries in reserve) 14.4 / 16.2, 152 (1,216) 15.2 / 16.4; 6 tiles to 330 (990) 13.1 / 12.9, 340 (1,020) 13.4 / 14.9, 400
+  // (1,200) 14.2 / 15.8; 72 tiles to 30 (1,080) 15.1 / 16.6, 36 (1,296) 17.6 / 17.1.
+  const u64 n_wgs = (u64)(p.ws.max_tiles - d.n_graphs) * n_groups;  // at least (the entries in reserve aside)
+  const bool four_per_cu = n_groups > 8 && !d.map_rank && (n_wgs <= 1000 || n_wgs > 1230);
+  const size_t unused_lds = four_per_cu ? 160 * 1024 / 4 - kMatBuf * 8 - 512 : 0;
   p.stream_once = n_groups == 1 && p.ws.max_tiles >= (u32)fdy__tune_get(FDY_TUNE_MAT_ONCE_TILES) ? 1u : 0u;
   // A grid of 2^32 threads in one dimension and more is cut to its low 32 bits, and no error says so (16,778,216 blocks
   // of 256: 1,000 run).  Main goes out in several launches beyond this many tiles, 136 GB of output to a map; the prep

@@ -50,14 +50,17 @@ def test_launches_under_patches(tiles, maps, launches):
     assert sum(v["n"] for v in timed.values()) == launches, timed
 
 
-@pytest.mark.parametrize("maps,launches", [(127, 1), (128, 1), (129, 2), (300, 2)])
-def test_launches_by_groups_of_maps(maps, launches):
+# tiles by groups of two maps: 64 groups are the most that resolve their own tiles; between 1,000 and 1,230 workgroups
+# five share a compute unit, on either side four
+@pytest.mark.parametrize("tiles,maps,launches", [(4, 127, 1), (4, 128, 1), (4, 129, 2), (4, 300, 2), (10, 200, 2), (10, 201, 2),
+                                                 (10, 246, 2), (10, 247, 2)])
+def test_launches_by_groups_of_maps(tiles, maps, launches):
     import paper_2604_06664_amd as fdy
     from tests.support import session
     from tests.test_gpu_tile_slices import places, problem
 
     rng = np.random.default_rng(maps)
-    n = 3 * TILE + 100
+    n = tiles * TILE - 100
     r = np.zeros(n // 3, L.RELOC)
     r["word"], r["region"], r["offset"] = places(rng, n, n // 3), rng.integers(0, 60, len(r)), rng.integers(0, 1 << 40, len(r))
     mp = problem(n, r, [0, len(r)], 60, rng)
