@@ -730,22 +730,23 @@ def test_materialize_stage_precedence_and_wrap(hip, oracle):
 
 
 def test_materialize_tile_boundaries_and_empty_graphs(hip, oracle):
-    """Templates of 0, 1, 2047, 2048, 2049 and 5000 words; overrides and patches placed on
-    the first / last word of tiles; outputs referencing templates in scrambled order."""
+    """Templates of 0, 1, 5000 words and lengths around a tile (2032 words) and its buffer (2048); overrides and patches
+    placed on the first / last word of both; outputs referencing templates in scrambled order."""
     rng = np.random.default_rng(11)
     table = small(1).table
-    lens = [0, 1, 2047, 2048, 2049, 5000]
+    lens = [0, 1, 2047, 2048, 2049, 5000, 2031, 2032, 2033]
     from synth.archive import fill_words
 
     words, *_ = fill_words(rng, sum(lens), table, 0.3, 0.05, "mix")
     off = np.concatenate([[0], np.cumsum(lens)]).astype(np.uint64)
     relocs, _ = oracle.scan(words, table)
     roff = oracle.reloc_segment(relocs, off)
-    graph_tmpl = np.array([5, 0, 3, 3, 1, 4, 2, 0, 5], np.uint32)
+    graph_tmpl = np.array([5, 0, 3, 3, 1, 4, 2, 0, 5, 8, 6, 7, 1, 7], np.uint32)
     ovr_l, ovr_off, patch_l, patch_off = [], [0], [], [0]
     for g, t in enumerate(graph_tmpl):
         n = lens[t]
-        spots = sorted({b for b in (0, 4, 8 * 2047, 8 * 2047 + 4, 8 * 2048, 8 * 2048 + 4, 8 * n - 4) if 0 <= b < 8 * n})
+        edges = [8 * k + half for k in (0, 2031, 2032, 2047, 2048, 4063, 4064) for half in (0, 4)]
+        spots = sorted({b for b in (*edges, 8 * n - 4) if 0 <= b < 8 * n})
         o = np.zeros(len(spots), L.OVR32)
         o["byte_off"], o["value"] = spots, rng.integers(0, 2**32, len(spots))
         ovr_l.append(o)
@@ -754,7 +755,7 @@ def test_materialize_tile_boundaries_and_empty_graphs(hip, oracle):
     for t in range(len(lens)):
         for r in range(R):
             n = lens[t]
-            spots = sorted({k for k in (0, 2047, 2048, 4095, 4096, n - 1) if 0 <= k < n}) if r != 1 else []
+            spots = sorted({k for k in (0, 2031, 2032, 2047, 2048, 4063, 4064, 4095, 4096, n - 1) if 0 <= k < n}) if r != 1 else []
             q = np.zeros(len(spots), L.PATCH)
             q["word"], q["value"] = spots, rng.integers(0, 2**63, len(spots))
             patch_l.append(q)
@@ -875,11 +876,11 @@ def test_materialize_lists_out_of_order_are_flagged(hip, oracle):
                         oracle.materialize(bad)
                     _, _, status = hip.materialize(bad)
                     assert status & L.ST_BAD_ORDER, (name, how, status)
-    # a long relocation list whose disorder sits exactly at a tile edge (words 2047 | 2048)
+    # a long relocation list whose disorder sits exactly at a tile edge (words 2031 | 2032)
     ar = small(4)
     mp = problem(oracle, ar)
     rel = mp.relocs.copy()
-    i = int(np.searchsorted(rel["word"], 2048))
+    i = int(np.searchsorted(rel["word"], 2032))
     assert 0 < i < len(rel) - 1
     rel[[i - 1, i]] = rel[[i, i - 1]]
     kw = {n: getattr(mp, n) for n in MatProblem.ARRAYS}

@@ -77,7 +77,7 @@ def test_slices_at_the_lines_between_launch_forms(n):
 
 
 @pytest.mark.parametrize("ranks", [0, 3])
-@pytest.mark.parametrize("maps,group", [(1, 0), (2, 0), (16, 0), (17, 0), (63, 64), (64, 64), (65, 64), (130, 100)])
+@pytest.mark.parametrize("maps,group", [(1, 0), (2, 0), (16, 0), (17, 0), (63, 64), (64, 64), (65, 64), (130, 64)])
 def test_maps_around_the_lines_of_a_group(maps, group, ranks):
     """Two maps to a workgroup by themselves, 64 at most; from nine groups on fewer workgroups to a compute unit (the
     others' launches are resolved by the workgroups themselves as well, up to eight maps each)."""
@@ -103,7 +103,38 @@ def test_maps_around_the_lines_of_a_group(maps, group, ranks):
                          patch_off=np.cumsum([0] + [len(e) for e in lists]).astype(np.uint64)) if ranks else {}))
     mp.new_base = rng.integers(0, 1 << 63, (maps, 100), dtype=np.uint64)
     try:
-        fdy.tune_set(fdy.TUNE_MAT_MAP_GROUP, group)
+        assert fdy.tune_set(fdy.TUNE_MAT_MAP_GROUP, group) == 0
         check_mat(session, orc, mp, tag=f"{maps} maps by {group}, {ranks} ranks")
     finally:
         fdy.tune_set(fdy.TUNE_MAT_MAP_GROUP, 0)
+
+
+@pytest.mark.parametrize("how", ["swap", "equal"])
+def test_disorder_at_every_seam(how):
+    """One relocation for every word of three tiles and a bit: neighbours out of order where one lane, wave, register or
+    tile of the check ends and the next begins (the one in front is read by another lane, or from memory)."""
+    from tests.support import session
+    from tests.test_gpu_tile_slices import problem
+
+    rng = np.random.default_rng(3)
+    n = 3 * TILE + 300
+    r = np.zeros(n, L.RELOC)
+    r["word"] = np.arange(n)
+    new_base = rng.integers(0, 1 << 63, (3, 1), dtype=np.uint64)
+    mp = problem(n, r, [0, n], 1, rng)
+    mp.new_base = new_base
+    out, _, status = session.materialize(mp, want_dims=False)
+    assert status == 0 and np.array_equal(out, np.repeat(new_base, n, axis=1))
+    seams = [1, 2, 63, 64, 65, 128, 192, 255, 257] + [256 * i for i in range(1, 8)] + [256 * i + 64 for i in range(1, 8)] + [TILE - 1]
+    for tile in range(4):
+        for at in [tile * TILE + s for s in seams] + [(tile + 1) * TILE]:
+            if at >= n:
+                continue
+            bad = r.copy()
+            if how == "swap":
+                bad[[at - 1, at]] = bad[[at, at - 1]]
+            else:
+                bad["word"][at] = bad["word"][at - 1]
+            mp = problem(n, bad, [0, n], 1, rng)
+            _, _, status = session.materialize(mp, want_dims=False)
+            assert status & L.ST_BAD_ORDER, at

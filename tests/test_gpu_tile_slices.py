@@ -1,6 +1,6 @@
 """The slices of relocations, overrides and rank patches that fall into an output tile: lists of lengths
-around the steps of a search by four or eight lanes, and tile counts on both sides of the one (2,048)
-from which a thread looks for a tile's ends alone."""
+around the steps of a search by four or eight lanes, and tile counts on both sides of the one (2,048, one of them in
+reserve) from which a thread looks for a tile's ends alone."""
 import numpy as np
 import pytest
 
@@ -9,7 +9,7 @@ from synth import MatProblem
 from synth import layout as L
 
 pytestmark = pytest.mark.gpu
-TILE = 2048
+TILE = 2032  # (test_gpu_mat_routes.py fails where this is not the kernel's)
 
 
 def problem(n, relocs, src_reloc_off, regions, rng, ranks=0, **lists):
@@ -64,7 +64,7 @@ def test_offsets_that_decrease_are_reported(tiles):
     assert status == 0
 
 
-@pytest.mark.parametrize("ranks", [1, 799, 800, 1599])  # 41 tiles: beyond 32,768 pairs a thread searches alone
+@pytest.mark.parametrize("ranks", [1, 799, 800, 1599])  # 41 tiles with the one in reserve: beyond 32,768 pairs (799 and 800 ranks) a thread searches alone
 @pytest.mark.parametrize("entries", [1, 9, 700])
 def test_slices_of_many_ranks(ranks, entries):
     from tests.support import session
