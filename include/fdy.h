@@ -482,12 +482,15 @@ int fdy_materialize(const fdy_mat_desc* h_desc, uint64_t* d_out_words, uint32_t*
  * For callers that cannot allocate device memory where they call from: code that runs under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same operation,
  * same outputs and status bits as fdy_materialize; the tile table and the other per-call
- * tables lie in a fixed array of fdy_materialize_static_limit() bytes (4 MiB) inside the
- * loaded library, one copy per GPU, held until the process ends.  The call allocates and
- * frees nothing.
- *   - FDY_ERR_WORKSPACE: the descriptor needs more than the fixed array holds
- *     (fdy_materialize_workspace_bytes(h_desc) > fdy_materialize_static_limit()); use
- *     fdy_materialize then.
+ * tables lie in a fixed array (6 MiB) inside the loaded library, one copy per GPU, held until
+ * the process ends.  The call allocates and frees nothing.
+ *   - FDY_ERR_WORKSPACE: the descriptor is too large; use fdy_materialize then.  What counts,
+ *     against fdy_materialize_static_limit() (4 MiB), is
+ *       256 + 3*up(8*(n_graphs + 1)) + up(64*t) + up(8*t*n_ranks),
+ *     t = ceil(out_words_per_map / 2048) + n_graphs, up() to whole 256 bytes, n_ranks 0
+ *     without map_rank.  fdy_materialize_workspace_bytes(h_desc) is this or, where many ranks
+ *     need more, up to half as much again: a descriptor whose workspace is at most the limit
+ *     is never refused, one whose workspace is above it may be accepted.
  *   - Every call on a GPU shares that GPU's array: calls that overlap in time on one GPU
  *     (different streams, no ordering between them) race.  Calls on one stream are fine.
  *   - The first call on each device looks the array's address up (with that device current);

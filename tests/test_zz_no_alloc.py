@@ -59,3 +59,38 @@ def test_materialize_static_equals_materialize(oracle):
     assert fdy.fdy_materialize_workspace_bytes(big.desc) > fdy.fdy_materialize_static_limit()
     rc = fdy.fdy_materialize_static(big.desc, big.d_out, big.d_dims, big.d_status, check=False)
     assert rc == fdy.FDY_ERR_WORKSPACE
+
+
+def test_the_most_ranks_that_the_fixed_array_takes(oracle):
+    """A graph of three tiles (with the one in reserve) whose tables are half as large again as what is asked for: the
+    last number of ranks that is accepted fills the array to its last bytes, one more is refused."""
+    import paper_2604_06664_amd as fdy
+    from synth import layout as L
+    from tests.support import session
+    from tests.test_gpu_tile_slices import places, problem
+
+    rng = np.random.default_rng(1)
+    n, ranks = 2040, 262_064  # 256 + 3 * 256 + 256 + 2 * 8 * ranks = 4 MiB
+    old = fdy.tune_set(fdy.TUNE_MAT_SELF_WGS, 0)
+    try:
+        for extra in (0, 1):
+            R = ranks + extra
+            lens = np.zeros(R, np.int64)
+            lens[[0, 1, R // 2, R - 1]] = 7, 300, 9, 500
+            patch = np.zeros(int(lens.sum()), L.PATCH)
+            patch["word"] = np.concatenate([places(rng, n, k) for k in lens[lens > 0]])
+            patch["value"] = rng.integers(0, 1 << 63, len(patch))
+            r = np.zeros(n // 3, L.RELOC)
+            r["word"], r["region"] = np.arange(n // 3) * 3, rng.integers(0, 50, n // 3)
+            mp = problem(n, r, [0, len(r)], 50, rng, R, map_rank=[R - 1, 1, R // 2], patch=patch,
+                         patch_off=np.cumsum(np.r_[0, lens]).astype(np.uint64))
+            run = session.MatRun(mp, want_dims=False)
+            assert fdy.fdy_materialize_workspace_bytes(run.desc) > fdy.fdy_materialize_static_limit()
+            rc = fdy.fdy_materialize_static(run.desc, run.d_out, None, run.d_status, check=False)
+            if extra:
+                assert rc == fdy.FDY_ERR_WORKSPACE
+            else:
+                out, _, status = run.result()
+                assert rc == 0 and status == 0 and np.array_equal(out, oracle.materialize(mp, False)[0])
+    finally:
+        fdy.tune_set(fdy.TUNE_MAT_SELF_WGS, old)
