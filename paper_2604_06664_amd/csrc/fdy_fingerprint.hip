@@ -319,8 +319,10 @@ __device__ __forceinline__ void find_boundary(const FpArgs& a, u32 b) {
 
 // One block per graph, then blocks with a boundary to each wave.  (Searched by a wave of the graph's own block, a
 // boundary's four round trips stood behind that wave's nodes: us of the launch before / now, 512 graphs of 576 nodes
-// 9.5 / 8.2, 67 of them 6.2 / 5.5, 67 graphs of 2,632 nodes, which the mixes bound, 8.1 / 8.0.)  A launch of one graph also writes the grouping: the
-// graph is its own template.
+// 9.5 / 8.2, 67 of them 6.2 / 5.5, 67 graphs of 2,632 nodes, which the mixes bound, 8.1 / 8.0.  Many graphs too, although
+// their blocks are through the chip before the boundaries' begin: of 576 nodes 1,024 12.4 / 10.2, 2,048 26.9 / 23.7, 4,096
+// 50.9 / 44.7, of 64 nodes 8,192 102 / 84, 20,000 82.7 / 65.4, of 16 nodes 2,048 20.7 / 19.9.)  A launch of one graph also
+// writes the grouping: the graph is its own template.
 __global__ __launch_bounds__(kFpBlock) void fp_key_kernel(FpArgs a) {
   __shared__ Seg s_seg[kFpBlock / 64];
   __shared__ u32 s_last;
@@ -337,19 +339,19 @@ __global__ __launch_bounds__(kFpBlock) void fp_key_kernel(FpArgs a) {
   u64 i = lo;
   // four nodes' loads and mixes side by side, then two, folded in order
   auto fold = [&](auto count) __attribute__((always_inline)) {
-    constexpr int N = decltype(count)::value;
-    NodeWords n[N];
-    u64 h[N];
+    constexpr int kCount = decltype(count)::value;
+    NodeWords n[kCount];
+    u64 h[kCount];
 #pragma unroll
-    for (int k = 0; k < N; ++k) n[k] = load_node(a.nodes + n0 + i + k);
+    for (int k = 0; k < kCount; ++k) n[k] = load_node(a.nodes + n0 + i + k);
 #pragma unroll
-    for (int k = 0; k < N; ++k) h[k] = node_hash(n[k], a.mask);
+    for (int k = 0; k < kCount; ++k) h[k] = node_hash(n[k], a.mask);
 #pragma unroll
-    for (int k = 0; k < N; ++k) {
+    for (int k = 0; k < kCount; ++k) {
       s.v = s.v * kP + h[k];
       s.p *= kP;
     }
-    i += N;
+    i += kCount;
   };
   while (i + 4 <= hi) fold(std::integral_constant<int, 4>{});
   if (i + 2 <= hi) fold(std::integral_constant<int, 2>{});
