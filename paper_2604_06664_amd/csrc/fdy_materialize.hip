@@ -52,7 +52,7 @@ constexpr int kMatBuf = 2048;             // words of a workgroup's tile buffer 
 constexpr int kLine = 16;                 // words of a 128-byte memory line
 // Words per tile.  A wave stores whole 128-byte lines, wherever the tile begins: a store that straddles two more lines
 // than it fills cost the launch 3 to 5 % (us per pass: 67 graphs to 8 ranks, 240 MB, 93.6 -> 91.2; to 256 maps, 1.56 GB,
-// 297 -> 287).  A line less than the buffer, so that a tile and the words in front of it in its first line are four
+// 297 -> 287) and wrote partial lines (256 maps 1,571.96 -> 1,559.29 MB by counter, of 1,559.27 of output).  A line less than the buffer, so that a tile and the words in front of it in its first line are four
 // 16-byte stores per thread: with a fifth for a few lanes, or with assignments that wrap, the gain went into registers.
 // The lines that two tiles share are left (without them 88.9 and 285).
 constexpr int kMatTile = kMatBuf - kLine;
@@ -869,8 +869,9 @@ __global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 fi
   // Everything that depends on the tile's entry alone is requested before any of it is looked at, in buffer loads that
   // need no branches: with a loop that waits for each piece of the template, a wait per register of relocation
   // entries, one more for the word in front of it, and two for an override, a workgroup spent a dozen round trips in a
-  // row here.  us of main: 512 graphs, 5.9 M words to one map 22.3 -> 15.1, 67 graphs to 8 ranks 54.8 -> 50.2, to 256 maps
-  // (of which most is the fill's 245) 281 -> 251; 67 graphs to one map, tiles resolved here, 10.6 -> 9.1.
+  // row here.  us of main among the kernels of a load, sixty passes warm, before this and the stores by whole lines / with both:
+  // 512 graphs, 5.9 M words to one map 22.1 / 16.0; 67 graphs to 8 ranks 54.3 / 51.4, to 256 maps (of which most is the
+  // fill's 245) 271 / 257; 67 graphs to one map, tiles resolved here, 9.9 / 8.8.
   v4u32 raw[kMatPre];
   auto request = [&](auto policy) __attribute__((always_inline)) {
     constexpr int kPolicy = decltype(policy)::value;
@@ -1307,8 +1308,8 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
   (void)hipGetLastError();  // drop any stale error left by earlier, unrelated runtime calls
 
   // Base maps per workgroup: two.  A workgroup writes each of its maps in turn, and the further apart the maps that are
-  // written at a time lie, the slower.  us of main with 1 / 2 / 3 / 4 / 8 maps: 67 graphs to 256 maps 329 / 252 / 279 / 285 /
-  // 294; of the call, 1,937 tiles to 8 ranks with 2 / 3 / 4 / 8 60.6 / 60.8 / 61.5 / 65.3.
+  // written at a time lie, the slower.  us of main with 1 / 2 / 3 / 4 / 8 maps, thirty passes warm: 67 graphs to 256 maps 342 / 257
+  // / 285 / 298 / 306, 67 graphs to 8 ranks 57.5 / 51.1 / 50.8 / 52.3 / 56.4.
   //
   // With rank patches, whose maps cost a workgroup three barriers each, a larger group is worth it where it lets the
   // launch resolve its own tiles, up to 4,608 tiles of all maps and sixteen maps: us of the call with two in two launches / more
@@ -1340,9 +1341,10 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
   p.map_group = mg < d.n_maps ? mg : d.n_maps;
   const u32 n_groups = (d.n_maps + p.map_group - 1) / p.map_group;
   // Where many maps are written, unused LDS keeps a compute unit to four workgroups instead of five: fewer places are
-  // written at a time.  us of main with five / four: 772,000 words to 16 maps (8 groups) 20.5 / 21.0, 32 37.0 / 35.2, 64
-  // 69.9 / 65.2, 128 133 / 126, 256 266 / 251; 5.9 M words to 8 maps 65.4 / 66.2, 32 maps 269 / 246; 3.7 M words to 32
-  // maps 157 / 158, with rank patches, whose barriers need the fifth, 175 / 183.  Not where five hold all workgroups at
+  // written at a time.  us of main with five / four, thirty passes warm: 772,000 words to 16 maps (8 groups) 21.0 / 21.3, 32
+  // 37.7 / 36.2, 64 71.0 / 66.6, 128 137 / 129, 256 275 / 256; 5.9 M words to 8 maps 68.4 / 68.5, 32 282 / 260; 3.7 M words to
+  // 32 maps 158 / 160, with rank patches, whose barriers need the fifth, 178 / 185.  (For some 60 passes after idle, while
+  // the card's power settles, all are slower and five are the better: 256 maps 292 / 317.)  Not where five hold all workgroups at
   // a time and four do not: us of the call with five / four, 16 tiles to 124 maps (992 workgroups) 14.4 / 14.1, 128 (1,024, and
   // the entries in reserve) 14.4 / 16.2, 152 (1,216) 15.2 / 16.4; 6 tiles to 330 (990) 13.1 / 12.9, 340 (1,020) 13.4 / 14.9, 400
   // (1,200) 14.2 / 15.8; 72 tiles to 30 (1,080) 15.1 / 16.6, 36 (1,296) 17.6 / 17.1.
