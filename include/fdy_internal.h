@@ -21,7 +21,8 @@ enum {
   FDY_TUNE_SCAN_SPIN_LIMIT = 2, /* polls of a predecessor tile before giving up            */
   FDY_TUNE_MAT_MAP_GROUP = 3,     /* base maps per materialize workgroup, 0 = automatic      */
   FDY_TUNE_SCAN_SMALL_LOG2 = 4, /* only in the answer of fdy_scan_staging_bytes             */
-  FDY_TUNE_MAT_SELF_WGS = 5,    /* materialize launches of up to this many workgroups       *
+  FDY_TUNE_MAT_SELF_WGS = 5,    /* materialize launches of up to this many workgroups (as  *
+                                 * many as tiles of 2,048 words would make)                *
                                  * resolve their tiles themselves (no prep launch); 0: none */
   FDY_TUNE_MAT_ONCE_TILES = 6,  /* a materialization of one map group over at least this many   *
                                  * tiles streams templates and relocation lists past the L2s  */

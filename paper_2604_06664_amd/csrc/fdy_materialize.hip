@@ -1321,10 +1321,13 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
   // 38.9 / 38.2, 44.5 / 43.6; to 8 60.6 / 61.5), and where full groups of four all run at a time (667 to 8 26.3 / 25.5, 449 to
   // 12 maps 26.2 / 25.3; to 10 22.5 / 23.2).
   const u64 self_limit = (u64)fdy__tune_get(FDY_TUNE_MAT_SELF_WGS);
+  // (The line was placed with tiles of 2,048 words: 260,087 words, all relocated, to 16 maps, 129 tiles by eight groups,
+  // 18.5 us in one launch, 25.7 in two; a quarter relocated 14.5 / 16.7.)
+  const u64 line_tiles = (d.out_words_per_map + kMatBuf - 1) / kMatBuf + d.n_graphs;
   auto resolves_itself = [&](u32 group) {
     const u32 groups = (d.n_maps + group - 1) / group;
     return d.n_graphs <= kSelfGraphs && group <= kSelfMaxGroup && groups <= kSelfGroups && p.ws.max_tiles &&
-           (u64)p.ws.max_tiles * groups <= self_limit;
+           line_tiles * groups <= self_limit;
   };
   u32 mg = (u32)fdy__tune_get(FDY_TUNE_MAT_MAP_GROUP);
   if (mg == 0) {
@@ -1359,8 +1362,9 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
   const u64 nb_dims_all = (d_out_dims && d.out_nodes_total) ? (d.out_nodes_total + 255) / 256 : 0;
   // A launch small enough that all its workgroups run side by side resolves its tiles itself.
   if (resolves_itself(p.map_group) && p.ws.max_tiles <= most && nb_dims_all <= most / 2) {
-    launch(FDY_PROF_MAT_MAIN, mat_main_kernel<true>, dim3(p.ws.max_tiles + (u32)nb_dims_all + kCheckBlocks, n_groups),
-           dim3(kMatBlock), 0, stream, p, 0u, p.ws.max_tiles, (u32)nb_dims_all);
+    launch(FDY_PROF_MAT_MAIN, mat_main_kernel<true>,
+           dim3(p.ws.max_tiles + (u32)nb_dims_all + kCheckBlocks, n_groups), dim3(kMatBlock), 0, stream, p, 0u,
+           p.ws.max_tiles, (u32)nb_dims_all);
     FDY_HIP_TRY(hipGetLastError());
     return FDY_OK;
   }

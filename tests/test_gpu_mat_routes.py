@@ -14,7 +14,7 @@ TILE = 2032
 @pytest.mark.parametrize("tiles,maps,launches", [
     (448, 4, 1), (448, 5, 1), (448, 6, 1), (448, 8, 1), (448, 9, 1), (448, 10, 1), (448, 11, 2),  # 449 * 11 > 4,608
     (866, 3, 1), (866, 5, 1), (866, 6, 2),
-    (1000, 3, 1), (1023, 4, 1), (1024, 3, 2), (1024, 5, 2), (1024, 6, 2),
+    (1000, 3, 1), (1031, 4, 1), (1032, 3, 2), (1032, 5, 2), (1032, 6, 2),  # 1,031 * 2,032 words are 1,023 * 2,048
     (266, 16, 1), (270, 17, 2),
     (159, 23, 1), (159, 32, 2),
     (23, 84, 1), (23, 96, 2), (23, 112, 1), (40, 62, 2), (40, 64, 1), (10, 256, 1), (10, 257, 2)])
@@ -75,3 +75,25 @@ def test_launches_by_groups_of_maps(tiles, maps, launches):
     out, _, status = run.result()
     assert status == 0 and np.array_equal(out, orc.materialize(mp, False)[0])
     assert sum(v["n"] for v in timed.values()) == launches, timed
+
+
+@pytest.mark.parametrize("n", [1, TILE - 1, TILE, TILE + 1, 2 * TILE, 2 * TILE + 1])
+def test_tiles_have_2032_words(n):
+    """One launch of main to each tile (and the one in reserve): what the other tests call a tile is one."""
+    import paper_2604_06664_amd as fdy
+    from tests.support import session
+    from tests.test_gpu_tile_slices import problem
+
+    mp = problem(n, np.zeros(0, L.RELOC), [0, 0], 1, np.random.default_rng(n))
+    run = session.MatRun(mp, want_dims=False)
+    old = fdy.tune_set(fdy.TUNE_MAT_MOST_BLOCKS, 1)
+    fdy.prof_enable(8)
+    try:
+        run.launch()
+        timed = fdy.prof_read()
+    finally:
+        fdy.prof_enable(0)
+        fdy.tune_set(fdy.TUNE_MAT_MOST_BLOCKS, old)
+    assert timed["mat_main_kernel"]["n"] == -(-n // TILE) + 1
+    out, _, status = run.result()
+    assert status == 0 and np.array_equal(out, orc.materialize(mp, False)[0])

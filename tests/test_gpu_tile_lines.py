@@ -58,10 +58,10 @@ def test_tiles_at_every_place_of_a_line(place):
         fdy.tune_set(fdy.TUNE_MAT_SELF_WGS, default)
 
 
-@pytest.mark.parametrize("n", [1023 * TILE, 1023 * TILE + 1, 2047 * TILE, 2047 * TILE + 1])
+@pytest.mark.parametrize("n", [1023 * 2048, 1023 * 2048 + 1, 2047 * TILE, 2047 * TILE + 1])
 def test_slices_at_the_lines_between_launch_forms(n):
-    """1,024 tiles (with the one that is reserved) are the last that a launch resolves by itself, 2,048 the last
-    whose ends several lanes look for."""
+    """1,023 times 2,048 words (and a tile in reserve) are the last that a launch resolves by itself, 2,048 tiles with
+    the one in reserve the last whose ends several lanes look for."""
     from tests.support import session
     from tests.test_gpu_parity import check_mat
     from tests.test_gpu_tile_slices import places, problem
