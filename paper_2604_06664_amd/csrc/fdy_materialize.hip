@@ -855,6 +855,7 @@ __global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 fi
     if (rl1 < rl0 && blockIdx.y == 0) raise_status(p.d_status, FDY_ST_BAD_ORDER);  // offsets that decrease: no list
     if (k0 == 0 && ent.reloc_lo != rl0 && blockIdx.y == 0) raise_status(p.d_status, FDY_ST_BAD_INDEX);
   } else {
+    if (j >= p.ws.max_tiles) return;  // (the grid is rounded up)
     ent = p.ws.tiles[j];
   }
   const u32 n = ent.n_words;
@@ -1360,10 +1361,22 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
   // launch's blocks of patch slices and of launch dimensions take several rounds.
   const u32 most = (u32)fdy__tune_get(FDY_TUNE_MAT_MOST_BLOCKS);
   const u64 nb_dims_all = (d_out_dims && d.out_nodes_total) ? (d.out_nodes_total + 255) / 256 : 0;
+  // Workgroups go to the eight XCDs in turn, one group of maps behind the other.  With a whole number of rounds to a group
+  // a tile's groups share an XCD, whose L2 has its template and list then; else that depends on the number of tiles.  us
+  // of the call, as they come / rounded up, graphs that are their own templates, tiles with those in reserve: a quarter of
+  // the words relocated, to 64 maps 41 tiles 17.9 / 17.6, 81 26.7 / 25.2, 129 37.8 / 34.6, to 8 maps 395 23.4 / 19.7, 1,478
+  // 59.5 / 55.2, 2,954 110.6 / 110.6; all relocated, to 64 maps 41 tiles 23.7 / 22.3, 81 40.6 / 32.6, to 16 maps 395 52.1 /
+  // 38.3.  With tiles resolved here 113 to 16 maps 19.9 / 16.2, 81 11.2 / 11.1, but 65 10.3 / 10.9 and 25 9.1 / 11.0: rounds of
+  // tiles and idle blocks come back to the same compute units.  Where graphs share templates, only beyond what
+  // one L2 holds of them: 434 tiles of 16 templates of 40 graphs 19.7 / 19.5, of 4 19.6 / 19.75, 3,391 of 22 of 512 84.4 / 87.0.
+  const u64 distinct = (u64)p.ws.max_tiles * d.n_templates / d.n_graphs;
+  const u32 own_from = d.n_templates < d.n_graphs ? ~0u : resolves_itself(p.map_group) ? 80 : 40;
+  const bool rounds = n_groups > 1 && (distinct >= 160 || p.ws.max_tiles >= own_from);
+  auto whole_rounds = [&](u32 blocks) { return rounds ? (blocks + 7) & ~7u : blocks; };
   // A launch small enough that all its workgroups run side by side resolves its tiles itself.
   if (resolves_itself(p.map_group) && p.ws.max_tiles <= most && nb_dims_all <= most / 2) {
     launch(FDY_PROF_MAT_MAIN, mat_main_kernel<true>,
-           dim3(p.ws.max_tiles + (u32)nb_dims_all + kCheckBlocks, n_groups), dim3(kMatBlock), 0, stream, p, 0u,
+           dim3(whole_rounds(p.ws.max_tiles + (u32)nb_dims_all + kCheckBlocks), n_groups), dim3(kMatBlock), 0, stream, p, 0u,
            p.ws.max_tiles, (u32)nb_dims_all);
     FDY_HIP_TRY(hipGetLastError());
     return FDY_OK;
@@ -1389,8 +1402,8 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
   }
   for (u32 first = 0; first < p.ws.max_tiles;) {
     const u32 n = p.ws.max_tiles - first < most ? p.ws.max_tiles - first : most;
-    launch(FDY_PROF_MAT_MAIN, mat_main_kernel<false>, dim3(n, n_groups), dim3(kMatBlock), unused_lds, stream, p, first,
-           0u, 0u);
+    launch(FDY_PROF_MAT_MAIN, mat_main_kernel<false>, dim3(first + n == p.ws.max_tiles ? whole_rounds(n) : n, n_groups),
+           dim3(kMatBlock), unused_lds, stream, p, first, 0u, 0u);
     FDY_HIP_TRY(hipGetLastError());
     first += n;
   }

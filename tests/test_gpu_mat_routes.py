@@ -77,6 +77,21 @@ def test_launches_by_groups_of_maps(tiles, maps, launches):
     assert sum(v["n"] for v in timed.values()) == launches, timed
 
 
+@pytest.mark.parametrize("tiles", [*range(38, 49), *range(78, 89), 160])  # (and one in reserve)
+def test_launches_of_whole_rounds(tiles):
+    """Rounded up to a multiple of eight from 40 tiles on, and from 80 where the workgroups resolve them."""
+    from tests.support import session
+    from tests.test_gpu_parity import check_mat
+    from tests.test_gpu_tile_slices import places, problem
+
+    rng = np.random.default_rng(tiles)
+    n = tiles * TILE - 1
+    r = np.zeros(n // 20, L.RELOC)
+    r["word"], r["region"], r["offset"] = places(rng, n, n // 20), rng.integers(0, 60, len(r)), rng.integers(0, 1 << 40, len(r))
+    mp = problem(n, r, [0, len(r)], 60, rng)  # three maps, two groups; resolved both ways
+    check_mat(session, orc, mp, tag=f"{tiles} tiles", want_dims=False)
+
+
 @pytest.mark.parametrize("n", [1, TILE - 1, TILE, TILE + 1, 2 * TILE, 2 * TILE + 1])
 def test_tiles_have_2032_words(n):
     """One launch of main to each tile (and the one in reserve): what the other tests call a tile is one."""
