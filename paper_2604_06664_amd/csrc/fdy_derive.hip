@@ -20,6 +20,8 @@
 // MoE archive (3.7 M words, 12,032 entries) took 31 us, 17 now.  Entries are few (a handful per
 // tile), hence the slots: the archive is read once.  Ordering inside a tile comes from ballots
 // over words in index order, low half before high half.
+#include <type_traits>
+
 #include "fdy_device.hpp"
 #include "fdy_internal.h"
 
@@ -142,18 +144,29 @@ template <bool kKeep>
 __device__ __forceinline__ u32 compare_tile(const DerTile& t, DerCounts& s_cnt, fdy_ovr32* dst, u64 room, u32 most) {
   static_assert(kDerBlock == 256, "a round's counts are four");
   const u32 tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // All words are requested before one is looked at, in buffer loads without branches (3.7 M words: 0.5 us of 45.5 per
-  // scan, fingerprint and derivation).  Words in index order: round i covers words [256 i, 256 i + 256), one per thread
+  // All words are requested before one is looked at, in buffer loads without branches, as many rounds of them as a short
+  // tile needs: us of the call, before / eight rounds always / now: 512 graphs of 11,520 words 23.6 / 22.2 / 22.2, 3.7 M words of 67
+  // with scan and fingerprint 45.8 / 45.1 / 45.1; 5,000 graphs of 500 words 41.3 / 45.8 / 40.0, 900 of 700 13.0 / 14.0 / 13.3, of 1,500
+  // 14.0 / 14.35 / 14.0; of 2,047 14.5 / 15.0 / 15.0.  Words in index order: round i covers words [256 i, 256 i + 256), one per thread
   u64 x[kDerRounds], va[kKeep ? kDerRounds : 1];
-  const __amdgpu_buffer_rsrc_t from_a = buffer(t.a, t.n * 8), from_b = buffer(t.b, t.n * 8);
   v2u32 ra[kDerRounds], rb[kDerRounds];
   u32 at = tid * 8;
   asm volatile("" : "+v"(at));  // (the eight offsets are not kept from tile to tile)
+  auto request = [&](auto rounds) __attribute__((always_inline)) {
+    constexpr int kRounds = decltype(rounds)::value;
+    const __amdgpu_buffer_rsrc_t from_a = buffer(t.a, t.n * 8), from_b = buffer(t.b, t.n * 8);
 #pragma unroll
-  for (int i = 0; i < kDerRounds; ++i) {
-    ra[i] = __builtin_amdgcn_raw_buffer_load_b64(from_a, at + (u32)i * kDerBlock * 8, 0, 0);
-    rb[i] = __builtin_amdgcn_raw_buffer_load_b64(from_b, at + (u32)i * kDerBlock * 8, 0, 0);
-  }
+    for (int i = 0; i < kRounds; ++i) {
+      ra[i] = __builtin_amdgcn_raw_buffer_load_b64(from_a, at + (u32)i * kDerBlock * 8, 0, 0);
+      rb[i] = __builtin_amdgcn_raw_buffer_load_b64(from_b, at + (u32)i * kDerBlock * 8, 0, 0);
+    }
+#pragma unroll
+    for (int i = kRounds; i < kDerRounds; ++i) ra[i] = rb[i] = v2u32{0, 0};
+  };
+  if (t.n <= 2 * kDerBlock) request(std::integral_constant<int, 2>{});
+  else if (t.n <= 4 * kDerBlock) request(std::integral_constant<int, 4>{});
+  else if (t.n <= 6 * kDerBlock) request(std::integral_constant<int, 6>{});
+  else request(std::integral_constant<int, kDerRounds>{});
 #pragma unroll
   for (int i = 0; i < kDerRounds; ++i) {
     const u64 a = pair64(ra[i].x, ra[i].y);

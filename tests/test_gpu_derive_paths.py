@@ -54,3 +54,18 @@ def test_many_tiles(graphs):
     parts = [base] + [flipped(rng, base, int(rng.integers(0, 90))) for _ in range(graphs - 1)]
     off = np.cumsum([0] + [len(p) for p in parts]).astype(np.uint64)
     check(np.concatenate(parts), off, [0] * graphs, [0])
+
+
+@pytest.mark.parametrize("n", [1, 256, 511, 512, 513, 1023, 1024, 1025, 1535, 1536, 1537, 2047, 2048, 2049, TILE + 512, TILE + 513])
+def test_lengths_around_whole_requests(n):
+    """A short tile asks for two, four, six or eight rounds of words: differences at both ends of each round."""
+    rng = np.random.default_rng(n)
+    base = rng.integers(0, 1 << 64, n, dtype=np.uint64)
+    at = sorted({k for e in range(0, n + 1, 256) for k in (e - 1, e) if 0 <= k < n} | {n - 1})
+    few, all_differ = base.copy(), base ^ np.uint64(0x100000001)
+    few[at[:15] + at[-1:]] ^= np.uint64(1 << 40)
+    ends = base.copy()
+    ends[at] ^= np.uint64(0x8000000000000001)
+    parts = [base, few, ends, all_differ, base]
+    off = np.cumsum([0] + [len(p) for p in parts]).astype(np.uint64)
+    check(np.concatenate(parts), off, [0] * len(parts), [0])
