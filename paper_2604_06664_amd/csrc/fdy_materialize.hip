@@ -56,6 +56,12 @@ constexpr int kLine = 16;                 // words of a 128-byte memory line
 // 16-byte stores per thread: with a fifth for a few lanes, or with assignments that wrap, the gain went into registers.
 // The lines that two tiles share are left (without them 88.9 and 285).
 constexpr int kMatTile = kMatBuf - kLine;
+// Tiles of a graph, and the words of one that has `left` words before its graph's end: a graph's last tile fills the
+// buffer before another is begun.  (Graphs of 2,033 to 2,048 words as two tiles: 2,000 of 2,040 to 8 maps 62 -> 89 us.)
+__device__ __forceinline__ u64 tiles_of(u64 nw) {
+  return nw > (u64)kMatBuf ? (nw - kLine + kMatTile - 1) / kMatTile : (u64)(nw != 0);
+}
+__device__ __forceinline__ u32 tile_words(u64 left) { return left <= (u64)kMatBuf ? (u32)left : (u32)kMatTile; }
 
 struct __attribute__((aligned(16))) MatTile {  // 48 B
   u64 src_word;  // index into src_words of the tile's first word
@@ -226,7 +232,7 @@ __global__ __launch_bounds__(1024) void mat_prep_graphs_kernel(MatParams p) {
     const u32 g = g0 + threadIdx.x;
     u64 nw = 0, nn = 0;
     if (g < G && !graph_sizes(p, g, nw, nn)) bad = true;
-    const u64 nt = (nw + kMatTile - 1) / kMatTile;
+    const u64 nt = tiles_of(nw);
     u64 tw, tn, tt;
     const u64 ew = block_excl_scan(nw, s_buf, tw);
     const u64 en = block_excl_scan(nn, s_buf, tn);
@@ -356,7 +362,7 @@ __device__ __forceinline__ TileGeom tile_geometry(const MatParams& p, const Prep
   const u64 w0 = d.src_word_off[q.s];
   const u64 nw = d.src_word_off[q.s + 1] - w0;
   q.k0 = ((u64)j - v.tile_off[q.g]) * kMatTile;
-  q.n = (u32)((nw - q.k0) < (u64)kMatTile ? (nw - q.k0) : (u64)kMatTile);
+  q.n = tile_words(nw - q.k0);
   q.src_word = w0 + q.k0;
   q.last = q.k0 + q.n == nw;
   return q;
@@ -701,7 +707,7 @@ __device__ __forceinline__ SelfSums self_sums(const MatParams& p, u64* buf, u64*
   for (u32 i = 0; i < kPer; ++i) {
     if (i * kMatBlock >= G) break;  // uniform
     const u32 g = i * kMatBlock + tid;
-    u64 e[3] = {nw[i], nn[i], (nw[i] + kMatTile - 1) / kMatTile}, sum[3];
+    u64 e[3] = {nw[i], nn[i], tiles_of(nw[i])}, sum[3];
     block_excl_scan3(e, sum, s_buf);
     if (g < G) {
       r.src[g] = from[i];
@@ -734,7 +740,7 @@ __device__ __forceinline__ bool self_tile(const MatParams& p, u32 j, u64* s_buf,
 #pragma unroll
   for (u32 i = 0; i < kPer; ++i) {
     if (i * kMatBlock >= G) break;  // uniform
-    const u64 tiles = (nw[i] + kMatTile - 1) / kMatTile;
+    const u64 tiles = tiles_of(nw[i]);
     u64 e[3] = {nw[i], nn[i], tiles}, sum[3];
     block_excl_scan3(e, sum, s_buf);
     const u64 k = j - (tt + e[2]);  // (wraps where the graph begins behind tile j)
@@ -743,10 +749,10 @@ __device__ __forceinline__ bool self_tile(const MatParams& p, u32 j, u64* s_buf,
       SelfTile q;
       q.src_word = rows[i].src_word + k0;
       q.out_word = tw + e[0] + k0;
-      q.n = left < (u64)kMatTile ? (u32)left : (u32)kMatTile;
+      q.n = tile_words(left);
       q.k0 = (u32)k0;
       q.tmpl = tmpl[i];
-      q.last = left <= (u64)kMatTile;
+      q.last = left <= (u64)kMatBuf;
       q.row = rows[i];
       *s_tile = q;
     }
@@ -1043,6 +1049,10 @@ __global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 fi
     // the global stores so that the next map's scatter can start while the stores drain.
     u64* out = p.out_words + (u64)m * d.out_words_per_map + ent.out_word;
     const u32 behind = (u32)((uintptr_t)out >> 3) & (kLine - 1);  // words of the first line in front of the tile
+    if (behind + n > (u32)kMatBuf) {  // (the same for all; seldom) what lies behind the fourth store
+      const u32 k = kMatBuf - behind + tid;
+      if (k < n) __builtin_nontemporal_store(buf[k], out + k);
+    }
     u32 twice = 2 * tid;
     asm volatile("" : "+v"(twice));  // (what follows from it is not kept across maps)
     const u32 at = twice - behind;  // (wraps below the tile's first word)
@@ -1127,7 +1137,7 @@ __global__ __launch_bounds__(256, 8) void mat_prep_tiles_kernel(MatParams p, u32
     for (u32 i = 0; i < kPer; ++i) {
       if (i * 256 >= G) break;  // uniform
       const u32 g = i * 256 + tid;
-      u64 e[3] = {nw[i], nn[i], (nw[i] + kMatTile - 1) / kMatTile}, sum[3];
+      u64 e[3] = {nw[i], nn[i], tiles_of(nw[i])}, sum[3];
       block_excl_scan3(e, sum, s_buf);
       if (g < G) {
         s_off[g] = nodes ? tn + e[1] : tw + e[0];

@@ -17,7 +17,8 @@ def test_tiles_at_every_place_of_a_line(place):
     from tests.support import session
 
     rng = np.random.default_rng(place)
-    lens = [1, 2, 15, 16, 17, TILE - 1, TILE, TILE + 1, TILE + 16, 2 * TILE, 2 * TILE + 1, 0]
+    lens = [1, 2, 15, 16, 17, TILE - 1, TILE, TILE + 1, TILE + 15, TILE + 16, TILE + 17, 2 * TILE, 2 * TILE + 1, 2 * TILE + 9,
+            2 * TILE + 16, 2 * TILE + 17, 3 * TILE + 15, 0]  # (a last tile has up to 2,048 words)
     off = np.cumsum([0] + lens).astype(np.uint64)
     W, regions = int(off[-1]), 50
     words = np.sort(rng.choice(W, W // 2, replace=False))
