@@ -1329,11 +1329,14 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
   // sixteen maps only once groups of two are more workgroups than run at a time, and four at most: 24 tiles to 96 maps
   // 14.0 / 16.1, to 160 19.0 / 17.7, 7 to 512 18.4 / 19.9; 160 to 24 20.8 / 19.9, to 32 24.3 / 25.2 (six).  In two launches
   // four are better up to five maps (1,001 tiles to 3, 4, 5 ranks 20.4 / 19.3, 22.3 / 22.0, 26.6 / 24.7; 1,937 33.1 / 31.5,
-  // 38.9 / 38.2, 44.5 / 43.6; to 8 60.6 / 61.5), and where full groups of four all run at a time (667 to 8 26.3 / 25.5, 449 to
-  // 12 maps 26.2 / 25.3; to 10 22.5 / 23.2).
+  // 38.9 / 38.2, 44.5 / 43.6; to 8 60.6 / 61.5), where full groups of four all run at a time (667 to 8 26.3 / 25.5, 449 to
+  // 12 maps 26.2 / 25.3; to 10 22.5 / 23.2), and where the templates are more than an L2 holds and come from afar for
+  // each group (6 M words to 8, 16 ranks 116 / 98, 213 / 181, 12 M to 16 404 / 350, 200 graphs of 40 templates to 8, 16 114 /
+  // 99, 212 / 177; of 10, 158 tiles, 90.4 / 92.5, 165 / 170; 2 M words to 8, 16 40.1 / 38.1, 66.0 / 67.6).
   const u64 self_limit = (u64)fdy__tune_get(FDY_TUNE_MAT_SELF_WGS);
   // (The line was placed with tiles of 2,048 words: 260,087 words, all relocated, to 16 maps, 129 tiles by eight groups,
   // 18.5 us in one launch, 25.7 in two; a quarter relocated 14.5 / 16.7.)
+  const u64 distinct = (u64)p.ws.max_tiles * d.n_templates / d.n_graphs;  // tiles that the templates have
   const u64 line_tiles = (d.out_words_per_map + kMatBuf - 1) / kMatBuf + d.n_graphs;
   auto resolves_itself = [&](u32 group) {
     const u32 groups = (d.n_maps + group - 1) / group;
@@ -1346,7 +1349,7 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
     if (d.map_rank && !resolves_itself(2)) {
       const u64 tiles = p.ws.max_tiles - d.n_graphs;  // at least (the entries in reserve aside)
       const bool few = d.n_maps <= 16, one_launch = (u64)p.ws.max_tiles * d.n_maps <= 4608;
-      if (d.n_maps <= 5 || (few && d.n_maps % 4 == 0 && tiles * (d.n_maps / 4) <= 1200)) mg = 4;
+      if (distinct >= 200 || d.n_maps <= 5 || (few && d.n_maps % 4 == 0 && tiles * (d.n_maps / 4) <= 1200)) mg = 4;
       if (one_launch && few && resolves_itself(8)) mg = 8;
       if (one_launch && (few || tiles * ((d.n_maps + 1) / 2) >= 1280) && resolves_itself(4)) mg = 4;
     }
@@ -1379,7 +1382,6 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
   // 38.3.  With tiles resolved here 113 to 16 maps 19.9 / 16.2, 81 11.2 / 11.1, but 65 10.3 / 10.9 and 25 9.1 / 11.0: rounds of
   // tiles and idle blocks come back to the same compute units.  Where graphs share templates, only beyond what
   // one L2 holds of them: 434 tiles of 16 templates of 40 graphs 19.7 / 19.5, of 4 19.6 / 19.75, 3,391 of 22 of 512 84.4 / 87.0.
-  const u64 distinct = (u64)p.ws.max_tiles * d.n_templates / d.n_graphs;
   const u32 own_from = d.n_templates < d.n_graphs ? ~0u : resolves_itself(p.map_group) ? 80 : 40;
   const bool rounds = n_groups > 1 && (distinct >= 160 || p.ws.max_tiles >= own_from);
   auto whole_rounds = [&](u32 blocks) { return rounds ? (blocks + 7) & ~7u : blocks; };

@@ -15,7 +15,7 @@ TILE = 2032
     (448, 4, 1), (448, 5, 1), (448, 6, 1), (448, 8, 1), (448, 9, 1), (448, 10, 1), (448, 11, 2),  # 449 * 11 > 4,608
     (866, 3, 1), (866, 5, 1), (866, 6, 2),
     (1000, 3, 1), (1031, 4, 1), (1032, 3, 2), (1032, 5, 2), (1032, 6, 2),  # 1,031 * 2,032 words are 1,023 * 2,048
-    (266, 16, 1), (270, 17, 2),
+    (266, 16, 1), (270, 17, 2), (198, 25, 2), (199, 25, 2),  # 199 + 1: groups of four
     (159, 23, 1), (159, 32, 2),
     (23, 84, 1), (23, 96, 2), (23, 112, 1), (40, 62, 2), (40, 64, 1), (10, 256, 1), (10, 257, 2)])
 def test_launches_under_patches(tiles, maps, launches):
