@@ -1320,7 +1320,9 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
 
   // Base maps per workgroup: two.  A workgroup writes each of its maps in turn, and the further apart the maps that are
   // written at a time lie, the slower.  us of main with 1 / 2 / 3 / 4 / 8 maps, thirty passes warm: 67 graphs to 256 maps 342 / 257
-  // / 285 / 298 / 306, 67 graphs to 8 ranks 57.5 / 51.1 / 50.8 / 52.3 / 56.4.
+  // / 285 / 298 / 306, 67 graphs to 8 ranks 57.5 / 51.1 / 50.8 / 52.3 / 56.4.  Four where the templates are more than the
+  // Infinity Cache holds (16,384 tiles are 268 MB) and each group reads them from HBM: us of the call with two / four, 3 % of
+  // the words relocated, 40 M words to 4 maps 388 / 351, 60 M to 3, 4, 8 489 / 404, 593 / 520, 1,182 / 1,018; 20 M 154 / 178.
   //
   // With rank patches, whose maps cost a workgroup three barriers each, a larger group is worth it where it lets the
   // launch resolve its own tiles, up to 4,608 tiles of all maps and sixteen maps: us of the call with two in two launches / more
@@ -1345,7 +1347,7 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
   };
   u32 mg = (u32)fdy__tune_get(FDY_TUNE_MAT_MAP_GROUP);
   if (mg == 0) {
-    mg = 2;
+    mg = distinct >= 16384 ? 4 : 2;
     if (d.map_rank && !resolves_itself(2)) {
       const u64 tiles = p.ws.max_tiles - d.n_graphs;  // at least (the entries in reserve aside)
       const bool few = d.n_maps <= 16, one_launch = (u64)p.ws.max_tiles * d.n_maps <= 4608;
