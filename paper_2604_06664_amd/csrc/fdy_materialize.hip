@@ -84,9 +84,10 @@ struct MatWs {
   u64* out_word_off;  // [G+1]
   u64* out_node_off;  // [G+1]
   u64* tile_off;      // [G+1]
-  MatTile* tiles;     // [max_tiles]
   uint2* tile_patch;  // [max_tiles * R]
+  MatTile* tiles;     // [n_entries], those from max_tiles on for no tile
   u32 max_tiles;
+  u32 n_entries;
 };
 
 struct MatParams {
@@ -398,7 +399,7 @@ __device__ __forceinline__ void prep_tiles_block(const MatParams& p, const PrepV
   }
   s_lo[tid] = make_uint2(reloc_lo, ovr_lo);
   __syncthreads();
-  if (tid >= kPrepTiles || j >= p.ws.max_tiles) return;
+  if (tid >= kPrepTiles || j >= p.ws.n_entries) return;
   MatTile* ent = &p.ws.tiles[j];
   if (!valid) {
     ent->n_words = 0;
@@ -445,7 +446,7 @@ __device__ __forceinline__ void prep_tile_group(const MatParams& p, const PrepVi
   const fdy_mat_desc& d = p.d;
   const u32 l = lane_id() & 31;
   if (v.n_tiles == 0) {  // (the same for all; no tile has a place)
-    if (l == 0 && j < p.ws.max_tiles) p.ws.tiles[j].n_words = 0;
+    if (l == 0 && j < p.ws.n_entries) p.ws.tiles[j].n_words = 0;
     return;
   }
   const bool valid = j < v.n_tiles;
@@ -473,7 +474,7 @@ __device__ __forceinline__ void prep_tile_group(const MatParams& p, const PrepVi
   e.ovr_hi = max((u32)__shfl(found, at + 24), e.ovr_lo);
   e.reloc_seg = rl0;
   e.pad = 0;
-  if (l != 0 || j >= p.ws.max_tiles) return;
+  if (l != 0 || j >= p.ws.n_entries) return;
   MatTile* ent = &p.ws.tiles[j];
   if (!valid) {
     ent->n_words = 0;
@@ -861,7 +862,6 @@ __global__ __launch_bounds__(kMatBlock) void mat_main_kernel(MatParams p, u32 fi
     if (rl1 < rl0 && blockIdx.y == 0) raise_status(p.d_status, FDY_ST_BAD_ORDER);  // offsets that decrease: no list
     if (k0 == 0 && ent.reloc_lo != rl0 && blockIdx.y == 0) raise_status(p.d_status, FDY_ST_BAD_INDEX);
   } else {
-    if (j >= p.ws.max_tiles) return;  // (the grid is rounded up)
     ent = p.ws.tiles[j];
   }
   const u32 n = ent.n_words;
@@ -1198,6 +1198,19 @@ bool desc_ok(const fdy_mat_desc* d) {
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
+// The size that is asked for: that of tables for tiles of 2,048 words and 64-byte entries, as ever, so that a caller's
+// sizes do not move, or what the tables take where that is more (248 ranks and more: up to 0.8 %, and an entry per rank).
+size_t asked_bytes(const fdy_mat_desc* d) {
+  const u64 tiles = (d->out_words_per_map + 2047) / 2048 + d->n_graphs;
+  const size_t per_graph = align256(((size_t)d->n_graphs + 1) * 8);
+  return align256(sizeof(MatHeader)) + 3 * per_graph + align256((size_t)tiles * 64) +
+         align256((size_t)tiles * (d->map_rank ? d->n_ranks : 0) * sizeof(uint2));
+}
+
+// The tile table is last, and is rounded up to whole rounds of the eight XCDs where that takes no more (always up to 32
+// ranks, from 40 tiles on): the entries beyond the tiles are marked unused like others in reserve, so that main, which a
+// launch may want in whole rounds (see materialize_launch), has no bound to test.  With a test there main of the kernels
+// of a load took 51.3 us for 67 graphs to 8 ranks, not 51.0.
 size_t layout(const fdy_mat_desc* d, unsigned char* base, MatWs* ws) {
   const u64 max_tiles = (d->out_words_per_map + kMatTile - 1) / kMatTile + d->n_graphs;
   const u32 R = d->map_rank ? d->n_ranks : 0;
@@ -1212,24 +1225,16 @@ size_t layout(const fdy_mat_desc* d, unsigned char* base, MatWs* ws) {
   w.out_word_off = (u64*)take(((size_t)d->n_graphs + 1) * 8);
   w.out_node_off = (u64*)take(((size_t)d->n_graphs + 1) * 8);
   w.tile_off = (u64*)take(((size_t)d->n_graphs + 1) * 8);
-  w.tiles = (MatTile*)take((size_t)max_tiles * sizeof(MatTile));
   w.tile_patch = (uint2*)take((size_t)max_tiles * R * sizeof(uint2));
+  const u64 in_rounds = (max_tiles + 7) & ~7ull;
+  const size_t asked = asked_bytes(d), least = off + align256((size_t)max_tiles * sizeof(MatTile));
+  const size_t need = asked > least ? asked : least;
+  const u64 n_entries = off + in_rounds * sizeof(MatTile) <= need ? in_rounds : max_tiles;
+  w.tiles = (MatTile*)take((size_t)n_entries * sizeof(MatTile));
   w.max_tiles = (u32)max_tiles;
+  w.n_entries = (u32)n_entries;
   if (ws) *ws = w;
-  return off;
-}
-
-// The size that is asked for: that of tables for tiles of 2,048 words and 64-byte entries, as ever, so that a caller's
-// sizes do not move, or what the tables take where that is more (248 ranks and more: up to 0.8 %, and an entry per rank).
-size_t asked_bytes(const fdy_mat_desc* d) {
-  const u64 tiles = (d->out_words_per_map + 2047) / 2048 + d->n_graphs;
-  const size_t per_graph = align256(((size_t)d->n_graphs + 1) * 8);
-  return align256(sizeof(MatHeader)) + 3 * per_graph + align256((size_t)tiles * 64) +
-         align256((size_t)tiles * (d->map_rank ? d->n_ranks : 0) * sizeof(uint2));
-}
-size_t workspace_need(const fdy_mat_desc* d) {
-  const size_t asked = asked_bytes(d), need = layout(d, nullptr, nullptr);
-  return asked > need ? asked : need;
+  return need;
 }
 
 }  // namespace
@@ -1239,7 +1244,7 @@ using namespace fdy;
 
 extern "C" size_t fdy_materialize_workspace_bytes(const fdy_mat_desc* h_desc) {
   if (!desc_ok(h_desc)) return 0;
-  return workspace_need(h_desc);
+  return layout(h_desc, nullptr, nullptr);
 }
 
 // Scratch of the entry point that allocates nothing (fdy_materialize_static): the tile table and
@@ -1308,7 +1313,7 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
   p.d = d;
   if (!d.map_rank) p.d.n_ranks = 0;
   if (!d_out_dims) p.d.out_nodes_total = 0;
-  const size_t need = workspace_need(&d);
+  const size_t need = layout(&d, nullptr, nullptr);
   if (!d_workspace || ((uintptr_t)d_workspace & 255) || workspace_bytes < need) return FDY_ERR_WORKSPACE;
   layout(&d, (unsigned char*)d_workspace, &p.ws);
   p.out_words = (u64*)d_out_words;
@@ -1386,24 +1391,26 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
   // one L2 holds of them: 434 tiles of 16 templates of 40 graphs 19.7 / 19.5, of 4 19.6 / 19.75, 3,391 of 22 of 512 84.4 / 87.0.
   const u32 own_from = d.n_templates < d.n_graphs ? ~0u : resolves_itself(p.map_group) ? 80 : 40;
   const bool rounds = n_groups > 1 && (distinct >= 160 || p.ws.max_tiles >= own_from);
-  auto whole_rounds = [&](u32 blocks) { return rounds ? (blocks + 7) & ~7u : blocks; };
   // A launch small enough that all its workgroups run side by side resolves its tiles itself.
   if (resolves_itself(p.map_group) && p.ws.max_tiles <= most && nb_dims_all <= most / 2) {
+    const u32 own_blocks = p.ws.max_tiles + (u32)nb_dims_all + kCheckBlocks;
     launch(FDY_PROF_MAT_MAIN, mat_main_kernel<true>,
-           dim3(whole_rounds(p.ws.max_tiles + (u32)nb_dims_all + kCheckBlocks), n_groups), dim3(kMatBlock), 0, stream, p, 0u,
-           p.ws.max_tiles, (u32)nb_dims_all);
+           dim3(rounds ? (own_blocks + 7) & ~7u : own_blocks, n_groups), dim3(kMatBlock), 0, stream, p, 0u, p.ws.max_tiles,
+           (u32)nb_dims_all);
     FDY_HIP_TRY(hipGetLastError());
     return FDY_OK;
   }
 
+  if (!rounds) p.ws.n_entries = p.ws.max_tiles;
   const bool own_sums = d.n_graphs <= kOwnSumsMax;
   if (!own_sums) {
     launch(FDY_PROF_MAT_PREP_GRAPHS, mat_prep_graphs_kernel, dim3(1), dim3(1024), 0, stream, p);
     FDY_HIP_TRY(hipGetLastError());
   }
   const u64 pairs = (u64)p.ws.max_tiles * p.d.n_ranks;  // (0 ranks without a rank map)
+  const u32 entries = p.ws.n_entries;
   const bool group_tiles = p.ws.max_tiles <= kGroupTiles, group_patch = pairs <= kGroupPairs;
-  u32 nb_tiles = group_tiles ? (p.ws.max_tiles + 7) / 8 : (p.ws.max_tiles + kPrepTiles - 1) / kPrepTiles;
+  u32 nb_tiles = group_tiles ? (entries + 7) / 8 : (entries + kPrepTiles - 1) / kPrepTiles;
   const u64 nb_patch_all = group_patch ? (pairs + 31) / 32 : (pairs + 255) / 256;
   const u32 nb_patch = !group_patch && nb_patch_all > most ? most : (u32)nb_patch_all;
   const u32 nb_dims = nb_dims_all > most / 2 ? (most + 1) / 2 : (u32)nb_dims_all;
@@ -1414,10 +1421,10 @@ static int materialize_launch(const fdy_mat_desc* h_desc, uint64_t* d_out_words,
            dim3(256), 0, stream, p, nb_tiles, nb_patch, group_tiles, group_patch);
     FDY_HIP_TRY(hipGetLastError());
   }
-  for (u32 first = 0; first < p.ws.max_tiles;) {
-    const u32 n = p.ws.max_tiles - first < most ? p.ws.max_tiles - first : most;
-    launch(FDY_PROF_MAT_MAIN, mat_main_kernel<false>, dim3(first + n == p.ws.max_tiles ? whole_rounds(n) : n, n_groups),
-           dim3(kMatBlock), unused_lds, stream, p, first, 0u, 0u);
+  for (u32 first = 0; first < entries;) {
+    const u32 n = entries - first < most ? entries - first : most;
+    launch(FDY_PROF_MAT_MAIN, mat_main_kernel<false>, dim3(n, n_groups), dim3(kMatBlock), unused_lds, stream, p, first,
+           0u, 0u);
     FDY_HIP_TRY(hipGetLastError());
     first += n;
   }

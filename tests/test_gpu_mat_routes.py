@@ -92,6 +92,34 @@ def test_launches_of_whole_rounds(tiles):
     check_mat(session, orc, mp, tag=f"{tiles} tiles", want_dims=False)
 
 
+@pytest.mark.parametrize("tiles", range(40, 49))
+def test_entries_of_no_tile_are_marked(tiles):
+    """A table that held a tile of one word in each of its entries, the graph's first."""
+    import paper_2604_06664_amd as fdy
+    from tests.support import session
+    from tests.test_gpu_tile_slices import problem
+
+    rng = np.random.default_rng(tiles)
+    n = tiles * TILE
+    r = np.zeros(1, L.RELOC)
+    mp = problem(n, r, [0, 1], 60, rng)
+    old = fdy.tune_set(fdy.TUNE_MAT_SELF_WGS, 0)
+    try:
+        run = session.MatRun(mp, want_dims=False)
+        ws = np.zeros(run.ws_bytes, np.uint8)
+        table = ws[1024:1024 + 48 * (tiles + 8)].view(np.uint32).reshape(-1, 12)  # behind the header and three offset lists
+        table[:, 4] = 1
+        run.d_ws.copy_(fdy.to_device(ws))
+        run.launch()
+    finally:
+        fdy.tune_set(fdy.TUNE_MAT_SELF_WGS, old)
+    out, _, status = run.result()
+    assert status == 0 and np.array_equal(out, orc.materialize(mp, False)[0])
+    after = fdy.to_host(run.d_ws, np.uint32, run.ws_bytes // 4)[256:][:12 * (tiles + 8)].reshape(-1, 12)[:, 4]
+    entries = (tiles + 1 + 7) // 8 * 8
+    assert (after[:tiles] == TILE).all() and not after[tiles:entries].any() and (after[entries:] == 1).all()
+
+
 @pytest.mark.parametrize("n", [1, TILE - 1, TILE, TILE + 1, 2 * TILE, 2 * TILE + 1])
 def test_tiles_have_2032_words(n):
     """One launch of main to each tile (and the one in reserve): what the other tests call a tile is one."""
