@@ -1210,7 +1210,7 @@ size_t asked_bytes(const fdy_mat_desc* d) {
 // The tile table is last, and is rounded up to whole rounds of the eight XCDs where that takes no more (always up to 32
 // ranks, from 40 tiles on): the entries beyond the tiles are marked unused like others in reserve, so that main, which a
 // launch may want in whole rounds (see materialize_launch), has no bound to test.  With a test there main of the kernels
-// of a load took 51.3 us for 67 graphs to 8 ranks, not 51.0.
+// of a load took 51.5 us for 67 graphs to 8 ranks, not 51.3.
 size_t layout(const fdy_mat_desc* d, unsigned char* base, MatWs* ws) {
   const u64 max_tiles = (d->out_words_per_map + kMatTile - 1) / kMatTile + d->n_graphs;
   const u32 R = d->map_rank ? d->n_ranks : 0;
