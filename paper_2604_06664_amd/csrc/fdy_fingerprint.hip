@@ -282,21 +282,23 @@ struct FpArgs {
 // of its own (the first 512 bytes of a prepared table are four lines with room in them), and the last
 // of each quarter at a fifth.  Additions to one line are served one after the other, 11.3 ns each,
 // whatever the address in it: 512 blocks took 5.8 us for that.  (Two round trips in a row cost 67
-// blocks more than they save: 0.8 us in all.)
-constexpr u32 kOneCounter = 160, kCounterLine = 128 / 4, kLastCounter = kCounterLine + 1;
+// blocks more than they save: 0.8 us in all.)  The one address is in the last of them: the first holds the table's header,
+// which every workgroup of the next scan reads, and comes from afar after an addition to its line.
+constexpr u32 kOneCounter = 160;
+constexpr int kCounterLine = -128 / 4, kLastCounter = 2 * kCounterLine + 1;
 // Called by one thread of each of the G blocks; true in the last.
 __device__ __forceinline__ bool count_block(u32* counter, u32 g, u32 G) {
   auto add = [](u32* c) { return __hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1; };
   if (G <= kOneCounter) return add(counter) == G;
   const u32 q = g & 3;
-  if (add(counter + q * kCounterLine) != (G - q + 3) / 4) return false;
+  if (add(counter + (int)q * kCounterLine) != (G - q + 3) / 4) return false;
   return add(counter + kLastCounter) == 4;
 }
 __device__ __forceinline__ void reset_counters(u32* counter, u32 G) {
   auto zero = [](u32* c) { __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
   zero(counter);
   if (G <= kOneCounter) return;
-  for (u32 q = 1; q < 4; ++q) zero(counter + q * kCounterLine);
+  for (u32 q = 1; q < 4; ++q) zero(counter + (int)q * kCounterLine);
   zero(counter + kLastCounter);
 }
 
@@ -544,6 +546,6 @@ extern "C" int fdy_segment_fingerprint(const fdy_reloc* d_relocs, const uint64_t
   a.word_off = (const u64*)d_word_off;
   a.reloc_off = (u64*)d_reloc_off;
   // the prepared table's first 512 bytes hold counters for this call (zero between calls)
-  a.counter = d_prepared ? (u32*)((unsigned char*)d_prepared + 64) : nullptr;
+  a.counter = d_prepared ? (u32*)((unsigned char*)d_prepared + 448) : nullptr;
   return fingerprint_launch(a, n_graphs, d_workspace, workspace_bytes, (hipStream_t)hip_stream);
 }

@@ -9,9 +9,10 @@ namespace fdy {
 constexpr u32 kFlatWorkers = 7, kFlatWorkersBig = 15;
 
 // Workers per workgroup.  Measured (us, 7 / 15
-// workers, a quarter pointers, 4,096 allocations): 17 sub-tiles 6.0 / 9.0, 1,024 9.4 / 9.2, 1,536
-// 10.3 / 9.6, 2,048 12.9 / 10.4, 4,096 23 / 14.5, 16,384 50 / 33: many small workgroups start
-// sooner and share the staging's latency, but each chunk costs a ticket and a look-back.
+// workers, a quarter pointers, 4,096 allocations): 586 sub-tiles 7.2 / 7.6, 1,368 8.0 / 7.9, 1,758 8.3 / 8.1, 2,344
+// 10.5 / 8.4, 3,321 12.3 / 9.3; 16,384 allocations, 1,016 sub-tiles 8.8 / 8.8, 1,368 9.2 / 8.9; with output and lines,
+// 1,368 11.7 / 12.8: many small workgroups start sooner and share the staging's latency, but each chunk costs a ticket and
+// a look-back.
 constexpr u32 kFlatFewSubs = 1536;
 __host__ __device__ __forceinline__ u32 flat_workers(u32 n_sub) {
   return n_sub < kFlatFewSubs ? kFlatWorkers : kFlatWorkersBig;
@@ -34,7 +35,8 @@ inline u32 flat_most_chunks(u32 max_sub) {
 // for which `states` hold the blocks, at most kFlatSpread, and no larger than the chunks can use.
 // us with 16 allocations and 2 % pointers, in chunk_state_bytes (32, 128 and 128 lines) / 256
 // lines / 512 / a line for each: 0.76 M words 10.1 / 8.6 / 8.7 / 8.8, 5.8 M 22.2 / 20.1 / 19.5 /
-// 19.5, 16.8 M 46.6 / 41.0 / 40.5 / 41.0.
+// 19.5, 16.8 M 46.6 / 41.0 / 40.5 / 41.0 (a state to a chunk, then; with five to sixteen, loads of 0.8 and 5.9 M words with 1 /
+// 8 / 32 / 64 / 512 lines: 25.3 / 25.3 / 24.2 / 23.9 / 23.9 and 63.8 / 63.0 / 62.8 / 62.2 / 61.7).
 constexpr u32 kFlatSpread = 9;
 __host__ __device__ __forceinline__ u32 flat_extent(u32 s, u32 n_chunks) {
   return (n_chunks + (8u << s) - 1) >> (s + 3) << (s + 3);
@@ -45,7 +47,7 @@ __host__ __device__ __forceinline__ u32 flat_spread(u32 n_chunks, u32 states) {
   return s;
 }
 
-// Bytes of chunk states that a launch of n_sub sub-tiles cannot do without: one state for eight
+// Bytes of chunk states that a launch of n_sub sub-tiles is asked for at least: one state for eight
 // of them, closer together than the scan likes.
 inline size_t chunk_state_bytes(u32 n_sub) { return ((size_t)((n_sub + 7) / 8) * 8 + 255) & ~(size_t)255; }
 
@@ -101,6 +103,24 @@ __host__ __device__ __forceinline__ u32 flat_next_turn(u32 turn, u32 n_chunks) {
 __host__ __device__ __forceinline__ u32 flat_to_clear(const FlatTurn& t, u32 i, u32 n_chunks) {
   const u32 at = state_at(t.s_dirty, i);
   return chunk_at(t.s, at) < n_chunks ? ~0u : at;
+}
+
+// What the states of an ordered scan hold.  Sixteen chunks take five: four with a 16-bit field for each of four chunks
+// (its hits, once they are known), and one for the hits of all chunks up to the sixteenth, once those are.  Either kind says
+// which it is and carries the parity of its launch: fields have their top bit set, a sum has none of the four top bits of
+// its 16-bit parts, so that whatever an earlier launch left in a place never looks like the other kind.
+__host__ __device__ __forceinline__ u32 scan_states(u32 n_chunks) { return 5 * ((n_chunks + 15) / 16); }
+__host__ __device__ __forceinline__ u32 fields_state(u32 chunk) { return 5 * (chunk >> 4) + ((chunk >> 2) & 3); }
+__host__ __device__ __forceinline__ u32 sum_state(u32 sixteen) { return 5 * sixteen + 4; }
+constexpr u32 kFieldHits = (1u << 14) - 1;
+__host__ __device__ __forceinline__ u32 make_field(u32 hits, u32 parity) { return 0x8000u | parity << 14 | hits; }
+__host__ __device__ __forceinline__ bool is_field(u32 field, u32 parity) { return field >> 14 == (2u | parity); }
+__host__ __device__ __forceinline__ u64 make_sum(u64 hits, u32 parity) {
+  return 1ull << 62 | (parity ? kFlatParity : 0) | (hits >> 30 & 0x7fff) << 32 | (hits >> 15 & 0x7fff) << 16 | (hits & 0x7fff);
+}
+__host__ __device__ __forceinline__ bool is_sum(u64 v, u32 parity) { return v >> 61 == (2u | parity); }
+__host__ __device__ __forceinline__ u64 sum_hits(u64 v) {
+  return (v >> 32 & 0x7fff) << 30 | (v >> 16 & 0x7fff) << 15 | (v & 0x7fff);
 }
 
 }  // namespace fdy

@@ -87,7 +87,23 @@ __host__ __device__ __forceinline__ size_t flat_level_bytes(u32 top_n, u32 bucke
 // The largest level 0 that is staged (plan_table keeps to it).
 constexpr u32 kMostTopLog2 = 14, kMostBucketLog2 = 13;
 
-// P: the launch's parameters (top, bstart, top_n, bucket_log2, table, n_alloc).  at_once: all pieces of the keys and
+// Where the keys are staged and what else a wave knows of them.  P: the launch's parameters (top, bstart, top_n,
+// bucket_log2, table, n_alloc).
+template <typename P>
+__host__ __device__ __forceinline__ FlatLevel flat_level(const P& p, unsigned char* smem) {
+  FlatLevel f;
+  const u32 key_vec = p.top_n / 4;
+  f.keys = smem;
+  f.bst = reinterpret_cast<const unsigned short*>(smem + (size_t)(key_vec * 16 + kFlatPad * 4));
+  f.last_at = key_vec * 16;
+  f.span_lo = p.table[0].base;
+  f.span_len = p.table[p.n_alloc - 1].base + p.table[p.n_alloc - 1].size - f.span_lo;
+  f.key_shift = key_shift_for(f.span_len, 31);
+  f.bucket_shift = bucket_shift_for(f.span_len, f.key_shift, p.bucket_log2);
+  return f;
+}
+
+// Stages the keys and their index.  at_once: all pieces of the keys and
 // their index are requested before the first arrives, and not each behind the one before.  For keys that a launch just
 // before has written, which come from afar: us of a rebase with its preparation, piece by piece / at once, 16,384
 // allocations, 100,003 words 11.7 / 10.2, 1.0 M 14.5 / 13.2, 5.0 M 26.9 / 25.4; 1,024 allocations 8.6 / 8.4, 11.4 / 11.3.  Keys of
@@ -98,7 +114,6 @@ constexpr u32 kMostTopLog2 = 14, kMostBucketLog2 = 13;
 // of 154 shorter with nodes.)
 template <u32 kThreads, typename P>
 __host__ __device__ __forceinline__ FlatLevel flat_stage(const P& p, unsigned char* smem, u32 tid, bool at_once) {
-  FlatLevel f;
   const u32 n_bst = (1u << p.bucket_log2) + 1;
   const u32 key_vec = p.top_n / 4, bst_vec = (n_bst * 2 + 15) / 16;
   uint4* dst = reinterpret_cast<uint4*>(smem);
@@ -128,14 +143,7 @@ __host__ __device__ __forceinline__ FlatLevel flat_stage(const P& p, unsigned ch
     for (u32 i = tid; i < bst_vec; i += kThreads) dst[key_vec + kFlatPad / 4 + i] = bs[i];
   }
   if (tid < kFlatPad / 4) dst[key_vec + tid] = make_uint4(~0u, ~0u, ~0u, ~0u);
-  f.keys = smem;
-  f.bst = reinterpret_cast<const unsigned short*>(smem + (size_t)(key_vec * 16 + kFlatPad * 4));
-  f.last_at = key_vec * 16;
-  f.span_lo = p.table[0].base;
-  f.span_len = p.table[p.n_alloc - 1].base + p.table[p.n_alloc - 1].size - f.span_lo;
-  f.key_shift = key_shift_for(f.span_len, 31);
-  f.bucket_shift = bucket_shift_for(f.span_len, f.key_shift, p.bucket_log2);
-  return f;
+  return flat_level(p, smem);
 }
 
 // Level 0 for N distances d = word - span_lo per lane: byte offset of the last key not above each

@@ -7,7 +7,8 @@
 //
 // Work decomposition.  Persistent workgroups, one per compute unit, stage the top level of the
 // table's hierarchy in LDS once.  Words come in sub-tiles of 512; a chunk is a sub-tile for each
-// of the workgroup's 15 (small inputs: 7) workers, handed out by an atomic ticket.  A worker
+// of the workgroup's 15 (small inputs: 7) workers; a workgroup's first is that of its own number, further ones are
+// handed out by atomic tickets.  A worker
 //   1. takes its 8 words per lane (16-byte coalesced non-temporal loads) and rejects every word
 //      outside the table's span;
 //   2. queues the surviving candidates and their places in LDS, in word order (ballot ranks), so
@@ -18,12 +19,13 @@
 //      eight entries (fdy_lines.hpp), or the table entry itself where level 0 has every base;
 //      where truncated keys lead a word too far, exact bases of what the keys stand for settle it;
 //      what became of a candidate stays in registers, 64 bits each;
-//   4. posts its hits; one barrier per chunk makes them and the next ticket visible.
+//   4. posts its hits, the last of the workers those of the chunk to everybody; one barrier per chunk makes them and the
+//      next ticket visible.
 // The sixteenth wave, the clerk, owns no words: it draws the tickets and finds the chunk's output
-// position by a decoupled look-back over per-chunk state words (flag and value in one 64-bit word,
-// agent-scope relaxed atomics) while the others search the next chunk.  The workers then write
-// the entries of the chunk before from registers, in ascending word order.  The input is read
-// once and the relocation table written once.
+// position by a decoupled look-back over what the chunks say of themselves (16 bits each, four to a word, and the hits so
+// far behind every sixteenth: one step looks at 256 chunks, which is what is in flight) while the others search the next
+// chunk.  The workers then write the entries of the chunk before from registers, in ascending word order.  The input is
+// read once and the relocation table written once.
 //
 // What bounds it.  A compute unit's vector L1 takes one divergent lane per clock and its
 // searches' chains of dependent requests cost 0.6-0.8 us a step; beside them stand the words
@@ -42,8 +44,16 @@
 //   the line before instead of a search where truncated keys lead a line too far                787 / 75 / 172
 //   fifteen workers                                                                            715 / 66 / 161
 //   the largest tables' rounds one by one but for sub-tiles with few candidates                685 / 67 / 158
+//   positions by one step over 256 chunks, not by 64 at a time; hits told by the last worker    671 / 65 / 150
+// A small launch is a chain of waits.  us of scans alone, one after the other, a quarter pointers, 4,096 allocations, 0.3 /
+// 0.7 / 1.2 / 1.7 M words: 7.7 / 9.9 / 10.2 / 11.3 with every chunk by ticket from one counter and positions by 64 chunks at
+// a time; 7.2 / 8.0 / 8.4 / 9.2 now.  Of a load of 0.8 M words 25.5 -> 23.5, of which first chunks without a ticket 1.1,
+// the look-back 0.6; 8.4 M positions at 4-byte stride 25.2 -> 22.1.
 // Tried and left: words requested before the search (they hold up its first fetch, which returns
-// behind them: 75 -> 90), tickets, counts and positions through a ring in LDS instead of the
+// behind them: 75 -> 90; behind the last fetch of the search, with the ticket there, a load of 5.9 M words 62.4 -> 66.1: a
+// compute unit's vector L1 answers in order, so that what comes from memory holds up every other wave's fetches as well),
+// the last chunk's position looked for while it is searched (62 -> 65, for the same reason), chunks in a fixed order
+// instead of tickets (62.3 -> 64.4), seven workers and two workgroups per compute unit at every size (62 -> 68), tickets, counts and positions through a ring in LDS instead of the
 // barrier (workers a chunk apart: 172 -> 215), two sub-tiles per worker and round with up to six
 // chains (seven workers: 787 -> 784, 75 -> 80), choosing among a node's keys as a tree of three
 // compares (everything a quarter slower).
@@ -65,9 +75,10 @@
 // same buffer and is left ready for the next call, marked with the launch's parity (FlatTurn), so
 // that a scan is one launch.
 //
-// Tickets are handed out in increasing order and a wave only ever waits for chunks with
-// smaller numbers, which are already owned by resident workgroups; the wait is bounded by a
-// spin limit after which FDY_ST_SPIN is raised and the kernel still terminates.
+// A wave only ever waits for chunks with smaller numbers.  Their workgroups need not be running yet (a first chunk is
+// nobody else's): a clerk that has waited long counts their hits itself, so that launches of several streams that share
+// the compute units never wait for each other.  The wait is bounded by a spin limit after which FDY_ST_SPIN is raised and
+// the kernel still terminates.
 //
 // Steps whose bodies hold a whole search are not written as loops: past a size the optimizer
 // declines to unroll even a `#pragma unroll` loop, and a rolled loop indexes the
@@ -99,7 +110,8 @@ struct ScanParams {
   fdy_reloc* relocs;
   u64 capacity;
   u64* d_count;
-  u32* ticket;
+  u32* queues;      // see ChunkQueue
+  u32 n_queues;
   const u32* top;  // [top_n] level-0 keys, padded with 0xffffffff
   const unsigned short* bstart;  // [n_buckets + 1] level-0 keys below each bucket's first key value
   u32 bucket_log2;  // log2(n_buckets)
@@ -122,26 +134,18 @@ struct ScanParams {
   u32 n_sub;            // sub-tiles
   u32* d_status;
   u32 spin_limit;
+  u32 patience;  // polls after which a waiting workgroup counts a chunk itself
   const u64* new_base;  // with a rebased output only: [n_alloc]
   u64* out;             // with a rebased output only: [n_words]
   u32* turn;            // what the launch before left (see FlatTurn)
   FlatRegion region;    // where its states lie (a prepared table's header says so itself)
 };
 
-constexpr u64 kFlagAgg = 1ull << 62;
-constexpr u64 kFlagInc = 2ull << 62;
-
 __device__ __forceinline__ u64 ld_state(const u64* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void st_state(u64* p, u64 v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ __forceinline__ u64 wave_sum_u64(u64 v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d);
-  return v;
 }
 
 // LDS traffic between lanes of one wave needs no hardware barrier (a wave's LDS operations
@@ -151,12 +155,11 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// Chunk states carry a 2-bit flag and a value in one 64-bit word (agent-scope relaxed
-// atomics; no fences needed because the payload travels in the same word as the flag): first
-// the chunk's hit total (flag AGG), later the inclusive prefix up to the chunk's end (flag
-// INC).  A chunk's exclusive prefix is found by walking the states backwards, 64 chunks per
-// step, summing totals until an inclusive prefix is met.  Waits are for chunks that are
-// already being processed, and they are bounded by the spin limit.
+// What chunks say of themselves (fdy_flat_state.hpp): a 16-bit field each, its hits, four to a state, and behind every
+// sixteenth the hits of all chunks so far, all written and read by agent-scope relaxed atomics (no fences: flag and
+// payload travel in one word).  A chunk's exclusive prefix is then one step back over 256 chunks: as many as a launch
+// has in flight, so that it rarely takes a second.  Waits are for chunks that are already being processed, and they are
+// bounded by the spin limit.
 __device__ __forceinline__ bool spin_once(u32& spins, u32 spin_limit, u32* d_status) {
   if (++spins > spin_limit) {  // give up, flag it, let everybody proceed
     if (lane_id() == 0) raise_status(d_status, FDY_ST_SPIN);
@@ -168,34 +171,74 @@ __device__ __forceinline__ bool spin_once(u32& spins, u32 spin_limit, u32* d_sta
 
 // The states of a launch of the flat scan.
 struct FlatStates {
-  u64* at;     // the region's first state
-  u32 s;       // spread (see state_at)
-  u64 parity;  // 0 or kFlatParity
-  __device__ __forceinline__ u64* place(u32 chunk) const { return &at[state_at(s, chunk)]; }
-  __device__ __forceinline__ void store(u32 chunk, u64 v) const { st_state(place(chunk), v ^ parity); }
+  u64* at;  // the region's first state
+  u32 s;    // spread (see state_at)
+  u32 parity;
+  __device__ __forceinline__ u64* place(u32 i) const { return &at[state_at(s, i)]; }
+  __device__ __forceinline__ void store_field(u32 chunk, u32 field) const {
+    unsigned short* q = reinterpret_cast<unsigned short*>(place(fields_state(chunk))) + (chunk & 3);
+    __hip_atomic_store(q, (unsigned short)field, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
 };
 
-// The number of hits in all chunks before `chunk`: 64 states per step, summed backwards as far as the first
-// inclusive prefix (before chunk 0: prefix 0).
-__device__ __forceinline__ u64 exclusive_prefix(const FlatStates& states, u32 chunk, u32 spin_limit, u32* d_status) {
+// The number of hits in all chunks before `chunk`.  Lane l looks at the four fields of one state, the first sixteen also at
+// the sums behind the sixteenths before; polls go to what is missing alone.  (64 chunks at a time: four or five round trips
+// in a row, us of a load of 0.8 M words 24.4 / 23.8 now, of 8.4 M positions at 4-byte stride 23.6 / 22.3.  Neighbouring
+// states in the same memory lines: 62 -> 64 for 5.9 M words.)  meanwhile(): called behind the first requests.
+//
+// Nothing says that the chunks before are being worked on: their workgroups may wait for a compute unit that others
+// hold.  After `patience` polls the nearest chunk without a total is counted here (count(c)), and its field written as
+// its workgroup will write it: no workgroup waits for one that need not be running.
+template <typename Count, typename Meanwhile>
+__device__ __forceinline__ u64 exclusive_prefix(const FlatStates& states, u32 chunk, u32 spin_limit, u32 patience,
+                                                u32* d_status, Count count, Meanwhile meanwhile) {
   const u32 l = lane_id();
   u64 excl = 0;
   u32 spins = 0;
-  for (int last = (int)chunk - 1; last >= 0;) {
-    const int idx = last - (int)l;
-    const u64 v = idx >= 0 ? ld_state(states.place((u32)idx)) ^ states.parity : kFlagInc;
-    const u32 flag = (u32)(v >> 61);  // the parity is the low bit: odd, another launch's
-    const u64 inc_mask = ballot(flag == (u32)(kFlagInc >> 61));
-    const u64 empty_mask = ballot(flag == 0 || (flag & 1));
-    const u32 first_inc = inc_mask ? (u32)__ffsll((long long)inc_mask) - 1 : 64;
-    const u64 need = first_inc >= 63 ? ~0ull : ((2ull << first_inc) - 1);  // lanes 0..first_inc
-    if (empty_mask & need) {
-      if (!spin_once(spins, spin_limit, d_status)) break;
-      continue;
+  // `end` chunks are left: their hits are wanted
+  if (chunk == 0) meanwhile();
+  for (u32 end = chunk; end > 0;) {
+    const u32 q = (end - 1) >> 2, g = end >> 4;  // the last state with fields that count; whole sixteenths
+    u64 v = 0, sum = 0;
+    if (l < g && l < 16) sum = ld_state(states.place(sum_state(g - 1 - l)));
+    if (l <= q) v = ld_state(states.place(fields_state(4 * (q - l))));
+    __builtin_amdgcn_sched_barrier(0);
+    if (end == chunk) meanwhile();
+    const u64 known = ballot(is_sum(sum, states.parity));
+    // chunks [from, end) are added up here, what lies before is known, or left for the next step
+    const u32 back = known ? (u32)__ffsll((long long)known) - 1 : 0u;
+    const u32 from = known ? (g - back) << 4 : q >= 64 ? 4 * (q - 63) : 0u;
+    u32 hits = 0;  // the lane's
+    for (;;) {
+      u32 missing = 0;
+      hits = 0;
+#pragma unroll
+      for (u32 k = 0; k < 4; ++k) {
+        const u32 c = 4 * (q - l) + k, field = (u32)(v >> (16 * k)) & 0xffffu;
+        const bool counts = l <= q && c >= from && c < end;
+        if (counts && !is_field(field, states.parity)) missing = c + 1;
+        hits += counts ? field & kFieldHits : 0u;
+      }
+      const u64 m = ballot(missing != 0);
+      if (m == 0) break;
+      if (!spin_once(spins, spin_limit, d_status)) return excl;
+      if (spins > patience) {
+        const u32 c = __shfl(missing, (int)__ffsll((long long)m) - 1) - 1;
+        const u32 total = count(c);
+        if (l == 0) states.store_field(c, make_field(total, states.parity));
+        spins = 0;
+      }
+      if (missing) v = ld_state(states.place(fields_state(4 * (q - l))));  // (the others' are there)
     }
-    excl += wave_sum_u64(((need >> l) & 1) ? (v & (kFlatParity - 1)) : 0);
-    if (first_inc < 64) break;
-    last -= 64;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) hits += __shfl_xor(hits, d);
+    excl += hits;
+    if (known) {
+      const u64 s = sum_hits(sum);
+      excl += (u64)(u32)__shfl((u32)s, (int)back) | (u64)(u32)__shfl((u32)(s >> 32), (int)back) << 32;
+      break;
+    }
+    end = from;
   }
   return excl;
 }
@@ -211,8 +254,8 @@ struct PreparedHeader {
 };
 constexpr u64 kPreparedMagic = 0x3159445f4c424154ull;  // "TABL_DY1"
 constexpr size_t kPreparedHeader = 256;
-constexpr size_t kPreparedTurn = 128;  // byte offset of the turn (fdy_segment_fingerprint's counters lie at 64, 192, 196, 320
-                                       // and 448: the last two behind the scan's own)
+constexpr size_t kPreparedTurn = 128;  // byte offset of the turn.  The first 512 bytes also hold the scan's queues (96, 224, 352, 480
+                                       // and 484) and the counters of fdy_segment_fingerprint (64, 192, 196, 320, 448)
 
 // Is the caller's prepared table one that was made for this table, this tuning and at least
 // this many words?  (The host cannot look into device memory without a round trip.)
@@ -232,53 +275,76 @@ __device__ __forceinline__ bool prepared_ok(const ScanParams& p) {
 // structures); p.n_words is then the number of positions, one less than the number of units.
 // A lane still takes 16-byte pieces, four positions each, and gets the unit that follows its
 // piece from the next lane (the last lane from the next piece, or from behind the sub-tile).
+//
+// The words are requested in one place and taken in another; the ragged tail, and sub-tiles past the end, are read
+// where they are taken (no word there is a candidate).
 template <bool kHalf>
-__device__ __forceinline__ void load_words(const ScanParams& p, u32 sub, u64 span_lo, u64 (&w)[kWpl]) {
+struct Words {
+  v4u32 v[kHalf ? 2 : kLoads];
+  u32 behind;
+};
+template <bool kHalf>
+__device__ __forceinline__ bool whole_sub(const ScanParams& p, u32 sub) {  // (kHalf: units wbase .. wbase + 512 exist)
+  return (u64)sub * kSub + kSub <= p.n_words;
+}
+template <bool kHalf>
+__device__ __forceinline__ Words<kHalf> request_words(const ScanParams& p, u32 sub) {
+  Words<kHalf> r = {};  // (nothing of the words before stays)
+  if (!whole_sub<kHalf>(p, sub)) return r;
   const u32 lane = lane_id();
   const u64 wbase = (u64)sub * kSub;
+  // streamed once: non-temporal, so that the table levels keep their place in L2
   if constexpr (kHalf) {
     static_assert(kWpl == 8, "two 16-byte pieces of four positions per lane");
     const u32* h = reinterpret_cast<const u32*>(p.words);
-    if (wbase + kSub <= p.n_words) {  // all 512 positions exist, hence units wbase .. wbase + 512
-      typedef u32 v4u32 __attribute__((ext_vector_type(4)));
-      v4u32 v[2];
 #pragma unroll
-      for (int k = 0; k < 2; ++k)
-        v[k] = __builtin_nontemporal_load(reinterpret_cast<const v4u32*>(h + wbase + (k * 64 + lane) * 4));
-      const u32 behind = h[wbase + kSub];
+    for (int k = 0; k < 2; ++k)
+      r.v[k] = __builtin_nontemporal_load(reinterpret_cast<const v4u32*>(h + wbase + (k * 64 + lane) * 4));
+    r.behind = h[wbase + kSub];
+  } else {
+#pragma unroll
+    for (int k = 0; k < kLoads; ++k)
+      r.v[k] = __builtin_nontemporal_load(reinterpret_cast<const v4u32*>(p.words + wbase + (k * 64 + lane) * 2));
+  }
+  return r;
+}
+template <bool kHalf>
+__device__ __forceinline__ void take_words(const ScanParams& p, u32 sub, u64 span_lo, const Words<kHalf>& r,
+                                           u64 (&w)[kWpl]) {
+  const u32 lane = lane_id();
+  const u64 wbase = (u64)sub * kSub;
+  if constexpr (kHalf) {
+    const u32* h = reinterpret_cast<const u32*>(p.words);
+    if (whole_sub<kHalf>(p, sub)) {
       u32 nx[2];
-      nx[0] = __shfl_down(v[0].x, 1);
-      nx[1] = __shfl_down(v[1].x, 1);
-      const u32 first1 = __shfl(v[1].x, 0);
+      nx[0] = __shfl_down(r.v[0].x, 1);
+      nx[1] = __shfl_down(r.v[1].x, 1);
+      const u32 first1 = __shfl(r.v[1].x, 0);
       if (lane == 63) {
         nx[0] = first1;
-        nx[1] = behind;
+        nx[1] = r.behind;
       }
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
-        w[4 * k + 0] = (u64)v[k].x | ((u64)v[k].y << 32);
-        w[4 * k + 1] = (u64)v[k].y | ((u64)v[k].z << 32);
-        w[4 * k + 2] = (u64)v[k].z | ((u64)v[k].w << 32);
-        w[4 * k + 3] = (u64)v[k].w | ((u64)nx[k] << 32);
+        w[4 * k + 0] = pair64(r.v[k].x, r.v[k].y);
+        w[4 * k + 1] = pair64(r.v[k].y, r.v[k].z);
+        w[4 * k + 2] = pair64(r.v[k].z, r.v[k].w);
+        w[4 * k + 3] = pair64(r.v[k].w, nx[k]);
       }
-    } else {  // the ragged tail, and sub-tiles past the end
+    } else {
 #pragma unroll
-      for (int r = 0; r < kWpl; ++r) {
-        const u64 q = wbase + ((r >> 2) * 64 + lane) * 4 + (r & 3);
-        w[r] = q < p.n_words ? ((u64)h[q] | ((u64)h[q + 1] << 32)) : span_lo - 1;  // outside the span
+      for (int i = 0; i < kWpl; ++i) {
+        const u64 q = wbase + ((i >> 2) * 64 + lane) * 4 + (i & 3);
+        w[i] = q < p.n_words ? pair64(h[q], h[q + 1]) : span_lo - 1;  // outside the span
       }
     }
-  } else if (wbase + kSub <= p.n_words) {
+  } else if (whole_sub<kHalf>(p, sub)) {
 #pragma unroll
     for (int k = 0; k < kLoads; ++k) {
-      // streamed once: non-temporal, so that the table levels keep their place in L2
-      typedef u64 v2u64 __attribute__((ext_vector_type(2)));
-      const v2u64 v =
-          __builtin_nontemporal_load(reinterpret_cast<const v2u64*>(p.words + wbase + (k * 64 + lane) * 2));
-      w[2 * k] = v.x;
-      w[2 * k + 1] = v.y;
+      w[2 * k] = pair64(r.v[k].x, r.v[k].y);
+      w[2 * k + 1] = pair64(r.v[k].z, r.v[k].w);
     }
-  } else {  // the ragged tail, and sub-tiles past the end (no word is read, none is a candidate)
+  } else {
 #pragma unroll
     for (int k = 0; k < kLoads; ++k) {
       const u64 idx = wbase + (k * 64 + lane) * 2;
@@ -286,6 +352,10 @@ __device__ __forceinline__ void load_words(const ScanParams& p, u32 sub, u64 spa
       w[2 * k + 1] = idx + 1 < p.n_words ? p.words[idx + 1] : span_lo - 1;
     }
   }
+}
+template <bool kHalf>
+__device__ __forceinline__ void load_words(const ScanParams& p, u32 sub, u64 span_lo, u64 (&w)[kWpl]) {
+  take_words<kHalf>(p, sub, span_lo, request_words<kHalf>(p, sub), w);
 }
 
 // Register r of a lane holds position (r / kPer * 64 + lane) * kPer + r % kPer of the sub-tile,
@@ -600,15 +670,44 @@ __device__ __forceinline__ u32 rank_candidates(u32 mask, Visit visit) {
   return Q;
 }
 
-// Ticket and turn are reset by whoever makes the launch's last draw: every workgroup has read
-// the turn before its first draw, so nobody looks at either again.
-__device__ __forceinline__ u32 flat_draw(const ScanParams& p, u32 turn, u32 last_draw) {
-  const u32 got = atomicAdd(p.ticket, 1u);
-  if (got == last_draw) {
-    __hip_atomic_store(p.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(p.turn, flat_next_turn(turn, p.n_chunks), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// How chunks are handed out.  A workgroup's first chunk is that of its own number, so that nothing stands between a
+// launch's begin and the request of its words; the others come from up to four queues, each with a counter in a memory
+// line of its own (additions to one line are served one after the other, 11.3 ns each).  Every workgroup draws from its
+// queue until that is empty, its first ticket being on its way while the keys are staged.  One queue for launches of many
+// chunks, whose workgroups wait for each other's less where they come in order, and for the smallest: us with one / four,
+// 0.8 M words 25.6 / 23.8 of a load, 3.7 M 91.3 / 89.7, 8.4 M positions 26.2 / 22.3; 2,185 chunks (300,007 allocations) 151.6 /
+// 156.2, 17,477 681 / 698.
+constexpr u32 kOneQueueChunks = 2048;
+struct ChunkQueue {
+  u32 n, q;  // queues, and this workgroup's
+  u32 more;  // chunks in it
+  u32 last;  // the draw after which nobody draws from it again
+};
+constexpr int kQueueStride = -128 / 4;
+__device__ __forceinline__ ChunkQueue chunk_queue(const ScanParams& p) {
+  ChunkQueue c;
+  c.n = gridDim.x >= 64 ? p.n_queues : 1;
+  c.q = blockIdx.x % c.n;
+  c.more = (p.n_chunks - gridDim.x + c.n - 1 - c.q) / c.n;
+  c.last = c.more + (gridDim.x + c.n - 1 - c.q) / c.n - 1;
+  return c;
+}
+__device__ __forceinline__ u32* counter_of(const ScanParams& p, const ChunkQueue& c) {
+  return p.queues + (int)c.q * kQueueStride;
+}
+__device__ __forceinline__ u32 draw(const ScanParams& p, const ChunkQueue& c) { return atomicAdd(counter_of(p, c), 1u); }
+// The chunk of a ticket.  Counters and turn are reset by whoever makes the last draw of all: every workgroup has read the
+// turn before its first draw, so nobody looks at any of them again.
+__device__ __forceinline__ u32 drawn_chunk(const ScanParams& p, const ChunkQueue& c, u32 turn, u32 got) {
+  if (got == c.last) {
+    auto zero = [](u32* at) { __hip_atomic_store(at, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    zero(counter_of(p, c));
+    if (c.n == 1 || atomicAdd(p.queues + 1, 1u) == c.n - 1) {
+      zero(p.queues + 1);
+      __hip_atomic_store(p.turn, flat_next_turn(turn, scan_states(p.n_chunks)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
   }
-  return got;
+  return got < c.more ? gridDim.x + got * c.n + c.q : p.n_chunks;
 }
 
 // A worker's sub-tile: round k's lane l has candidate 64 k + l.
@@ -718,48 +817,89 @@ __device__ __forceinline__ void stash_words(u64* stash, const u64 (&w)[kWpl]) {
   }
 }
 
+// The hits of a chunk, by one wave: for a workgroup that has waited too long for them.
+template <int kW, int kDepth, bool kHalf>
+__device__ __forceinline__ u32 count_chunk(const ScanParams& p, const FlatLevel& f, u32 chunk) {
+  u32 total = 0;
+  const u32 sh0 = 3 * p.levels + p.f0_log2;
+#pragma unroll 1
+  for (u32 i = 0; i < (u32)kW * kWpl; ++i) {
+    const u64 at = ((u64)chunk * kW + i / kWpl) * kSub + (i % kWpl) * 64 + lane_id();
+    const u64 d[1] = {at < p.n_words ? word_at<kHalf>(p, at) - f.span_lo : ~0ull};
+    bool hit = false;
+    if (d[0] < f.span_len) {
+      u32 key[1];
+      flat_place<1>(f, d, key, [](bool b) { return ballot(b) != 0; });
+      const u64 w = d[0] + f.span_lo, unit = key[0] >> 2;
+      u32 lo = (u32)(unit << sh0), hi = p.n_alloc - lo < (1ull << sh0) ? p.n_alloc : lo + (1u << sh0), n;
+      if (p.table[lo].base > w) {  // (truncated keys lead too far)
+        hi = lo ? lo : 1;
+        lo = 0;
+      }
+      u64x2 e;
+      find_exact(p.table, lo, hi, w, n, e);
+      hit = w - e.x < e.y;
+    }
+    total += __popcll(ballot(hit));
+  }
+  return total;
+}
+
 // The ordered scan.
 template <int kW, int kDepth, bool kHalf, bool kOut>
 __global__ __launch_bounds__((kW + 1) * 64) void scan_kernel(ScanParams p) {
-  constexpr u32 kThreads = (kW + 1) * 64;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  __shared__ u32 s_next[2], s_cnt[2][kW], s_turn;
+  __shared__ u32 s_next[2], s_cnt[2][kW], s_sum[2];
   __shared__ u64 s_excl[2];
+  __shared__ FlatStates s_states;
   const u32 tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const bool clerk = wave == kW;
   u32 turn = 0;  // (lies in the prepared table's first block, which the check reads too)
   if (clerk) turn = __hip_atomic_load(p.turn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (!prepared_ok(p)) {  // every workgroup sees the same: nothing is read or written
+  u32 chunk = blockIdx.x;
+  Words<kHalf> raw = {};
+  // Small workgroups request their words ahead of everything; those of many workers behind the keys, which would wait for
+  // 60 KB of them.  (us of a load ahead / behind: 217 workgroups of seven workers 23.5 / 24.1, 256 of fifteen 61.8 / 61.1.)
+  constexpr bool kAhead = kW == (int)kFlatWorkers;
+  if (kAhead && !clerk) raw = request_words<kHalf>(p, chunk * kW + wave);
+  FlatRegion region = p.region;  // (the header's first block as well)
+  if (p.prepared) region = FlatRegion{(long long)p.prepared[4], (u32)p.prepared[5]};
+  if (!prepared_ok(p)) {  // every workgroup sees the same: nothing is written
     if (blockIdx.x == 0 && tid == 0) raise_status(p.d_status, FDY_ST_BAD_PREPARED);
     return;
   }
-  const bool single = gridDim.x >= p.n_chunks;  // every workgroup's first draw is its only chunk
-  // the draw after which nobody draws again
-  const u32 last_draw = single ? gridDim.x - 1 : p.n_chunks + gridDim.x - 1;
-  if (clerk && lane == 0) {
+  const ChunkQueue queue = chunk_queue(p);
+  u32 got = 0;
+  FlatTurn t;
+  FlatStates states;
+  const u32 n_states = scan_states(p.n_chunks);
+  if (clerk) {  // meanwhile the others stage the keys
     asm volatile("" : "+v"(turn) : : "memory");  // the turn has arrived before the draw goes out
-    s_turn = turn;
-    s_next[0] = flat_draw(p, turn, last_draw);
+    if (lane == 0) got = draw(p, queue);
+    t = flat_turn(uniform(turn), n_states, region.states);
+    states = FlatStates{reinterpret_cast<u64*>(reinterpret_cast<unsigned char*>(p.cstate) + region.first), t.s, t.parity};
+    if (lane == 0) {
+      s_sum[0] = s_sum[1] = 0;
+      s_states = states;
+    }
+  } else {
+    (void)flat_stage<kW * 64>(p, smem_raw, tid, false);
   }
-  const FlatLevel f = flat_stage<kThreads>(p, smem_raw, tid, false);
+  if (!kAhead && !clerk) raw = request_words<kHalf>(p, chunk * kW + wave);
+  const FlatLevel f = flat_level(p, smem_raw);
   __syncthreads();
-  u32 chunk = s_next[0];
   if (clerk) {
-    FlatRegion region = p.region;
-    if (p.prepared) region = FlatRegion{(long long)p.prepared[4], (u32)p.prepared[5]};
-    const FlatTurn t = flat_turn(s_turn, p.n_chunks, region.states);
-    const FlatStates states{reinterpret_cast<u64*>(reinterpret_cast<unsigned char*>(p.cstate) + region.first), t.s,
-                            t.parity ? kFlatParity : 0ull};
     for (u32 i = blockIdx.x * 64 + lane; i < t.dirty; i += gridDim.x * 64) {
-      const u32 at = flat_to_clear(t, i, p.n_chunks);
+      const u32 at = flat_to_clear(t, i, n_states);
       if (at != ~0u) st_state(&states.at[at], 0);
     }
     u32 prev = 0, prev_total = 0, b = 1;
     // the exclusive prefix of the chunk before, for the workers that wait to write it
-    auto close = [&](u32 slot) {
-      const u64 excl = exclusive_prefix(states, prev, p.spin_limit, p.d_status);
+    auto close = [&](u32 slot, auto meanwhile) __attribute__((always_inline)) {
+      const u64 excl = exclusive_prefix(states, prev, p.spin_limit, p.patience, p.d_status,
+                                        [&](u32 c) { return count_chunk<kW, kDepth, kHalf>(p, f, c); }, meanwhile);
       if (lane == 0) {
-        if (prev != 0) states.store(prev, kFlagInc | (excl + prev_total));
+        if ((prev & 15) == 15) st_state(states.place(sum_state(prev >> 4)), make_sum(excl + prev_total, states.parity));
         if (prev + 1 == p.n_chunks) {  // the last chunk: the grand total
           *p.d_count = excl + prev_total;
           if (excl + prev_total > p.capacity) raise_status(p.d_status, FDY_ST_CAPACITY);
@@ -769,22 +909,28 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_kernel(ScanParams p) {
     };
     bool have_prev = false;
     for (; chunk < p.n_chunks; b ^= 1) {
-      u32 next = p.n_chunks;
-      if (lane == 0 && !single) next = flat_draw(p, turn, last_draw);
-      if (have_prev) close(b);
-      if (lane == 0) s_next[b] = next;
+      if (lane == 0 && have_prev) got = draw(p, queue);
+      auto tell = [&] {  // (an empty queue's only ticket is not waited for)
+        if (lane == 0) s_next[b] = queue.more ? drawn_chunk(p, queue, turn, got) : p.n_chunks;
+      };
+      if (have_prev) close(b, tell);
+      else tell();
+      if (lane == 0 && queue.more == 0) (void)drawn_chunk(p, queue, turn, got);
       __syncthreads();
       u32 total = 0;
 #pragma unroll
       for (int i = 0; i < kW; ++i) total += s_cnt[b][i];
-      if (lane == 0) states.store(chunk, (chunk == 0 ? kFlagInc : kFlagAgg) | total);
+      if (chunk + 1 == p.n_chunks) {  // what the last sixteenth has no chunks for is nobody else's to write
+        if (lane > (chunk & 15) && lane < 16) states.store_field((chunk & ~15u) + lane, 0);
+        if (lane == 16 && (chunk & 15) != 15) st_state(states.place(sum_state(chunk >> 4)), 0);
+      }
       prev = chunk;
       prev_total = total;
       have_prev = true;
       chunk = s_next[b];
     }
     if (have_prev) {
-      close(b);
+      close(b, [] {});
       __syncthreads();
     }
     return;
@@ -814,14 +960,14 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_kernel(ScanParams p) {
   };
   Forms m = pick_forms<kDepth>(p);
   if constexpr (kDepth == 1) m.settle = units_share_keys(f, p.n_lines);
-  u64 w[kWpl];
-  load_words<kHalf>(p, chunk * kW + wave, f.span_lo, w);
   Results cur, prev;
   u32 prev_before = 0, b = 1;
   bool have_prev = false;
   for (; chunk < p.n_chunks; b ^= 1) {
     cur.sub = chunk * kW + wave;
     cur.H = 0;
+    u64 w[kWpl];
+    take_words<kHalf>(p, cur.sub, f.span_lo, raw, w);
     if constexpr (kOut) stash_words<kHalf>(stash, w);
     cur.Q = rank_candidates<kHalf>(flat_candidates(f, w), [&](int k, u32 rank) {
       places[rank] = (unsigned short)pos_in_sub<kHalf>(k, lane);
@@ -831,10 +977,19 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_kernel(ScanParams p) {
     if constexpr (kDepth != 0) count_marked(m, cur.Q);
     wave_lds_fence();
     if constexpr (kOut) unstash_words(p, cur.sub, stash);
-    if (lane == 0) s_cnt[b][wave] = cur.H;
+    if (lane == 0) {
+      s_cnt[b][wave] = cur.H;
+      // the last of the workers tells the chunk's hits, ahead of the barrier and of what the others request behind it
+      const u32 sum = atomicAdd(&s_sum[b], 1u << 16 | cur.H) + (1u << 16 | cur.H);
+      if (sum >> 16 == (u32)kW) {
+        s_sum[b ^ 1] = 0;
+        const FlatStates st = s_states;
+        st.store_field(chunk, make_field(sum & 0xffffu, st.parity));
+      }
+    }
     __syncthreads();  // counts, the next ticket and the previous chunk's prefix are visible
     chunk = s_next[b];
-    load_words<kHalf>(p, chunk * kW + wave, f.span_lo, w);  // in flight during the write
+    raw = request_words<kHalf>(p, chunk * kW + wave);  // in flight during the write
     u32 before = 0;
 #pragma unroll
     for (int i = 0; i < kW; ++i) before += (u32)i < wave ? s_cnt[b][i] : 0;
@@ -1366,7 +1521,7 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
     if (!fused) {
       region = flat_region(n_sub, tp.spare, workspace_bytes - kStateHeader - tp.bytes);
       a.cstate = cstate + region.first / 8;
-      a.n_states = flat_extent(flat_spread(n_chunks, region.states), n_chunks);
+      a.n_states = flat_extent(flat_spread(scan_states(n_chunks), region.states), scan_states(n_chunks));
     }
     a.d_count = nothing ? (u64*)d_count : nullptr;
     const u32 n_init = init_threads(tp, a.n_states);
@@ -1389,8 +1544,11 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
   p.relocs = d_relocs;
   p.capacity = reloc_capacity;
   p.d_count = (u64*)d_count;
-  // state: counter 0 = ticket, 2..3 = hit accumulator (64 bits), 8 = turn (a prepared table's lies in its header)
-  p.ticket = (u32*)state;
+  // state: 2..3 = hit accumulator (64 bits), 8 = turn, 56 and 24 = queues.  A prepared table's turn and queues lie in its
+  // first 512 bytes, which are four memory lines with room in them.
+  p.queues = d_prepared ? (u32*)const_cast<void*>(d_prepared) + 120 : (u32*)state + 56;
+  p.n_queues = n_chunks > kOneQueueChunks ? 1 : d_prepared ? 4 : 2;
+  p.patience = (u32)fdy__tune_get(FDY_TUNE_SCAN_PATIENCE);
   p.acc = (u64*)state + 1;
   p.turn = d_prepared ? (u32*)const_cast<void*>(d_prepared) + kPreparedTurn / 4 : (u32*)state + 8;
   p.region = region;
