@@ -87,26 +87,46 @@ __device__ __forceinline__ u32 wave_lower_bound(KeyFn key, u32 lo, u32 hi, u64 t
   return lo;
 }
 
+// What another lane holds, by the data-parallel primitives of the vector unit: a shift to the right by 1, 2, 4 or 8 within
+// rows of 16 lanes, or the last lane of the row (of the half) before for the rows in kRows; `otherwise` in lanes that have no
+// such neighbour.  All lanes of the wave take part.  (Through LDS, as __shfl_up goes, six steps of three 64-bit sums wait for
+// each other and for those of the compute unit's other waves: 3 to 7 us of a prep launch for 512 graphs, 2 to 5 now.  us of
+// whole loads, through LDS / now: sums of graphs, 67 graphs 23.4 / 22.6, to 8 ranks 88.5 / 87.9, derivation 44.3 / 43.2;
+// the fold of fingerprints as well 67 graphs 22.6 / 22.2, of 2,632 nodes 87.3 / 86.3, 512 graphs 60.1 / 58.8, one of 512
+// nodes 16.9 / 15.8.)
+template <int kCtrl, int kRows = 0xf>
+__device__ __forceinline__ u32 dpp(u32 v, u32 otherwise) {
+  return (u32)__builtin_amdgcn_update_dpp((int)otherwise, (int)v, kCtrl, kRows, 0xf, false);
+}
+template <int kCtrl, int kRows = 0xf>
+__device__ __forceinline__ u64 dpp(u64 v, u64 otherwise) {
+  return pair64(dpp<kCtrl, kRows>((u32)v, (u32)otherwise), dpp<kCtrl, kRows>((u32)(v >> 32), (u32)(otherwise >> 32)));
+}
+constexpr int kShr1 = 0x111, kShr2 = 0x112, kShr4 = 0x114, kShr8 = 0x118;  // row_shr
+constexpr int kOfRow = 0x142, kOfHalf = 0x143;                            // row_bcast:15 (rows 1 and 3), :31 (rows 2 and 3)
+
+// Inclusive scan of a value per lane over a wave.
+template <typename T>
+__device__ __forceinline__ T wave_incl_scan(T v) {
+  v += dpp<kShr1>(v, (T)0);
+  v += dpp<kShr2>(v, (T)0);
+  v += dpp<kShr4>(v, (T)0);
+  v += dpp<kShr8>(v, (T)0);
+  v += dpp<kOfRow, 0xa>(v, (T)0);
+  v += dpp<kOfHalf, 0xc>(v, (T)0);
+  return v;
+}
+
 // Exclusive scan of one u64 per thread over a workgroup of whole waves (at most 1024 threads);
 // returns the exclusive prefix and sets `total` (same in every thread).  s_buf: 17 u64 of LDS.
 __device__ inline u64 block_excl_scan(u64 v, u64* s_buf, u64& total) {
   const u32 l = lane_id(), w = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
-  u64 inc = v;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const u64 o = __shfl_up(inc, d);
-    if (l >= (u32)d) inc += o;
-  }
+  const u64 inc = wave_incl_scan(v);
   if (l == 63) s_buf[w] = inc;
   __syncthreads();
   if (w == 0) {
     const u64 x = l < n_waves ? s_buf[l] : 0;
-    u64 xi = x;
-#pragma unroll
-    for (int d = 1; d < 16; d <<= 1) {
-      const u64 o = __shfl_up(xi, d);
-      if (l >= (u32)d) xi += o;
-    }
+    const u64 xi = wave_incl_scan(x);
     if (l < 16) s_buf[l] = xi - x;
     if (l == 15) s_buf[16] = xi;
   }

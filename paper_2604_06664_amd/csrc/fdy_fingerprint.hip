@@ -358,29 +358,29 @@ __global__ __launch_bounds__(kFpBlock) void fp_key_kernel(FpArgs a) {
   while (i + 4 <= hi) fold(std::integral_constant<int, 4>{});
   if (i + 2 <= hi) fold(std::integral_constant<int, 2>{});
   if (i < hi) fold(std::integral_constant<int, 1>{});
-  // ordered reduction inside the wave: lane l absorbs lane l+d (its right neighbour block)
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    Seg r;
-    r.v = __shfl_down(s.v, d);
-    r.p = __shfl_down(s.p, d);
-    if ((lane_id() & (2 * d - 1)) == 0) s = combine(s, r);
-  }
-  if (lane_id() == 0) s_seg[tid >> 6] = s;
+  // ordered reduction inside the wave: a lane is absorbed by its right neighbour, the last lane has all of them
+  auto absorb = [&](auto ctrl, auto rows) __attribute__((always_inline)) {
+    constexpr int kCtrl = decltype(ctrl)::value, kRows = decltype(rows)::value;
+    s = combine(Seg{dpp<kCtrl, kRows>(s.v, (u64)0), dpp<kCtrl, kRows>(s.p, (u64)1)}, s);
+  };
+  using std::integral_constant;
+  absorb(integral_constant<int, kShr1>{}, integral_constant<int, 0xf>{});
+  absorb(integral_constant<int, kShr2>{}, integral_constant<int, 0xf>{});
+  absorb(integral_constant<int, kShr4>{}, integral_constant<int, 0xf>{});
+  absorb(integral_constant<int, kShr8>{}, integral_constant<int, 0xf>{});
+  absorb(integral_constant<int, kOfRow>{}, integral_constant<int, 0xa>{});
+  absorb(integral_constant<int, kOfHalf>{}, integral_constant<int, 0xc>{});
+  if (lane_id() == 63) s_seg[tid >> 6] = s;
   __syncthreads();
   Seg t{0, 1};
   if (tid < 64) {  // the waves' segments, again as a tree (one after the other 0.4 us longer)
     static_assert(kFpBlock / 64 == 8, "three steps");
     t = s_seg[tid & 7];
-#pragma unroll
-    for (int d = 1; d < 8; d <<= 1) {
-      Seg r;
-      r.v = __shfl_down(t.v, d);
-      r.p = __shfl_down(t.p, d);
-      if ((tid & (2 * d - 1)) == 0) t = combine(t, r);
-    }
+    t = combine(Seg{dpp<kShr1>(t.v, (u64)0), dpp<kShr1>(t.p, (u64)1)}, t);
+    t = combine(Seg{dpp<kShr2>(t.v, (u64)0), dpp<kShr2>(t.p, (u64)1)}, t);
+    t = combine(Seg{dpp<kShr4>(t.v, (u64)0), dpp<kShr4>(t.p, (u64)1)}, t);
   }
-  if (tid == 0) {
+  if (tid == 7) {  // (lanes 0 to 7 of the first row hold the eight in order)
     const u64 key = mix(mix(N) * t.p + t.v);
     if (G == 1) {
       a.keys[g] = key;

@@ -193,12 +193,7 @@ __device__ __forceinline__ void block_excl_scan3(u64 (&v)[3], u64 (&total)[3], u
   const u32 l = lane_id(), w = threadIdx.x >> 6;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    u64 inc = v[k];
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const u64 o = __shfl_up(inc, d);
-      if (l >= (u32)d) inc += o;
-    }
+    const u64 inc = wave_incl_scan(v[k]);
     if (l == 63) s_buf[k * 4 + w] = inc;
     v[k] = inc - v[k];
   }

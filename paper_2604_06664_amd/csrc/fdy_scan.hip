@@ -230,9 +230,7 @@ __device__ __forceinline__ u64 exclusive_prefix(const FlatStates& states, u32 ch
       }
       if (missing) v = ld_state(states.place(fields_state(4 * (q - l))));  // (the others' are there)
     }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) hits += __shfl_xor(hits, d);
-    excl += hits;
+    excl += (u32)__builtin_amdgcn_readlane((int)wave_incl_scan(hits), 63);
     if (known) {
       const u64 s = sum_hits(sum);
       excl += (u64)(u32)__shfl((u32)s, (int)back) | (u64)(u32)__shfl((u32)(s >> 32), (int)back) << 32;
