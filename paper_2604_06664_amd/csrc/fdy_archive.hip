@@ -17,6 +17,8 @@
 
 #include <algorithm>
 #include <new>
+#include <system_error>
+#include <thread>
 #include <utility>
 #include <vector>
 
@@ -91,14 +93,16 @@ extern "C" uint32_t fdy_archive_elem_bytes(uint32_t kind) {
   }
 }
 
-extern "C" uint64_t fdy_archive_sum(const void* h_bytes, size_t n) {
-  const unsigned char* p = static_cast<const unsigned char*>(h_bytes);
+namespace {
+
+// The sum of n bytes as they would count behind `before` words of a section; with a partial last word only at its end.
+uint64_t sum_behind(const unsigned char* p, size_t n, uint64_t before) {
   const size_t k = n / 8;
   // Word i counts 2 i + 1 times.  In rows of kLanes words that takes no multiplication: with S the sum
   // of a column's words so far and T the sum of those S, a column of R rows has T = sum of (R - m) times
   // its word of row m.  Columns side by side are vector additions (16 bytes: what every host of
   // this library has), where a 64-bit product per word was bound by the multiplier: opening 11 MB
-  // from the page cache took 301 us, 131 now.  (All pages mapped ahead by MADV_POPULATE_READ: 152.)
+  // from the page cache took 301 us, 131 then.  (All pages mapped ahead by MADV_POPULATE_READ: 152.)
   typedef uint64_t pair __attribute__((vector_size(16)));
   constexpr size_t kPairs = 4, kLanes = 2 * kPairs;
   pair S[kPairs] = {}, T[kPairs] = {};
@@ -115,20 +119,56 @@ extern "C" uint64_t fdy_archive_sum(const void* h_bytes, size_t n) {
   uint64_t s0 = 0;
   for (size_t j = 0; j < kLanes; ++j) {
     const uint64_t sum = S[j / 2][j % 2];
-    s0 += 2 * kLanes * (rows * sum - T[j / 2][j % 2]) + (2 * j + 1) * sum;
+    s0 += 2 * kLanes * (rows * sum - T[j / 2][j % 2]) + (2 * (j + before) + 1) * sum;
   }
   size_t i = rows * kLanes;
   for (; i < k; ++i) {
     uint64_t w;
     memcpy(&w, p + i * 8, 8);
-    s0 += w * (2 * (uint64_t)i + 1);
+    s0 += w * (2 * (i + before) + 1);
   }
   if (n % 8) {
     uint64_t w = 0;
     memcpy(&w, p + k * 8, n % 8);
-    s0 += w * (2 * (uint64_t)k + 1);
+    s0 += w * (2 * (k + before) + 1);
   }
   return s0;
+}
+
+// Calls part(i) for i < parts, side by side: the first on the caller's thread, the others each on one of their own, which
+// has ended when this returns.  A thread that cannot be had: its part is the caller's.  (Threads that wait between the
+// calls would have to be given back, and would not be there after a fork.)
+constexpr uint32_t kMostParts = 4;
+template <typename Part>
+void side_by_side(uint32_t parts, const Part& part) {
+  std::thread others[kMostParts];
+  for (uint32_t i = 1; i < parts; ++i) {
+    try {
+      others[i] = std::thread([&part, i] { part(i); });
+    } catch (const std::system_error&) {
+    } catch (const std::bad_alloc&) {
+    }
+  }
+  part(0);
+  for (uint32_t i = 1; i < parts; ++i) {
+    if (others[i].joinable()) others[i].join();
+    else part(i);
+  }
+}
+// How many parts are worth a thread each.  us, 11 MB from the page cache, one / three / four / eight parts: opened with all sums
+// 131 / 81 / 79 / 126, content check 155 / 84 / 73 / 95, the whole load of the file 730 / 566 / 534 / 590; below 2 MB (which
+// takes 26 and 17) a thread costs what it saves.
+uint32_t parts_of(uint64_t bytes) {
+  const uint64_t n = std::min<uint64_t>(bytes / (1u << 20), kMostParts);
+  if (n < 2) return 1;
+  const uint64_t cpus = std::thread::hardware_concurrency();  // (2 us to ask)
+  return (uint32_t)(cpus && cpus < n ? cpus : n);
+}
+
+}  // namespace
+
+extern "C" uint64_t fdy_archive_sum(const void* h_bytes, size_t n) {
+  return sum_behind(static_cast<const unsigned char*>(h_bytes), n, 0);
 }
 
 namespace {
@@ -312,9 +352,27 @@ extern "C" int fdy_archive_open(const char* path, uint32_t flags, fdy_archive** 
   for (int& s : a->slot) s = -1;
   for (uint32_t i = 0; i < h.n_sections; ++i) a->slot[a->dir[i].kind] = (int)i;
   if (flags & FDY_ARCHIVE_VERIFY_SUMS) {
+    // (the sections one behind the other, cut into parts of a size)
+    uint64_t total = 0;
+    for (uint32_t i = 0; i < h.n_sections; ++i) total += a->dir[i].count * a->dir[i].elem_bytes;
+    const uint32_t parts = parts_of(total);
+    uint64_t sums[kMostParts][FDY_ARCHIVE_MAX_SECTIONS] = {};
+    side_by_side(parts, [&](uint32_t k) {
+      const uint64_t lo = total / parts * k, hi = k + 1 == parts ? total : total / parts * (k + 1);
+      uint64_t at = 0;  // where the section begins
+      for (uint32_t i = 0; i < h.n_sections; ++i) {
+        const uint64_t n = a->dir[i].count * a->dir[i].elem_bytes;
+        const auto inside = [&](uint64_t x) { return x <= at ? 0 : x >= at + n ? n : (x - at) / 64 * 64; };
+        const uint64_t from = inside(lo), to = inside(hi);
+        if (from < to) sums[k][i] = sum_behind(a->map + a->dir[i].offset + from, (size_t)(to - from), from / 8);
+        at += n;
+      }
+    });
     for (uint32_t i = 0; i < h.n_sections; ++i) {
       const DirEntry& e = a->dir[i];
-      if (fdy_archive_sum(a->map + e.offset, (size_t)(e.count * e.elem_bytes)) != e.sum) {
+      uint64_t sum = 0;
+      for (uint32_t k = 0; k < parts; ++k) sum += sums[k][i];
+      if (sum != e.sum) {
         char text[96];
         snprintf(text, sizeof text, "section %s: sum does not match", kind_name(e.kind));
         return reject(FDY_ERR_CHECKSUM, text);
@@ -374,6 +432,35 @@ const char* offsets_violation(const View<uint64_t>& off, uint64_t len, uint64_t 
   return nullptr;
 }
 
+// The nodes and relocations of source graphs [from, to), as content_check wants them.  (Without a branch per condition:
+// four times as long.)
+struct Graphs {
+  View<fdy_alloc> table;
+  View<uint64_t> words, word_off, node_off, reloc_off;
+  View<fdy_node> nodes;
+  View<fdy_reloc> relocs;
+};
+bool graphs_ok(const Graphs& a, uint64_t from, uint64_t to) {
+  for (uint64_t s = from; s < to; ++s) {
+    uint64_t blob_bytes = 0;
+    for (uint64_t i = a.node_off[s]; i < a.node_off[s + 1]; ++i) {
+      if (a.nodes[i].blob_len % 8) return false;
+      blob_bytes += a.nodes[i].blob_len;
+    }
+    const uint64_t w_lo = a.word_off[s], w_hi = a.word_off[s + 1];
+    if (blob_bytes != (w_hi - w_lo) * 8) return false;
+    uint64_t least = w_lo;  // of the next entry's word
+    for (uint64_t i = a.reloc_off[s]; i < a.reloc_off[s + 1]; ++i) {
+      const fdy_reloc& r = a.relocs[i];
+      if (r.word < least || r.word >= w_hi) return false;
+      least = (uint64_t)r.word + 1;
+      if (r.region >= a.table.n || r.offset >= a.table[r.region].size) return false;
+      if (a.words[r.word] != a.table[r.region].base + r.offset) return false;
+    }
+  }
+  return true;
+}
+
 int content_check(const fdy_archive* a, fdy_archive_info* out) {
   const auto bad = [](const char* fmt, auto... args) { return fail(FDY_ERR_CONTENT, fmt, args...); };
   const auto table = view<fdy_alloc>(a, FDY_SEC_TABLE);
@@ -412,7 +499,19 @@ int content_check(const fdy_archive* a, fdy_archive_info* out) {
   if (const char* v = offsets_violation(node_off, S + 1, nodes.n)) return bad("NODE_OFF %s", v);
   if (const char* v = offsets_violation(reloc_off, S + 1, relocs.n)) return bad("RELOC_OFF %s", v);
 
-  for (uint64_t s = 0; s < S; ++s) {
+  // Large archives have their graphs looked at side by side, cut where their relocations are even; whatever is wrong is
+  // then found, and named, one after the other.
+  const Graphs graphs{table, words, word_off, node_off, reloc_off, nodes, relocs};
+  const uint32_t parts = parts_of(relocs.n * sizeof(fdy_reloc) + nodes.n * sizeof(fdy_node));
+  bool ok[kMostParts] = {};
+  side_by_side(parts, [&](uint32_t i) {
+    const auto cut = [&](uint32_t i) {
+      if (i == 0 || i == parts) return i ? S : 0;
+      return (uint64_t)(std::lower_bound(reloc_off.p, reloc_off.p + S, relocs.n * i / parts) - reloc_off.p);
+    };
+    ok[i] = graphs_ok(graphs, cut(i), cut(i + 1));
+  });
+  if (!std::all_of(ok, ok + parts, [](bool b) { return b; })) for (uint64_t s = 0; s < S; ++s) {
     uint64_t blob_bytes = 0;
     for (uint64_t i = node_off[s]; i < node_off[s + 1]; ++i) {
       if (nodes[i].blob_len % 8) return bad("NODES: node %llu has a blob length that is not a multiple of 8", (unsigned long long)i);
