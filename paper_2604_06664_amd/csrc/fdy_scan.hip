@@ -169,16 +169,20 @@ __device__ __forceinline__ bool spin_once(u32& spins, u32 spin_limit, u32* d_sta
   return true;
 }
 
+__device__ __forceinline__ void st_field(unsigned short* p, u32 field) {
+  __hip_atomic_store(p, (unsigned short)field, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // The states of a launch of the flat scan.
 struct FlatStates {
   u64* at;  // the region's first state
   u32 s;    // spread (see state_at)
   u32 parity;
   __device__ __forceinline__ u64* place(u32 i) const { return &at[state_at(s, i)]; }
-  __device__ __forceinline__ void store_field(u32 chunk, u32 field) const {
-    unsigned short* q = reinterpret_cast<unsigned short*>(place(fields_state(chunk))) + (chunk & 3);
-    __hip_atomic_store(q, (unsigned short)field, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __device__ __forceinline__ unsigned short* field_of(u32 chunk) const {
+    return reinterpret_cast<unsigned short*>(place(fields_state(chunk))) + (chunk & 3);
   }
+  __device__ __forceinline__ void store_field(u32 chunk, u32 field) const { st_field(field_of(chunk), field); }
 };
 
 // The number of hits in all chunks before `chunk`.  Lane l looks at the four fields of one state, the first sixteen also at
@@ -849,7 +853,7 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_kernel(ScanParams p) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   __shared__ u32 s_next[2], s_cnt[2][kW], s_sum[2];
   __shared__ u64 s_excl[2];
-  __shared__ FlatStates s_states;
+  __shared__ u64 s_field[2];  // where the chunk tells its hits, and in the lowest bit the parity
   const u32 tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const bool clerk = wave == kW;
   u32 turn = 0;  // (lies in the prepared table's first block, which the check reads too)
@@ -859,6 +863,10 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_kernel(ScanParams p) {
   // Small workgroups request their words ahead of everything; those of many workers behind the keys, which would wait for
   // 60 KB of them.  (us of a load ahead / behind: 217 workgroups of seven workers 23.5 / 24.1, 256 of fifteen 61.8 / 61.1.)
   constexpr bool kAhead = kW == (int)kFlatWorkers;
+  // Who tells a chunk's hits: the last of many workers, ahead of the barrier, or the clerk of few behind it.  us by the
+  // clerk / by the last worker: seven workers, 0.5 M words 7.4 / 7.6, 0.3 M positions at 4-byte stride 6.2 / 6.5; fifteen, 2^27
+  // words with output 681 / 673.
+  constexpr bool kWorkersTell = kW != (int)kFlatWorkers;
   if (kAhead && !clerk) raw = request_words<kHalf>(p, chunk * kW + wave);
   FlatRegion region = p.region;  // (the header's first block as well)
   if (p.prepared) region = FlatRegion{(long long)p.prepared[4], (u32)p.prepared[5]};
@@ -878,7 +886,7 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_kernel(ScanParams p) {
     states = FlatStates{reinterpret_cast<u64*>(reinterpret_cast<unsigned char*>(p.cstate) + region.first), t.s, t.parity};
     if (lane == 0) {
       s_sum[0] = s_sum[1] = 0;
-      s_states = states;
+      s_field[1] = (u64)states.field_of(chunk) | states.parity;
     }
   } else {
     (void)flat_stage<kW * 64>(p, smem_raw, tid, false);
@@ -909,7 +917,10 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_kernel(ScanParams p) {
     for (; chunk < p.n_chunks; b ^= 1) {
       if (lane == 0 && have_prev) got = draw(p, queue);
       auto tell = [&] {  // (an empty queue's only ticket is not waited for)
-        if (lane == 0) s_next[b] = queue.more ? drawn_chunk(p, queue, turn, got) : p.n_chunks;
+        if (lane != 0) return;
+        const u32 next = queue.more ? drawn_chunk(p, queue, turn, got) : p.n_chunks;
+        s_next[b] = next;
+        if (kWorkersTell && next < p.n_chunks) s_field[b ^ 1] = (u64)states.field_of(next) | states.parity;
       };
       if (have_prev) close(b, tell);
       else tell();
@@ -918,6 +929,7 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_kernel(ScanParams p) {
       u32 total = 0;
 #pragma unroll
       for (int i = 0; i < kW; ++i) total += s_cnt[b][i];
+      if (!kWorkersTell && lane == 0) states.store_field(chunk, make_field(total, states.parity));
       if (chunk + 1 == p.n_chunks) {  // what the last sixteenth has no chunks for is nobody else's to write
         if (lane > (chunk & 15) && lane < 16) states.store_field((chunk & ~15u) + lane, 0);
         if (lane == 16 && (chunk & 15) != 15) st_state(states.place(sum_state(chunk >> 4)), 0);
@@ -978,11 +990,13 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_kernel(ScanParams p) {
     if (lane == 0) {
       s_cnt[b][wave] = cur.H;
       // the last of the workers tells the chunk's hits, ahead of the barrier and of what the others request behind it
-      const u32 sum = atomicAdd(&s_sum[b], 1u << 16 | cur.H) + (1u << 16 | cur.H);
-      if (sum >> 16 == (u32)kW) {
-        s_sum[b ^ 1] = 0;
-        const FlatStates st = s_states;
-        st.store_field(chunk, make_field(sum & 0xffffu, st.parity));
+      if constexpr (kWorkersTell) {
+        const u64 to = s_field[b];
+        const u32 sum = atomicAdd(&s_sum[b], 1u << 16 | cur.H) + (1u << 16 | cur.H);
+        if (sum >> 16 == (u32)kW) {
+          s_sum[b ^ 1] = 0;
+          st_field(reinterpret_cast<unsigned short*>(to & ~1ull), make_field(sum & 0xffffu, (u32)to & 1));
+        }
       }
     }
     __syncthreads();  // counts, the next ticket and the previous chunk's prefix are visible
