@@ -19,8 +19,8 @@
 //      eight entries (fdy_lines.hpp), or the table entry itself where level 0 has every base;
 //      where truncated keys lead a word too far, exact bases of what the keys stand for settle it;
 //      what became of a candidate stays in registers, 64 bits each;
-//   4. posts its hits, the last of the workers those of the chunk to everybody; one barrier per chunk makes them and the
-//      next ticket visible.
+//   4. posts its hits, the last of fifteen workers those of the chunk to everybody (of seven: the clerk does, behind the
+//      barrier); one barrier per chunk makes them and the next ticket visible.
 // The sixteenth wave, the clerk, owns no words: it draws the tickets and finds the chunk's output
 // position by a decoupled look-back over what the chunks say of themselves (16 bits each, four to a word, and the hits so
 // far behind every sixteenth: one step looks at 256 chunks, which is what is in flight) while the others search the next
