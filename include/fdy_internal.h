@@ -28,9 +28,7 @@ enum {
                                  * tiles streams templates and relocation lists past the L2s  */
   FDY_TUNE_MAT_MOST_BLOCKS = 7, /* most blocks that a materialize launch has for tiles, and    *
                                  * for patch slices; more take further launches, or rounds    */
-  FDY_TUNE_SCAN_PATIENCE = 8,   /* polls after which a scan's workgroup counts the hits of a       *
-                                 * chunk that it waits for itself                              */
-  FDY_TUNE_COUNT = 9
+  FDY_TUNE_COUNT = 8
 };
 
 int fdy__tune_get(int knob);

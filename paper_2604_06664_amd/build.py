@@ -33,7 +33,7 @@ def build_lib(verbose=False):
 
 
 TOY_SRC = [os.path.join(ROOT, "tests", "toy_graph", f) for f in ("toy_graph.hip", "install_scale.hip",
-                                                                "arena_graph.hip")]
+                                                                "arena_graph.hip", "hold_units.hip")]
 TOY_LIB = os.path.join(ROOT, "tests", "toy_graph", "libtoy_graph.so")
 
 

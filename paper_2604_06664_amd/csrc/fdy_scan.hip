@@ -7,8 +7,7 @@
 //
 // Work decomposition.  Persistent workgroups, one per compute unit, stage the top level of the
 // table's hierarchy in LDS once.  Words come in sub-tiles of 512; a chunk is a sub-tile for each
-// of the workgroup's 15 (small inputs: 7) workers; a workgroup's first is that of its own number, further ones are
-// handed out by atomic tickets.  A worker
+// of the workgroup's 15 (small inputs: 7) workers, handed out by an atomic ticket.  A worker
 //   1. takes its 8 words per lane (16-byte coalesced non-temporal loads) and rejects every word
 //      outside the table's span;
 //   2. queues the surviving candidates and their places in LDS, in word order (ballot ranks), so
@@ -46,9 +45,8 @@
 //   the largest tables' rounds one by one but for sub-tiles with few candidates                685 / 67 / 158
 //   positions by one step over 256 chunks, not by 64 at a time; hits told by the last worker    671 / 65 / 150
 // A small launch is a chain of waits.  us of scans alone, one after the other, a quarter pointers, 4,096 allocations, 0.3 /
-// 0.7 / 1.2 / 1.7 M words: 7.7 / 9.9 / 10.2 / 11.3 with every chunk by ticket from one counter and positions by 64 chunks at
-// a time; 7.2 / 8.0 / 8.4 / 9.2 now.  Of a load of 0.8 M words 25.5 -> 23.5, of which first chunks without a ticket 1.1,
-// the look-back 0.6; 8.4 M positions at 4-byte stride 25.2 -> 22.1.
+// 0.8 / 1.7 / 5.9 M words: 7.2 / 8.9 / 11.0 / 23.0 with positions by 64 chunks at a time; 7.1 / 8.6 / 10.5 / 21.7 now;
+// 8.4 M positions at 4-byte stride 24.7 / 23.1.
 // Tried and left: words requested before the search (they hold up its first fetch, which returns
 // behind them: 75 -> 90; behind the last fetch of the search, with the ticket there, a load of 5.9 M words 62.4 -> 66.1: a
 // compute unit's vector L1 answers in order, so that what comes from memory holds up every other wave's fetches as well),
@@ -75,10 +73,9 @@
 // same buffer and is left ready for the next call, marked with the launch's parity (FlatTurn), so
 // that a scan is one launch.
 //
-// A wave only ever waits for chunks with smaller numbers.  Their workgroups need not be running yet (a first chunk is
-// nobody else's): a clerk that has waited long counts their hits itself, so that launches of several streams that share
-// the compute units never wait for each other.  The wait is bounded by a spin limit after which FDY_ST_SPIN is raised and
-// the kernel still terminates.
+// Tickets are handed out in increasing order and a wave only ever waits for chunks with
+// smaller numbers, which are already owned by resident workgroups: a launch never waits for a compute unit that another
+// kernel holds.  The wait is bounded by a spin limit after which FDY_ST_SPIN is raised and the kernel still terminates.
 //
 // Steps whose bodies hold a whole search are not written as loops: past a size the optimizer
 // declines to unroll even a `#pragma unroll` loop, and a rolled loop indexes the
@@ -110,8 +107,7 @@ struct ScanParams {
   fdy_reloc* relocs;
   u64 capacity;
   u64* d_count;
-  u32* queues;      // see ChunkQueue
-  u32 n_queues;
+  u32* ticket;
   const u32* top;  // [top_n] level-0 keys, padded with 0xffffffff
   const unsigned short* bstart;  // [n_buckets + 1] level-0 keys below each bucket's first key value
   u32 bucket_log2;  // log2(n_buckets)
@@ -134,7 +130,6 @@ struct ScanParams {
   u32 n_sub;            // sub-tiles
   u32* d_status;
   u32 spin_limit;
-  u32 patience;  // polls after which a waiting workgroup counts a chunk itself
   const u64* new_base;  // with a rebased output only: [n_alloc]
   u64* out;             // with a rebased output only: [n_words]
   u32* turn;            // what the launch before left (see FlatTurn)
@@ -189,13 +184,9 @@ struct FlatStates {
 // the sums behind the sixteenths before; polls go to what is missing alone.  (64 chunks at a time: four or five round trips
 // in a row, us of a load of 0.8 M words 24.4 / 23.8 now, of 8.4 M positions at 4-byte stride 23.6 / 22.3.  Neighbouring
 // states in the same memory lines: 62 -> 64 for 5.9 M words.)  meanwhile(): called behind the first requests.
-//
-// Nothing says that the chunks before are being worked on: their workgroups may wait for a compute unit that others
-// hold.  After `patience` polls the nearest chunk without a total is counted here (count(c)), and its field written as
-// its workgroup will write it: no workgroup waits for one that need not be running.
-template <typename Count, typename Meanwhile>
-__device__ __forceinline__ u64 exclusive_prefix(const FlatStates& states, u32 chunk, u32 spin_limit, u32 patience,
-                                                u32* d_status, Count count, Meanwhile meanwhile) {
+template <typename Meanwhile>
+__device__ __forceinline__ u64 exclusive_prefix(const FlatStates& states, u32 chunk, u32 spin_limit, u32* d_status,
+                                                Meanwhile meanwhile) {
   const u32 l = lane_id();
   u64 excl = 0;
   u32 spins = 0;
@@ -214,24 +205,17 @@ __device__ __forceinline__ u64 exclusive_prefix(const FlatStates& states, u32 ch
     const u32 from = known ? (g - back) << 4 : q >= 64 ? 4 * (q - 63) : 0u;
     u32 hits = 0;  // the lane's
     for (;;) {
-      u32 missing = 0;
+      bool missing = false;
       hits = 0;
 #pragma unroll
       for (u32 k = 0; k < 4; ++k) {
         const u32 c = 4 * (q - l) + k, field = (u32)(v >> (16 * k)) & 0xffffu;
         const bool counts = l <= q && c >= from && c < end;
-        if (counts && !is_field(field, states.parity)) missing = c + 1;
+        if (counts && !is_field(field, states.parity)) missing = true;
         hits += counts ? field & kFieldHits : 0u;
       }
-      const u64 m = ballot(missing != 0);
-      if (m == 0) break;
+      if (ballot(missing) == 0) break;
       if (!spin_once(spins, spin_limit, d_status)) return excl;
-      if (spins > patience) {
-        const u32 c = __shfl(missing, (int)__ffsll((long long)m) - 1) - 1;
-        const u32 total = count(c);
-        if (l == 0) states.store_field(c, make_field(total, states.parity));
-        spins = 0;
-      }
       if (missing) v = ld_state(states.place(fields_state(4 * (q - l))));  // (the others' are there)
     }
     excl += (u32)__builtin_amdgcn_readlane((int)wave_incl_scan(hits), 63);
@@ -256,8 +240,8 @@ struct PreparedHeader {
 };
 constexpr u64 kPreparedMagic = 0x3159445f4c424154ull;  // "TABL_DY1"
 constexpr size_t kPreparedHeader = 256;
-constexpr size_t kPreparedTurn = 128;  // byte offset of the turn.  The first 512 bytes also hold the scan's queues (96, 224, 352, 480
-                                       // and 484) and the counters of fdy_segment_fingerprint (64, 192, 196, 320, 448)
+constexpr size_t kPreparedTurn = 128;  // byte offset of the turn.  The first 512 bytes also hold the scan's ticket (384) and
+                                       // the counters of fdy_segment_fingerprint (64, 192, 196, 320, 448)
 
 // Is the caller's prepared table one that was made for this table, this tuning and at least
 // this many words?  (The host cannot look into device memory without a round trip.)
@@ -672,44 +656,19 @@ __device__ __forceinline__ u32 rank_candidates(u32 mask, Visit visit) {
   return Q;
 }
 
-// How chunks are handed out.  A workgroup's first chunk is that of its own number, so that nothing stands between a
-// launch's begin and the request of its words; the others come from up to four queues, each with a counter in a memory
-// line of its own (additions to one line are served one after the other, 11.3 ns each).  Every workgroup draws from its
-// queue until that is empty, its first ticket being on its way while the keys are staged.  One queue for launches of many
-// chunks, whose workgroups wait for each other's less where they come in order, and for the smallest: us with one / four,
-// 0.8 M words 25.6 / 23.8 of a load, 3.7 M 91.3 / 89.7, 8.4 M positions 26.2 / 22.3; 2,185 chunks (300,007 allocations) 151.6 /
-// 156.2, 17,477 681 / 698.
-constexpr u32 kOneQueueChunks = 2048;
-struct ChunkQueue {
-  u32 n, q;  // queues, and this workgroup's
-  u32 more;  // chunks in it
-  u32 last;  // the draw after which nobody draws from it again
-};
-constexpr int kQueueStride = -128 / 4;
-__device__ __forceinline__ ChunkQueue chunk_queue(const ScanParams& p) {
-  ChunkQueue c;
-  c.n = gridDim.x >= 64 ? p.n_queues : 1;
-  c.q = blockIdx.x % c.n;
-  c.more = (p.n_chunks - gridDim.x + c.n - 1 - c.q) / c.n;
-  c.last = c.more + (gridDim.x + c.n - 1 - c.q) / c.n - 1;
-  return c;
-}
-__device__ __forceinline__ u32* counter_of(const ScanParams& p, const ChunkQueue& c) {
-  return p.queues + (int)c.q * kQueueStride;
-}
-__device__ __forceinline__ u32 draw(const ScanParams& p, const ChunkQueue& c) { return atomicAdd(counter_of(p, c), 1u); }
-// The chunk of a ticket.  Counters and turn are reset by whoever makes the last draw of all: every workgroup has read the
-// turn before its first draw, so nobody looks at any of them again.
-__device__ __forceinline__ u32 drawn_chunk(const ScanParams& p, const ChunkQueue& c, u32 turn, u32 got) {
-  if (got == c.last) {
-    auto zero = [](u32* at) { __hip_atomic_store(at, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-    zero(counter_of(p, c));
-    if (c.n == 1 || atomicAdd(p.queues + 1, 1u) == c.n - 1) {
-      zero(p.queues + 1);
-      __hip_atomic_store(p.turn, flat_next_turn(turn, scan_states(p.n_chunks)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+// Chunks are handed out by one ticket counter, the first ones too: a workgroup only ever waits for chunks with smaller
+// numbers, and those are in the hands of workgroups that run.  (First chunks by workgroup number, further ones from four
+// counters: 0.8 / 1.7 / 5.9 M words 8.6 / 10.5 / 21.7 -> 7.7 / 8.6 / 19.8 us, but where other kernels hold compute units,
+// the workgroups that run wait for those that cannot: 5.9 M words with 32 of 256 units held 46 -> 3,500 us.)  Counter and
+// turn are reset by whoever makes the launch's last draw: every workgroup has read the turn before its first draw, so
+// nobody looks at either again.
+__device__ __forceinline__ u32 draw(const ScanParams& p) { return atomicAdd(p.ticket, 1u); }
+__device__ __forceinline__ u32 drawn(const ScanParams& p, u32 turn, u32 last_draw, u32 got) {
+  if (got == last_draw) {
+    __hip_atomic_store(p.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(p.turn, flat_next_turn(turn, scan_states(p.n_chunks)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  return got < c.more ? gridDim.x + got * c.n + c.q : p.n_chunks;
+  return got;
 }
 
 // A worker's sub-tile: round k's lane l has candidate 64 k + l.
@@ -819,34 +778,6 @@ __device__ __forceinline__ void stash_words(u64* stash, const u64 (&w)[kWpl]) {
   }
 }
 
-// The hits of a chunk, by one wave: for a workgroup that has waited too long for them.
-template <int kW, int kDepth, bool kHalf>
-__device__ __forceinline__ u32 count_chunk(const ScanParams& p, const FlatLevel& f, u32 chunk) {
-  u32 total = 0;
-  const u32 sh0 = 3 * p.levels + p.f0_log2;
-#pragma unroll 1
-  for (u32 i = 0; i < (u32)kW * kWpl; ++i) {
-    const u64 at = ((u64)chunk * kW + i / kWpl) * kSub + (i % kWpl) * 64 + lane_id();
-    const u64 d[1] = {at < p.n_words ? word_at<kHalf>(p, at) - f.span_lo : ~0ull};
-    bool hit = false;
-    if (d[0] < f.span_len) {
-      u32 key[1];
-      flat_place<1>(f, d, key, [](bool b) { return ballot(b) != 0; });
-      const u64 w = d[0] + f.span_lo, unit = key[0] >> 2;
-      u32 lo = (u32)(unit << sh0), hi = p.n_alloc - lo < (1ull << sh0) ? p.n_alloc : lo + (1u << sh0), n;
-      if (p.table[lo].base > w) {  // (truncated keys lead too far)
-        hi = lo ? lo : 1;
-        lo = 0;
-      }
-      u64x2 e;
-      find_exact(p.table, lo, hi, w, n, e);
-      hit = w - e.x < e.y;
-    }
-    total += __popcll(ballot(hit));
-  }
-  return total;
-}
-
 // The ordered scan.
 template <int kW, int kDepth, bool kHalf, bool kOut>
 __global__ __launch_bounds__((kW + 1) * 64) void scan_kernel(ScanParams p) {
@@ -858,42 +789,39 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_kernel(ScanParams p) {
   const bool clerk = wave == kW;
   u32 turn = 0;  // (lies in the prepared table's first block, which the check reads too)
   if (clerk) turn = __hip_atomic_load(p.turn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  u32 chunk = blockIdx.x;
-  Words<kHalf> raw = {};
-  // Small workgroups request their words ahead of everything; those of many workers behind the keys, which would wait for
-  // 60 KB of them.  (us of a load ahead / behind: 217 workgroups of seven workers 23.5 / 24.1, 256 of fifteen 61.8 / 61.1.)
-  constexpr bool kAhead = kW == (int)kFlatWorkers;
   // Who tells a chunk's hits: the last of many workers, ahead of the barrier, or the clerk of few behind it.  us by the
   // clerk / by the last worker: seven workers, 0.5 M words 7.4 / 7.6, 0.3 M positions at 4-byte stride 6.2 / 6.5; fifteen, 2^27
   // words with output 681 / 673.
   constexpr bool kWorkersTell = kW != (int)kFlatWorkers;
-  if (kAhead && !clerk) raw = request_words<kHalf>(p, chunk * kW + wave);
   FlatRegion region = p.region;  // (the header's first block as well)
   if (p.prepared) region = FlatRegion{(long long)p.prepared[4], (u32)p.prepared[5]};
   if (!prepared_ok(p)) {  // every workgroup sees the same: nothing is written
     if (blockIdx.x == 0 && tid == 0) raise_status(p.d_status, FDY_ST_BAD_PREPARED);
     return;
   }
-  const ChunkQueue queue = chunk_queue(p);
-  u32 got = 0;
+  const bool single = gridDim.x >= p.n_chunks;  // every workgroup's first draw is its only chunk
+  // the draw after which nobody draws again
+  const u32 last_draw = single ? gridDim.x - 1 : p.n_chunks + gridDim.x - 1;
   FlatTurn t;
   FlatStates states;
   const u32 n_states = scan_states(p.n_chunks);
   if (clerk) {  // meanwhile the others stage the keys
     asm volatile("" : "+v"(turn) : : "memory");  // the turn has arrived before the draw goes out
-    if (lane == 0) got = draw(p, queue);
+    u32 got = 0;
+    if (lane == 0) got = draw(p);
     t = flat_turn(uniform(turn), n_states, region.states);
     states = FlatStates{reinterpret_cast<u64*>(reinterpret_cast<unsigned char*>(p.cstate) + region.first), t.s, t.parity};
     if (lane == 0) {
       s_sum[0] = s_sum[1] = 0;
-      s_field[1] = (u64)states.field_of(chunk) | states.parity;
+      s_next[0] = drawn(p, turn, last_draw, got);
+      if (kWorkersTell && got < p.n_chunks) s_field[1] = (u64)states.field_of(got) | states.parity;
     }
   } else {
     (void)flat_stage<kW * 64>(p, smem_raw, tid, false);
   }
-  if (!kAhead && !clerk) raw = request_words<kHalf>(p, chunk * kW + wave);
   const FlatLevel f = flat_level(p, smem_raw);
   __syncthreads();
+  u32 chunk = s_next[0];
   if (clerk) {
     for (u32 i = blockIdx.x * 64 + lane; i < t.dirty; i += gridDim.x * 64) {
       const u32 at = flat_to_clear(t, i, n_states);
@@ -902,8 +830,7 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_kernel(ScanParams p) {
     u32 prev = 0, prev_total = 0, b = 1;
     // the exclusive prefix of the chunk before, for the workers that wait to write it
     auto close = [&](u32 slot, auto meanwhile) __attribute__((always_inline)) {
-      const u64 excl = exclusive_prefix(states, prev, p.spin_limit, p.patience, p.d_status,
-                                        [&](u32 c) { return count_chunk<kW, kDepth, kHalf>(p, f, c); }, meanwhile);
+      const u64 excl = exclusive_prefix(states, prev, p.spin_limit, p.d_status, meanwhile);
       if (lane == 0) {
         if ((prev & 15) == 15) st_state(states.place(sum_state(prev >> 4)), make_sum(excl + prev_total, states.parity));
         if (prev + 1 == p.n_chunks) {  // the last chunk: the grand total
@@ -915,16 +842,16 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_kernel(ScanParams p) {
     };
     bool have_prev = false;
     for (; chunk < p.n_chunks; b ^= 1) {
-      if (lane == 0 && have_prev) got = draw(p, queue);
-      auto tell = [&] {  // (an empty queue's only ticket is not waited for)
+      u32 got = p.n_chunks;
+      if (lane == 0 && !single) got = draw(p);
+      auto tell = [&] {
         if (lane != 0) return;
-        const u32 next = queue.more ? drawn_chunk(p, queue, turn, got) : p.n_chunks;
-        s_next[b] = next;
-        if (kWorkersTell && next < p.n_chunks) s_field[b ^ 1] = (u64)states.field_of(next) | states.parity;
+        if (!single) (void)drawn(p, turn, last_draw, got);
+        s_next[b] = got;
+        if (kWorkersTell && got < p.n_chunks) s_field[b ^ 1] = (u64)states.field_of(got) | states.parity;
       };
       if (have_prev) close(b, tell);
       else tell();
-      if (lane == 0 && queue.more == 0) (void)drawn_chunk(p, queue, turn, got);
       __syncthreads();
       u32 total = 0;
 #pragma unroll
@@ -970,6 +897,7 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_kernel(ScanParams p) {
   };
   Forms m = pick_forms<kDepth>(p);
   if constexpr (kDepth == 1) m.settle = units_share_keys(f, p.n_lines);
+  Words<kHalf> raw = request_words<kHalf>(p, chunk * kW + wave);
   Results cur, prev;
   u32 prev_before = 0, b = 1;
   bool have_prev = false;
@@ -1556,11 +1484,9 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
   p.relocs = d_relocs;
   p.capacity = reloc_capacity;
   p.d_count = (u64*)d_count;
-  // state: 2..3 = hit accumulator (64 bits), 8 = turn, 56 and 24 = queues.  A prepared table's turn and queues lie in its
-  // first 512 bytes, which are four memory lines with room in them.
-  p.queues = d_prepared ? (u32*)const_cast<void*>(d_prepared) + 120 : (u32*)state + 56;
-  p.n_queues = n_chunks > kOneQueueChunks ? 1 : d_prepared ? 4 : 2;
-  p.patience = (u32)fdy__tune_get(FDY_TUNE_SCAN_PATIENCE);
+  // state: 2..3 = hit accumulator (64 bits), 8 = turn (a prepared table's lies in its header), 32 = ticket, in a memory
+  // line of its own
+  p.ticket = (u32*)state + 32;
   p.acc = (u64*)state + 1;
   p.turn = d_prepared ? (u32*)const_cast<void*>(d_prepared) + kPreparedTurn / 4 : (u32*)state + 8;
   p.region = region;

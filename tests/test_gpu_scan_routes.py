@@ -93,9 +93,8 @@ def test_bounded_wait_and_the_calls_after(n_alloc, n):
 
 @pytest.mark.parametrize("top_log2,n_alloc", [(14, 300), (14, 16384), (14, 20000), (14, 140000), (4, 301)])
 @pytest.mark.parametrize("n", [40 * SUB + 3, 1500 * SUB, 8000 * SUB + 511])
-def test_chunks_counted_by_those_who_wait_for_them(top_log2, n_alloc, n):
-    """Without patience every workgroup counts whatever chunk before its own is not through: the same table, scanned by
-    words and by 4-byte positions, and calls with patience in between."""
+def test_one_prepared_table_by_every_form_in_turn(top_log2, n_alloc, n):
+    """The same table, scanned by words again and again, by 4-byte positions and with output."""
     import paper_2604_06664_amd as fdy
     from tests.support import session
     from tests.test_gpu_flat_scan import table_of, words_of
@@ -103,7 +102,6 @@ def test_chunks_counted_by_those_who_wait_for_them(top_log2, n_alloc, n):
 
     rng = np.random.default_rng(n_alloc + n)
     old = fdy.tune_set(fdy.TUNE_SCAN_TOP_LOG2, top_log2)
-    patience = fdy.tune_get(fdy.TUNE_SCAN_PATIENCE)
     try:
         for shape in ("spread", "run"):
             t = table_of(rng, n_alloc, shape)
@@ -112,14 +110,12 @@ def test_chunks_counted_by_those_who_wait_for_them(top_log2, n_alloc, n):
             units = words.view(np.uint32)[1:n]
             ref4, cnt4 = orc.scan_stride4(units, t)
             run = session.ScanRun(words, t, prepared=True)
-            for p in (0, patience, 0):
-                fdy.tune_set(fdy.TUNE_SCAN_PATIENCE, p)
+            for again in range(3):
                 run.launch()
                 got, have, status = run.result()
-                assert status == 0 and have == cnt and np.array_equal(got, ref), (shape, p)
+                assert status == 0 and have == cnt and np.array_equal(got, ref), (shape, again)
             got, have, status = session.scan_stride4(units, t, prepared=False)
             assert status == 0 and have == cnt4 and np.array_equal(got, ref4), shape
-            check_scan_out(session, orc, words, t, rng.integers(0, 1 << 63, n_alloc, dtype=np.uint64), tag="no patience")
+            check_scan_out(session, orc, words, t, rng.integers(0, 1 << 63, n_alloc, dtype=np.uint64), tag="in turn")
     finally:
         fdy.tune_set(fdy.TUNE_SCAN_TOP_LOG2, old)
-        fdy.tune_set(fdy.TUNE_SCAN_PATIENCE, patience)
