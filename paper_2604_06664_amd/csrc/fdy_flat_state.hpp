@@ -105,11 +105,17 @@ __host__ __device__ __forceinline__ u32 flat_to_clear(const FlatTurn& t, u32 i, 
   return chunk_at(t.s, at) < n_chunks ? ~0u : at;
 }
 
-// What the states of an ordered scan hold.  Sixteen chunks take five: four with a 16-bit field for each of four chunks
+// What the states of an ordered scan hold.  With more than 64 chunks, sixteen of them take five: four with a 16-bit field for each of four chunks
 // (its hits, once they are known), and one for the hits of all chunks up to the sixteenth, once those are.  Either kind says
 // which it is and carries the parity of its launch: fields have their top bit set, a sum has none of the four top bits of
 // its 16-bit parts, so that whatever an earlier launch left in a place never looks like the other kind.
-__host__ __device__ __forceinline__ u32 scan_states(u32 n_chunks) { return 5 * ((n_chunks + 15) / 16); }
+// Launches of few chunks have a state for each, with the chunk's field in its lowest 16 bits and nothing above.
+constexpr u32 kFewChunks = 64;
+static_assert(kFewChunks < kFlatFewSubs / kFlatWorkersBig, "workgroups of many workers never have few chunks");
+__host__ __device__ __forceinline__ bool few_chunks(u32 n_chunks) { return n_chunks <= kFewChunks; }
+__host__ __device__ __forceinline__ u32 scan_states(u32 n_chunks) {
+  return few_chunks(n_chunks) ? n_chunks : 5 * ((n_chunks + 15) / 16);
+}
 __host__ __device__ __forceinline__ u32 fields_state(u32 chunk) { return 5 * (chunk >> 4) + ((chunk >> 2) & 3); }
 __host__ __device__ __forceinline__ u32 sum_state(u32 sixteen) { return 5 * sixteen + 4; }
 constexpr u32 kFieldHits = (1u << 14) - 1;

@@ -31,7 +31,7 @@ int main() {
       expect(is_sum(v, p) && !is_sum(v, p ^ 1) && sum_hits(v) == hits, "sum", p, (u32)hits);
       for (u32 k = 0; k < 4; ++k) expect(!((v >> (16 * k)) & 0x8000), "sum taken for a field", p, k);
     }
-  for (u32 most : {1u, 2u, 15u, 16u, 17u, 100u, 256u, 1000u, 2300u})
+  for (u32 most : {1u, 2u, 15u, 16u, 17u, 63u, 64u, 65u, 66u, 80u, 100u, 256u, 1000u, 2300u})
     for (u32 spare : {0u, 512u, 32768u}) {
       const u32 max_sub = most * kFlatWorkers;
       const FlatRegion g = flat_region(max_sub, spare, chunk_state_bytes(max_sub));
@@ -40,13 +40,18 @@ int main() {
       for (u32 launch = 0; launch < 40; ++launch) {
         u32 n = 1 + (u32)(next(r) % most);
         if (launch % 3 == 0) n = most;
+        if (launch % 5 == 4 && most > kFewChunks) n = kFewChunks + 1 - launch % 2;  // both kinds of launches in turn
+        const bool few = few_chunks(n);
         const u32 m = scan_states(n);
         const FlatTurn t = flat_turn(turn, m, g.states);
         expect(flat_extent(t.s, m) <= g.states, "extent", n, g.states);
-        auto field = [&](u32 c) { return (u32)(mem[state_at(t.s, fields_state(c))] >> (16 * (c & 3))) & 0xffffu; };
+        auto field = [&](u32 c) {
+          if (few) return (u32)mem[state_at(t.s, c)] & 0xffffu;
+          return (u32)(mem[state_at(t.s, fields_state(c))] >> (16 * (c & 3))) & 0xffffu;
+        };
         auto put = [&](u32 c, u32 v) {
-          u64& w = mem[state_at(t.s, fields_state(c))];
-          w = (w & ~(0xffffull << (16 * (c & 3)))) | (u64)v << (16 * (c & 3));
+          u64& w = mem[state_at(t.s, few ? c : fields_state(c))];
+          w = few ? (u64)v : (w & ~(0xffffull << (16 * (c & 3)))) | (u64)v << (16 * (c & 3));
         };
         auto sum = [&](u32 i) -> u64& { return mem[state_at(t.s, sum_state(i))]; };
         std::vector<u32> order(n);
@@ -56,18 +61,18 @@ int main() {
         for (u32 at = 0; at < n; ++at) {
           const u32 c = order[at], probe = (u32)(next(r) % n);
           expect(is_field(field(probe), t.parity) == (told[probe] != 0), "field", n, probe);
-          if (n >= 16) expect(is_sum(sum(probe % (n / 16)), t.parity) == (summed[probe % (n / 16)] != 0), "sum", n, probe % (n / 16));
+          if (!few) expect(is_sum(sum(probe % (n / 16)), t.parity) == (summed[probe % (n / 16)] != 0), "sum", n, probe % (n / 16));
           const u32 hits = (u32)(next(r) % 7681);
           put(c, make_field(hits, t.parity));
           told[c] = 1;
           expect(is_field(field(c), t.parity) && (field(c) & kFieldHits) == hits, "told", n, c);
-          if (c % 16 == 15) {
+          if (!few && c % 16 == 15) {
             sum(c / 16) = make_sum((u64)c * 4000000, t.parity);
             summed[c / 16] = 1;
           }
-          if (c + 1 == n)
+          if (!few && c + 1 == n)
             for (u32 i = c + 1; i % 16; ++i) put(i, 0);
-          if (c + 1 == n && c % 16 != 15) sum(c / 16) = 0;
+          if (!few && c + 1 == n && c % 16 != 15) sum(c / 16) = 0;
         }
         for (u32 i = 0; i < t.dirty; ++i) {
           const u32 at = flat_to_clear(t, i, m);

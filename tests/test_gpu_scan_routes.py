@@ -119,3 +119,25 @@ def test_one_prepared_table_by_every_form_in_turn(top_log2, n_alloc, n):
             check_scan_out(session, orc, words, t, rng.integers(0, 1 << 63, n_alloc, dtype=np.uint64), tag="in turn")
     finally:
         fdy.tune_set(fdy.TUNE_SCAN_TOP_LOG2, old)
+
+
+@pytest.mark.parametrize("n_alloc", [300, 20000, 140000])  # level 0 alone, lines, nodes
+def test_launches_of_few_and_many_chunks_in_turn(n_alloc):
+    """Up to 64 chunks have a state each, more of them share states: calls of both kinds on one prepared table."""
+    from tests.support import session
+    from tests.test_gpu_flat_scan import table_of, words_of
+
+    rng = np.random.default_rng(n_alloc)
+    t = table_of(rng, n_alloc, "spread")
+    words = words_of(rng, 1600 * SUB, t, 0.25)
+    runs = []
+    for n in (1, 7 * SUB, 63 * 7 * SUB, 64 * 7 * SUB - 1, 64 * 7 * SUB, 64 * 7 * SUB + 1, 65 * 7 * SUB, 1535 * SUB, 1600 * SUB):
+        runs.append((session.ScanRun(words[:n], t), *orc.scan(words[:n], t)))
+    big = runs[-1][0]
+    big.prepare(len(words))
+    for k in rng.permutation(4 * len(runs)):
+        run, ref, cnt = runs[k % len(runs)]
+        run.d_prepared, run.d_table = big.d_prepared, big.d_table
+        run.launch()
+        got, have, status = run.result()
+        assert status == 0 and have == cnt and np.array_equal(got, ref), run.n_words
