@@ -28,7 +28,9 @@ enum {
                                  * tiles streams templates and relocation lists past the L2s  */
   FDY_TUNE_MAT_MOST_BLOCKS = 7, /* most blocks that a materialize launch has for tiles, and    *
                                  * for patch slices; more take further launches, or rounds    */
-  FDY_TUNE_COUNT = 8
+  FDY_TUNE_ARCHIVE_PARTS = 8,   /* parts that an archive's sums and contents are looked at in,  *
+                                 * whatever their size and the processors; 0: as many as pay  */
+  FDY_TUNE_COUNT = 9
 };
 
 int fdy__tune_get(int knob);

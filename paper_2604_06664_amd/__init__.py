@@ -29,6 +29,7 @@ TUNE_SCAN_SMALL_LOG2 = 4
 TUNE_MAT_SELF_WGS = 5
 TUNE_MAT_ONCE_TILES = 6
 TUNE_MAT_MOST_BLOCKS = 7
+TUNE_ARCHIVE_PARTS = 8
 
 
 class FdyError(RuntimeError):

@@ -23,6 +23,7 @@
 #include <vector>
 
 #include "fdy_archive.h"
+#include "fdy_internal.h"
 
 namespace {
 
@@ -159,6 +160,7 @@ void side_by_side(uint32_t parts, const Part& part) {
 // 131 / 81 / 79 / 126, content check 155 / 84 / 73 / 95, the whole load of the file 730 / 566 / 534 / 590; below 2 MB (which
 // takes 26 and 17) a thread costs what it saves.
 uint32_t parts_of(uint64_t bytes) {
+  if (const int asked = fdy__tune_get(FDY_TUNE_ARCHIVE_PARTS)) return (uint32_t)asked;
   const uint64_t n = std::min<uint64_t>(bytes / (1u << 20), kMostParts);
   if (n < 2) return 1;
   const uint64_t cpus = std::thread::hardware_concurrency();  // (2 us to ask)
@@ -432,33 +434,40 @@ const char* offsets_violation(const View<uint64_t>& off, uint64_t len, uint64_t 
   return nullptr;
 }
 
-// The nodes and relocations of source graphs [from, to), as content_check wants them.  (Without a branch per condition:
-// four times as long.)
+// The nodes and relocations of source graphs [from, to), as content_check wants them.
 struct Graphs {
   View<fdy_alloc> table;
   View<uint64_t> words, word_off, node_off, reloc_off;
   View<fdy_node> nodes;
   View<fdy_reloc> relocs;
 };
-bool graphs_ok(const Graphs& a, uint64_t from, uint64_t to) {
+// What is wrong first, in the order of the graphs: a text with a place for the number of what it names.
+struct Violation {
+  const char* text = nullptr;  // null: nothing
+  uint64_t index = 0;
+};
+Violation graphs_violation(const Graphs& a, uint64_t from, uint64_t to) {
   for (uint64_t s = from; s < to; ++s) {
     uint64_t blob_bytes = 0;
     for (uint64_t i = a.node_off[s]; i < a.node_off[s + 1]; ++i) {
-      if (a.nodes[i].blob_len % 8) return false;
+      if (a.nodes[i].blob_len % 8) return {"NODES: node %llu has a blob length that is not a multiple of 8", i};
       blob_bytes += a.nodes[i].blob_len;
     }
     const uint64_t w_lo = a.word_off[s], w_hi = a.word_off[s + 1];
-    if (blob_bytes != (w_hi - w_lo) * 8) return false;
+    if (blob_bytes != (w_hi - w_lo) * 8)
+      return {"source graph %llu: blob lengths of its nodes do not add up to its words", s};
     uint64_t least = w_lo;  // of the next entry's word
     for (uint64_t i = a.reloc_off[s]; i < a.reloc_off[s + 1]; ++i) {
       const fdy_reloc& r = a.relocs[i];
-      if (r.word < least || r.word >= w_hi) return false;
+      if (r.word < least || r.word >= w_hi) return {"RELOCS: entry %llu is outside its graph's words or not ascending", i};
       least = (uint64_t)r.word + 1;
-      if (r.region >= a.table.n || r.offset >= a.table[r.region].size) return false;
-      if (a.words[r.word] != a.table[r.region].base + r.offset) return false;
+      if (r.region >= a.table.n || r.offset >= a.table[r.region].size)
+        return {"RELOCS: entry %llu names a region or offset outside the table", i};
+      if (a.words[r.word] != a.table[r.region].base + r.offset)
+        return {"RELOCS: entry %llu does not match the word it describes", i};
     }
   }
-  return true;
+  return {};
 }
 
 int content_check(const fdy_archive* a, fdy_archive_info* out) {
@@ -499,39 +508,20 @@ int content_check(const fdy_archive* a, fdy_archive_info* out) {
   if (const char* v = offsets_violation(node_off, S + 1, nodes.n)) return bad("NODE_OFF %s", v);
   if (const char* v = offsets_violation(reloc_off, S + 1, relocs.n)) return bad("RELOC_OFF %s", v);
 
-  // Large archives have their graphs looked at side by side, cut where their relocations are even; whatever is wrong is
-  // then found, and named, one after the other.
+  // Large archives have their graphs looked at side by side, cut where their relocations are even.  The first part that
+  // finds something wrong holds what is wrong first.
   const Graphs graphs{table, words, word_off, node_off, reloc_off, nodes, relocs};
   const uint32_t parts = parts_of(relocs.n * sizeof(fdy_reloc) + nodes.n * sizeof(fdy_node));
-  bool ok[kMostParts] = {};
+  Violation found[kMostParts];
   side_by_side(parts, [&](uint32_t i) {
     const auto cut = [&](uint32_t i) {
       if (i == 0 || i == parts) return i ? S : 0;
       return (uint64_t)(std::lower_bound(reloc_off.p, reloc_off.p + S, relocs.n * i / parts) - reloc_off.p);
     };
-    ok[i] = graphs_ok(graphs, cut(i), cut(i + 1));
+    found[i] = graphs_violation(graphs, cut(i), cut(i + 1));
   });
-  if (!std::all_of(ok, ok + parts, [](bool b) { return b; })) for (uint64_t s = 0; s < S; ++s) {
-    uint64_t blob_bytes = 0;
-    for (uint64_t i = node_off[s]; i < node_off[s + 1]; ++i) {
-      if (nodes[i].blob_len % 8) return bad("NODES: node %llu has a blob length that is not a multiple of 8", (unsigned long long)i);
-      blob_bytes += nodes[i].blob_len;
-    }
-    if (blob_bytes != (word_off[s + 1] - word_off[s]) * 8)
-      return bad("source graph %llu: blob lengths of its nodes do not add up to its words", (unsigned long long)s);
-    const uint64_t w_lo = word_off[s], w_hi = word_off[s + 1];
-    uint64_t prev = 0;
-    for (uint64_t i = reloc_off[s]; i < reloc_off[s + 1]; ++i) {
-      const fdy_reloc& r = relocs[i];
-      if (r.word < w_lo || r.word >= w_hi || (i > reloc_off[s] && r.word <= prev))
-        return bad("RELOCS: entry %llu is outside its graph's words or not ascending", (unsigned long long)i);
-      prev = r.word;
-      if (r.region >= A || r.offset >= table[r.region].size)
-        return bad("RELOCS: entry %llu names a region or offset outside the table", (unsigned long long)i);
-      if (words[r.word] != table[r.region].base + r.offset)
-        return bad("RELOCS: entry %llu does not match the word it describes", (unsigned long long)i);
-    }
-  }
+  for (uint32_t i = 0; i < parts; ++i)
+    if (found[i].text) return bad(found[i].text, (unsigned long long)found[i].index);
 
   for (uint64_t t = 0; t < T; ++t)
     if (tmpl_graph[t] >= S) return bad("TMPL_GRAPH: template %llu names a source graph that is not stored", (unsigned long long)t);
