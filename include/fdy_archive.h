@@ -35,6 +35,10 @@
  *
  * These are host-side calls; only fdy_archive_upload touches the GPU.  An open archive is
  * read-only and may be used from several threads.  Return codes are those of fdy.h.
+ * fdy_archive_open with FDY_ARCHIVE_VERIFY_SUMS, fdy_archive_check and fdy_archive_mat_desc look
+ * at 2 MiB or more with up to four threads, the caller's among them: the others are started
+ * by the call (with the caller's signal mask and processor affinity) and have ended when it
+ * returns; where one cannot be started, the caller does its share.
  */
 #ifndef FDY_ARCHIVE_H
 #define FDY_ARCHIVE_H
