@@ -29,21 +29,21 @@ inline u32 flat_most_chunks(u32 max_sub) {
   return most;
 }
 
-// Neighbouring chunks' states are spread over 2^s lines of 64 bytes, eight to a line: every
+// Neighbouring states are spread over 2^s lines of 64 bytes, eight to a line: every
 // workgroup in flight reads its predecessors', and states that lie closer are served by too few
 // memory channels.  State i lies at state_at(s, i) of blocks of 2^s * 8 states; s is the largest
-// for which `states` hold the blocks, at most kFlatSpread, and no larger than the chunks can use.
+// for which `states` hold the blocks, at most kFlatSpread, and no larger than the launch's states can use.
 // us with 16 allocations and 2 % pointers, in chunk_state_bytes (32, 128 and 128 lines) / 256
 // lines / 512 / a line for each: 0.76 M words 10.1 / 8.6 / 8.7 / 8.8, 5.8 M 22.2 / 20.1 / 19.5 /
 // 19.5, 16.8 M 46.6 / 41.0 / 40.5 / 41.0 (a state to a chunk, then; with five to sixteen, loads of 0.8 and 5.9 M words with 1 /
 // 8 / 32 / 64 / 512 lines: 25.3 / 25.3 / 24.2 / 23.9 / 23.9 and 63.8 / 63.0 / 62.8 / 62.2 / 61.7).
 constexpr u32 kFlatSpread = 9;
-__host__ __device__ __forceinline__ u32 flat_extent(u32 s, u32 n_chunks) {
-  return (n_chunks + (8u << s) - 1) >> (s + 3) << (s + 3);
+__host__ __device__ __forceinline__ u32 flat_extent(u32 s, u32 n_states) {
+  return (n_states + (8u << s) - 1) >> (s + 3) << (s + 3);
 }
-__host__ __device__ __forceinline__ u32 flat_spread(u32 n_chunks, u32 states) {
+__host__ __device__ __forceinline__ u32 flat_spread(u32 n_states, u32 states) {
   u32 s = kFlatSpread;
-  while (s > 0 && (flat_extent(s, n_chunks) > states || (1u << (s - 1)) >= n_chunks)) --s;
+  while (s > 0 && (flat_extent(s, n_states) > states || (1u << (s - 1)) >= n_states)) --s;
   return s;
 }
 
@@ -56,7 +56,7 @@ inline size_t chunk_state_bytes(u32 n_sub) { return ((size_t)((n_sub + 7) / 8) *
 // of the chunk states, are states as well.
 struct FlatRegion {
   long long first;  // bytes from the first chunk state
-  u32 states;       // as many as the widest spread can use, at most
+  u32 states;       // at most what the widest spread of a state per chunk uses: no launch has more (see scan_states)
 };
 inline FlatRegion flat_region(u32 max_sub, u32 spare, size_t bytes) {
   FlatRegion r{-(long long)spare, 0};
@@ -85,30 +85,30 @@ __host__ __device__ __forceinline__ u32 chunk_at(u32 s, u32 place) {  // the inv
 // The states are left ready for the next launch without a count of the workgroups that are through
 // (256 additions to one address at 12 ns each, at the end of the launch where nothing hides
 // them): a state carries the parity of its launch, launches alternate, and a state of the other
-// parity counts as empty.  A launch writes the state of each of its chunks; those of the launch
+// parity counts as empty.  A launch writes all of its states; those of the launch
 // before that it does not write itself it clears, so that the next but one finds its own parity
-// nowhere.  `turn`, kept from launch to launch: chunks of the launch before << 1 | parity of
+// nowhere.  `turn`, kept from launch to launch: states of the launch before << 1 | parity of
 // the next.
 constexpr u64 kFlatParity = 1ull << 61;
 struct FlatTurn {
   u32 s, parity;           // of this launch
-  u32 dirty, s_dirty;      // chunks of the launch before, and how their states are spread
+  u32 dirty, s_dirty;      // states of the launch before, and how they are spread
 };
-__host__ __device__ __forceinline__ FlatTurn flat_turn(u32 turn, u32 n_chunks, u32 states) {
-  return FlatTurn{flat_spread(n_chunks, states), turn & 1, turn >> 1, flat_spread(turn >> 1, states)};
+__host__ __device__ __forceinline__ FlatTurn flat_turn(u32 turn, u32 n_states, u32 states) {
+  return FlatTurn{flat_spread(n_states, states), turn & 1, turn >> 1, flat_spread(turn >> 1, states)};
 }
-__host__ __device__ __forceinline__ u32 flat_next_turn(u32 turn, u32 n_chunks) { return n_chunks << 1 | (~turn & 1); }
-// Where chunk i of the launch before left its state, if this launch (n_chunks of its own) has to
-// clear it; else ~0.
-__host__ __device__ __forceinline__ u32 flat_to_clear(const FlatTurn& t, u32 i, u32 n_chunks) {
+__host__ __device__ __forceinline__ u32 flat_next_turn(u32 turn, u32 n_states) { return n_states << 1 | (~turn & 1); }
+// Where state i of the launch before lies, if this launch (n_states of its own) has to clear it; else ~0.
+__host__ __device__ __forceinline__ u32 flat_to_clear(const FlatTurn& t, u32 i, u32 n_states) {
   const u32 at = state_at(t.s_dirty, i);
-  return chunk_at(t.s, at) < n_chunks ? ~0u : at;
+  return chunk_at(t.s, at) < n_states ? ~0u : at;
 }
 
-// What the states of an ordered scan hold.  With more than 64 chunks, sixteen of them take five: four with a 16-bit field for each of four chunks
-// (its hits, once they are known), and one for the hits of all chunks up to the sixteenth, once those are.  Either kind says
-// which it is and carries the parity of its launch: fields have their top bit set, a sum has none of the four top bits of
-// its 16-bit parts, so that whatever an earlier launch left in a place never looks like the other kind.
+// What the states of an ordered scan hold.  With more than 64 chunks, sixteen of them take five: four with a 16-bit field
+// for each of four chunks (its hits, once they are known), and one for the hits of all chunks up to the sixteenth, once
+// those are.  Either kind says which it is and carries the parity of its launch: fields have their top bit set, a sum has
+// none of the four top bits of its 16-bit parts, so that whatever an earlier launch left in a place never looks like the
+// other kind.
 // Launches of few chunks have a state for each, with the chunk's field in its lowest 16 bits and nothing above.
 constexpr u32 kFewChunks = 64;
 static_assert(kFewChunks < kFlatFewSubs / kFlatWorkersBig, "workgroups of many workers never have few chunks");

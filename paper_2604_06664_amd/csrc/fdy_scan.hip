@@ -806,6 +806,8 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_kernel(ScanParams p) {
   __shared__ u32 s_next[2], s_cnt[2][kW], s_sum[2];
   __shared__ u64 s_excl[2];
   __shared__ u64 s_field[2];  // where the chunk tells its hits, and in the lowest bit the parity
+  static_assert((u32)kW * kSub <= kFieldHits && (u32)kW * kSub < 1u << 16 && kW < 1 << 16,
+                "a chunk's hits fit its field, and s_sum below the number of workers that are through");
   const u32 tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const bool clerk = wave == kW;
   u32 turn = 0;  // (lies in the prepared table's first block, which the check reads too)

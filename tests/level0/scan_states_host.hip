@@ -2,6 +2,7 @@
 // of launches of many sizes over one region, in which no field or sum may look written before its chunk has written
 // it, whichever kind of state an earlier launch left in its place.
 #include <cstdio>
+#include <utility>
 #include <vector>
 
 #include "fdy_flat_state.hpp"
@@ -32,8 +33,9 @@ int main() {
       for (u32 k = 0; k < 4; ++k) expect(!((v >> (16 * k)) & 0x8000), "sum taken for a field", p, k);
     }
   for (u32 most : {1u, 2u, 15u, 16u, 17u, 63u, 64u, 65u, 66u, 80u, 100u, 256u, 1000u, 2300u})
-    for (u32 spare : {0u, 512u, 32768u}) {
-      const u32 max_sub = most * kFlatWorkers;
+    for (const auto& [spare, workers] : {std::pair{0u, kFlatWorkers}, {512u, kFlatWorkers}, {32768u, kFlatWorkers},
+                                         {0u, kFlatWorkersBig}, {512u, kFlatWorkersBig}, {32768u, kFlatWorkersBig}}) {
+      const u32 max_sub = most * workers;
       const FlatRegion g = flat_region(max_sub, spare, chunk_state_bytes(max_sub));
       std::vector<u64> mem(g.states, 0);
       u32 turn = 0;
