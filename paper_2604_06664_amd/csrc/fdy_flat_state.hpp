@@ -8,21 +8,30 @@ namespace fdy {
 
 constexpr u32 kFlatWorkers = 7, kFlatWorkersBig = 15;
 
-// Workers per workgroup.  Measured (us, 7 / 15
-// workers, a quarter pointers, 4,096 allocations): 586 sub-tiles 7.2 / 7.6, 1,368 8.0 / 7.9, 1,758 8.3 / 8.1, 2,344
-// 10.5 / 8.4, 3,321 12.3 / 9.3; 16,384 allocations, 1,016 sub-tiles 8.8 / 8.8, 1,368 9.2 / 8.9; with output and lines,
-// 1,368 11.7 / 12.8: many small workgroups start sooner and share the staging's latency, but each chunk costs a ticket and
-// a look-back.
-constexpr u32 kFlatFewSubs = 1536;
-__host__ __device__ __forceinline__ u32 flat_workers(u32 n_sub) {
-  return n_sub < kFlatFewSubs ? kFlatWorkers : kFlatWorkersBig;
+// Workers per workgroup.  Many small workgroups start sooner and share the staging's latency, but each chunk costs a
+// look-back and a ticket, of which the first are drawn by all workgroups at once, 11.3 ns each.  us, 7 / 15 workers, a
+// quarter pointers, scans alone:
+//   sub-tiles                       700           830           980           1,250         1,530         1,758
+//   4,096 allocations               7.7 / 7.4     7.8 / 7.6     8.4 / 8.0     8.8 / 8.3     9.4 / 8.6     9.7 / 8.9
+//   2 % pointers                    7.2 / 7.0     7.4 / 7.2     7.8 / 7.2     8.1 / 7.4     8.6 / 7.8
+//   95 %                            10.1 / 10.8   10.3 / 11.1   11.0 / 11.4   11.6 / 12.0   12.4 / 12.5
+//   with output                     8.8 / 8.9     8.8 / 9.1     9.3 / 9.4     9.8 / 9.8     10.4 / 10.1
+//   4-byte positions                7.6 / 6.9     7.3 / 7.0     8.1 / 7.0     8.1 / 7.4     8.7 / 7.8
+//   nothing prepared                11.3 / 11.0   11.6 / 11.3   12.1 / 11.6   12.5 / 11.9   13.0 / 12.2
+//   16 allocations, 2 %             6.8 / 7.1     7.0 / 7.3     7.4 / 7.3     7.8 / 7.5     8.1 / 7.7
+//   16,384                          8.8 / 8.0     8.8 / 8.0     9.6 / 8.4     10.0 / 8.9    10.4 / 9.5    10.8 / 9.3
+// Tables with lines or nodes, whose searches are longer, at 1,368 / 1,758 / 2,344: 20,000 allocations, with output, 11.4 / 12.6,
+// 12.4 / 13.0, 19.1 / 13.7; 140,000 12.2 / 12.7, 12.9 / 13.0.
+constexpr u32 kFlatFewSubs = 1536, kFlatFewSubsWhole = 976;  // (whole: level 0 holds every base)
+__host__ __device__ __forceinline__ u32 flat_workers(u32 n_sub, bool whole = false) {
+  return n_sub < (whole ? kFlatFewSubsWhole : kFlatFewSubs) ? kFlatWorkers : kFlatWorkersBig;
 }
-__host__ __device__ __forceinline__ u32 flat_chunks(u32 n_sub) {
-  const u32 w = flat_workers(n_sub);
+__host__ __device__ __forceinline__ u32 flat_chunks(u32 n_sub, bool whole = false) {
+  const u32 w = flat_workers(n_sub, whole);
   return (n_sub + w - 1) / w;
 }
 
-// Most chunks of a launch of up to max_sub sub-tiles.
+// Most chunks of a launch of up to max_sub sub-tiles, whatever the table.
 inline u32 flat_most_chunks(u32 max_sub) {
   u32 most = flat_chunks(max_sub);
   if (max_sub >= kFlatFewSubs && flat_chunks(kFlatFewSubs - 1) > most) most = flat_chunks(kFlatFewSubs - 1);
@@ -111,7 +120,8 @@ __host__ __device__ __forceinline__ u32 flat_to_clear(const FlatTurn& t, u32 i, 
 // other kind.
 // Launches of few chunks have a state for each, with the chunk's field in its lowest 16 bits and nothing above.
 constexpr u32 kFewChunks = 64;
-static_assert(kFewChunks < kFlatFewSubs / kFlatWorkersBig, "workgroups of many workers never have few chunks");
+static_assert(kFewChunks < kFlatFewSubsWhole / kFlatWorkersBig && kFlatFewSubsWhole < kFlatFewSubs,
+              "workgroups of many workers never have few chunks");
 __host__ __device__ __forceinline__ bool few_chunks(u32 n_chunks) { return n_chunks <= kFewChunks; }
 __host__ __device__ __forceinline__ u32 scan_states(u32 n_chunks) {
   return few_chunks(n_chunks) ? n_chunks : 5 * ((n_chunks + 15) / 16);

@@ -813,8 +813,9 @@ __global__ __launch_bounds__((kW + 1) * 64) void scan_kernel(ScanParams p) {
   u32 turn = 0;  // (lies in the prepared table's first block, which the check reads too)
   if (clerk) turn = __hip_atomic_load(p.turn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   // Who tells a chunk's hits: the last of many workers, ahead of the barrier, or the clerk of few behind it.  us by the
-  // clerk / by the last worker: seven workers, 0.5 M words 7.4 / 7.6, 0.3 M positions at 4-byte stride 6.2 / 6.5; fifteen, 2^27
-  // words with output 681 / 673.
+  // clerk / by the last worker, a quarter pointers: seven workers, 0.3 M words 7.08 / 7.15, 0.6 M and 16,384 allocations 9.55 /
+  // 9.70, 0.7 M with lines and output 11.83 / 12.00; fifteen, 1.7 M words 10.64 / 10.50, 5.9 M 22.1 / 21.8, 8.4 M 4-byte
+  // positions 23.2 / 23.1, 12.3 M with lines and output 68.1 / 68.4, 2^27 with nodes and output 1,363 / 1,347.
   constexpr bool kWorkersTell = kW != (int)kFlatWorkers;
   FlatRegion region = p.region;  // (the header's first block as well)
   if (p.prepared) region = FlatRegion{(long long)p.prepared[4], (u32)p.prepared[5]};
@@ -1454,7 +1455,8 @@ static int scan_launch(const uint64_t* d_words, uint64_t n_words, const fdy_allo
   TablePlan tp;
   if (!plan_table(n_alloc, &tp)) return FDY_ERR_INVALID_ARG;
   const u32 n_sub = sub_tiles(n_words);
-  const u32 workers = flat_workers(n_sub), n_chunks = flat_chunks(n_sub);
+  const bool whole = tp.levels == 0;
+  const u32 workers = flat_workers(n_sub, whole), n_chunks = flat_chunks(n_sub, whole);
   // where things lie
   unsigned char* ws = (unsigned char*)d_workspace;
   unsigned char* state;

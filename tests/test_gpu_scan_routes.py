@@ -131,7 +131,8 @@ def test_launches_of_few_and_many_chunks_in_turn(n_alloc):
     t = table_of(rng, n_alloc, "spread")
     words = words_of(rng, 1600 * SUB, t, 0.25)
     runs = []
-    for n in (1, 7 * SUB, 63 * 7 * SUB, 64 * 7 * SUB - 1, 64 * 7 * SUB, 64 * 7 * SUB + 1, 65 * 7 * SUB, 1535 * SUB, 1600 * SUB):
+    for n in (1, 7 * SUB, 63 * 7 * SUB, 64 * 7 * SUB - 1, 64 * 7 * SUB, 64 * 7 * SUB + 1, 65 * 7 * SUB, 975 * SUB, 975 * SUB + 1, 1535 * SUB,
+              1600 * SUB):
         runs.append((session.ScanRun(words[:n], t), *orc.scan(words[:n], t)))
     big = runs[-1][0]
     big.prepare(len(words))
