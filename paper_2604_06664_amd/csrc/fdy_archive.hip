@@ -158,7 +158,11 @@ void side_by_side(uint32_t parts, const Part& part) {
 }
 // How many parts are worth a thread each.  us, 11 MB from the page cache, one / three / four / eight parts: opened with all sums
 // 131 / 81 / 79 / 126, content check 155 / 84 / 73 / 95, the whole load of the file 730 / 566 / 534 / 590; below 2 MB (which
-// takes 26 and 17) a thread costs what it saves.
+// takes 26 and 17) a thread costs what it saves.  Larger files, one / two / three / four parts, opened with all sums and
+// the content check: 50 MB 2,050 / 1,177 / 851 / 687 and 1,910 / 973 / 739 / 548, 83 MB 3,448 / 2,065 / 1,435 / 1,178 and
+// 2,677 / 1,592 / 1,124 / 901.  The first time that a process looks at a file the threads meet its pages for the first time
+// as well: 11 MB 236 / 267 / 218 / 204 and 155 / 178 / 142 / 158, so that little is gained there, 83 MB 3,441 / 2,446 / 1,668 /
+// 1,490 and 2,775 / 1,924 / 1,353 / 1,433.
 uint32_t parts_of(uint64_t bytes) {
   if (const int asked = fdy__tune_get(FDY_TUNE_ARCHIVE_PARTS)) return (uint32_t)asked;
   const uint64_t n = std::min<uint64_t>(bytes / (1u << 20), kMostParts);

@@ -91,9 +91,9 @@ __device__ __forceinline__ u32 wave_lower_bound(KeyFn key, u32 lo, u32 hi, u64 t
 // rows of 16 lanes, or the last lane of the row (of the half) before for the rows in kRows; `otherwise` in lanes that have no
 // such neighbour.  All lanes of the wave take part.  (Through LDS, as __shfl_up goes, six steps of three 64-bit sums wait for
 // each other and for those of the compute unit's other waves: 3 to 7 us of a prep launch for 512 graphs, 2 to 5 now.  us of
-// whole loads, through LDS / now: sums of graphs, 67 graphs 23.4 / 22.6, to 8 ranks 88.5 / 87.9, derivation 44.3 / 43.2;
-// the fold of fingerprints as well 67 graphs 22.6 / 22.2, of 2,632 nodes 87.3 / 86.3, 512 graphs 60.1 / 58.8, one of 512
-// nodes 16.9 / 15.8.)
+// whole passes, scans over a wave through LDS / so: load of 67 graphs 24.7 / 23.9, of 67 of 2,632 nodes for 8 ranks 88.8 /
+// 87.3, of 512 graphs 61.9 / 60.4, save 45.1 / 43.1; the ordered fold of fingerprints 24.2 / 23.9, 87.6 / 87.3, 60.6 / 60.4,
+// 43.3 / 43.0; for one graph of 512 nodes neither shows, 16.5 to 17.)
 template <int kCtrl, int kRows = 0xf>
 __device__ __forceinline__ u32 dpp(u32 v, u32 otherwise) {
   return (u32)__builtin_amdgcn_update_dpp((int)otherwise, (int)v, kCtrl, kRows, 0xf, false);

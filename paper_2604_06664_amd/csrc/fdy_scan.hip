@@ -34,8 +34,8 @@
 // per compute unit.  Hence 128 registers: candidates (or the stash) in LDS in place of the words,
 // 64 bits per result, wide lines one chain at a time, and no window, staging area or second search for
 // dense stretches (eight rounds hold a whole sub-tile).  They are just enough: with nodes and an output
-// four values are spilled (20 bytes of scratch a lane), and the instances for tables with lines keep
-// 20 to 50 scalars in lanes of vector registers.  Measured on the way (us; 2^27 words, 2^20 allocations, with
+// four values are spilled (20 bytes of scratch a lane), and fifteen-worker instances keep 2 to 6 scalars in lanes of vector
+// registers, for tables with lines 20 to 28, with nodes 44 to 62.  Measured on the way (us; 2^27 words, 2^20 allocations, with
 // output / 12.3 M words, 65,537 byte-granular allocations, with output / 33.5 M words, 300,007
 // allocations with 8 GiB regions, without):
 //   eight waves of 256 registers, two sub-tiles in hand, tables read through up to two nodes   758 / 95 / 227
@@ -43,9 +43,9 @@
 //   the line before instead of a search where truncated keys lead a line too far                787 / 75 / 172
 //   fifteen workers                                                                            715 / 66 / 161
 //   the largest tables' rounds one by one but for sub-tiles with few candidates                685 / 67 / 158
-//   positions by one step over 256 chunks, not by 64 at a time; hits told by the last worker    671 / 65 / 150
+//   positions by one step over 256 chunks, not by 64 at a time; hits told by the last worker    670 / 65 / 152
 // A small launch is a chain of waits.  us of scans alone, one after the other, a quarter pointers, 4,096 allocations, 0.3 /
-// 0.8 / 1.7 / 5.9 M words: 7.2 / 8.9 / 11.0 / 23.0 with positions by 64 chunks at a time; 7.1 / 8.6 / 10.5 / 21.7 now;
+// 0.8 / 1.7 / 5.9 M words: 7.2 / 8.9 / 11.0 / 23.0 with positions by 64 chunks at a time; 7.1 / 8.6 / 10.5 / 21.8 so;
 // 8.4 M positions at 4-byte stride 24.7 / 23.1.
 // Tried and left: words requested before the search (they hold up its first fetch, which returns
 // behind them: 75 -> 90; behind the last fetch of the search, with the ticket there, a load of 5.9 M words 62.4 -> 66.1: a
@@ -181,9 +181,9 @@ struct FlatStates {
 };
 
 // The number of hits in all chunks before `chunk`.  Lane l looks at the four fields of one state, the first sixteen also at
-// the sums behind the sixteenths before; polls go to what is missing alone.  (64 chunks at a time: four or five round trips
-// in a row, us of a load of 0.8 M words 24.4 / 23.8 now, of 8.4 M positions at 4-byte stride 23.6 / 22.3.  Neighbouring
-// states in the same memory lines: 62 -> 64 for 5.9 M words.)  meanwhile(): called behind the first requests.
+// the sums behind the sixteenths before; polls go to what is missing alone.  (64 chunks at a time, four or five round trips
+// in a row: 23.0 us for 5.9 M words, 21.8 so.  The ticket drawn behind the first requests 22.5, behind the whole step 22.6.
+// Neighbouring states in the same memory lines: a load of 5.9 M words 62 -> 64.)  meanwhile(): called behind the first requests.
 template <typename Meanwhile>
 __device__ __forceinline__ u64 exclusive_prefix(const FlatStates& states, u32 chunk, u32 spin_limit, u32* d_status,
                                                 Meanwhile meanwhile) {
